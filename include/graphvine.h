@@ -25,7 +25,9 @@
  * the graph's current device, owned by the caller and read (or written) in
  * stream order on the graph's stream; the caller keeps it alive until that
  * stream has passed the call.  The library never frees caller memory.  The
- * graph owns all of its internal memory; gv_graph_destroy releases it.
+ * graph owns all of its internal memory; gv_graph_destroy releases it (the
+ * library keeps at most 4 GiB of large freed buffers per process for the next
+ * graphs, and frees them when an allocation does not fit).
  * A gv_graph must be used by one host thread at a time.
  *
  * Errors.  Every int-returning function returns a GV_* code; no C++ exception

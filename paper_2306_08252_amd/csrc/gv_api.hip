@@ -46,11 +46,12 @@ int guarded(gv_graph* g, F&& f) {
 
 void free_graph(gv_graph* g) {
     if (!g) return;
-    hipStreamSynchronize(g->ctx.stream);
+    // buffers go back to the cache only when the work that used them is done
+    bool idle = hipStreamSynchronize(g->ctx.stream) == hipSuccess && !g->dead;
     g->ctx.release();
     gv_graph::Overlap& o = g->ov;
     if (o.stream) {
-        hipStreamSynchronize(o.stream);
+        idle = hipStreamSynchronize(o.stream) == hipSuccess && idle;
         o.ctx.release();
         hipEvent_t evs[] = {o.sorted[0],  o.sorted[1],  o.done[0],  o.done[1], o.fence,
                             o.msorted[0], o.msorted[1], o.mdone[0], o.mdone[1]};
@@ -59,14 +60,13 @@ void free_graph(gv_graph* g) {
         hipStreamDestroy(o.stream);
         o.stream = nullptr;
     }
-    o.scr.release();
-    for (auto& m : o.mix) m.release();
-    g->scratch.release();
-    for (auto& v : g->vscr) v.release();
-    g->cscr.release();
-    void* mem[] = {g->mem_pool,   g->mem_free, g->mem_dir,  g->mem_dfree, g->mem_vt,
-                   g->mem_active, g->mem_ctr,  g->mem_bown, g->mem_vlost, g->mem_apool,
-                   g->mem_chain};
+    o.scr.release(idle);
+    for (auto& m : o.mix) m.release(idle);
+    g->scratch.release(idle);
+    for (auto& v : g->vscr) v.release(idle);
+    g->cscr.release(idle);
+    dev_free(g->mem_pool, idle);
+    void* mem[] = {g->mem_vt, g->mem_active, g->mem_ctr, g->mem_vlost, g->mem_chain};
     for (void* p : mem)
         if (p) hipFree(p);
     if (g->hctr) hipHostFree(g->hctr);

@@ -46,9 +46,8 @@ static bool sort_keys(gv_graph* g, uint64_t* k0, uint64_t* k1, uint64_t n, int b
 }
 
 // ------------------------------------------------------------------ init
-__global__ __launch_bounds__(kThreads) void k_init_vt(GraphView g, uint64_t n_active) {
+__global__ __launch_bounds__(kThreads) void k_init_active(GraphView g, uint64_t n_active) {
     const uint64_t v = tidx();
-    if (v < g.n_cap) g.vt[v] = VRec{0u, 0u, kNoDir, 0u};
     const uint64_t words = (g.n_cap + 31) / 32;
     if (v < words) {
         const uint64_t lo = v * 32;
@@ -59,117 +58,141 @@ __global__ __launch_bounds__(kThreads) void k_init_vt(GraphView g, uint64_t n_ac
     }
 }
 
-// keys of the initial edges; an id out of range raises a flag (a plain store,
-// taken only on error) that the host checks before any id is used as an index
-__global__ __launch_bounds__(kThreads) void k_init_pack(GraphView g, const uint32_t* src,
-                                                        const uint32_t* dst, uint64_t m,
-                                                        uint64_t n, uint64_t* keys) {
-    const uint64_t i = tidx();
-    if (i >= m) return;
-    const uint32_t s = src[i], d = dst[i];
-    if ((uint64_t)s >= n || (uint64_t)d >= n) g.ctr->vany = 1;
-    keys[i] = ((uint64_t)s << g.L) | d;
+// keys of the initial edges with the sort's digit counts (per workgroup); an
+// id out of range raises a flag (a plain store, taken only on error) that the
+// host checks before any id is used as an index
+__global__ __launch_bounds__(kOsThreads) void k_init_pack(GraphView g, const uint32_t* src,
+                                                          const uint32_t* dst, uint64_t m,
+                                                          uint64_t n, int passes, uint64_t* keys,
+                                                          uint32_t* hpart) {
+    __shared__ uint32_t h[kOsHistCopies][8][kRadix];
+    const uint32_t t = threadIdx.x;
+    for (int i = t; i < kOsHistCopies * 8 * kRadix; i += kOsThreads) (&h[0][0][0])[i] = 0;
+    __syncthreads();
+    const uint32_t copy = kOsHistCopies == 1 ? 0u : (t >> 6) & (kOsHistCopies - 1);
+    bool bad = false;
+    const uint64_t ntiles = (m + kOsTile - 1) / kOsTile;
+    for (uint64_t tl = blockIdx.x; tl < ntiles; tl += gridDim.x) {
+        const uint64_t base = tl * kOsTile;
+        uint32_t su[kOsRounds], du[kOsRounds];
+#pragma unroll
+        for (int j = 0; j < kOsRounds; ++j) {
+            const uint64_t i = base + (uint64_t)j * kOsThreads + t;
+            su[j] = i < m ? src[i] : 0u;
+            du[j] = i < m ? dst[i] : 0u;
+        }
+#pragma unroll
+        for (int j = 0; j < kOsRounds; ++j) {
+            const uint64_t i = base + (uint64_t)j * kOsThreads + t;
+            if (i >= m) continue;
+            bad |= ((uint64_t)su[j] >= n) | ((uint64_t)du[j] >= n);
+            const uint64_t key = ((uint64_t)su[j] << g.L) | du[j];
+            keys[i] = key;
+            for (int p = 0; p < passes; ++p)
+                atomicAdd(&h[copy][p][(uint32_t)(key >> (p * kRadixBits)) & (kRadix - 1)], 1u);
+        }
+    }
+    if (bad) g.ctr->vany = 1;
+    __syncthreads();
+    uint32_t* out = hpart + (uint64_t)blockIdx.x * passes * kRadix;
+    for (int i = t; i < passes * kRadix; i += kOsThreads) {
+        uint32_t x = 0;
+#pragma unroll
+        for (int c = 0; c < kOsHistCopies; ++c) x += h[c][i / kRadix][i % kRadix];
+        out[i] = x;
+    }
 }
 
-// first occurrence of a key in the low half, first occurrence of a source in
-// the high half: one scan yields the unique positions, the number of distinct
-// edges and the number of vertices of non-zero degree
+// Scan over the sorted keys: first occurrences in the low half, first
+// occurrences of a source in the high half.  The sink compacts the distinct
+// keys and writes each source's run of them, [run[v].x, run[v].y): a source's
+// first key ends the run before it.
 struct FirstIn {
     const uint64_t* keys;
-    uint64_t m;
     uint32_t L;
-    __device__ unsigned long long operator()(uint64_t i) const {
-        if (i >= m) return 0ull;
-        if (i == 0) return 1ull | (1ull << 32);
-        const uint64_t a = keys[i - 1], b = keys[i];
-        return (a != b ? 1ull : 0ull) | ((a >> L) != (b >> L) ? (1ull << 32) : 0ull);
+    struct Rec {
+        uint64_t k, p;
+    };
+    __device__ uint64_t limit(uint64_t m) const { return m; }
+    __device__ Rec load(uint64_t i, bool) const { return Rec{keys[i], keys[i ? i - 1 : 0]}; }
+    __device__ void deref(Rec&) const {}
+    __device__ unsigned long long value(uint64_t i, const Rec& r) const {
+        const unsigned long long first = i == 0 || r.k != r.p;
+        const unsigned long long head = i == 0 || (r.k >> L) != (r.p >> L);
+        return first | (head << 32);
     }
 };
 
-struct LowOut {
-    uint32_t* a;
-    __device__ void operator()(uint64_t i, unsigned long long v) const { a[i] = (uint32_t)v; }
+struct FirstOut {
+    uint32_t L;
+    uint64_t* ukeys;
+    uint2* run;
+    __device__ void operator()(uint64_t i, const FirstIn::Rec& r, uint64_t m,
+                               unsigned long long pre) const {
+        const uint32_t pos = (uint32_t)pre;
+        const bool first = i == 0 || r.k != r.p;
+        if (first) ukeys[pos] = r.k;
+        if (i == 0 || (r.k >> L) != (r.p >> L)) {
+            run[r.k >> L].x = pos;
+            if (i) run[r.p >> L].y = pos;
+        }
+        if (i + 1 == m) run[r.k >> L].y = pos + (first ? 1u : 0u);
+    }
 };
-
-__global__ __launch_bounds__(kThreads) void k_init_unique(const uint64_t* keys, const uint32_t* pos,
-                                                          uint64_t m, uint64_t* ukeys) {
-    const uint64_t i = tidx();
-    if (i < m && (i == 0 || keys[i] != keys[i - 1])) ukeys[pos[i]] = keys[i];
-}
-
-// run starts: first position of each source in the unique list -> aux
-__global__ __launch_bounds__(kThreads) void k_init_runs(GraphView g, const uint64_t* ukeys,
-                                                        uint64_t mu) {
-    const uint64_t p = tidx();
-    if (p >= mu) return;
-    const uint32_t v = (uint32_t)(ukeys[p] >> g.L);
-    if (p == 0 || (uint32_t)(ukeys[p - 1] >> g.L) != v) g.vt[v].aux = (uint32_t)p;
-}
-
-__global__ __launch_bounds__(kThreads) void k_init_deg(GraphView g, const uint64_t* ukeys,
-                                                       uint64_t mu) {
-    const uint64_t p = tidx();
-    if (p >= mu) return;
-    const uint32_t v = (uint32_t)(ukeys[p] >> g.L);
-    if (p + 1 == mu || (uint32_t)(ukeys[p + 1] >> g.L) != v)
-        g.vt[v].deg = (uint32_t)(p + 1) - g.vt[v].aux;
-}
 
 // per vertex: blocks in the low half, directory entries in the high half
 struct LayoutIn {
     GraphView g;
+    const uint2* run;
     __device__ unsigned long long operator()(uint64_t v) const {
         if (v >= g.n_cap) return 0ull;
-        const uint32_t nb = nblocks(g, g.vt[v].deg);
+        const uint2 r = run[v];
+        const uint32_t nb = nblocks(g, r.y - r.x);
         const unsigned long long de = nb >= 2 ? (1ull << ceil_log2(nb)) : 0ull;
         return (unsigned long long)nb | (de << 32);
     }
 };
 
-__global__ __launch_bounds__(kThreads) void k_init_layout(GraphView g,
+__global__ __launch_bounds__(kThreads) void k_init_layout(GraphView g, const uint2* run,
                                                           const unsigned long long* off) {
     const uint64_t v = tidx();
     if (v >= g.n_cap) return;
-    VRec r = g.vt[v];
+    const uint2 q = run[v];
+    VRec r{q.y - q.x, 0u, kNoDir, 0u};
     const uint32_t nb = nblocks(g, r.deg);
-    const uint32_t boff = (uint32_t)off[v];
-    const uint32_t doff = (uint32_t)(off[v] >> 32);
-    r.aux = 0;
-    if (nb == 0) {
-        r.dir = 0;
-        r.dcls = kNoDir;
-    } else if (nb == 1) {
-        r.dir = boff;
-        r.dcls = kNoDir;
-    } else {
-        r.dir = doff;
+    if (nb == 1) {
+        r.dir = (uint32_t)off[v];
+    } else if (nb) {
+        r.dir = (uint32_t)(off[v] >> 32);
         r.dcls = ceil_log2(nb);
-        for (uint32_t j = 0; j < nb; ++j) g.dir[(uint64_t)doff + j] = boff + j;
     }
-    for (uint32_t j = 0; j < nb; ++j) g.bown[(uint64_t)boff + j] = make_uint2((uint32_t)v, j);
     g.vt[v] = r;
 }
 
 // scatter: edge p of the sorted unique list goes to slot (p - run start) of
-// its vertex's contiguous blocks
+// its vertex's contiguous blocks; a block's first edge also writes the
+// block's owner record and directory entry (a thread per vertex that wrote
+// them took 200 us on R-MAT 2^20 / 2^24: the longest adjacency has 4096
+// blocks)
 __global__ __launch_bounds__(kThreads) void k_init_scatter(GraphView g, const uint64_t* ukeys,
-                                                           const uint32_t* runstart,
+                                                           const uint2* run,
                                                            const unsigned long long* off,
                                                            uint64_t mu) {
     const uint64_t p = tidx();
     if (p >= mu) return;
     const uint64_t k = ukeys[p];
     const uint32_t v = (uint32_t)(k >> g.L);
-    const uint32_t s = (uint32_t)p - runstart[v];
-    const uint64_t blk = (uint32_t)off[v] + (s >> g.log2B);
-    const uint64_t a = (blk << g.log2B) + (s & (g.B - 1));
+    const uint2 q = run[v];
+    const unsigned long long o = off[v];
+    const uint32_t s = (uint32_t)p - q.x;
+    const uint32_t j = s >> g.log2B, blk = (uint32_t)o + j;
+    const uint64_t a = ((uint64_t)blk << g.log2B) + (s & (g.B - 1));
     g.pool[a] = (uint32_t)(k & ((1ull << g.L) - 1));
     attr_zero(g, a);
-}
-
-__global__ __launch_bounds__(kThreads) void k_save_runstart(GraphView g, uint32_t* runstart) {
-    const uint64_t v = tidx();
-    if (v < g.n_cap) runstart[v] = g.vt[v].aux;
+    if ((s & (g.B - 1)) == 0) {
+        g.bown[blk] = make_uint2(v, j);
+        if (q.y - q.x > g.B) g.dir[(o >> 32) + j] = blk;
+    }
 }
 
 __global__ void k_init_counters(GraphView g, unsigned long long blocks, unsigned long long dents,
@@ -201,8 +224,7 @@ void bulk_build(gv_graph* g, uint64_t n, const uint32_t* src, const uint32_t* ds
                 const gv_config& cfg) {
     Ctx& c = g->ctx;
     GraphView& v = g->v;
-    const uint64_t vgrid = div_up(std::max<uint64_t>(v.n_cap, (v.n_cap + 31) / 32), kThreads);
-    c.launch("init_vt", k_init_vt, vgrid, kThreads, v, n);
+    c.launch("init_active", k_init_active, div_up((v.n_cap + 31) / 32, kThreads), kThreads, v, n);
     set_u32(g, &v.ctr->vany, 0);
 
     const int bits = 2 * (int)v.L;
@@ -210,23 +232,23 @@ void bulk_build(gv_graph* g, uint64_t n, const uint32_t* src, const uint32_t* ds
     struct Arr {
         uint64_t* k0;
         uint64_t* k1;
-        uint32_t* pos;
         unsigned long long* part;
         uint32_t* state;
         unsigned long long* off;
         unsigned long long* part64;
-        uint32_t* runstart;
+        uint2* run;
     } A{};
-    const uint64_t state_words = m > 1 ? os_words(m, bits) : 0;
+    const bool sorts = m > 1 && bits > 0;
+    const uint64_t state_words = sorts ? os_words(m, bits) : 0;
     auto carve = [&](Carver& cv) {
         A.k0 = cv.take<uint64_t>(std::max<uint64_t>(m, 1));
         A.k1 = cv.take<uint64_t>(std::max<uint64_t>(m, 1));
-        A.pos = cv.take<uint32_t>(m + 1);
-        A.part = cv.take<unsigned long long>(scan_partials_needed(m + 1));
-        A.state = cv.take<uint32_t>(std::max<uint64_t>(state_words, 1));
+        A.part = cv.take<unsigned long long>(scan2_parts(m));
+        // (a single key's digits are counted too, for no pass)
+        A.state = cv.take<uint32_t>(std::max<uint64_t>(state_words, 8 * kRadix));
         A.off = cv.take<unsigned long long>(v.n_cap + 1);
         A.part64 = cv.take<unsigned long long>(scan_partials_needed(v.n_cap + 1));
-        A.runstart = cv.take<uint32_t>(v.n_cap);
+        A.run = cv.take<uint2>(v.n_cap);
     };
     {
         Carver mz(nullptr);
@@ -236,33 +258,38 @@ void bulk_build(gv_graph* g, uint64_t n, const uint32_t* src, const uint32_t* ds
         carve(cv);
     }
     uint64_t* ukeys = nullptr;
+    zero_words(c, (uint32_t*)A.run, 2 * v.n_cap);
     if (m > 0) {
         if (m >= kOsMaxKeys) fail(GV_EINVAL, "2^30 or more edges");
-        const uint64_t grid = div_up(m, kThreads);
-        c.launch("init_pack", k_init_pack, grid, kThreads, v, src, dst, m, n, A.k0);
-        const bool flip = m > 1 && sort_keys(g, A.k0, A.k1, m, bits, A.state);
-        uint64_t* keys = flip ? A.k1 : A.k0;
-        ukeys = flip ? A.k0 : A.k1;
-        scan_excl<unsigned long long>(c, FirstIn{keys, m, v.L}, LowOut{A.pos}, m + 1, A.part,
-                                      &v.ctr->edges);
+        const int passes = sorts ? os_passes(bits) : 0;
+        if (sorts) zero_words(c, A.state, os_zero_words(m, bits));
+        c.launch("init_pack", k_init_pack, os_hist_groups(m), kOsThreads, v, src, dst, m, n,
+                 passes, A.k0, sorts ? os_hpart(A.state, m, bits) : A.state);
+        bool flip = false;
+        if (sorts) {
+            set_u32(g, &v.ctr->sort_err, 0);
+            os_hist_sum(c, A.state, m, bits, nullptr, nullptr, nullptr, nullptr);
+            flip = onesweep_passes<uint64_t, false>(c, A.k0, A.k1, nullptr, nullptr, nullptr, m,
+                                                    bits, A.state, &v.ctr->sort_err);
+        }
         read_counters(g);
         if (g->hctr->vany) fail(GV_ERANGE, "edge id >= num_vertices");
+        if (sorts && g->hctr->sort_err) fail(GV_EDEVICE, "sort look-back did not complete");
+        uint64_t* keys = flip ? A.k1 : A.k0;
+        ukeys = flip ? A.k0 : A.k1;
+        scan2(c, "init_unique", FirstIn{keys, v.L}, FirstOut{v.L, ukeys, A.run}, m, A.part,
+              &v.ctr->edges);
+        read_counters(g);
+        if (g->hctr->err_wait) fail(GV_EDEVICE, "a scan's wait ran out");
         mu = g->hctr->edges & 0xffffffffull;
         nonzero = g->hctr->edges >> 32;
-        c.launch("init_unique", k_init_unique, grid, kThreads, (const uint64_t*)keys,
-                 (const uint32_t*)A.pos, m, ukeys);
-        const uint64_t ugrid = div_up(mu, kThreads);
-        c.launch("init_runs", k_init_runs, ugrid, kThreads, v, (const uint64_t*)ukeys, mu);
-        c.launch("init_deg", k_init_deg, ugrid, kThreads, v, (const uint64_t*)ukeys, mu);
     }
     uint32_t B = cfg.block_slots ? cfg.block_slots : paper_block_rule(mu, nonzero);
     v.B = B;
     v.log2B = log2_exact(B);
 
-    c.launch("save_runstart", k_save_runstart, div_up(v.n_cap, kThreads), kThreads, v,
-             A.runstart);
-    scan_excl<unsigned long long>(c, LayoutIn{v}, ArrOut<unsigned long long>{A.off}, v.n_cap + 1,
-                                  A.part64, &v.ctr->edges);
+    scan_excl<unsigned long long>(c, LayoutIn{v, A.run}, ArrOut<unsigned long long>{A.off},
+                                  v.n_cap + 1, A.part64, &v.ctr->edges);
     read_counters(g);
     const uint64_t blocks = g->hctr->edges & 0xffffffffull;
     const uint64_t dents = g->hctr->edges >> 32;
@@ -275,37 +302,35 @@ void bulk_build(gv_graph* g, uint64_t n, const uint32_t* src, const uint32_t* ds
                                              : 4 * cap_blocks + (1ull << 20);
     dir_cap = std::min<uint64_t>(dir_cap, 0xfffffff0ull);
     if (dents > dir_cap) fail(GV_ENOMEM, "directory too small for the initial graph");
-    hip_check(hipMalloc(&g->mem_pool, std::max<uint64_t>(cap_blocks * B * 4ull, 4)),
-              "hipMalloc pool");
-    hip_check(hipMalloc(&g->mem_free, std::max<uint64_t>(cap_blocks * 4ull, 4)),
-              "hipMalloc free list");
-    hip_check(hipMalloc(&g->mem_bown, std::max<uint64_t>(cap_blocks * 8ull, 8)),
-              "hipMalloc block owners");
-    if (v.A)
-        hip_check(hipMalloc(&g->mem_apool, cap_blocks * B * 4ull * v.A), "hipMalloc attributes");
-    hip_check(hipMalloc(&g->mem_dir, std::max<uint64_t>(dir_cap * 4ull, 4)), "hipMalloc dir");
     uint64_t dfree_total = 0;
     for (int k = 0; k < kMaxClass; ++k) {
         v.dfree_base[k] = dfree_total;
         dfree_total += (k == 0) ? 0 : (dir_cap >> k);
     }
-    hip_check(hipMalloc(&g->mem_dfree, std::max<uint64_t>(dfree_total * 4ull, 4)),
-              "hipMalloc dir free");
-    v.pool = (uint32_t*)g->mem_pool;
-    v.free_stack = (uint32_t*)g->mem_free;
-    v.bown = (uint2*)g->mem_bown;
-    v.apool = (uint32_t*)g->mem_apool;
-    v.dir = (uint32_t*)g->mem_dir;
-    v.dfree = (uint32_t*)g->mem_dfree;
+    // one allocation: pool, free list, block owners, directory, its free
+    // lists, attributes
+    auto carve_pool = [&](Carver& cv) {
+        v.pool = cv.take<uint32_t>(std::max<uint64_t>(cap_blocks * B, 1));
+        v.free_stack = cv.take<uint32_t>(std::max<uint64_t>(cap_blocks, 1));
+        v.bown = cv.take<uint2>(std::max<uint64_t>(cap_blocks, 1));
+        v.dir = cv.take<uint32_t>(std::max<uint64_t>(dir_cap, 1));
+        v.dfree = cv.take<uint32_t>(std::max<uint64_t>(dfree_total, 1));
+        v.apool = v.A ? cv.take<uint32_t>(cap_blocks * B * v.A) : nullptr;
+    };
+    Carver mp(nullptr);
+    carve_pool(mp);
+    dev_malloc(&g->mem_pool, mp.used, "hipMalloc pool");
+    Carver cp(g->mem_pool);
+    carve_pool(cp);
     v.cap_blocks = cap_blocks;
     v.dir_cap = dir_cap;
     g->item_slots = cap_blocks * B;
 
     c.launch("init_layout", k_init_layout, div_up(v.n_cap, kThreads), kThreads, v,
-             (const unsigned long long*)A.off);
+             (const uint2*)A.run, (const unsigned long long*)A.off);
     if (mu > 0)
         c.launch("init_scatter", k_init_scatter, div_up(mu, kThreads), kThreads, v,
-                 (const uint64_t*)ukeys, (const uint32_t*)A.runstart,
+                 (const uint64_t*)ukeys, (const uint2*)A.run,
                  (const unsigned long long*)A.off, mu);
     c.launch("init_counters", k_init_counters, 1, 1, v, (unsigned long long)blocks,
              (unsigned long long)dents, (unsigned long long)mu);
@@ -321,44 +346,435 @@ struct DegIn {
     }
 };
 
-// one wave per vertex: checksum of its edges and (optionally) its keys at
-// its CSR offset
-__global__ __launch_bounds__(kThreads) void k_dump_gather(GraphView g,
-                                                          const unsigned long long* offs,
-                                                          uint64_t* keys) {
-    const uint32_t lane = lane_id();
-    const uint64_t nw = (uint64_t)gridDim.x * kWaves;
+// Sums of a dump, striped over 64 lines (the host adds them up).
+constexpr int kStripeSum = 2, kStripeEdges = 3;
+
+// Classes of rows by degree: a dump orders rows of up to kRowLane entries by
+// 16 lanes each, and up to kRowMid by a wave in registers.  Longer rows are
+// listed and ordered by workgroups, as bitmaps of the destinations where the
+// table is small enough, else up to kRowBig entries in LDS and longer ones by
+// the one-sweep sort as (row, destination) keys.
+constexpr uint32_t kRowLane = 16, kRowMid = 1024, kRowBig = 16384;
+enum { kRowsBig = 0, kRowsHuge = 1, kHugeEdges = 2 };
+
+// Clears the sums and counts the rows past kRowMid by class (and the entries
+// of the longest), for the host to size their lists.
+__global__ __launch_bounds__(kThreads) void k_dump_begin(GraphView g) {
+    DevCounters* c = g.ctr;
+    const uint32_t t = threadIdx.x;
+    if (t < 64) c->stripe[t][kStripeSum] = c->stripe[t][kStripeEdges] = 0ull;
+    if (t < 4) {
+        c->rows[t] = 0ull;
+        c->row_at[t] = 0u;
+    }
+}
+
+__global__ __launch_bounds__(kThreads) void k_dump_classes(GraphView g, uint32_t rowbig) {
+    __shared__ unsigned long long lds[kWaves];
+    unsigned long long big = 0, huge = 0, edges = 0;
+    const uint64_t stride = (uint64_t)gridDim.x * kThreads;
+    for (uint64_t v = tidx(); v < g.n_cap; v += stride) {
+        const uint32_t d = g.vt[v].deg;
+        big += d > kRowMid && d <= rowbig;
+        huge += d > rowbig;
+        edges += d > rowbig ? d : 0u;
+    }
+    big = block_sum(big, lds);
+    huge = block_sum(huge, lds);
+    edges = block_sum(edges, lds);
+    if (threadIdx.x == 0) {
+        if (big) atomicAdd(&g.ctr->rows[kRowsBig], big);
+        if (huge) atomicAdd(&g.ctr->rows[kRowsHuge], huge);
+        if (edges) atomicAdd(&g.ctr->rows[kHugeEdges], edges);
+    }
+}
+
+// Count and checksum of the stored edges by a pass over the pool's handed-out
+// blocks, a thread per slot of a block: the block's owner record names the
+// vertex and index it was last given to, and it holds edges when that vertex
+// still holds the block there.  Bound: HBM (4 B per slot, 8 B per block); the
+// vertex records and directory entries of neighbouring blocks are neighbours
+// after a bulk build.  A wave per vertex took 2320 us on R-MAT 2^20 / 2^24
+// (the longest row, 65 thousand entries, was one wave's chain of loads); this
+// pass takes 68.
+__global__ __launch_bounds__(kThreads) void k_dump_checksum(GraphView g) {
+    __shared__ unsigned long long lds[kWaves];
+    unsigned long long h = 0, e = 0;
+    const uint64_t n = (uint64_t)g.ctr->bump << g.log2B;
+    const uint64_t stride = (uint64_t)gridDim.x * kThreads;
+    for (uint64_t a = tidx(); a < n; a += stride) {
+        const uint32_t b = (uint32_t)(a >> g.log2B);
+        const uint2 ow = g.bown[b];
+        const uint32_t x = g.pool[a];
+        if (ow.x >= g.n_cap) continue;  // (never for a block handed out)
+        const VRec r = g.vt[ow.x];
+        if (ow.y >= nblocks(g, r.deg)) continue;
+        const uint64_t s = ((uint64_t)ow.y << g.log2B) + (a & (g.B - 1));
+        if (s >= r.deg || block_of(g, r, ow.y) != b) continue;
+        h += mix64(((uint64_t)ow.x << 32) | x);
+        ++e;
+    }
+    h = block_sum(h, lds);
+    e = block_sum(e, lds);
+    if (threadIdx.x == 0) {
+        atomicAdd(&g.ctr->stripe[blockIdx.x & 63][kStripeSum], h);
+        atomicAdd(&g.ctr->stripe[blockIdx.x & 63][kStripeEdges], e);
+    }
+}
+
+// Bitonic networks in a wave's registers: element i = j * 64 + lane in x[j].
+// A step of distance h < 64 exchanges lanes (data-parallel moves within 16
+// lanes, row swaps for 16 and 32), one of h >= 64 exchanges registers; both
+// are compile-time, so a step is three or four vector instructions per
+// register.  (The same networks on LDS words took 17 instructions per
+// compare-exchange in address arithmetic: 280 us for the rows of 65 to 1024
+// entries of R-MAT 2^20 / 2^24.)
+template <uint32_t H>
+__device__ __forceinline__ void lane_minmax(uint32_t x, uint32_t& mn, uint32_t& mx) {
+    if constexpr (H >= 16) {
+        // both results hold the lower and the upper rows' values
+        const auto r = H == 16 ? __builtin_amdgcn_permlane16_swap(x, x, false, false)
+                               : __builtin_amdgcn_permlane32_swap(x, x, false, false);
+        mn = min((uint32_t)r[0], (uint32_t)r[1]);
+        mx = max((uint32_t)r[0], (uint32_t)r[1]);
+    } else {
+        uint32_t y;
+        if constexpr (H == 1) y = __builtin_amdgcn_update_dpp(0u, x, 0xB1, 0xf, 0xf, true);
+        else if constexpr (H == 2) y = __builtin_amdgcn_update_dpp(0u, x, 0x4E, 0xf, 0xf, true);
+        else if constexpr (H == 4) y = __builtin_amdgcn_ds_swizzle(x, (4 << 10) | 0x1f);
+        else y = __builtin_amdgcn_update_dpp(0u, x, 0x128, 0xf, 0xf, true);
+        mn = min(x, y);
+        mx = max(x, y);
+    }
+}
+
+// the steps of distance H, H / 2, ... 1 of the merge of runs of K elements
+template <uint32_t E, uint32_t K, uint32_t H>
+__device__ __forceinline__ void wave_merge(uint32_t (&x)[E], uint32_t lane) {
+    if constexpr (H >= 64) {
+        constexpr uint32_t hj = H / 64;
+#pragma unroll
+        for (uint32_t j = 0; j < E; ++j) {
+            if (j & hj) continue;
+            const uint32_t a = min(x[j], x[j + hj]), b = max(x[j], x[j + hj]);
+            const bool up = ((j * 64) & K) == 0;
+            x[j] = up ? a : b;
+            x[j + hj] = up ? b : a;
+        }
+    } else {
+#pragma unroll
+        for (uint32_t j = 0; j < E; ++j) {
+            uint32_t mn, mx;
+            lane_minmax<H>(x[j], mn, mx);
+            const bool up = K < 64 ? (lane & K) == 0 : ((j * 64) & K) == 0;
+            x[j] = ((lane & H) == 0) == up ? mn : mx;
+        }
+    }
+    if constexpr (H > 1) wave_merge<E, K, H / 2>(x, lane);
+}
+
+template <uint32_t E, uint32_t N, uint32_t K = 2>
+__device__ __forceinline__ void wave_sort(uint32_t (&x)[E], uint32_t lane) {
+    wave_merge<E, K, K / 2>(x, lane);
+    if constexpr (K < N) wave_sort<E, N, K * 2>(x, lane);
+}
+
+// Bitonic sort of the m (a power of two) words at s by the nt threads of a
+// workgroup.
+__device__ __forceinline__ void lds_bitonic(uint32_t* s, uint32_t m, uint32_t t, uint32_t nt) {
+    for (uint32_t k = 2; k <= m; k <<= 1) {
+        for (uint32_t h = k >> 1; h > 0; h >>= 1) {
+            __syncthreads();
+            for (uint32_t c = t; c < m / 2; c += nt) {
+                const uint32_t i = ((c & ~(h - 1)) << 1) | (c & (h - 1));
+                const uint32_t a = s[i], b = s[i + h];
+                if ((a > b) == ((i & k) == 0)) {
+                    s[i] = b;
+                    s[i + h] = a;
+                }
+            }
+        }
+    }
+    __syncthreads();
+}
+
+// A row of up to E * 64 entries, in a wave's registers; returns the lane's
+// share of the row's checksum.
+template <uint32_t E>
+__device__ __forceinline__ unsigned long long dump_row(const GraphView& g, uint64_t u,
+                                                       const VRec& r, uint32_t lane,
+                                                       uint32_t* out) {
+    uint32_t x[E];
     unsigned long long h = 0;
-    for (uint64_t u = gwave(); u < g.n_cap; u += nw) {
+#pragma unroll
+    for (uint32_t j = 0; j < E; ++j)
+        x[j] = g.pool[slot_addr(g, r, min(j * 64 + lane, r.deg - 1))];
+#pragma unroll
+    for (uint32_t j = 0; j < E; ++j) {
+        const bool in = j * 64 + lane < r.deg;
+        h += in ? mix64((u << 32) | x[j]) : 0ull;
+        x[j] = in ? x[j] : kTomb;
+    }
+    wave_sort<E, E * 64>(x, lane);
+#pragma unroll
+    for (uint32_t j = 0; j < E; ++j)
+        if (j * 64 + lane < r.deg) out[j * 64 + lane] = x[j];
+    return h;
+}
+
+// Rows of up to kRowMid entries, ordered in registers and written at their CSR
+// offsets: four vertices per wave per round, 16 lanes each; a row past
+// kRowLane entries is taken by the whole wave.  Longer rows are listed by
+// class (a few per thousand: listing the rows of 65 to 1024 entries as well,
+// 50 thousand appends to one counter, took 300 us).  Adds up the checksum of
+// the rows it writes.
+__global__ __launch_bounds__(kThreads) void k_dump_rows(GraphView g,
+                                                        const unsigned long long* offs,
+                                                        uint32_t* out, uint32_t* big,
+                                                        uint32_t* huge, uint32_t rowbig) {
+    __shared__ unsigned long long lds[kWaves];
+    const uint32_t lane = lane_id(), sub = lane & 15;
+    unsigned long long h = 0;
+    // A wave's place in a round turns by a large odd step from round to round:
+    // with a plain stride (a power of two) one wave takes the vertices that
+    // share their low bits, and on R-MAT tables the longest rows are those of
+    // few set bits (1500 us instead of 255).
+    const uint32_t nw = gridDim.x * kWaves, turn = (uint32_t)(nw * 0.618) | 1u;
+    uint32_t at = gwave();
+    for (uint64_t q0 = 0; q0 * 4 < g.n_cap; q0 += nw, at = (at + turn) % nw) {
+        const uint64_t q = q0 + at;
+        const uint64_t u = q * 4 + (lane >> 4);
+        const bool live = u < g.n_cap;
+        const VRec r = live ? g.vt[u] : VRec{0u, 0u, kNoDir, 0u};
+        const uint32_t d = r.deg;
+        const uint64_t off = live ? offs[u] : 0ull;
+        uint32_t x[1] = {kTomb};
+        if (d <= kRowLane && sub < d) {
+            x[0] = g.pool[slot_addr(g, r, sub)];
+            h += mix64((u << 32) | x[0]);
+        }
+        // (the last merge ascends in every group of 16)
+        wave_sort<1, kRowLane / 2>(x, sub);
+        wave_merge<1, 64, kRowLane / 2>(x, sub);
+        if (d <= kRowLane && sub < d) out[off + sub] = x[0];
+        const bool head = sub == 0;
+        uint64_t m = ballot(head && d > kRowLane && d <= kRowMid);
+        while (m) {
+            const int l = __ffsll((unsigned long long)m) - 1;
+            m &= m - 1;
+            VRec w;
+            w.deg = __builtin_amdgcn_readlane(r.deg, l);
+            w.dir = __builtin_amdgcn_readlane(r.dir, l);
+            w.dcls = __builtin_amdgcn_readlane(r.dcls, l);
+            const uint64_t wu = q * 4 + ((uint32_t)l >> 4);
+            uint32_t* wo = out + __shfl((unsigned long long)off, l, 64);
+            if (w.deg <= 64) h += dump_row<1>(g, wu, w, lane, wo);
+            else if (w.deg <= 128) h += dump_row<2>(g, wu, w, lane, wo);
+            else if (w.deg <= 256) h += dump_row<4>(g, wu, w, lane, wo);
+            else if (w.deg <= 512) h += dump_row<8>(g, wu, w, lane, wo);
+            else h += dump_row<16>(g, wu, w, lane, wo);
+        }
+        if (ballot(head && d > kRowMid)) {
+            DevCounters* c = g.ctr;
+            wave_append(head && d > kRowMid && d <= rowbig, (uint32_t)u, &c->row_at[kRowsBig],
+                        big);
+            wave_append(head && d > rowbig, (uint32_t)u, &c->row_at[kRowsHuge], huge);
+        }
+    }
+    h = block_sum(h, lds);
+    if (threadIdx.x == 0 && h) atomicAdd(&g.ctr->stripe[blockIdx.x & 63][kStripeSum], h);
+}
+
+// Rows past kRowMid entries on tables of up to 2^kWinMaxLog vertices: a
+// workgroup per (row, window of 2^kWinLogBits destinations) marks the row's
+// destinations of its window in an LDS bitmap and writes the set bits in
+// order, after the row's destinations below the window (counted on the way).
+// Bound: a sweep of the 128 KB bitmap and a pass over the row, whatever the
+// row's length: 132 us for the 1350 rows of 1025 to 66 thousand entries of
+// R-MAT 2^20 / 2^24, where an LDS bitonic network (225 us) and the one-sweep
+// sort for rows past 16384 (100 us) took longer.  From 2^23 vertices on, with
+// eight windows or more per row, the network is the shorter one.  Word w sits at w + w / 32,
+// so that the 32 words of each thread start in different banks.
+constexpr uint32_t kWinLogBits = 20, kWinMaxLog = 22;
+constexpr uint32_t kWinWords = 1u << (kWinLogBits - 5);
+constexpr uint32_t kWinThreads = 1024, kWinPer = kWinWords / kWinThreads;
+static_assert(kWinPer == 32, "a padding word per thread");
+__global__ __launch_bounds__(kWinThreads) void k_dump_rows_win(GraphView g,
+                                                               const unsigned long long* offs,
+                                                               uint32_t* out,
+                                                               const uint32_t* list,
+                                                               uint32_t rows, uint32_t nwin) {
+    __shared__ uint32_t bm[kWinWords + kWinThreads];
+    __shared__ uint32_t s_w[kWinThreads / 64], s_low;
+    const uint32_t t = threadIdx.x, w = t >> 6;
+    unsigned long long h = 0;
+    for (uint64_t it = blockIdx.x; it < (uint64_t)rows * nwin; it += gridDim.x) {
+        const uint32_t u = list[it / nwin], win = (uint32_t)(it % nwin);
         const VRec r = g.vt[u];
-        for (uint32_t s = lane; s < r.deg; s += 64) {
-            const uint32_t x = g.pool[slot_addr(g, r, s)];
+        uint32_t* o = out + offs[u];
+        for (uint32_t i = t; i < kWinWords + kWinThreads; i += kWinThreads) bm[i] = 0u;
+        if (t == 0) s_low = 0u;
+        __syncthreads();
+        uint32_t low = 0;
+        constexpr uint32_t kU = 8;
+        for (uint32_t s0 = t; s0 < r.deg; s0 += kU * kWinThreads) {
+            uint32_t x[kU];
+#pragma unroll
+            for (uint32_t j = 0; j < kU; ++j)
+                x[j] = g.pool[slot_addr(g, r, min(s0 + j * kWinThreads, r.deg - 1))];
+#pragma unroll
+            for (uint32_t j = 0; j < kU; ++j) {
+                if (s0 + j * kWinThreads >= r.deg) continue;
+                const uint32_t q = x[j] >> kWinLogBits;
+                if (win == 0) h += mix64(((uint64_t)u << 32) | x[j]);
+                low += q < win;
+                if (q == win) {
+                    const uint32_t b = x[j] & ((1u << kWinLogBits) - 1), wd = b >> 5;
+                    atomicOr(&bm[wd + (wd >> 5)], 1u << (b & 31));
+                }
+            }
+        }
+        low = wave_sum(low);
+        if (lane_id() == 0 && low) atomicAdd(&s_low, low);
+        __syncthreads();
+        uint32_t word[kWinPer], cnt = 0;
+#pragma unroll
+        for (uint32_t i = 0; i < kWinPer; ++i) {
+            word[i] = bm[t * (kWinPer + 1) + i];
+            cnt += __popc(word[i]);
+        }
+        const uint32_t inc = wave_incl_scan(cnt);
+        if (lane_id() == 63) s_w[w] = inc;
+        __syncthreads();
+        uint32_t pos = s_low + inc - cnt;
+        for (uint32_t i = 0; i < kWinThreads / 64; ++i) pos += i < w ? s_w[i] : 0u;
+        const uint32_t v0 = (win << kWinLogBits) + t * kWinPer * 32;
+#pragma unroll
+        for (uint32_t i = 0; i < kWinPer; ++i) {
+            uint32_t m = word[i];
+            while (m) {
+                const uint32_t b = __builtin_ctz(m);
+                m &= m - 1;
+                if (pos < r.deg) o[pos] = v0 + i * 32 + b;
+                ++pos;
+            }
+        }
+        __syncthreads();  // the words and sums are used again
+    }
+    h = wave_sum(h);
+    if (lane_id() == 0 && h) atomicAdd(&g.ctr->stripe[(blockIdx.x + w) & 63][kStripeSum], h);
+}
+
+// Rows of kRowMid + 1 to kRowBig entries on larger tables: a workgroup each,
+// a bitonic network on LDS words.
+__global__ __launch_bounds__(kOsThreads) void k_dump_rows_big(GraphView g,
+                                                              const unsigned long long* offs,
+                                                              uint32_t* out, const uint32_t* list,
+                                                              uint32_t rows) {
+    __shared__ uint32_t s[kRowBig];
+    const uint32_t t = threadIdx.x;
+    unsigned long long h = 0;
+    for (uint32_t k = blockIdx.x; k < rows; k += gridDim.x) {
+        const uint64_t u = list[k];
+        const VRec r = g.vt[u];
+        const uint32_t d = min(r.deg, kRowBig);
+        const uint64_t off = offs[u];
+        uint32_t m = 2;
+        while (m < d) m <<= 1;
+        for (uint32_t i = t; i < m; i += kOsThreads) {
+            uint32_t x = kTomb;
+            if (i < d) {
+                x = g.pool[slot_addr(g, r, i)];
+                h += mix64((u << 32) | x);
+            }
+            s[i] = x;
+        }
+        lds_bitonic(s, m, t, kOsThreads);
+        for (uint32_t i = t; i < d; i += kOsThreads) out[off + i] = s[i];
+        __syncthreads();  // the next row reuses the words
+    }
+    h = wave_sum(h);
+    if (lane_id() == 0 && h)
+        atomicAdd(&g.ctr->stripe[(blockIdx.x + (t >> 6)) & 63][kStripeSum], h);
+}
+
+// Rows past kRowBig entries: their (row, destination) keys, kHugeParts
+// workgroups per vertex; hoff[k] = entries of the rows before row k.
+constexpr uint32_t kHugeParts = 64;
+__global__ __launch_bounds__(kThreads) void k_dump_huge_offs(GraphView g, const uint32_t* huge,
+                                                             uint32_t rows,
+                                                             unsigned long long* hoff) {
+    __shared__ unsigned long long lds[kWaves];
+    unsigned long long carry = 0;
+    for (uint32_t b = 0; b < rows; b += kThreads) {
+        const uint32_t k = b + threadIdx.x;
+        const unsigned long long d = k < rows ? g.vt[huge[k]].deg : 0u;
+        unsigned long long tot;
+        const unsigned long long ex = block_excl_scan(d, lds, tot);
+        if (k < rows) hoff[k] = carry + ex;
+        carry += tot;
+    }
+}
+
+__global__ __launch_bounds__(kThreads) void k_dump_huge_gather(GraphView g, const uint32_t* huge,
+                                                               uint32_t rows,
+                                                               const unsigned long long* hoff,
+                                                               uint64_t* keys) {
+    unsigned long long h = 0;
+    const uint32_t part = blockIdx.x % kHugeParts, rowg = gridDim.x / kHugeParts;
+    for (uint32_t k = blockIdx.x / kHugeParts; k < rows; k += rowg) {
+        const uint64_t u = huge[k];
+        const VRec r = g.vt[u];
+        for (uint64_t s = (uint64_t)part * kThreads + threadIdx.x; s < r.deg;
+             s += (uint64_t)kHugeParts * kThreads) {
+            const uint32_t x = g.pool[slot_addr(g, r, (uint32_t)s)];
             h += mix64((u << 32) | x);
-            if (keys) keys[offs[u] + s] = (u << g.L) | x;
+            keys[hoff[k] + s] = ((uint64_t)k << g.L) | x;
         }
     }
     h = wave_sum(h);
-    if (lane == 0 && h) atomicAdd(&g.ctr->checksum, h);
+    if (lane_id() == 0 && h) atomicAdd(&g.ctr->stripe[gwave() & 63][kStripeSum], h);
 }
 
-__global__ __launch_bounds__(kThreads) void k_dump_extract(const uint64_t* keys, uint64_t e,
-                                                           uint32_t L, uint32_t* dst) {
+__global__ __launch_bounds__(kThreads) void k_dump_huge_out(GraphView g, const uint32_t* huge,
+                                                            const unsigned long long* hoff,
+                                                            const unsigned long long* offs,
+                                                            const uint64_t* keys, uint64_t n,
+                                                            uint32_t* out) {
     const uint64_t i = tidx();
-    if (i < e) dst[i] = (uint32_t)(keys[i] & ((1ull << L) - 1));
+    if (i >= n) return;
+    const uint64_t key = keys[i];
+    const uint32_t k = (uint32_t)(key >> g.L);
+    out[offs[huge[k]] + (i - hoff[k])] = (uint32_t)(key & ((1ull << g.L) - 1));
+}
+
+// checksum and edge count added up over the stripes of the last counter read
+static uint64_t stripe_sum(const gv_graph* g, int k) {
+    uint64_t s = 0;
+    for (int i = 0; i < 64; ++i) s += g->hctr->stripe[i][k];
+    return s;
 }
 
 void dump(gv_graph* g, uint64_t* offsets, uint32_t* dst, uint64_t cap, uint64_t* checksum,
           uint64_t* edges) {
     Ctx& c = g->ctx;
     const GraphView& v = g->v;
-    // offsets go to the caller's array, or to scratch when only the count and
-    // checksum are wanted
+    auto count_only = [&] {
+        c.launch("dump_checksum", k_dump_checksum, resident_grid(k_dump_checksum, kThreads),
+                 kThreads, v);
+        read_counters(g);
+        *checksum = stripe_sum(g, kStripeSum);
+        *edges = stripe_sum(g, kStripeEdges);
+    };
+    c.launch("dump_begin", k_dump_begin, 1, kThreads, v);
+    if (!dst || !offsets) return count_only();
+    const bool win = v.L <= kWinMaxLog;  // no row is huge then
+    const uint32_t rowbig = win ? 0xFFFFFFFFu : kRowBig;
     unsigned long long* offs = (unsigned long long*)offsets;
     unsigned long long* part = nullptr;
     {
         auto carve = [&](Carver& cv) {
             part = cv.take<unsigned long long>(scan_partials_needed(v.n_cap + 1));
-            if (!offsets) offs = cv.take<unsigned long long>(v.n_cap + 1);
         };
         Carver mz(nullptr);
         carve(mz);
@@ -368,26 +784,31 @@ void dump(gv_graph* g, uint64_t* offsets, uint32_t* dst, uint64_t cap, uint64_t*
     }
     scan_excl<unsigned long long>(c, DegIn{v}, ArrOut<unsigned long long>{offs}, v.n_cap + 1, part,
                                   &v.ctr->edges);
-    set_u64(g, &v.ctr->checksum, 0);
-    const uint64_t wgrid = std::min<uint64_t>(div_up(v.n_cap, kWaves), 4096);
-    c.launch("dump_checksum", k_dump_gather, wgrid, kThreads, v,
-             (const unsigned long long*)offs, (uint64_t*)nullptr);
+    c.launch("dump_classes", k_dump_classes,
+             std::min<uint64_t>(div_up(v.n_cap, (uint64_t)kThreads * 4), 1024), kThreads, v,
+             rowbig);
     read_counters(g);
     const uint64_t e = g->hctr->edges;
     *edges = e;
-    *checksum = g->hctr->checksum;
-    if (!dst || !offsets) return;
-    if (cap < e) fail(GV_ERANGE, "dump buffer too small");
-    if (e == 0) return;
-    // keys (u << L | x) at CSR positions; one sort then orders the
-    // destinations of every vertex
+    if (cap < e) {
+        count_only();
+        fail(GV_ERANGE, "dump buffer too small");
+    }
+    if (e >= kOsMaxKeys) fail(GV_EINVAL, "2^30 or more edges");
+    const uint64_t nbig = g->hctr->rows[kRowsBig];
+    const uint64_t nhuge = g->hctr->rows[kRowsHuge], ehuge = g->hctr->rows[kHugeEdges];
+    uint32_t *big = nullptr, *huge = nullptr, *state = nullptr;
+    unsigned long long* hoff = nullptr;
     uint64_t *k0 = nullptr, *k1 = nullptr;
-    uint32_t* state = nullptr;
-    const int bits = 2 * (int)v.L;
+    const int bits = (int)v.L + (int)ceil_log2(std::max<uint64_t>(nhuge, 1));
     auto carve2 = [&](Carver& cv) {
-        k0 = cv.take<uint64_t>(e);
-        k1 = cv.take<uint64_t>(e);
-        state = cv.take<uint32_t>(os_words(std::max<uint64_t>(e, 2), bits));
+        big = cv.take<uint32_t>(std::max<uint64_t>(nbig, 1));
+        huge = cv.take<uint32_t>(std::max<uint64_t>(nhuge, 1));
+        if (!nhuge) return;
+        hoff = cv.take<unsigned long long>(nhuge);
+        k0 = cv.take<uint64_t>(ehuge);
+        k1 = cv.take<uint64_t>(ehuge);
+        state = cv.take<uint32_t>(os_words(ehuge, bits));
     };
     {
         Carver mz(nullptr);
@@ -396,12 +817,34 @@ void dump(gv_graph* g, uint64_t* offsets, uint32_t* dst, uint64_t cap, uint64_t*
         Carver cv(g->scratch.ptr);
         carve2(cv);
     }
-    c.launch("dump_gather", k_dump_gather, wgrid, kThreads, v, (const unsigned long long*)offs,
-             k0);
-    const bool flip = e > 1 && sort_keys(g, k0, k1, e, bits, state);
-    c.launch("dump_extract", k_dump_extract, div_up(e, kThreads), kThreads,
-             (const uint64_t*)(flip ? k1 : k0), e, v.L, dst);
-    hip_check(hipStreamSynchronize(c.stream), "hipStreamSynchronize");
+    const unsigned long long* co = offs;
+    c.launch("dump_rows", k_dump_rows,
+             std::min<uint64_t>(div_up(v.n_cap, (uint64_t)kThreads / 16),
+                                resident_grid(k_dump_rows, kThreads)),
+             kThreads, v, co, dst, big, huge, rowbig);
+    if (nbig && win) {
+        const uint32_t nwin = v.L > kWinLogBits ? 1u << (v.L - kWinLogBits) : 1u;
+        c.launch("dump_rows", k_dump_rows_win,
+                 std::min<uint64_t>(nbig * nwin, resident_grid(k_dump_rows_win, kWinThreads)),
+                 kWinThreads, v, co, dst, (const uint32_t*)big, (uint32_t)nbig, nwin);
+    } else if (nbig) {
+        c.launch("dump_rows", k_dump_rows_big,
+                 std::min<uint64_t>(nbig, resident_grid(k_dump_rows_big, kOsThreads)), kOsThreads,
+                 v, co, dst, (const uint32_t*)big, (uint32_t)nbig);
+    }
+    if (nhuge) {
+        const uint32_t gy = (uint32_t)std::min<uint64_t>(nhuge, 1024);
+        c.launch("dump_huge", k_dump_huge_offs, 1, kThreads, v, (const uint32_t*)huge,
+                 (uint32_t)nhuge, hoff);
+        c.launch("dump_huge", k_dump_huge_gather, (uint64_t)gy * kHugeParts, kThreads, v,
+                 (const uint32_t*)huge, (uint32_t)nhuge, (const unsigned long long*)hoff, k0);
+        const bool flip = sort_keys(g, k0, k1, ehuge, bits, state);
+        c.launch("dump_huge", k_dump_huge_out, div_up(ehuge, kThreads), kThreads, v,
+                 (const uint32_t*)huge, (const unsigned long long*)hoff, co,
+                 (const uint64_t*)(flip ? k1 : k0), ehuge, dst);
+    }
+    read_counters(g);
+    *checksum = stripe_sum(g, kStripeSum);
 }
 
 // ------------------------------------------------------------------ adjacency
@@ -692,11 +1135,8 @@ void relayout(gv_graph* g, uint32_t block_slots) {
     hip_check(hipStreamSynchronize(c.stream), "hipStreamSynchronize");
     // from here the old layout is gone: a failure leaves the graph unusable
     g->dead = true;
-    for (void** p : {&g->mem_pool, &g->mem_free, &g->mem_dir, &g->mem_dfree, &g->mem_bown,
-                     &g->mem_apool}) {
-        if (*p) hipFree(*p);
-        *p = nullptr;
-    }
+    dev_free(g->mem_pool, true);  // (the stream was waited for)
+    g->mem_pool = nullptr;
     gv_config cfg{};
     cfg.block_slots = block_slots;
     cfg.pool_bytes = budget;

@@ -648,9 +648,9 @@ int cbt_guarded(gv_cbt* g, F&& f) {
 
 static void cbt_free(gv_cbt* g) {
     if (!g) return;
-    hipStreamSynchronize(g->ctx.stream);
+    const bool idle = hipStreamSynchronize(g->ctx.stream) == hipSuccess && !g->dead;
     g->ctx.release();
-    g->scratch.release();
+    g->scratch.release(idle);
     void* mem[] = {g->mem_pool, g->mem_child, g->mem_queue, g->mem_vt, g->mem_ctr};
     for (void* p : mem)
         if (p) hipFree(p);

@@ -101,6 +101,9 @@ struct DevCounters {
     // verification
     unsigned long long live_edges;     // edges stored
     unsigned long long checksum, edges, violations;
+    // rows of a dump past one wave's registers, counted and listed by class
+    unsigned long long rows[4];
+    uint32_t row_at[4];
     uint32_t vmax, vany;
 };
 

@@ -53,17 +53,12 @@ struct gv_graph {
         unsigned long long capture = 0;
     } ov;
     // device allocations owned by the graph
-    void* mem_pool = nullptr;
-    void* mem_free = nullptr;
-    void* mem_dir = nullptr;
-    void* mem_dfree = nullptr;
+    void* mem_pool = nullptr;   // pool, free list, owners, directory, attributes
     void* mem_vt = nullptr;
     void* mem_active = nullptr;
     void* mem_ctr = nullptr;
     void* mem_chain = nullptr;  // ChainState of the graph's stream
-    void* mem_bown = nullptr;
     void* mem_vlost = nullptr;
-    void* mem_apool = nullptr;
     bool dead = false;            // set after a device failure
 };
 

@@ -209,6 +209,136 @@ struct Carver {
     }
 };
 
+// Large device buffers (a graph's pool and scratch) go through a small cache:
+// a freed one is kept and given to the next request it fits (at most a
+// quarter larger).  hipFree of a buffer past 64 MiB takes about 230 us here,
+// hipMalloc 40 us, and the driver hands freed memory back slowly: a program
+// that builds and drops graphs of 1 GB each waited 18 ms per graph once the
+// card's 288 GB had been through its hands.  What is kept is bounded
+// (kCacheMax over all devices, the oldest goes first), is freed when a
+// request does not fit the card, and is dropped when it was passed over by
+// kCacheAge requests and frees.  Callers free a buffer only after waiting for
+// the streams that used it, so the next owner may use any stream.
+constexpr size_t kCacheMin = (size_t)32 << 20;
+constexpr size_t kCacheMax = (size_t)4 << 30;
+constexpr uint64_t kCacheAge = 64;
+struct DevCache {
+    struct Buf {
+        void* p;
+        size_t bytes;
+        int dev;
+        uint64_t stamp;
+    };
+    std::mutex mu;
+    std::vector<Buf> idle, live;
+    uint64_t clock = 0;
+
+    // takes out of the idle list what is too old or past the bound (the lock
+    // is held; the caller frees it afterwards)
+    void trim(std::vector<Buf>& out, size_t bound) {
+        size_t total = 0;
+        for (size_t i = idle.size(); i-- > 0;) {  // newest last
+            total += idle[i].bytes;
+            if (total > bound || clock - idle[i].stamp > kCacheAge) {
+                total -= idle[i].bytes;
+                out.push_back(idle[i]);
+                idle.erase(idle.begin() + (long)i);
+            }
+        }
+    }
+};
+
+inline DevCache& dev_cache() {
+    static DevCache* c = new DevCache;  // outlives every graph
+    return *c;
+}
+
+inline void dev_free_all(const std::vector<DevCache::Buf>& bufs) {
+    for (const DevCache::Buf& b : bufs) (void)hipFree(b.p);
+}
+
+inline void dev_malloc(void** out, size_t bytes, const char* what) {
+    if (bytes < kCacheMin) {
+        hip_check(hipMalloc(out, bytes), what);
+        return;
+    }
+    int dev = 0;
+    hip_check(hipGetDevice(&dev), "hipGetDevice");
+    DevCache& c = dev_cache();
+    std::vector<DevCache::Buf> old;
+    bool got = false;
+    {
+        std::lock_guard<std::mutex> lock(c.mu);
+        ++c.clock;
+        size_t best = c.idle.size();
+        for (size_t i = 0; i < c.idle.size(); ++i) {
+            const DevCache::Buf& b = c.idle[i];
+            if (b.dev == dev && b.bytes >= bytes && b.bytes <= bytes + bytes / 4 &&
+                (best == c.idle.size() || b.bytes < c.idle[best].bytes))
+                best = i;
+        }
+        c.live.reserve(c.live.size() + 1);
+        if (best < c.idle.size()) {
+            *out = c.idle[best].p;
+            c.live.push_back(c.idle[best]);
+            c.idle.erase(c.idle.begin() + (long)best);
+            got = true;
+        }
+        old.reserve(c.idle.size());
+        c.trim(old, kCacheMax);
+    }
+    dev_free_all(old);
+    if (got) return;
+    hipError_t e = hipMalloc(out, bytes);
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        old.clear();
+        {
+            std::lock_guard<std::mutex> lock(c.mu);
+            old.reserve(c.idle.size());
+            c.trim(old, 0);
+        }
+        dev_free_all(old);
+        e = hipMalloc(out, bytes);
+    }
+    hip_check(e, what);
+    std::lock_guard<std::mutex> lock(c.mu);
+    try {
+        c.live.push_back({*out, bytes, dev, 0});
+    } catch (...) {
+        // not listed: dev_free then frees it at once
+    }
+}
+
+// `reuse`: the streams that used the buffer were waited for
+inline void dev_free(void* p, bool reuse) {
+    if (!p) return;
+    DevCache& c = dev_cache();
+    std::vector<DevCache::Buf> old;
+    {
+        std::lock_guard<std::mutex> lock(c.mu);
+        ++c.clock;
+        for (size_t i = 0; i < c.live.size(); ++i) {
+            if (c.live[i].p != p) continue;
+            DevCache::Buf b = c.live[i];
+            c.live.erase(c.live.begin() + (long)i);
+            if (reuse && b.bytes <= kCacheMax) {
+                b.stamp = c.clock;
+                try {
+                    old.reserve(c.idle.size() + 1);
+                    c.idle.push_back(b);
+                    p = nullptr;
+                } catch (...) {
+                }
+            }
+            break;
+        }
+        if (!p) c.trim(old, kCacheMax);
+    }
+    dev_free_all(old);
+    if (p) (void)hipFree(p);
+}
+
 // Growable device scratch buffer owned by a graph.
 struct Scratch {
     void* ptr = nullptr;
@@ -218,17 +348,17 @@ struct Scratch {
         if (bytes <= cap) return;
         if (ptr) {
             hip_check(hipStreamSynchronize(s), "hipStreamSynchronize");
-            hip_check(hipFree(ptr), "hipFree");
+            dev_free(ptr, true);
             ptr = nullptr;
             cap = 0;
         }
         size_t want = bytes + bytes / 4 + (1 << 20);
-        hip_check(hipMalloc(&ptr, want), "hipMalloc scratch");
+        dev_malloc(&ptr, want, "hipMalloc scratch");
         cap = want;
         ++gen;
     }
-    void release() {
-        if (ptr) hipFree(ptr);
+    void release(bool reuse) {
+        dev_free(ptr, reuse);
         ptr = nullptr;
         cap = 0;
     }

@@ -334,18 +334,41 @@ __global__ __launch_bounds__(kThreads) void k_scan2_reduce(In in, uint64_t n,
 }
 
 // Exclusive scan of the nt tile sums in place (one workgroup), for inputs
-// with more tiles than the apply kernel adds up itself.
-static __global__ __launch_bounds__(kThreads) void k_scan2_partials(unsigned long long* part,
-                                                                    uint64_t nt) {
-    __shared__ unsigned long long lds[kWaves];
+// with more tiles than the apply kernel adds up itself.  A serial chain of
+// rounds: 1024 threads take 8 sums each per round, so 4900 tiles (10^7
+// elements) are one round of 6 us (256 threads with one sum each took 46).
+constexpr int kPartThreads = 1024, kPartItems = 8;
+static __global__ __launch_bounds__(kPartThreads) void k_scan2_partials(unsigned long long* part,
+                                                                        uint64_t nt) {
+    __shared__ unsigned long long lds[kPartThreads / 64];
     unsigned long long carry = 0;
-    for (uint64_t b = 0; b < nt; b += kThreads) {
-        const uint64_t i = b + threadIdx.x;
-        const unsigned long long x = i < nt ? part[i] : 0ull;
-        unsigned long long tot;
-        const unsigned long long ex = block_excl_scan(x, lds, tot);
-        if (i < nt) part[i] = carry + ex;
-        carry += tot;
+    const int w = threadIdx.x >> 6;
+    for (uint64_t b = 0; b < nt; b += (uint64_t)kPartThreads * kPartItems) {
+        const uint64_t i0 = b + (uint64_t)threadIdx.x * kPartItems;
+        unsigned long long x[kPartItems], sum = 0;
+#pragma unroll
+        for (int j = 0; j < kPartItems; ++j) x[j] = part[i0 + j < nt ? i0 + j : nt - 1];
+#pragma unroll
+        for (int j = 0; j < kPartItems; ++j) {
+            x[j] = i0 + j < nt ? x[j] : 0ull;
+            sum += x[j];
+        }
+        const unsigned long long inc = wave_incl_scan(sum);
+        if (lane_id() == 63) lds[w] = inc;
+        __syncthreads();
+        unsigned long long run = carry + inc - sum;
+#pragma unroll
+        for (int k = 0; k < kPartThreads / 64; ++k) {
+            const unsigned long long v = lds[k];
+            run += k < w ? v : 0ull;
+            carry += v;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < kPartItems; ++j) {
+            if (i0 + j < nt) part[i0 + j] = run;
+            run += x[j];
+        }
     }
 }
 
@@ -548,7 +571,7 @@ __global__ __launch_bounds__(kThreads) void k_scan2_chain(In in, Out out, uint64
 }
 
 // tiles the apply kernel adds up itself; beyond, a middle kernel scans them
-constexpr uint64_t kScan2MaxTiles = 8192;
+constexpr uint64_t kScan2MaxTiles = 2048;
 // partial words any scan2 over n elements needs
 inline uint64_t scan2_parts(uint64_t n) {
     return div_up(std::max<uint64_t>(n, 1), (uint64_t)kThreads * kScan2MinItems);
@@ -582,7 +605,7 @@ void scan2(Ctx& c, const char* name, In in, Out out, uint64_t n, unsigned long l
     // a single tile adds no earlier partials: the apply kernel is the scan
     if (nt > 1) c.launch(name, k_scan2_reduce<In>, nt, kThreads, in, n, part);
     const int scanned = nt > kScan2MaxTiles ? 1 : 0;
-    if (scanned) c.launch(name, k_scan2_partials, 1, kThreads, part, nt);
+    if (scanned) c.launch(name, k_scan2_partials, 1, kPartThreads, part, nt);
     c.launch(name, k_scan2_apply<In, Out>, nt, kThreads, in, out, n,
              (const unsigned long long*)part, scanned, total);
 }
