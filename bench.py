@@ -102,16 +102,17 @@ def bytes_model(name, per_launch):
         # packing kernel (and the valid-pair counts) into the pass histograms
         return 4 * 256 * P * (groups + 1) + 4 * groups
     if name == "pack":
-        # pairs in, keys and mark bytes out, the batch's look-back state
-        # cleared, per-group digit counts out
-        return 8 * k + 8 * k + k + 4 * (64 + P * tiles * 256 + P * ((tiles + 15) // 16) * 256) \
+        # pairs in, keys out, the batch's look-back state cleared, per-group
+        # digit counts out
+        return 8 * k + 8 * k + 4 * (64 + P * tiles * 256 + P * ((tiles + 15) // 16) * 256) \
             + 4 * 256 * P * groups
     if name == "segments":
-        return 8 * k + k + 4 * k + 8 * T  # keys in; flags, ranks, segment starts out
-    if name == "items":
-        return 8 * T + 16 * T + 32 * T  # segment list, vertex records, items out
-    if name == "append":
-        return k + k + 4 * k + 4 * per_launch["W"] + 16 * T
+        # keys and vertex records in; marks, source records, work items out
+        return 8 * k + k + 16 * T + 32 * T + 32 * T
+    if name in ("plan_insert", "plan_delete"):
+        return k + 32 * T + 8 * T  # marks and source records in, their plan out
+    if name == "commit":
+        return 8 * k + k + 32 * T + 4 * per_launch["W"] + 16 * T
     if name == "compact":
         return 8 * per_launch["M"] + 16 * T + 4 * per_launch["FREED"]
     return None
@@ -276,7 +277,7 @@ KERNEL_SYMBOLS = {
     "probe_delete": "gv::k_probe<1,",
     "probe_query": "gv::k_probe<2,",
     "compact": "gv::k_compact(",
-    "append": "gv::k_append(",
+    "commit": "gv::k_commit<",
 }
 
 
@@ -684,7 +685,7 @@ def main():
     if args.summarize_traffic:
         k = args.batch
         grid = {"sort_pass": (k + 4095) // 4096, "probe_insert": None, "probe_delete": None,
-                "probe_query": None, "compact": None, "append": (k + 255) // 256,
+                "probe_query": None, "compact": None, "commit": None,
                 "sort_hist": None, "pack": min((k + 4095) // 4096, 256)}
         summarize_traffic(*args.summarize_traffic[:4], grid, args.summarize_traffic[4],
                           args.command)

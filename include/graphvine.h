@@ -343,7 +343,9 @@ typedef struct {
  *   max_run_pairs  longest run coalesced, in pairs (0: 2^28; a batch
  *                  longer than the limit runs alone)
  *   small_sort_max insert / delete batches of at most this many pairs
- *                  (<= 4096) are packed and sorted by one workgroup
+ *                  (<= 4096) are packed and sorted by rank in one kernel; the
+ *                  largest value, 4096, stands for the library's own limit
+ *                  (16384 pairs) while overlap is 0
  *   probe_group    lanes that probe one work item against its batch
  *                  segment: 16, 32 (default) or 64
  *   probe_unroll   adjacency slots per lane per search step: 2, 4 (default)

@@ -279,7 +279,7 @@ int gv_set_edge_attrs(gv_graph* g, const uint32_t* d_src, const uint32_t* d_dst,
         if (st) {
             read_counters(g);
             check_sort(g);
-            const uint64_t valid = g->hctr->tot[0];  // valid pairs of the batch
+            const uint64_t valid = g->hctr->st_valid;
             st->applied = g->hctr->st_applied;
             st->rejected = n - valid;
             st->batch_duplicates = valid - g->hctr->n_uniq;

@@ -77,20 +77,16 @@ struct DevCounters {
     uint32_t plan_dtop[kMaxClass];     // dfree_cnt before the batch
     uint32_t plan_dff[kMaxClass];      // segments popped per class
     unsigned long long plan_dbump[kMaxClass]; // first bump offset per class
-    // sizes of the current batch
-    uint32_t n_valid, n_T, n_items, n_aux;
+    // distinct ids of a vertex batch, distinct pairs of an attribute write
     unsigned long long n_uniq;
-    uint32_t sum_a, sum_b;             // scan totals of the current batch
     // errors: err_batch is reset per batch, err_sticky accumulates; err_wait
     // is set if a bounded look-back wait ever ran out
-    uint32_t err_batch, err_sticky, err_wait, n_big;
-    uint32_t n_heavy;                  // sources left to whole waves this batch
+    uint32_t err_batch, err_sticky, err_wait;
     uint32_t err_order;                // a batch's sorted keys failed their check
     uint32_t sort_n, sort_err;  // count and look-back error word of whole-graph sorts
     // vertex delete: slots hit, vertices touched, hole entries reserved
     unsigned long long vd_hits, vd_touched, vd_pairs;
-    // totals of the single-pass scans of the current batch
-    unsigned long long tot[8];
+    unsigned long long st_valid;       // valid pairs of the last attribute write
     // statistics of the last batch
     unsigned long long st_applied, st_rejected, st_dups;
     // cumulative work counters

@@ -2,41 +2,41 @@
 //
 // One pipeline serves the three operations (GraphVine Sec. 4.5-4.6, Alg. 1-3,
 // re-designed for wave64):
-//   pack      insert / delete: one kernel validates each pair against the
-//             activity bitmap and writes its key (src << L) | dst in place
-//             (an invalid pair gets the all-ones key, which sorts last),
-//             clears the batch's look-back state and counters and counts
-//             the sort's digits per workgroup.  Query: a kernel clears the
-//             state, then a two-kernel scan writes the valid pairs,
-//             compacted, with their input positions (invalid pairs are
-//             answered 0 right away).
-//   sort      onesweep LSD radix sort of the valid keys on 2L bits: the batch
-//             is grouped by source and ordered by destination inside each
-//             source segment (the paper's host CSR conversion, Sec. 4.3).
-//   segments  scan over the sorted keys: segment heads give the touched
-//             sources T and their segment starts; first occurrences give the
-//             distinct pairs.
-//   items     scan over T: each touched adjacency is cut into work items of
-//             `chunk` slots, written as self-contained 32-byte descriptors
-//             (slot range, batch segment, block directory); a source with a
-//             single small block and a short segment becomes one small item.
-//   probe     small items one per lane (slots and segment loaded whole, all
-//             pairs compared); the others by lane groups that stage the
-//             segment's destinations in LDS, stream slots (directory entry,
-//             then slot) and binary-search each slot value.
+//   pack +    every pair is checked against the activity bitmap and becomes the
+//   sort      key (src << L) | dst; an invalid pair gets a key past every valid
+//             one.  Up to kRankMax pairs one kernel packs and sorts by rank;
+//             larger batches are packed with the digit counts and go through
+//             the onesweep LSD radix sort (queries compact their valid pairs
+//             with their input positions first).  The batch is then grouped by
+//             source and ordered by destination inside each source segment
+//             (the paper's host CSR conversion, Sec. 4.3).
+//   segments  one kernel over tiles of the sorted keys: segment heads give the
+//             touched sources T (a 32-byte record each: segment, vertex record)
+//             and repeated pairs; each touched adjacency is cut into work
+//             items of `chunk` slots.  A tile takes its sources' and items'
+//             places with one atomic each, so T is in tile order only inside a
+//             tile, and no scan over the batch is needed.
+//   probe     sources with few slots and a short segment by four lanes each
+//             (slots and segment loaded whole, all pairs compared); the others
+//             by lane groups that stage the segment's destinations in LDS,
+//             stream slots (directory entry, then slot) and binary-search each
+//             slot value.
 //             Insert: mark batch entries that already exist (set semantics).
 //             Delete: mark hits, remember their slot, tombstone the slot.
 //             Query:  mark every query equal to a stored edge.
-//   insert:   keep = first occurrence and not present (scan); per-source
-//             block demand and directory growth; a one-wave plan, run by the
-//             demand scan's last workgroup, checks capacity before any state
-//             is written (all-or-nothing); blocks come from the free-list top
-//             first, then the bump pointer (the prefix-sum pop of Sec. 4.5.1,
-//             without atomics); append; grow; old directory segments freed.
+//   plan      insert and delete, the same tiles: each source's kept pairs
+//             (neither repeated nor present) or hits, block demand or freed
+//             blocks, directory growth; the tile's share is placed with one
+//             atomic.  The last tile to finish runs the one-wave plan: an
+//             insert checks capacity before any state is written
+//             (all-or-nothing; blocks come from the free-list top first, then
+//             the bump pointer: the prefix-sum pop of Sec. 4.5.1).
+//   insert:   commit: kept pairs to slots deg + rank, new block ids,
+//             directory moves and vertex records; old directory segments freed.
 //   delete:   per-source compaction pairs the holes below the new degree with
 //             the survivors above it, by rank (one launch: a workgroup per
 //             hub first, then lanes and waves for the other sources); emptied
-//             blocks are pushed on the free list at scanned positions
+//             blocks are pushed on the free list at planned positions
 //             (reclamation, Sec. 4.2).
 //   query:    answers are scattered back to input order.
 #include <algorithm>
@@ -47,7 +47,6 @@
 
 namespace gv {
 
-constexpr uint8_t kHead = 1, kUniq = 2;
 // The probe's shape is picked at run time (gv_tuning) among compiled
 // variants: G lanes per work item (16, 32, 64) and U slots per lane per step
 // (2, 4, 8).
@@ -72,16 +71,34 @@ constexpr uint32_t kRelease = 0x80000000u;     // flag bit in the per-source dem
 constexpr uint32_t kHeavy = 0x100u;            // flag bit in t_dreq: whole waves grow this source
 constexpr uint32_t kClassMask = 0xFFu;         // t_dreq & kClassMask: requested class or kNoDir
 
-// scan-total slots in DevCounters::tot
-enum {
-    kTotValid = 0, kTotSeg = 1, kTotItems = 2, kTotA = 3, kTotB = 4, kTotHash = 5,
-    kTotNoHash = 6  // set for a batch whose keys arrived sorted: no multiset check
-};
 // probe mode of the attribute calls: a query that also records the slot of
 // every occurrence it finds
 constexpr int kLocate = 3;
-// stripe[k][kStripeHash]: per-workgroup sums of mix64 over the sorted keys
-constexpr int kStripeHash = 1;
+
+// Counters of one batch, in the batch's own buffer (with the sort overlap on,
+// a batch's packing clears them while the batch before it still uses its
+// own), cleared by its first kernel.  Every word that a kernel adds to from
+// all of its workgroups and then uses is a word of its own that each
+// workgroup touches once.
+struct alignas(128) BatchCtr {
+    unsigned long long n_valid, key_sum;  // valid pairs, and the mix64 sum of their keys
+    unsigned long long alloc_t;           // touched sources placed
+    uint32_t n_big, n_heavy;              // sources left to workgroups / to whole waves
+    uint32_t nohash, pad0;                // keys arrived sorted: no multiset check
+    unsigned long long pad1[11];
+    unsigned long long alloc_i;           // work items placed
+    unsigned long long pad2[15];
+    // insert: blocks needed (low), directory segments given back (high);
+    // delete: blocks freed (low), sources for whole waves (high)
+    unsigned long long demand;
+    unsigned long long pad3[15];
+    unsigned long long changed;           // pairs kept (insert), hits (delete)
+    unsigned long long pad4[15];
+    unsigned long long done;              // tiles planned
+    unsigned long long pad5[15];
+    unsigned long long stripe[64][16];    // kStripe* sums, a line each
+};
+enum { kStripeHash = 0, kStripeUniq = 1, kStripeBlocks = 2 };
 
 // self-contained work item: slots [s0, s1) of vertex v, batch segment [lo, hi);
 // block j is dir[dirbase + j] when the vertex has a directory segment, else
@@ -91,11 +108,19 @@ struct alignas(16) Item {
     uint32_t v, dirbase, blk0, dcls;
 };
 
-// per-source compaction descriptor (delete)
-struct alignas(16) CDesc {
+// A touched source: its batch segment [lo, hi), its vertex record as it was
+// before the batch, then (plan) its kept pairs or hits r and the first of its
+// blocks, needed or freed, among those of the tile that holds lo.
+struct alignas(16) Src {
     uint32_t lo, hi, r, v;
     uint32_t deg, dir, dcls, need;
 };
+
+// Tiles of sorted positions: the segments, plan and commit kernels of a batch
+// take one workgroup per tile of 2^tl positions.
+constexpr uint32_t kTileLogMin = 6, kTileLogMax = 12;
+constexpr uint32_t kTileMax = 1u << kTileLogMax;
+constexpr uint32_t kTileRows = 4;  // positions per thread, at most
 
 // attribute call of a query batch: get (out) or set (in), n * A words
 struct AttrOp {
@@ -104,62 +129,69 @@ struct AttrOp {
 };
 
 struct BatchArrays {
+    BatchCtr* bc;
     uint64_t* keys0;
     uint64_t* keys1;
     uint32_t* vals0;
     uint32_t* vals1;
-    uint8_t* flags;
     uint8_t* mark;
-    uint32_t* a;        // segment index of each valid key
-    uint32_t* b;        // n+1: exclusive count of kept (insert) / found (delete)
     uint32_t* hitpos;   // delete, attribute calls: slot index of each hit
     uint32_t* holes;    // delete: hole slots per segment
-    uint32_t* t_vtx;    // touched source per segment
-    uint32_t* t_start;  // n+1: segment start; t_start[n_T] = n_valid
-    uint32_t* t_need;   // n+1: blocks needed (insert), scanned
+    Src* srcs;          // touched sources
+    uint2* tiles;       // per tile: its first source, its sources
+    uint2* carry;       // insert, per tile: the source whose segment runs into
+                        // the tile, and that source's kept pairs before it
+    uint32_t* tbase;    // per tile: first of its blocks among the batch's
     uint32_t* t_dreq;   // insert: requested directory class or kNoDir
     uint32_t* t_drank;  // insert: rank among requests of that class
     uint32_t* t_dold;   // insert: replaced directory segment offset
     uint32_t* t_doldc;  // insert: replaced directory segment class or kNoDir
     uint32_t* rel;      // insert: sources that give back a directory segment
-    CDesc* cdesc;       // delete: compaction descriptors
     uint32_t* big;      // delete: sources with more than kBigR hits
     uint32_t* heavy;    // sources left to whole waves
     Item* items;        // work items
-    Item* small;        // per touched source: its small item or an empty entry
-    unsigned long long* part;  // scan partials
+    unsigned long long* part;  // scan partials (query)
     uint32_t* state;    // zeroed look-back state of the sort
     uint64_t state_words;
     uint32_t* vpart;    // insert / delete: valid pairs per packing workgroup
     unsigned long long* hpart;  // insert / delete: mix64 sum of valid keys per packing workgroup
-    unsigned long long* stot;   // overlapped sort: valid pairs and their mix64 sum
 };
+
+// log2 of the positions per tile for a batch of n pairs: about 512 tiles, so
+// that two workgroups per compute unit share the work, between one wave's
+// width (smaller tiles would only add workgroups) and the LDS arrays' size.
+static uint32_t tile_log(uint64_t n) {
+    uint32_t tl = kTileLogMin;
+    while (tl < kTileLogMax && (n >> tl) > 512) ++tl;
+    return tl;
+}
 
 static void carve_batch(Carver& cv, BatchArrays& A, uint64_t n, uint64_t icap, EdgeMode mode,
                         int bits) {
     A = BatchArrays{};
+    const uint64_t nt = div_up(n, 1ull << tile_log(n));
+    A.bc = cv.take<BatchCtr>(1);
     A.keys0 = cv.take<uint64_t>(n);
     A.keys1 = cv.take<uint64_t>(n);
     if (mode == kQuery) {
         A.vals0 = cv.take<uint32_t>(n);
         A.vals1 = cv.take<uint32_t>(n);
+        A.part = cv.take<unsigned long long>(scan2_parts(n));
     }
-    A.flags = cv.take<uint8_t>(n);
     A.mark = cv.take<uint8_t>(n);
-    A.a = cv.take<uint32_t>(n);
-    A.b = cv.take<uint32_t>(n + 1);
-    if (mode == kQuery) A.hitpos = cv.take<uint32_t>(n);  // attribute calls
+    if (mode != kInsert) A.hitpos = cv.take<uint32_t>(n);  // (query: attribute calls)
     if (mode == kDelete) {
-        A.hitpos = cv.take<uint32_t>(n);
         A.holes = cv.take<uint32_t>(n);
-        A.cdesc = cv.take<CDesc>(n);
         A.big = cv.take<uint32_t>(n);
     }
-    A.heavy = cv.take<uint32_t>(n);
-    A.t_vtx = cv.take<uint32_t>(n);
-    A.t_start = cv.take<uint32_t>(n + 1);
-    A.t_need = cv.take<uint32_t>(n + 1);
+    if (mode != kQuery) {
+        A.heavy = cv.take<uint32_t>(n);
+        A.tbase = cv.take<uint32_t>(nt);
+    }
+    A.srcs = cv.take<Src>(n);
+    A.tiles = cv.take<uint2>(nt);
     if (mode == kInsert) {
+        A.carry = cv.take<uint2>(nt);
         A.t_dreq = cv.take<uint32_t>(n);
         A.t_drank = cv.take<uint32_t>(n);
         A.t_dold = cv.take<uint32_t>(n);
@@ -167,13 +199,10 @@ static void carve_batch(Carver& cv, BatchArrays& A, uint64_t n, uint64_t icap, E
         A.rel = cv.take<uint32_t>(n);
     }
     A.items = cv.take<Item>(icap);
-    A.small = cv.take<Item>(n);
-    A.part = cv.take<unsigned long long>(scan2_parts(n + 1));
     A.state_words = os_zero_words(n, bits);  // the part the batch zeroes
     A.state = cv.take<uint32_t>(os_words(n, bits));
     A.vpart = cv.take<uint32_t>(kHistGroups);
     A.hpart = cv.take<unsigned long long>(kHistGroups);
-    A.stot = cv.take<unsigned long long>(2);
 }
 
 __device__ __forceinline__ uint64_t thread_index() {
@@ -185,22 +214,17 @@ __device__ __forceinline__ uint32_t global_wave() {
 }
 
 // ------------------------------------------------------------------ begin
-// Per-batch counters, cleared by the first kernel of a batch (threads 0..63
-// of its first workgroup).
-__device__ __forceinline__ void clear_batch_counters(DevCounters* c, uint32_t t) {
-    if (t == 0) {
-        c->err_batch = 0;
-        c->n_big = 0;
-        c->n_heavy = 0;
-        for (int k = 0; k < 8; ++k) c->tot[k] = 0;
-    }
-    if (t < 64) c->stripe[t][kStripeHash] = 0;
+// Clears the batch's counters; called by one whole workgroup of nt threads.
+__device__ __forceinline__ void clear_batch(BatchCtr* bc, uint32_t t, uint32_t nt) {
+    uint32_t* w = (uint32_t*)bc;
+    for (uint32_t i = t; i < sizeof(BatchCtr) / 4; i += nt) w[i] = 0u;
 }
 
-__global__ __launch_bounds__(kThreads) void k_begin(GraphView g, uint32_t* state, uint64_t words) {
+__global__ __launch_bounds__(kThreads) void k_begin(BatchCtr* bc, uint32_t* state,
+                                                    uint64_t words) {
     const uint64_t stride = (uint64_t)gridDim.x * kThreads;
     for (uint64_t i = thread_index(); i < words; i += stride) state[i] = 0;
-    if (blockIdx.x == 0) clear_batch_counters(g.ctr, threadIdx.x);
+    if (blockIdx.x == 0) clear_batch(bc, threadIdx.x, kThreads);
 }
 
 // ------------------------------------------------------------------ pack
@@ -226,10 +250,8 @@ struct PackOut {
     uint64_t* keys;
     uint32_t* vals;     // queries: input position of each valid key
     uint8_t* answer;    // queries: invalid pairs are answered here
-    uint8_t* mark;
     __device__ void operator()(uint64_t i, const PackIn::Rec& r, uint64_t,
                                unsigned long long pos) const {
-        mark[i] = 0;
         if (r.ok) {
             keys[pos] = ((uint64_t)r.s << L) | r.d;
             if (vals) vals[pos] = (uint32_t)i;
@@ -244,17 +266,16 @@ struct PackOut {
 // all-ones key of the sort's bit width, which sorts after every valid key.
 // All such keys are equal, so whether or not a valid pair shares that key,
 // the first n_valid sorted keys are exactly the valid ones.  The same kernel
-// clears the batch's look-back state (and, with clear_ctr, the batch
-// counters) and counts the sort's digits (per workgroup, summed by the next
-// kernel together with the valid pairs).
+// clears the batch's look-back state and counters and counts the sort's
+// digits (per workgroup, summed by the next kernel together with the valid
+// pairs).
 __global__ __launch_bounds__(kOsThreads) void k_pack_hist(GraphView g, const uint32_t* src,
                                                           const uint32_t* dst, uint64_t n,
                                                           int passes, uint64_t sentinel,
-                                                          uint64_t* keys, uint8_t* mark,
+                                                          uint64_t* keys, BatchCtr* bc,
                                                           uint32_t* state, uint64_t zero_words,
                                                           uint32_t* hpart, uint32_t* vpart,
-                                                          unsigned long long* kpart,
-                                                          int clear_ctr) {
+                                                          unsigned long long* kpart) {
     __shared__ uint32_t h[kOsHistCopies][8][kRadix];
     __shared__ uint32_t s_v[kOsWaves];
     __shared__ unsigned long long s_k[kOsWaves];
@@ -262,7 +283,7 @@ __global__ __launch_bounds__(kOsThreads) void k_pack_hist(GraphView g, const uin
     for (uint64_t i = (uint64_t)blockIdx.x * kOsThreads + t; i < zero_words;
          i += (uint64_t)gridDim.x * kOsThreads)
         state[i] = 0;
-    if (clear_ctr && blockIdx.x == 0) clear_batch_counters(g.ctr, t);
+    if (blockIdx.x == 0) clear_batch(bc, t, kOsThreads);
     for (int i = t; i < kOsHistCopies * 8 * kRadix; i += kOsThreads) (&h[0][0][0])[i] = 0;
     __syncthreads();
     const uint32_t copy = kOsHistCopies == 1 ? 0u : (t >> 6) & (kOsHistCopies - 1);
@@ -287,7 +308,6 @@ __global__ __launch_bounds__(kOsThreads) void k_pack_hist(GraphView g, const uin
             if (i >= n) continue;
             const uint64_t key = ok[j] ? ((uint64_t)su[j] << g.L) | du[j] : sentinel;
             keys[i] = key;
-            mark[i] = 0;
             valid += ok[j] ? 1u : 0u;
             khash += ok[j] ? mix64(key) : 0ull;
             for (int p = 0; p < passes; ++p)
@@ -320,203 +340,34 @@ __global__ __launch_bounds__(kOsThreads) void k_pack_hist(GraphView g, const uin
     }
 }
 
-// Insert and delete batches of at most kOsTile pairs: one workgroup packs
-// the pairs as k_pack_hist does and sorts the keys in LDS, every radix pass
-// in the same kernel (the ranking of k_os_pass on a single tile, so no
-// look-back), instead of the pack, histogram and pass kernels.  Writes the
-// sorted keys to `keys` and the valid-pair count to tot[kTotValid].
-__global__ __launch_bounds__(kOsThreads) void k_pack_sort_tile(GraphView g, const uint32_t* src,
-                                                               const uint32_t* dst, uint64_t n,
-                                                               int passes, uint64_t sentinel,
-                                                               uint64_t* keys, uint8_t* mark) {
-    __shared__ TileSortLds lds;
-    __shared__ unsigned long long s_v[kOsWaves];
-    const uint32_t t = threadIdx.x;
-    const int w = t >> 6;
-    clear_batch_counters(g.ctr, t);
-    uint64_t key[kOsRounds];
-    unsigned long long valid = 0, khash = 0;
-#pragma unroll
-    for (int j = 0; j < kOsRounds; ++j) {
-        const uint64_t i = (uint64_t)j * kOsThreads + t;
-        const uint32_t su = i < n ? src[i] : 0u, du = i < n ? dst[i] : 0u;
-        const bool ok = active_bit(g, su) & active_bit(g, du);
-        key[j] = ok ? ((uint64_t)su << g.L) | du : sentinel;
-        if (i < n) {
-            mark[i] = 0;
-            valid += ok ? 1u : 0u;
-            khash += ok ? mix64(key[j]) : 0ull;
-        }
+// Batches of at most kRankMax pairs: packed and sorted by rank (gv_prim.h).
+struct EdgeKeys {
+    GraphView g;
+    const uint32_t* src;
+    const uint32_t* dst;
+    uint8_t* answer;  // queries: invalid pairs are answered here
+    BatchCtr* bc;
+    __device__ uint64_t load(uint64_t i) const {
+        const uint32_t s = src[i], d = dst[i];
+        const bool ok = active_bit(g, s) & active_bit(g, d);
+        return ok ? ((uint64_t)s << g.L) | d : 1ull << (2 * g.L);
     }
-    tile_sort(key, n, passes, sentinel, lds);
-#pragma unroll
-    for (int j = 0; j < kOsRounds; ++j) {
-        const uint64_t i = (uint64_t)j * kOsThreads + t;
-        if (i < n) keys[i] = key[j];
+    __device__ void own(uint64_t i, uint64_t key) const {
+        if (answer && (key >> (2 * g.L))) answer[i] = 0;
     }
-    valid = wave_sum(valid);
-    khash = wave_sum(khash);
-    __shared__ unsigned long long s_k[kOsWaves];
-    if (lane_id() == 0) {
-        s_v[w] = valid;
-        s_k[w] = khash;
+    // by the first workgroup, which sees every key
+    __device__ void begin(uint32_t t, uint32_t nt) const { clear_batch(bc, t, nt); }
+    __device__ bool counted(uint64_t key) const { return (key >> (2 * g.L)) == 0; }
+    __device__ void totals(unsigned long long n, unsigned long long sum) const {
+        bc->n_valid = n;
+        bc->key_sum = sum;
     }
-    __syncthreads();
-    if (t == 0) {
-        unsigned long long x = 0, y = 0;
-        for (int k = 0; k < kOsWaves; ++k) {
-            x += s_v[k];
-            y += s_k[k];
-        }
-        g.ctr->tot[kTotValid] = x;
-        g.ctr->tot[kTotHash] = y;
-    }
-}
-
-// Query batches of at most kOsTile pairs: one workgroup packs each valid pair
-// as its key with its input position in the low 12 bits (an invalid pair is
-// answered 0 here and gets the all-ones key, after every valid one), sorts
-// the tile in LDS, and writes the valid keys and their positions compacted,
-// as the packing scan and the sort leave them.
-constexpr int kTilePosBits = 12;  // kOsTile = 4096 positions
-__global__ __launch_bounds__(kOsThreads) void k_query_sort_tile(GraphView g, const uint32_t* src,
-                                                                const uint32_t* dst, uint64_t n,
-                                                                int passes, uint64_t* keys,
-                                                                uint32_t* vals, uint8_t* answer,
-                                                                uint8_t* mark) {
-    __shared__ TileSortLds lds;
-    __shared__ uint32_t s_v[kOsWaves];
-    const uint32_t t = threadIdx.x;
-    clear_batch_counters(g.ctr, t);
-    uint64_t key[kOsRounds];
-    uint32_t valid = 0;
-#pragma unroll
-    for (int j = 0; j < kOsRounds; ++j) {
-        const uint64_t i = (uint64_t)j * kOsThreads + t;
-        const uint32_t su = i < n ? src[i] : 0u, du = i < n ? dst[i] : 0u;
-        const bool ok = i < n && active_bit(g, su) && active_bit(g, du);
-        key[j] = ok ? ((((uint64_t)su << g.L) | du) << kTilePosBits) | i : ~0ull;
-        if (i < n) {
-            mark[i] = 0;
-            if (!ok && answer) answer[i] = 0;
-        }
-        valid += ok ? 1u : 0u;
-    }
-    tile_sort(key, n, passes, ~0ull, lds);
-    const uint32_t vw = (uint32_t)wave_sum((unsigned long long)valid);
-    if (lane_id() == 0) s_v[t >> 6] = vw;
-    __syncthreads();
-    uint32_t nv = 0;
-    for (int k = 0; k < kOsWaves; ++k) nv += s_v[k];
-#pragma unroll
-    for (int j = 0; j < kOsRounds; ++j) {
-        const uint64_t i = (uint64_t)j * kOsThreads + t;
-        if (i < nv) {
-            keys[i] = key[j] >> kTilePosBits;
-            vals[i] = (uint32_t)(key[j] & ((1u << kTilePosBits) - 1));
-        }
-    }
-    if (t == 0) g.ctr->tot[kTotValid] = nv;
-}
+};
 
 // ------------------------------------------------------------------ segments
-struct SegIn {
-    const uint64_t* keys;
-    const DevCounters* ctr;
-    uint32_t L;
-    // valid pairs: tot[kTotValid], or (sort overlap) the count the packing
-    // left in the batch's buffer, with the key sum after it
-    const unsigned long long* nvalid;
-    // sort overlap: the batch counters, cleared by begin() and given the
-    // packing's count and key sum (the previous batch used them until now)
-    DevCounters* clr;
-    struct Rec {
-        uint64_t k, p;
-    };
-    __device__ void begin() const {
-        if (!clr) return;
-        clear_batch_counters(clr, threadIdx.x);
-        if (threadIdx.x == 0) {
-            clr->tot[kTotValid] = nvalid[0];
-            clr->tot[kTotHash] = nvalid[1];
-        }
-    }
-    // no segments after a look-back wait ran out (the keys are not sorted)
-    __device__ uint64_t limit(uint64_t n) const {
-        return ctr->err_wait ? 0ull : min((uint64_t)*nvalid, n);
-    }
-    __device__ Rec load(uint64_t i, bool ok) const {
-        const uint64_t j = ok ? i : 0;
-        return Rec{keys[j], keys[j ? j - 1 : 0]};
-    }
-    __device__ void deref(Rec&) const {}
-    __device__ unsigned long long value(uint64_t i, const Rec& r) const {
-        const unsigned long long head = i == 0 || (r.k >> L) != (r.p >> L);
-        const unsigned long long uniq = i == 0 || r.k != r.p;
-        return head | (uniq << 32);
-    }
-};
-
-// The segment scan also checks the sort: every key is at least its
-// predecessor (else err_order = 2), and the mix64 sum of the sorted keys,
-// added up per workgroup in the hash stripes, must equal the packed keys'
-// sum (compared by the probe, which runs next but one).
-struct SegOut {
-    uint32_t L;
-    uint8_t* flags;
-    uint32_t* a;
-    uint32_t* t_vtx;
-    uint32_t* t_start;
-    DevCounters* ctr;
-    __device__ void operator()(uint64_t i, const SegIn::Rec& r, uint64_t nv,
-                               unsigned long long pre) const {
-        if (i >= nv) {
-            if (i == 0) t_start[0] = 0;
-            return;
-        }
-        if (i > 0 && r.k < r.p) ctr->err_order = 2;
-        const bool head = i == 0 || (r.k >> L) != (r.p >> L);
-        const bool uniq = i == 0 || r.k != r.p;
-        const uint32_t t = (uint32_t)pre + (head ? 1u : 0u) - 1u;  // segment of key i
-        flags[i] = (head ? kHead : 0) | (uniq ? kUniq : 0);
-        a[i] = t;
-        if (head) {
-            // masked to the table: a valid key's source is below 2^L already;
-            // the mask keeps even a corrupted key's record read in bounds
-            t_vtx[t] = (uint32_t)(r.k >> L) & (uint32_t)((1ull << L) - 1);
-            t_start[t] = (uint32_t)i;
-        }
-        if (i + 1 == nv) t_start[t + 1] = (uint32_t)nv;
-    }
-    __device__ unsigned long long tally(uint64_t, const SegIn::Rec& r) const { return mix64(r.k); }
-    __device__ void commit(unsigned long long sum) const {
-        atomicAdd(&ctr->stripe[blockIdx.x & 63][kStripeHash], sum);
-    }
-};
-
-// ------------------------------------------------------------------ items
-// a touched source, its batch segment and its vertex record
-struct TouchRec {
-    uint32_t v, lo, hi;
-    VRec r;
-};
-
-__device__ __forceinline__ TouchRec load_touched(const uint32_t* t_vtx, const uint32_t* t_start,
-                                                 uint64_t t, bool ok) {
-    const uint64_t j = ok ? t : 0;
-    const uint32_t v0 = t_vtx[j], lo0 = t_start[j], hi0 = t_start[j + 1];
-    TouchRec x;
-    x.v = ok ? v0 : 0u;
-    x.lo = ok ? lo0 : 0u;
-    x.hi = ok ? hi0 : 0u;
-    return x;
-}
-
 // Small items: a source with at most kSmallLanes * kSmallDeg slots and at
 // most kSmallSeg pairs in its batch segment is probed by kSmallLanes lanes,
-// kSmallDeg slots each, instead of a lane group.  Their descriptors go to a
-// second array indexed by touched source, where the other sources get an
-// empty entry (s1 = 0).
+// kSmallDeg slots each, from its source record; it has no work items.
 constexpr uint32_t kSmallDeg = 16;    // slots per lane (whole 16-byte groups of a block)
 constexpr uint32_t kSmallLanes = 4;   // lanes per small item
 #ifndef GV_SMALL_SEG
@@ -527,92 +378,213 @@ __device__ __forceinline__ bool small_item(uint32_t B, uint32_t deg, uint32_t le
     return B >= 4 && deg > 0 && deg <= kSmallLanes * kSmallDeg && len <= kSmallSeg;
 }
 
-struct ItemIn {
-    static constexpr int kItems = 2;  // large records: fewer per thread
-    GraphView g;
-    const uint32_t* t_vtx;
-    const uint32_t* t_start;
-    uint32_t chunk;  // adjacency slots per work item
-    using Rec = TouchRec;
-    __device__ uint64_t limit(uint64_t n) const {
-        return batch_failed(g.ctr) ? 0ull : min((uint64_t)(uint32_t)g.ctr->tot[kTotSeg], n);
-    }
-    __device__ Rec load(uint64_t t, bool ok) const { return load_touched(t_vtx, t_start, t, ok); }
-    __device__ void deref(Rec& x) const { x.r = g.vt[x.v]; }
-    __device__ unsigned long long value(uint64_t, const Rec& x) const {
-        const unsigned long long items =
-            small_item(g.B, x.r.deg, x.hi - x.lo) ? 0ull : (x.r.deg + chunk - 1) / chunk;
-        return items | ((unsigned long long)nblocks(g, x.r.deg) << 32);
-    }
-};
+// Valid pairs of the batch: none after a look-back wait ran out (the keys are
+// not sorted).
+__device__ __forceinline__ uint64_t batch_pairs(const DevCounters* c, const BatchCtr* bc,
+                                                uint64_t n) {
+    return c->err_wait ? 0ull : min((uint64_t)bc->n_valid, n);
+}
 
-// A source's work items: one per `chunk` slots.  A lane writes up to
-// kLaneItems of them; sources with more are written by all the lanes of the
-// wave that make the call, one item each per store.  The scan calls the sink
-// for elements below its size only, so in the last wave of a scan some lanes
-// may not take part: the loop counts the lanes that do.
-constexpr uint32_t kLaneItems = 16;
+// First position in keys[lo, hi) whose key is at least x, by one wave: 64
+// probes a step.
+__device__ __forceinline__ uint64_t wave_lower_bound(const uint64_t* keys, uint64_t lo,
+                                                     uint64_t hi, uint64_t x) {
+    const uint32_t lane = lane_id();
+    while (lo < hi) {
+        const uint64_t step = (hi - lo + 63) / 64;
+        const uint64_t p = lo + lane * step;
+        const uint64_t less = ballot(p < hi && keys[p] < x);
+        if (!less) return lo;
+        const uint64_t k = popc64(less);  // (the keys are in order)
+        lo += (k - 1) * step + 1;
+        hi = min(hi, lo - 1 + step);
+    }
+    return lo;
+}
 
-struct ItemOut {
-    Item* items;
-    Item* small;        // per touched source: its small item, or s1 = 0
-    uint32_t B;
-    uint64_t icap;      // capacity of items (the scan of distinct sources stays below it)
-    uint32_t chunk;     // adjacency slots per work item
-    uint32_t* shits;    // delete: small-item hits per source, zeroed here for the others
-    __device__ void operator()(uint64_t t, const TouchRec& x, uint64_t lim,
-                               unsigned long long pre) const {
-        const bool live = t < lim;
-        const VRec r = x.r;
-        const bool small = live && small_item(B, r.deg, x.hi - x.lo);
-        const uint32_t cnt = live && !small ? (r.deg + chunk - 1) / chunk : 0u;
-        const uint32_t base = (uint32_t)pre;
+// Exclusive ranks of a flag over a tile's positions (row j of thread t is
+// position j * T + t), by ballots: one LDS exchange of the per-wave counts.
+// Returns the number of set flags; cnt holds kTileRows * T / 64 words.
+template <int T, uint32_t R>
+__device__ __forceinline__ uint32_t tile_ranks(const bool (&f)[R], uint32_t (&rank)[R],
+                                               uint32_t* cnt) {
+    constexpr uint32_t W = T / 64, N = R * W;
+    static_assert(N <= 64, "one wave scans the counts");
+    const uint32_t w = threadIdx.x >> 6;
+    uint64_t m[R];
+#pragma unroll
+    for (uint32_t j = 0; j < R; ++j) {
+        m[j] = ballot(f[j]);
+        if (lane_id() == 0) cnt[j * W + w] = popc64(m[j]);
+    }
+    __syncthreads();
+    const uint32_t c = lane_id() < N ? cnt[lane_id()] : 0u;
+    const uint32_t inc = wave_incl_scan(c);  // every wave for itself
+#pragma unroll
+    for (uint32_t j = 0; j < R; ++j)
+        rank[j] = __shfl(inc - c, (int)(j * W + w), 64) + rank_below(m[j]);
+    const uint32_t total = __shfl(inc, 63, 64);
+    __syncthreads();
+    return total;
+}
+
+// exclusive scan across T threads and their sum; lds holds T / 64 words
+template <int T, typename V>
+__device__ __forceinline__ V tile_scan(V x, V* lds, V& total) {
+    const V inc = wave_incl_scan(x);
+    const int w = threadIdx.x >> 6;
+    if (lane_id() == 63) lds[w] = inc;
+    __syncthreads();
+    V off = 0, tot = 0;
+#pragma unroll
+    for (int i = 0; i < T / 64; ++i) {
+        const V v = lds[i];
+        off += i < w ? v : V(0);
+        tot += v;
+    }
+    __syncthreads();
+    total = tot;
+    return off + inc - x;
+}
+
+// Segments, sources and work items of a tile of the sorted keys.  Also writes
+// the marks (dup_mark: 1 on a repeated pair, which an insert does not keep),
+// checks the sort (every key at least its predecessor, else err_order = 2;
+// the mix64 sum of the sorted keys goes to the hash stripes, which the probe
+// compares with the packed keys' sum) and counts distinct pairs and blocks.
+//
+// A segment that runs past the tile belongs to the tile of its head, which
+// finds its end by a wave-wide search.  Work items are written by all the
+// threads of the workgroup, each finding its item's source among the tile's
+// (a hub's items spread over the workgroup).  Bound: the latency of key ->
+// vertex record -> item; it replaces two scans over the batch (their reduce
+// and apply kernels, a middle one past 2^21 pairs, and 32 bytes written per
+// source for its small item): 10^4 pairs 21.8 -> 10.0 us, 10^6 pairs 33.3 ->
+// 25.5 us, 10^7 pairs 218 -> 114 us (R-MAT 2^20 / 2^24, the last 2^22 / 2^26).
+template <int T>
+__global__ __launch_bounds__(T) void k_segments(GraphView g, const uint64_t* keys, uint64_t n,
+                                                BatchCtr* bc, uint32_t tl, uint8_t* mark,
+                                                int dup_mark, Src* srcs, uint2* tiles,
+                                                Item* items, uint64_t icap, uint32_t chunk) {
+    constexpr uint32_t kTile = T * kTileRows;
+    __shared__ uint32_t s_pos[kTile + 1], s_base[kTile + 1];
+    __shared__ uint32_t s_cnt[kTileRows * T / 64];
+    __shared__ uint32_t s_scan[T / 64];
+    __shared__ unsigned long long s_sum[3];
+    __shared__ uint32_t s_end, s_t0, s_i0;
+    const uint32_t t = threadIdx.x;
+    const uint64_t lim = batch_pairs(g.ctr, bc, n);
+    const uint64_t p0 = (uint64_t)blockIdx.x << tl;
+    if (p0 >= lim) {
+        if (t == 0) tiles[blockIdx.x] = make_uint2(0u, 0u);
+        return;
+    }
+    const uint32_t np = (uint32_t)min((uint64_t)1 << tl, lim - p0);
+    const uint32_t L = g.L;
+    if (t < 3) s_sum[t] = 0ull;
+    uint64_t k[kTileRows], q[kTileRows];
+#pragma unroll
+    for (uint32_t j = 0; j < kTileRows; ++j) {
+        const uint64_t i = p0 + min(j * T + t, np - 1);
+        k[j] = keys[i];
+        q[j] = keys[i ? i - 1 : 0];
+    }
+    bool head[kTileRows];
+    unsigned long long hash = 0, uniq = 0;
+    bool bad = false;
+#pragma unroll
+    for (uint32_t j = 0; j < kTileRows; ++j) {
+        const uint32_t p = j * T + t;
+        const bool in = p < np, first = p0 + p == 0;
+        head[j] = in && (first || (k[j] >> L) != (q[j] >> L));
+        const bool un = in && (first || k[j] != q[j]);
+        uniq += un;
+        bad |= in && !first && k[j] < q[j];
+        hash += in ? mix64(k[j]) : 0ull;
+        if (in) mark[p0 + p] = (dup_mark && !un) ? 1 : 0;
+    }
+    if (bad) g.ctr->err_order = 2;
+    uint32_t rank[kTileRows];
+    const uint32_t nh = tile_ranks<T>(head, rank, s_cnt);
+    // the sources' places, while the records are read
+    if (t == 0) s_t0 = nh ? (uint32_t)atomicAdd(&bc->alloc_t, (unsigned long long)nh) : 0u;
+#pragma unroll
+    for (uint32_t j = 0; j < kTileRows; ++j)
+        if (head[j]) s_pos[rank[j]] = j * T + t;
+    if (t < 64) {
+        // the end of the segment that holds the tile's last key
+        const uint64_t pe = p0 + np;
+        uint64_t end = pe;
+        if (pe < lim) {
+            const uint64_t v = keys[pe - 1] >> L;
+            if ((keys[pe] >> L) == v) end = wave_lower_bound(keys, pe, lim, (v + 1) << L);
+        }
+        if (t == 0) s_end = (uint32_t)end;
+    }
+    hash = wave_sum(hash);
+    uniq = wave_sum(uniq);
+    if (lane_id() == 0) {
+        atomicAdd(&s_sum[0], hash);
+        atomicAdd(&s_sum[1], uniq);
+    }
+    __syncthreads();
+    const uint32_t t0 = s_t0;
+    uint32_t ni = 0;  // the tile's work items
+    unsigned long long blocks = 0;
+    for (uint32_t h0 = 0; h0 < nh; h0 += T) {
+        const uint32_t h = h0 + t;
+        uint32_t cnt = 0;
+        if (h < nh) {
+            Src x;
+            x.lo = (uint32_t)p0 + s_pos[h];
+            x.hi = h + 1 < nh ? (uint32_t)p0 + s_pos[h + 1] : s_end;
+            // masked to the table: a valid key's source is below 2^L already;
+            // the mask keeps even a corrupted key's record read in bounds
+            x.v = (uint32_t)(keys[x.lo] >> L) & (uint32_t)((1ull << L) - 1);
+            const VRec r = g.vt[x.v];
+            x.r = 0;
+            x.deg = r.deg;
+            x.dir = r.dir;
+            x.dcls = r.dcls;
+            x.need = 0;
+            srcs[t0 + h] = x;
+            blocks += nblocks(g, r.deg);
+            if (!small_item(g.B, r.deg, x.hi - x.lo)) cnt = (r.deg + chunk - 1) / chunk;
+        }
+        uint32_t tot;
+        const uint32_t ex = tile_scan<T>(cnt, s_scan, tot);
+        if (h < nh) s_base[h] = ni + ex;
+        ni += tot;
+    }
+    blocks = wave_sum(blocks);
+    if (lane_id() == 0 && blocks) atomicAdd(&s_sum[2], blocks);
+    if (t == 0) {
+        tiles[blockIdx.x] = make_uint2(t0, nh);
+        s_i0 = ni ? (uint32_t)atomicAdd(&bc->alloc_i, (unsigned long long)ni) : 0u;
+    }
+    __syncthreads();  // (the source records are in place for the workgroup)
+    if (t < 3) atomicAdd(&bc->stripe[blockIdx.x & 63][t], s_sum[t]);
+    for (uint32_t m = t; m < ni; m += T) {
+        // the last source whose items start at or before m
+        uint32_t lo = 0, hi = nh;
+        while (hi - lo > 1) {
+            const uint32_t mid = (lo + hi) >> 1;
+            if (s_base[mid] <= m) lo = mid;
+            else hi = mid;
+        }
+        const Src x = srcs[t0 + lo];
         Item it;
+        it.s0 = (m - s_base[lo]) * chunk;
+        it.s1 = min(x.deg, it.s0 + chunk);
         it.lo = x.lo;
         it.hi = x.hi;
         it.v = x.v;
-        it.dirbase = r.dcls != kNoDir ? r.dir : 0u;
-        it.blk0 = r.dcls != kNoDir ? 0u : r.dir;
-        it.dcls = r.dcls;
-        if (small) {
-            Item w = it;
-            w.s0 = 0;
-            w.s1 = r.deg;
-            this->small[t] = w;
-        } else if (live) {
-            *(uint4*)&this->small[t] = make_uint4(0u, 0u, 0u, 0u);
-            if (shits) shits[t] = 0u;
-        }
-        if (cnt <= kLaneItems) {
-            for (uint32_t c = 0; c < cnt; ++c) {
-                it.s0 = c * chunk;
-                it.s1 = min(r.deg, it.s0 + chunk);
-                if (base + c < icap) items[base + c] = it;
-            }
-        }
-        const uint64_t act = ballot(true);
-        const uint32_t nact = popc64(act), me = rank_below(act);
-        uint64_t m = ballot(cnt > kLaneItems);
-        while (m) {
-            const int l = __ffsll((unsigned long long)m) - 1;
-            m &= m - 1;
-            Item w;
-            w.lo = __shfl(it.lo, l, 64);
-            w.hi = __shfl(it.hi, l, 64);
-            w.v = __shfl(it.v, l, 64);
-            w.dirbase = __shfl(it.dirbase, l, 64);
-            w.blk0 = __shfl(it.blk0, l, 64);
-            w.dcls = __shfl(it.dcls, l, 64);
-            const uint32_t wdeg = __shfl(r.deg, l, 64);
-            const uint32_t wcnt = __shfl(cnt, l, 64), wbase = __shfl(base, l, 64);
-            for (uint32_t c = me; c < wcnt; c += nact) {
-                w.s0 = c * chunk;
-                w.s1 = min(wdeg, w.s0 + chunk);
-                if ((uint64_t)wbase + c < icap) items[wbase + c] = w;
-            }
-        }
+        it.dirbase = x.dcls != kNoDir ? x.dir : 0u;
+        it.blk0 = x.dcls != kNoDir ? 0u : x.dir;
+        it.dcls = x.dcls;
+        if ((uint64_t)s_i0 + m < icap) items[(uint64_t)s_i0 + m] = it;
     }
-};
+}
 
 // ------------------------------------------------------------------ probe
 __device__ __forceinline__ void wave_lds_sync() {
@@ -643,10 +615,9 @@ __device__ __forceinline__ void probe_load(const GraphView& g, const Item& I, co
 }
 
 // Searches of the U slots of a lane run in lockstep, so that each step
-// issues U independent reads and waits once.  Returns the lane's hits
-// (delete: slots tombstoned).
+// issues U independent reads and waits once.
 template <int MODE, int G, int U>
-__device__ __forceinline__ uint32_t probe_search(const GraphView& g, const Item& I, uint32_t s,
+__device__ __forceinline__ void probe_search(const GraphView& g, const Item& I, uint32_t s,
                                                  const uint32_t (&x)[U],
                                                  const uint64_t (&addr)[U], const uint32_t* st,
                                                  uint32_t steps, uint32_t shift,
@@ -710,7 +681,6 @@ __device__ __forceinline__ uint32_t probe_search(const GraphView& g, const Item&
 #pragma unroll
         for (int u = 0; u < U; ++u) hit[u] = p[u] < len && kv[u] == (vbase | x[u]);
     }
-    uint32_t nhit = 0;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
         const uint32_t si = s + u * G;
@@ -722,7 +692,6 @@ __device__ __forceinline__ uint32_t probe_search(const GraphView& g, const Item&
             mark[pos] = 1;
             hitpos[pos] = si;
             g.pool[addr[u]] = kTomb;
-            ++nhit;
         } else {
             const uint64_t target = vbase | x[u];
             for (uint32_t j = pos; j < I.hi && keys[j] == target; ++j) {
@@ -731,7 +700,6 @@ __device__ __forceinline__ uint32_t probe_search(const GraphView& g, const Item&
             }
         }
     }
-    return nhit;
 }
 
 // Lane q of a small item's lanes probes slots [q * kSmallDeg, (q + 1) *
@@ -739,14 +707,12 @@ __device__ __forceinline__ uint32_t probe_search(const GraphView& g, const Item&
 // loaded whole and compared pairwise.  Same marks as the group search: insert
 // and delete mark the first occurrence of a stored pair (delete also records
 // the slot and tombstones it), query marks every occurrence.  A stored pair
-// sits in one slot, so one lane at most marks a segment entry.  Returns the
-// lane's hits (delete).
+// sits in one slot, so one lane at most marks a segment entry.
 template <int MODE>
-__device__ __forceinline__ uint32_t probe_small(const GraphView& g, const Item& I, uint32_t q,
-                                                const uint64_t* keys, uint8_t* mark,
-                                                uint32_t* hitpos) {
-    uint32_t nhit = 0;
-    const uint32_t deg = I.s1;
+__device__ __forceinline__ void probe_small(const GraphView& g, const Src& I, uint32_t q,
+                                            const uint64_t* keys, uint8_t* mark,
+                                            uint32_t* hitpos) {
+    const uint32_t deg = I.deg;
     const uint32_t len = I.hi - I.lo;
     const uint32_t first = q * kSmallDeg;
     const uint32_t* klo = (const uint32_t*)keys;  // low words: destinations
@@ -762,7 +728,7 @@ __device__ __forceinline__ uint32_t probe_small(const GraphView& g, const Item& 
     for (uint32_t u = 0; u < kSmallDeg; u += 4) {
         const uint32_t sl = first + u;
         const uint32_t j = sl >> g.log2B;
-        const uint32_t blk = I.dcls != kNoDir ? g.dir[I.dirbase + (sl < deg ? j : 0u)] : I.blk0;
+        const uint32_t blk = I.dcls != kNoDir ? g.dir[I.dir + (sl < deg ? j : 0u)] : I.dir;
         a[u / 4] = ((uint64_t)blk << g.log2B) + (sl & (g.B - 1));
     }
 #pragma unroll
@@ -789,54 +755,38 @@ __device__ __forceinline__ uint32_t probe_small(const GraphView& g, const Item& 
         if (MODE == kDelete) {
             hitpos[I.lo + j] = first + hu;
             g.pool[a[hu / 4] + (hu & 3)] = kTomb;
-            ++nhit;
         }
     }
-    return nhit;
 }
 
-// shits (delete): per touched source, the hits of its small item (written
-// for every small item; the items scan zeroes the other sources' entries)
 template <int MODE, int G, int U>
 __global__ __launch_bounds__(kThreads) void k_probe(GraphView g, const uint64_t* keys,
-                                                    const Item* items, const Item* small,
-                                                    uint8_t* mark, uint32_t* hitpos,
-                                                    uint32_t* shits) {
+                                                    const BatchCtr* bc, const Item* items,
+                                                    const Src* srcs, uint8_t* mark,
+                                                    uint32_t* hitpos) {
     __shared__ uint32_t stage[kWaves * (64 / G)][kStage];
-    __shared__ uint32_t s_hits[kWaves * (64 / G)];  // delete: hits of a group's item
-    if (MODE == kDelete) {
-        if (threadIdx.x < kWaves * (64 / G)) s_hits[threadIdx.x] = 0u;
-        __syncthreads();
-    }
     if (batch_failed(g.ctr)) return;
     if (MODE == kInsert || MODE == kDelete) {
         // the sorted keys must be the packed keys: their mix64 sums agree
-        // (per-workgroup sums of the segment scan in 64 stripes; one load a lane)
-        const unsigned long long sorted = wave_sum(g.ctr->stripe[lane_id()][kStripeHash]);
-        if (!g.ctr->tot[kTotNoHash] && sorted != g.ctr->tot[kTotHash]) {
+        // (per-workgroup sums of the segments kernel in 64 stripes; one load a lane)
+        const unsigned long long sorted = wave_sum(bc->stripe[lane_id()][kStripeHash]);
+        if (!bc->nohash && sorted != bc->key_sum) {
             if (lane_id() == 0) g.ctr->err_order = 3;
             return;
         }
     }
     {
         // small items first, kSmallLanes consecutive lanes per touched source
-        const uint64_t nq = (uint64_t)(uint32_t)g.ctr->tot[kTotSeg] * kSmallLanes;
+        const uint64_t nq = bc->alloc_t * kSmallLanes;
         const uint64_t stride = (uint64_t)gridDim.x * kThreads;
         for (uint64_t k = (uint64_t)blockIdx.x * kThreads + threadIdx.x; k < nq; k += stride) {
-            const Item I = small[k / kSmallLanes];
+            const Src I = srcs[k / kSmallLanes];
             const uint32_t q = (uint32_t)(k % kSmallLanes);
-            uint32_t h = 0;
-            if (I.s1 > q * kSmallDeg) h = probe_small<MODE>(g, I, q, keys, mark, hitpos);
-            if (MODE == kDelete) {
-                // the item's kSmallLanes lanes are consecutive and all here
-                static_assert(kSmallLanes == 4, "two exchange steps");
-                h += __shfl_xor(h, 1, 64);
-                h += __shfl_xor(h, 2, 64);
-                if (q == 0 && I.s1 > 0) shits[k / kSmallLanes] = h;
-            }
+            if (small_item(g.B, I.deg, I.hi - I.lo) && I.deg > q * kSmallDeg)
+                probe_small<MODE>(g, I, q, keys, mark, hitpos);
         }
     }
-    const uint32_t nitems = (uint32_t)g.ctr->tot[kTotItems];
+    const uint32_t nitems = (uint32_t)bc->alloc_i;
     const uint32_t lane = lane_id();
     const uint32_t gl = lane & (G - 1);
     const uint32_t gid_local = (threadIdx.x >> 6) * (64 / G) + (lane / G);
@@ -907,9 +857,7 @@ __global__ __launch_bounds__(kThreads) void k_probe(GraphView g, const uint64_t*
             uint32_t x2[U];
             uint64_t a2[U];
             if (more) probe_load<MODE, G, U>(g, I, dp, s + G * U, x2, a2);
-            const uint32_t nhit = probe_search<MODE, G, U>(g, I, s, x, addr, st, steps, shift,
-                                                           keys, mark, hitpos);
-            if (MODE == kDelete && nhit) atomicAdd(&s_hits[gid_local], nhit);
+            probe_search<MODE, G, U>(g, I, s, x, addr, st, steps, shift, keys, mark, hitpos);
             if (!more) break;
             s += G * U;
 #pragma unroll
@@ -918,143 +866,220 @@ __global__ __launch_bounds__(kThreads) void k_probe(GraphView g, const uint64_t*
                 addr[u] = a2[u];
             }
         }
-        // the item's hits (summed in LDS over its steps) go to its source's
-        // count: one add per group
         wave_lds_sync();
-        if (MODE == kDelete && gl == 0) {
-            const uint32_t h = s_hits[gid_local];
-            if (h) {
-                atomicAdd(&g.vlost[I.v], h);
-                s_hits[gid_local] = 0u;
-            }
-        }
         if (itn >= nitems) break;
         it = itn;
         I = In;
     }
 }
 
-// ------------------------------------------------------------------ insert
-struct KeepIn {
-    const uint8_t* flags;
-    const uint8_t* mark;
-    const DevCounters* ctr;
-    struct Rec {
-        uint8_t f, m;
-    };
-    __device__ uint64_t limit(uint64_t n) const {
-        return batch_failed(ctr) ? 0ull : min((uint64_t)ctr->tot[kTotValid], n);
-    }
-    __device__ Rec load(uint64_t i, bool ok) const {
-        const uint64_t j = ok ? i : 0;
-        return Rec{flags[j], mark[j]};
-    }
-    __device__ void deref(Rec&) const {}
-    __device__ unsigned long long value(uint64_t, const Rec& r) const {
-        return ((r.f & kUniq) && !r.m) ? 1ull : 0ull;
-    }
-};
+// ------------------------------------------------------------------ plan
+__device__ __forceinline__ void plan_insert(const GraphView& g, const BatchCtr* bc, uint64_t n,
+                                            int sticky);
+__device__ __forceinline__ void plan_delete(const GraphView& g, const BatchCtr* bc, uint64_t n);
 
-struct U32Out {
-    uint32_t* a;
-    template <typename R>
-    __device__ void operator()(uint64_t i, const R&, uint64_t, unsigned long long v) const {
-        a[i] = (uint32_t)v;
-    }
-};
-
-__global__ __launch_bounds__(kThreads) void k_plan_ins(GraphView g, const uint32_t* t_vtx,
-                                                       const uint32_t* t_start, const uint32_t* b,
-                                                       uint32_t* t_need, uint32_t* t_dreq,
-                                                       uint32_t* t_drank, uint32_t* heavy) {
-    __shared__ uint32_t lcnt[kMaxClass];
-    __shared__ uint32_t lbase[kMaxClass];
-    if (threadIdx.x < kMaxClass) lcnt[threadIdx.x] = 0;
-    __syncthreads();
-    const uint64_t t = thread_index();
-    if (batch_failed(g.ctr)) return;  // uniform over the launch
-    const uint32_t nT = (uint32_t)g.ctr->tot[kTotSeg];
-    uint32_t cls = kNoDir, lrank = 0;
-    bool big = false;
-    if (t < nT) {
-        const uint32_t kp = b[t_start[t + 1]] - b[t_start[t]];
-        const VRec r = g.vt[t_vtx[t]];
-        const uint32_t nb0 = nblocks(g, r.deg), nb1 = nblocks(g, r.deg + kp);
-        const uint64_t cap0 = r.dcls == kNoDir ? 1ull : (1ull << r.dcls);
-        if (nb1 > cap0) {
-            cls = ceil_log2(nb1);
-            lrank = atomicAdd(&lcnt[cls], 1u);
-        }
-        // top bit: the source gives back a directory segment
-        t_need[t] = (nb1 - nb0) | (cls != kNoDir && r.dcls != kNoDir ? kRelease : 0u);
-        big = (cls != kNoDir && nb0 > kLaneCopy) || nb1 - nb0 > kLaneCopy;
-        // the grow kernel takes this decision from here: its heavy sources'
-        // records change while other waves still run the lane loop, so it
-        // must not be made again from the record there
-        t_dreq[t] = cls | (big ? kHeavy : 0u);
-    }
-    wave_append(big, (uint32_t)t, &g.ctr->n_heavy, heavy);
-    __syncthreads();
-    if (threadIdx.x < kMaxClass) {
-        const uint32_t c = lcnt[threadIdx.x];
-        lbase[threadIdx.x] = c ? atomicAdd(&g.ctr->dreq[threadIdx.x], c) : 0u;
-    }
-    __syncthreads();
-    if (t < nT && cls != kNoDir) t_drank[t] = lbase[cls] + lrank;
+// a source that one lane compacts by itself
+__device__ __forceinline__ bool lane_compactable(uint32_t r, uint32_t lo, uint32_t hi) {
+    return r <= kLaneR && hi - lo <= kLaneSeg;
 }
 
-// blocks needed in the low half, directory segments given back in the high
-// half (their rank is their slot in the release list)
-struct NeedIn {
-    const uint32_t* t_need;
-    const DevCounters* ctr;
-    struct Rec {
-        uint32_t need;
-    };
-    __device__ uint64_t limit(uint64_t n) const {
-        return batch_failed(ctr) ? 0ull : min((uint64_t)(uint32_t)ctr->tot[kTotSeg], n);
-    }
-    __device__ Rec load(uint64_t t, bool ok) const { return Rec{t_need[ok ? t : 0]}; }
-    __device__ void deref(Rec&) const {}
-    __device__ unsigned long long value(uint64_t, const Rec& r) const {
-        return (unsigned long long)(r.need & ~kRelease) | ((unsigned long long)(r.need >> 31) << 32);
-    }
-};
+// Kept pairs (insert: mark 0) or hits (delete: mark 1) of positions [a, b), by
+// one wave.
+template <bool INS>
+__device__ __forceinline__ uint32_t wave_count(const uint8_t* mark, uint64_t a, uint64_t b) {
+    uint32_t c = 0;
+    for (uint64_t p = a + lane_id(); p < b; p += 64) c += INS ? mark[p] == 0 : mark[p] != 0;
+    return wave_sum(c);
+}
 
-__device__ __forceinline__ void plan_batch(const GraphView& g, uint64_t n, int sticky);
-
-struct NeedOut {
-    uint32_t* t_need;
-    uint32_t* rel;
-    GraphView g;
-    uint64_t n;
-    int sticky;
-    __device__ void operator()(uint64_t t, const NeedIn::Rec& r, uint64_t lim,
-                               unsigned long long pre) const {
-        t_need[t] = (uint32_t)pre;
-        if (t < lim && (r.need & kRelease)) rel[(uint32_t)(pre >> 32)] = (uint32_t)t;
+// What every touched source of a tile needs: its kept pairs or hits r, then
+// (insert) its blocks and directory request, or (delete) its freed blocks and
+// who compacts it.  The tile's blocks and listed sources are placed with one
+// atomic on the batch's demand; the last tile to finish runs the batch's
+// plan.  The words the plan adds up are written by returning atomics only, so
+// every tile's share is in them once its `done` is counted, and no fence is
+// needed.  A segment that runs past the tile is counted by its head's tile,
+// one wave per further tile (insert: which also leaves the running count to
+// those tiles).
+//
+// Bound: latency (marks, then source records: both streams).  It replaces a
+// scan over the pairs, a kernel over the sources and a scan over them
+// (insert: 19 -> 9.3 us at 10^4 pairs, 46 -> 22 at 10^6), or a scan over the
+// sources that read their records anew and two hit counters kept by the probe
+// (delete: 8.3 -> 8.0 us, with the counters and a last kernel of 3.4 us gone).
+template <bool INS, int T>
+__global__ __launch_bounds__(T) void k_plan(GraphView g, uint64_t n, BatchCtr* bc, uint32_t tl,
+                                            const uint8_t* mark, Src* srcs, const uint2* tiles,
+                                            uint2* carry, uint32_t* tbase, uint32_t* t_dreq,
+                                            uint32_t* t_drank, uint32_t* list, uint32_t* list2,
+                                            int sticky) {
+    constexpr uint32_t kTile = T * kTileRows;
+    __shared__ uint32_t s_pre[kTile + 1];
+    __shared__ uint32_t s_cnt[kTileRows * T / 64];
+    __shared__ unsigned long long s_scan[T / 64];
+    __shared__ uint32_t lcnt[kMaxClass], lbase[kMaxClass];
+    __shared__ uint32_t s_tail[T / 64];
+    __shared__ unsigned long long s_demand;
+    __shared__ uint32_t s_last;
+    const uint32_t t = threadIdx.x, w = t >> 6;
+    // (an order check that failed leaves nothing to plan)
+    const uint64_t lim = batch_failed(g.ctr) ? 0ull : min((uint64_t)bc->n_valid, n);
+    const uint64_t p0 = (uint64_t)blockIdx.x << tl;
+    const uint32_t np = p0 < lim ? (uint32_t)min((uint64_t)1 << tl, lim - p0) : 0u;
+    if (t < kMaxClass) lcnt[t] = 0;
+    unsigned long long changed = 0;
+    if (np) {  // uniform over the workgroup
+        const uint2 td = tiles[blockIdx.x];
+        const uint32_t t0 = td.x, nh = td.y;
+        bool f[kTileRows];
+        uint32_t rank[kTileRows];
+#pragma unroll
+        for (uint32_t j = 0; j < kTileRows; ++j) {
+            const uint32_t p = j * T + t;
+            const uint8_t m = mark[p0 + min(p, np - 1)];
+            f[j] = p < np && (INS ? m == 0 : m != 0);
+        }
+        const uint32_t tot = tile_ranks<T>(f, rank, s_cnt);
+#pragma unroll
+        for (uint32_t j = 0; j < kTileRows; ++j) {
+            const uint32_t p = j * T + t;
+            if (p < np) s_pre[p] = rank[j];
+        }
+        if (t == 0) s_pre[np] = tot;
+        changed = tot;
+        __syncthreads();
+        // the rest of a segment that runs past the tile
+        uint32_t tail = 0;
+        const uint64_t pe = p0 + np;
+        if (nh) {
+            const Src last = srcs[t0 + nh - 1];
+            if (last.hi > pe) {
+                const uint32_t in_tile = tot - s_pre[last.lo - (uint32_t)p0];
+                const uint64_t b0 = blockIdx.x + 1, b1 = ((uint64_t)last.hi - 1) >> tl;
+                for (uint64_t b = b0; b <= b1; b += T / 64) {
+                    const uint64_t mb = b + w;
+                    uint32_t c = 0;
+                    if (mb <= b1)
+                        c = wave_count<INS>(mark, mb << tl,
+                                            min((uint64_t)last.hi, (mb + 1) << tl));
+                    if (lane_id() == 0) s_tail[w] = c;
+                    __syncthreads();
+                    uint32_t before = 0, all = 0;
+                    for (uint32_t i = 0; i < T / 64; ++i) {
+                        const uint32_t x = s_tail[i];
+                        before += i < w ? x : 0u;
+                        all += x;
+                    }
+                    if (INS && mb <= b1 && lane_id() == 0)
+                        carry[mb] = make_uint2(t0 + nh - 1, in_tile + tail + before);
+                    tail += all;
+                    __syncthreads();
+                }
+            }
+        }
+        // the sources: blocks (low) and listed sources (high) of the tile
+        unsigned long long run = 0;
+        uint32_t cls[kTileRows], lrank[kTileRows], lpos[kTileRows];
+        bool listed[kTileRows];
+#pragma unroll
+        for (uint32_t j = 0; j < kTileRows; ++j) {
+            cls[j] = kNoDir;
+            listed[j] = false;
+            if (j * T >= nh) continue;  // uniform
+            const uint32_t h = j * T + t;
+            uint32_t need = 0;
+            bool heavy = false;
+            if (h < nh) {
+                Src x = srcs[t0 + h];
+                x.r = s_pre[(uint32_t)(min((uint64_t)x.hi, pe) - p0)] -
+                      s_pre[x.lo - (uint32_t)p0] + (h + 1 == nh ? tail : 0u);
+                if (INS) {
+                    const uint32_t nb0 = nblocks(g, x.deg), nb1 = nblocks(g, x.deg + x.r);
+                    const uint64_t cap0 = x.dcls == kNoDir ? 1ull : (1ull << x.dcls);
+                    if (nb1 > cap0) {
+                        cls[j] = ceil_log2(nb1);
+                        lrank[j] = atomicAdd(&lcnt[cls[j]], 1u);
+                    }
+                    need = nb1 - nb0;
+                    // the source gives back a directory segment
+                    listed[j] = cls[j] != kNoDir && x.dcls != kNoDir;
+                    // the commit kernel takes this decision from here: its
+                    // heavy sources' records change while other waves still
+                    // run the lane loop, so it must not be made again there
+                    heavy = (cls[j] != kNoDir && nb0 > kLaneCopy) || need > kLaneCopy;
+                    t_dreq[t0 + h] = cls[j] | (heavy ? kHeavy : 0u);
+                } else if (x.r) {
+                    need = nblocks(g, x.deg) - nblocks(g, x.deg - x.r);
+                    listed[j] = x.r <= kBigR && !lane_compactable(x.r, x.lo, x.hi);
+                    if (x.r > kBigR) list2[atomicAdd(&bc->n_big, 1u)] = t0 + h;
+                }
+                lpos[j] = t0 + h;
+                srcs[t0 + h].r = x.r;
+            }
+            if (INS) wave_append(heavy, t0 + h, &bc->n_heavy, list2);
+            unsigned long long all;
+            const unsigned long long ex = tile_scan<T>(
+                (unsigned long long)need | ((unsigned long long)listed[j] << 32), s_scan, all);
+            if (h < nh) srcs[t0 + h].need = (uint32_t)(run + ex);
+            if (!INS || cls[j] == kNoDir) lrank[j] = 0;
+            // (the list place, until the tile's base is known)
+            rank[j] = (uint32_t)((run + ex) >> 32);
+            run += all;
+        }
+        if (INS) {
+            if (t < kMaxClass) {
+                const uint32_t c = lcnt[t];
+                lbase[t] = c ? atomicAdd(&g.ctr->dreq[t], c) : 0u;
+            }
+        }
+        if (t == 0) {
+            s_demand = run ? atomicAdd(&bc->demand, run) : 0ull;
+            tbase[blockIdx.x] = (uint32_t)s_demand;
+        }
+        __syncthreads();
+        const uint32_t lb = (uint32_t)(s_demand >> 32);
+#pragma unroll
+        for (uint32_t j = 0; j < kTileRows; ++j) {
+            if (listed[j]) list[lb + rank[j]] = lpos[j];
+            if (INS && cls[j] != kNoDir) t_drank[lpos[j]] = lbase[cls[j]] + lrank[j];
+        }
     }
-    __device__ void finish() const { plan_batch(g, n, sticky); }
-};
+    if (t == 0) {
+        // (the value returned by each atomic is used before the next is issued)
+        const unsigned long long had = changed ? atomicAdd(&bc->changed, changed) : 0ull;
+        s_last = had != ~0ull && atomicAdd(&bc->done, 1ull) == gridDim.x - 1 ? 1u : 0u;
+    }
+    __syncthreads();
+    if (s_last && t < 64) {
+        if (INS) plan_insert(g, bc, n, sticky);
+        else plan_delete(g, bc, n);
+    }
+}
+
+// sums the plan adds up from atomics of other workgroups
+template <typename V>
+__device__ __forceinline__ V ld_agent(const V* p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
 
 // Allocation plan for the whole batch, one wave (a lane per directory class):
 // capacity is checked before any state is written, so a failing batch leaves
-// the graph unchanged.  Run by the first wave of the demand scan's last
-// workgroup, once the scan total (blocks needed) is written.
-__device__ __forceinline__ void plan_batch(const GraphView& g, uint64_t n, int sticky) {
+// the graph unchanged.  Run by the first wave of the last tile planned.
+__device__ __forceinline__ void plan_insert(const GraphView& g, const BatchCtr* bc, uint64_t n,
+                                            int sticky) {
     DevCounters* c = g.ctr;
     const uint32_t k = lane_id();
     if (batch_failed(c)) {
-        // nothing is committed; append, grow and release see the error
+        // nothing is committed; commit and release see the error
         if (k == 0) c->err_batch = GV_EDEVICE;
         return;
     }
     const bool cl = k < kMaxClass;
-    const unsigned long long N = c->tot[kTotB] & 0xffffffffull;
+    const unsigned long long N = ld_agent(&bc->demand) & 0xffffffffull;
     const unsigned long long free0 = c->free_cnt, bump0 = c->bump;
     const unsigned long long ff = N < free0 ? N : free0;
     const unsigned long long fb = N - ff;
-    const uint32_t req = cl ? c->dreq[k] : 0u;
+    const uint32_t req = cl ? ld_agent(&c->dreq[k]) : 0u;
     const uint32_t have = cl ? c->dfree_cnt[k] : 0u;
     const uint32_t dff = req < have ? req : have;
     const unsigned long long grow = cl ? (unsigned long long)(req - dff) << k : 0ull;
@@ -1072,15 +1097,16 @@ __device__ __forceinline__ void plan_batch(const GraphView& g, uint64_t n, int s
         }
     }
     const unsigned long long live = wave_sum(cl ? (unsigned long long)req << k : 0ull);
+    const unsigned long long nuniq = wave_sum(bc->stripe[k][kStripeUniq]);
+    const unsigned long long blocks = wave_sum(bc->stripe[k][kStripeBlocks]);
     if (k != 0) return;
-    const unsigned long long nv = c->tot[kTotValid];
-    const unsigned long long nT = c->tot[kTotSeg] & 0xffffffffull;
-    const unsigned long long nuniq = c->tot[kTotSeg] >> 32;
-    const unsigned long long applied = c->tot[kTotA];
+    const unsigned long long nv = min((uint64_t)bc->n_valid, n);
+    const unsigned long long applied = ld_agent(&bc->changed);
     c->c_batches[kInsert] += 1;
     c->c_pairs[kInsert] += n;
-    c->c_touched[kInsert] += nT;
-    c->c_scanned[kInsert] += (c->tot[kTotItems] >> 32) << g.log2B;
+    c->c_touched[kInsert] += bc->alloc_t;
+    c->c_scanned[kInsert] += blocks << g.log2B;
+    c->err_batch = 0;
     if (!ok) {
         c->err_batch = GV_ENOMEM;
         if (sticky && !c->err_sticky) c->err_sticky = GV_ENOMEM;
@@ -1102,40 +1128,40 @@ __device__ __forceinline__ void plan_batch(const GraphView& g, uint64_t n, int s
     c->live_edges += applied;
 }
 
-// One wave per touched source: grow its directory segment if needed (copy the
-// old entries) and record the ids of its new blocks.
+// The free-list places and the statistics of a delete batch, one wave.
+__device__ __forceinline__ void plan_delete(const GraphView& g, const BatchCtr* bc, uint64_t n) {
+    DevCounters* c = g.ctr;
+    const uint32_t k = lane_id();
+    if (batch_failed(c)) {
+        if (k == 0) c->err_batch = GV_EDEVICE;
+        return;
+    }
+    const unsigned long long nuniq = wave_sum(bc->stripe[k][kStripeUniq]);
+    const unsigned long long blocks = wave_sum(bc->stripe[k][kStripeBlocks]);
+    if (k != 0) return;
+    const unsigned long long nv = min((uint64_t)bc->n_valid, n);
+    const unsigned long long applied = ld_agent(&bc->changed);
+    const unsigned long long freed = ld_agent(&bc->demand) & 0xffffffffull;
+    c->err_batch = 0;
+    c->plan_free_top = c->free_cnt;  // the compaction pushes above it
+    c->free_cnt += freed;
+    c->st_applied = applied;
+    c->st_rejected = n - nv;
+    c->st_dups = nv - nuniq;
+    c->c_batches[kDelete] += 1;
+    c->c_pairs[kDelete] += n;
+    c->c_touched[kDelete] += bc->alloc_t;
+    c->c_scanned[kDelete] += blocks << g.log2B;
+    c->c_freed_blocks += freed;
+    c->live_edges -= applied;
+}
+
+// ------------------------------------------------------------------ insert
 // id of the p-th block the batch allocates (free-list top first, then bump)
 __device__ __forceinline__ uint32_t planned_block(const GraphView& g, const DevCounters* c,
                                                   uint64_t p) {
     return p < c->plan_from_free ? g.free_stack[c->plan_free_top - 1 - p]
                                  : (uint32_t)(c->plan_bump0 + (p - c->plan_from_free));
-}
-
-// Append: every kept pair is written to slot deg + rank of its source, read
-// from the vertex record as it was before the batch; new blocks come from
-// the allocation plan, so this runs before the directory is updated.
-__global__ __launch_bounds__(kThreads) void k_append(GraphView g, const uint64_t* keys,
-                                                     const uint8_t* flags, const uint8_t* mark,
-                                                     const uint32_t* a, const uint32_t* b,
-                                                     const uint32_t* t_vtx,
-                                                     const uint32_t* t_start,
-                                                     const uint32_t* t_need) {
-    const DevCounters* c = g.ctr;
-    if (c->err_batch) return;
-    const uint64_t i = thread_index();
-    if (i >= c->tot[kTotValid]) return;
-    const uint8_t f = flags[i], m = mark[i];
-    const uint32_t t = a[i], bi = b[i];
-    const uint64_t key = keys[i];
-    if (!(f & kUniq) || m) return;
-    const uint32_t v = t_vtx[t], lo = t_start[t], p0 = t_need[t];
-    const VRec r = g.vt[v];
-    const uint32_t sl = r.deg + (bi - b[lo]);
-    const uint32_t j = sl >> g.log2B, nb0 = nblocks(g, r.deg);
-    const uint32_t blk = j < nb0 ? block_of(g, r, j) : planned_block(g, c, (uint64_t)p0 + (j - nb0));
-    const uint64_t sa = ((uint64_t)blk << g.log2B) + (sl & (g.B - 1));
-    g.pool[sa] = (uint32_t)(key & ((1ull << g.L) - 1));
-    attr_zero(g, sa);
 }
 
 __device__ __forceinline__ uint32_t planned_segment(const GraphView& g, const DevCounters* c,
@@ -1145,108 +1171,173 @@ __device__ __forceinline__ uint32_t planned_segment(const GraphView& g, const De
                : (uint32_t)(c->plan_dbump[cls] + ((unsigned long long)(rk - c->plan_dff[cls]) << cls));
 }
 
-// Grow: every touched source with kept pairs gets its new block ids (and,
-// when its block count outgrows its directory segment, a new segment holding
-// a copy of the old entries) and its new vertex record.  A lane takes a
-// source that copies and adds at most kLaneCopy entries; the others, listed
-// (and flagged kHeavy) by the planning kernel, are taken by whole waves.
-// The lane loop skips the flagged sources by the flag: a wave that has left
-// the lane loop may already have written a heavy source's new record, and a
-// decision made again from that record could take the source a second time.
-__global__ __launch_bounds__(kThreads) void k_grow(GraphView g, const uint32_t* t_vtx,
-                                                   const uint32_t* t_start, const uint32_t* b,
-                                                   const uint32_t* t_need, const uint32_t* t_dreq,
-                                                   const uint32_t* t_drank, uint32_t* t_dold,
-                                                   uint32_t* t_doldc, const uint32_t* heavy) {
+// A source's new blocks and directory: a lane for a source that copies and
+// adds at most kLaneCopy entries.
+__device__ __forceinline__ void grow_lane(const GraphView& g, const DevCounters* c, const Src& x,
+                                          uint64_t p0, uint32_t cls, uint32_t rk,
+                                          uint32_t* t_dold, uint32_t* t_doldc, uint32_t t) {
+    const VRec r{x.deg, x.dir, x.dcls, 0u};
+    const uint32_t nb0 = nblocks(g, x.deg), nb1 = nblocks(g, x.deg + x.r);
+    VRec nr = r;
+    nr.deg = x.deg + x.r;
+    if (cls != kNoDir) {
+        const uint32_t off = planned_segment(g, c, cls, rk);
+        // (a record keeps its segment when its degree drops, down to zero,
+        // so nb0 may be 0 here: then entry 0 of the segment is read)
+        uint32_t old[kLaneCopy];
+#pragma unroll
+        for (uint32_t j = 0; j < kLaneCopy; ++j)
+            old[j] = block_of(g, r, min(j, nb0 ? nb0 - 1 : 0u));
+#pragma unroll
+        for (uint32_t j = 0; j < kLaneCopy; ++j)
+            if (j < nb0) g.dir[(uint64_t)off + j] = old[j];
+        t_dold[t] = r.dir;
+        t_doldc[t] = r.dcls;
+        nr.dir = off;
+        nr.dcls = cls;
+    }
+    const uint32_t nnew = nb1 - nb0;
+    if (nnew) {
+        uint32_t ids[kLaneCopy];
+#pragma unroll
+        for (uint32_t j = 0; j < kLaneCopy; ++j) ids[j] = planned_block(g, c, p0 + min(j, nnew - 1));
+#pragma unroll
+        for (uint32_t j = 0; j < kLaneCopy; ++j) {
+            if (j >= nnew) continue;
+            if (nr.dcls == kNoDir) nr.dir = ids[j];  // the only block, inline
+            else g.dir[(uint64_t)nr.dir + nb0 + j] = ids[j];
+            g.bown[ids[j]] = make_uint2(x.v, nb0 + j);
+        }
+    }
+    g.vt[x.v] = nr;
+}
+
+// Commit of an insert, the tiles of the segments kernel: every kept pair is
+// written to slot deg + rank of its source, and every source with kept pairs
+// gets its new block ids (and, when its block count outgrows its directory
+// segment, a new segment holding a copy of the old entries) and its new
+// vertex record.  Sources that copy or add more entries than a lane takes,
+// listed (and flagged kHeavy) by the plan, are taken by whole waves.  Both
+// read the records as they were before the batch from the sources' own
+// copies, and only directory entries that the batch does not write, so they
+// need no order between them.  One kernel in place of two, each with its own
+// pass over flags, ranks and segment starts (10^4 pairs: 9.6 -> 7.0 us).
+template <int T>
+__global__ __launch_bounds__(T) void k_commit(GraphView g, const uint64_t* keys, uint64_t n,
+                                              const BatchCtr* bc, uint32_t tl,
+                                              const uint8_t* mark, const Src* srcs,
+                                              const uint2* tiles, const uint2* carry,
+                                              const uint32_t* tbase, const uint32_t* t_dreq,
+                                              const uint32_t* t_drank, uint32_t* t_dold,
+                                              uint32_t* t_doldc, const uint32_t* heavy) {
+    constexpr uint32_t kTile = T * kTileRows;
+    __shared__ uint32_t s_pre[kTile];
+    __shared__ uint32_t s_cnt[kTileRows * T / 64], s_cnt2[kTileRows * T / 64];
     const DevCounters* c = g.ctr;
     if (c->err_batch) return;
-    const uint32_t nT = (uint32_t)c->tot[kTotSeg];
-    const uint32_t lane = lane_id();
-    const uint32_t stride = gridDim.x * kThreads;
-    for (uint32_t base = global_wave() * 64; base < nT; base += stride) {
-        const bool live = base + lane < nT;
-        const uint32_t t = live ? base + lane : nT - 1;
-        const uint32_t v = t_vtx[t], lo = t_start[t], hi = t_start[t + 1];
-        const uint32_t p0 = t_need[t], req = t_dreq[t], rk = t_drank[t];
-        const uint32_t kp = b[hi] - b[lo];
-        if (!live || !kp || (req & kHeavy)) continue;
-        const uint32_t cls = req & kClassMask;
-        const VRec r = g.vt[v];  // only this lane writes it
-        const uint32_t nb0 = nblocks(g, r.deg), nb1 = nblocks(g, r.deg + kp);
-        VRec nr = r;
-        nr.deg = r.deg + kp;
-        if (cls != kNoDir) {
-            const uint32_t off = planned_segment(g, c, cls, rk);
-            // (a record keeps its segment when its degree drops, down to zero,
-            // so nb0 may be 0 here: then entry 0 of the segment is read)
-            uint32_t old[kLaneCopy];
+    const uint32_t t = threadIdx.x;
+    const uint64_t lim = min((uint64_t)bc->n_valid, n);
+    const uint64_t p0 = (uint64_t)blockIdx.x << tl;
+    const uint32_t L = g.L;
+    if (p0 < lim) {  // uniform over the workgroup
+        const uint32_t np = (uint32_t)min((uint64_t)1 << tl, lim - p0);
+        const uint2 td = tiles[blockIdx.x];
+        const uint32_t t0 = td.x, nh = td.y, base0 = tbase[blockIdx.x];
+        uint64_t k[kTileRows], q[kTileRows];
+        uint8_t m[kTileRows];
 #pragma unroll
-            for (uint32_t j = 0; j < kLaneCopy; ++j)
-                old[j] = block_of(g, r, min(j, nb0 ? nb0 - 1 : 0u));
-#pragma unroll
-            for (uint32_t j = 0; j < kLaneCopy; ++j)
-                if (j < nb0) g.dir[(uint64_t)off + j] = old[j];
-            t_dold[t] = r.dir;
-            t_doldc[t] = r.dcls;
-            nr.dir = off;
-            nr.dcls = cls;
+        for (uint32_t j = 0; j < kTileRows; ++j) {
+            const uint64_t i = p0 + min(j * T + t, np - 1);
+            k[j] = keys[i];
+            q[j] = keys[i ? i - 1 : 0];
+            m[j] = mark[i];
         }
-        const uint32_t nnew = nb1 - nb0;
-        if (nnew) {
-            uint32_t ids[kLaneCopy];
+        bool head[kTileRows], kept[kTileRows];
+        uint32_t hr[kTileRows], kr[kTileRows];
 #pragma unroll
-            for (uint32_t j = 0; j < kLaneCopy; ++j)
-                ids[j] = planned_block(g, c, (uint64_t)p0 + min(j, nnew - 1));
+        for (uint32_t j = 0; j < kTileRows; ++j) {
+            const uint32_t p = j * T + t;
+            head[j] = p < np && (p0 + p == 0 || (k[j] >> L) != (q[j] >> L));
+            kept[j] = p < np && m[j] == 0;
+        }
+        tile_ranks<T>(head, hr, s_cnt);
+        tile_ranks<T>(kept, kr, s_cnt2);
 #pragma unroll
-            for (uint32_t j = 0; j < kLaneCopy; ++j) {
-                if (j >= nnew) continue;
-                if (nr.dcls == kNoDir) nr.dir = ids[j];  // the only block, inline
-                else g.dir[(uint64_t)nr.dir + nb0 + j] = ids[j];
-                g.bown[ids[j]] = make_uint2(v, nb0 + j);
+        for (uint32_t j = 0; j < kTileRows; ++j) s_pre[j * T + t] = kr[j];
+        __syncthreads();
+#pragma unroll
+        for (uint32_t j = 0; j < kTileRows; ++j) {
+            if (!kept[j]) continue;
+            const uint32_t h = hr[j] + (head[j] ? 1u : 0u);  // heads up to this position
+            uint32_t ts = t0 + h - 1, rank, pb = base0;
+            Src x;
+            if (h) {
+                x = srcs[ts];
+                rank = kr[j] - s_pre[x.lo - (uint32_t)p0];
+            } else {  // a segment that began in an earlier tile
+                const uint2 cr = carry[blockIdx.x];
+                x = srcs[cr.x];
+                rank = cr.y + kr[j];
+                pb = tbase[x.lo >> tl];
             }
+            const VRec r{x.deg, x.dir, x.dcls, 0u};
+            const uint32_t sl = r.deg + rank;
+            const uint32_t b = sl >> g.log2B, nb0 = nblocks(g, r.deg);
+            const uint32_t blk = b < nb0 ? block_of(g, r, b)
+                                         : planned_block(g, c, (uint64_t)pb + x.need + (b - nb0));
+            const uint64_t sa = ((uint64_t)blk << g.log2B) + (sl & (g.B - 1));
+            g.pool[sa] = (uint32_t)(k[j] & ((1ull << L) - 1));
+            attr_zero(g, sa);
         }
-        g.vt[v] = nr;
+        for (uint32_t h = t; h < nh; h += T) {
+            const Src x = srcs[t0 + h];
+            const uint32_t req = t_dreq[t0 + h];
+            if (!x.r || (req & kHeavy)) continue;
+            const uint32_t cls = req & kClassMask;
+            const uint32_t rk = cls != kNoDir ? t_drank[t0 + h] : 0u;
+            grow_lane(g, c, x, (uint64_t)base0 + x.need, cls, rk, t_dold, t_doldc, t0 + h);
+        }
     }
-    const uint32_t nh = c->n_heavy;
-    const uint32_t nw = gridDim.x * kWaves;
-    for (uint32_t k = global_wave(); k < nh; k += nw) {
-        const uint32_t t = heavy[k];
-        const uint32_t v = t_vtx[t];
-        const VRec r = g.vt[v];
-        const uint32_t kp = b[t_start[t + 1]] - b[t_start[t]];
-        const uint32_t nb0 = nblocks(g, r.deg), nb1 = nblocks(g, r.deg + kp);
-        const uint32_t cls = t_dreq[t] & kClassMask;
+    const uint32_t nh = bc->n_heavy, lane = lane_id();
+    const uint32_t nw = gridDim.x * (T / 64);
+    for (uint32_t i = blockIdx.x * (T / 64) + (t >> 6); i < nh; i += nw) {
+        const uint32_t ts = heavy[i];
+        const Src x = srcs[ts];
+        const VRec r{x.deg, x.dir, x.dcls, 0u};
+        const uint32_t nb0 = nblocks(g, r.deg), nb1 = nblocks(g, r.deg + x.r);
+        const uint32_t cls = t_dreq[ts] & kClassMask;
         VRec nr = r;
-        nr.deg = r.deg + kp;
+        nr.deg = r.deg + x.r;
         if (cls != kNoDir) {
-            const uint32_t off = planned_segment(g, c, cls, t_drank[t]);
+            const uint32_t off = planned_segment(g, c, cls, t_drank[ts]);
             for (uint32_t j = lane; j < nb0; j += 64) g.dir[(uint64_t)off + j] = block_of(g, r, j);
             if (lane == 0) {
-                t_dold[t] = r.dir;
-                t_doldc[t] = r.dcls;
+                t_dold[ts] = r.dir;
+                t_doldc[ts] = r.dcls;
             }
             nr.dir = off;
             nr.dcls = cls;
         }
-        const uint64_t p0 = t_need[t];
+        const uint64_t pb = (uint64_t)tbase[x.lo >> tl] + x.need;
         for (uint32_t j = nb0 + lane; j < nb1; j += 64) {
-            const uint32_t blk = planned_block(g, c, p0 + (j - nb0));
+            const uint32_t blk = planned_block(g, c, pb + (j - nb0));
             g.dir[(uint64_t)nr.dir + j] = blk;
-            g.bown[blk] = make_uint2(v, j);
+            g.bown[blk] = make_uint2(x.v, j);
         }
-        if (lane == 0) g.vt[v] = nr;
+        if (lane == 0) g.vt[x.v] = nr;
     }
 }
 
 // Old directory segments of the sources that moved go on the per-class free
 // lists (after the commit kernel has taken its segments from them).
-__global__ __launch_bounds__(kThreads) void k_final_ins(GraphView g, const uint32_t* rel,
+__global__ __launch_bounds__(kThreads) void k_final_ins(GraphView g, const BatchCtr* bc,
+                                                        const uint32_t* rel,
                                                         const uint32_t* t_dold,
                                                         const uint32_t* t_doldc) {
     __shared__ uint32_t lcnt[kMaxClass];
     __shared__ uint32_t lbase[kMaxClass];
     __shared__ unsigned long long lfreed;
-    const uint32_t nrel = g.ctr->err_batch ? 0u : (uint32_t)(g.ctr->tot[kTotB] >> 32);
+    const uint32_t nrel = g.ctr->err_batch ? 0u : (uint32_t)(bc->demand >> 32);
     for (uint32_t base = blockIdx.x * kThreads; base < nrel; base += gridDim.x * kThreads) {
         if (threadIdx.x < kMaxClass) lcnt[threadIdx.x] = 0;
         if (threadIdx.x == 0) lfreed = 0;
@@ -1275,81 +1366,6 @@ __global__ __launch_bounds__(kThreads) void k_final_ins(GraphView g, const uint3
 
 // ------------------------------------------------------------------ delete
 
-// a source that one lane compacts by itself
-__device__ __forceinline__ bool lane_compactable(uint32_t r, uint32_t lo, uint32_t hi) {
-    return r <= kLaneR && hi - lo <= kLaneSeg;
-}
-
-// a touched source of a delete batch with its hit count r
-struct FreedRec {
-    TouchRec x;
-    uint32_t r;   // hits
-    uint32_t rg;  // of which counted by group items (in the vertex scratch word)
-};
-
-struct FreedIn {
-    static constexpr int kItems = 4;  // large records: fewer per thread
-    GraphView g;
-    const uint32_t* t_vtx;
-    const uint32_t* t_start;
-    const uint32_t* shits;
-    using Rec = FreedRec;
-    __device__ uint64_t limit(uint64_t n) const {
-        return batch_failed(g.ctr) ? 0ull : min((uint64_t)(uint32_t)g.ctr->tot[kTotSeg], n);
-    }
-    __device__ Rec load(uint64_t t, bool ok) const {
-        return Rec{load_touched(t_vtx, t_start, t, ok), shits[ok ? t : 0], 0u};
-    }
-    // the source's hits: its small item's count plus what its group items
-    // added to its vertex scratch word
-    __device__ void deref(Rec& f) const {
-        f.x.r = g.vt[f.x.v];
-        f.rg = g.vlost[f.x.v];
-        f.r += f.rg;
-    }
-    // freed blocks in the low half; in the high half, 1 for a source that a
-    // whole wave compacts (its rank among those is its slot in the list)
-    __device__ unsigned long long value(uint64_t, const Rec& f) const {
-        const uint32_t d = f.x.r.deg;
-        if (!f.r) return 0ull;
-        const unsigned long long mid =
-            f.r <= kBigR && !lane_compactable(f.r, f.x.lo, f.x.hi) ? 1ull : 0ull;
-        return (unsigned long long)(nblocks(g, d) - nblocks(g, d - f.r)) | (mid << 32);
-    }
-};
-
-// Also clears each source's hit count (the vertex scratch word is zero
-// between calls) and adds the hits of every workgroup into tot[kTotA].
-struct FreedOut {
-    DevCounters* ctr;
-    CDesc* cd;
-    uint32_t* big;
-    uint32_t* mid;  // sources for whole waves
-    uint32_t* vlost;
-    __device__ void operator()(uint64_t t, const FreedRec& f, uint64_t lim,
-                               unsigned long long pre) const {
-        if (t >= lim) return;
-        if (f.rg) vlost[f.x.v] = 0u;
-        if (f.r && f.r <= kBigR && !lane_compactable(f.r, f.x.lo, f.x.hi))
-            mid[(uint32_t)(pre >> 32)] = (uint32_t)t;
-        CDesc c;
-        c.lo = f.x.lo;
-        c.hi = f.x.hi;
-        c.r = f.r;
-        c.v = f.x.v;
-        c.deg = f.x.r.deg;
-        c.dir = f.x.r.dir;
-        c.dcls = f.x.r.dcls;
-        c.need = (uint32_t)pre;
-        cd[t] = c;
-        if (c.r > kBigR) big[atomicAdd(&ctr->n_big, 1u)] = (uint32_t)t;
-    }
-    __device__ unsigned long long tally(uint64_t, const FreedRec& f) const { return f.r; }
-    __device__ void commit(unsigned long long sum) const {
-        if (sum) atomicAdd(&ctr->tot[kTotA], sum);
-    }
-};
-
 // Compaction of every touched source with at most kBigR hits: holes below the
 // new degree (taken in batch order) receive the survivors found above it (in
 // slot order), and emptied blocks go on the free list.  A lane takes a source
@@ -1357,20 +1373,21 @@ struct FreedOut {
 // whole wave in turn.
 __device__ __forceinline__ void compact_body(const GraphView& g, const uint8_t* mark,
                                              const uint32_t* hitpos, uint32_t* holes,
-                                             const CDesc* cdesc, const uint32_t* mid,
-                                             uint32_t vb, uint32_t vg) {
+                                             const BatchCtr* bc, const Src* srcs,
+                                             const uint32_t* tbase, uint32_t tl,
+                                             const uint32_t* mid, uint32_t vb, uint32_t vg) {
     const uint32_t gwave = (vb * kThreads + threadIdx.x) >> 6;
     const DevCounters* c = g.ctr;
-    const uint32_t nT = (uint32_t)c->tot[kTotSeg];
+    const uint32_t nT = (uint32_t)bc->alloc_t;
     const uint32_t lane = lane_id();
     const uint64_t below = (1ull << lane) - 1;
     const uint32_t stride = vg * kThreads;
-    const unsigned long long fbase = c->free_cnt;
+    const unsigned long long fbase = c->plan_free_top;
     const uint32_t bm = g.B - 1;
     unsigned long long moved = 0;
     for (uint32_t base = gwave * 64; base < nT; base += stride) {
         const bool live = base + lane < nT;
-        const CDesc D = cdesc[live ? base + lane : nT - 1];
+        const Src D = srcs[live ? base + lane : nT - 1];
         if (live && D.r && lane_compactable(D.r, D.lo, D.hi)) {
             const VRec rec{D.deg, D.dir, D.dcls, 0u};
             const uint32_t d = D.deg, dn = d - D.r;
@@ -1432,7 +1449,7 @@ __device__ __forceinline__ void compact_body(const GraphView& g, const uint8_t* 
             }
             moved += nmove;
             const uint32_t nb0 = nblocks(g, d), nb1 = nblocks(g, dn);
-            const unsigned long long pb = fbase + D.need;
+            const unsigned long long pb = fbase + tbase[D.lo >> tl] + D.need;
 #pragma unroll
             for (uint32_t k = 0; k < kLaneR; ++k)
                 if (nb1 + k < nb0) g.free_stack[pb + k] = block_of(g, rec, nb1 + k);
@@ -1444,11 +1461,11 @@ __device__ __forceinline__ void compact_body(const GraphView& g, const uint8_t* 
     }
     // sources with more hits or longer segments, listed by the freed scan:
     // one wave each
-    const uint32_t nmid = (uint32_t)(c->tot[kTotB] >> 32);
+    const uint32_t nmid = (uint32_t)(bc->demand >> 32);
     const uint32_t nw = vg * kWaves;
     for (uint32_t k = gwave; k < nmid; k += nw) {
         {
-            const CDesc H = cdesc[mid[k]];
+            const Src H = srcs[mid[k]];
             const VRec rec{H.deg, H.dir, H.dcls, 0u};
             const uint32_t d = H.deg, dn = d - H.r;
             uint32_t nh = 0;
@@ -1487,7 +1504,7 @@ __device__ __forceinline__ void compact_body(const GraphView& g, const uint8_t* 
             }
             moved += lane == 0 ? ns : 0;
             const uint32_t nb0 = nblocks(g, d), nb1 = nblocks(g, dn);
-            const unsigned long long pb = fbase + H.need;
+            const unsigned long long pb = fbase + tbase[H.lo >> tl] + H.need;
             for (uint32_t j = nb1 + lane; j < nb0; j += 64)
                 g.free_stack[pb + (j - nb1)] = block_of(g, rec, j);
             if (lane == 0) {
@@ -1505,16 +1522,17 @@ __device__ __forceinline__ void compact_body(const GraphView& g, const uint8_t* 
 // One workgroup per source with more than kBigR hits (hubs), same pairing.
 __device__ __forceinline__ void compact_big_body(const GraphView& g, const uint8_t* mark,
                                                  const uint32_t* hitpos, uint32_t* holes,
-                                                 const CDesc* cdesc, const uint32_t* big,
-                                                 uint32_t vb, uint32_t vg) {
+                                                 const BatchCtr* bc, const Src* srcs,
+                                                 const uint32_t* tbase, uint32_t tl,
+                                                 const uint32_t* big, uint32_t vb,
+                                                 uint32_t vg) {
     __shared__ uint32_t lds[kWaves];
-    const DevCounters* c = g.ctr;
-    const uint32_t nbig = c->n_big;
-    const unsigned long long fbase = c->free_cnt;
+    const uint32_t nbig = bc->n_big;
+    const unsigned long long fbase = g.ctr->plan_free_top;
     const uint32_t tid = threadIdx.x;
     unsigned long long moved = 0;
     for (uint32_t q = vb; q < nbig; q += vg) {
-        const CDesc D = cdesc[big[q]];
+        const Src D = srcs[big[q]];
         const VRec rec{D.deg, D.dir, D.dcls, 0u};
         const uint32_t d = D.deg, dn = d - D.r;
         uint32_t nh = 0;
@@ -1554,7 +1572,7 @@ __device__ __forceinline__ void compact_big_body(const GraphView& g, const uint8
         }
         moved += tid == 0 ? ns : 0;
         const uint32_t nb0 = nblocks(g, d), nb1 = nblocks(g, dn);
-        const unsigned long long pb = fbase + D.need;
+        const unsigned long long pb = fbase + tbase[D.lo >> tl] + D.need;
         for (uint32_t j = nb1 + tid; j < nb0; j += kThreads)
             g.free_stack[pb + (j - nb1)] = block_of(g, rec, j);
         if (tid == 0) {
@@ -1572,52 +1590,34 @@ __device__ __forceinline__ void compact_big_body(const GraphView& g, const uint8
 // (they run longest, so they start first), the rest the other sources.
 __global__ __launch_bounds__(kThreads) void k_compact(GraphView g, const uint8_t* mark,
                                                       const uint32_t* hitpos, uint32_t* holes,
-                                                      const CDesc* cdesc, const uint32_t* mid,
-                                                      const uint32_t* big, uint32_t nbig) {
+                                                      const BatchCtr* bc, const Src* srcs,
+                                                      const uint32_t* tbase, uint32_t tl,
+                                                      const uint32_t* mid, const uint32_t* big,
+                                                      uint32_t nbig) {
     if (batch_failed(g.ctr)) return;
     if (blockIdx.x < nbig)
-        compact_big_body(g, mark, hitpos, holes, cdesc, big, blockIdx.x, nbig);
+        compact_big_body(g, mark, hitpos, holes, bc, srcs, tbase, tl, big, blockIdx.x, nbig);
     else
-        compact_body(g, mark, hitpos, holes, cdesc, mid, blockIdx.x - nbig, gridDim.x - nbig);
-}
-
-
-__global__ void k_final_del(GraphView g, uint64_t n) {
-    DevCounters* c = g.ctr;
-    if (batch_failed(c)) {
-        c->err_batch = GV_EDEVICE;
-        return;
-    }
-    const unsigned long long nv = c->tot[kTotValid];
-    const unsigned long long nT = c->tot[kTotSeg] & 0xffffffffull;
-    const unsigned long long nuniq = c->tot[kTotSeg] >> 32;
-    const unsigned long long applied = c->tot[kTotA];
-    const unsigned long long freed = c->tot[kTotB] & 0xffffffffull;
-    c->free_cnt += freed;
-    c->st_applied = applied;
-    c->st_rejected = n - nv;
-    c->st_dups = nv - nuniq;
-    c->c_batches[kDelete] += 1;
-    c->c_pairs[kDelete] += n;
-    c->c_touched[kDelete] += nT;
-    c->c_scanned[kDelete] += (c->tot[kTotItems] >> 32) << g.log2B;
-    c->c_freed_blocks += freed;
-    c->live_edges -= applied;
+        compact_body(g, mark, hitpos, holes, bc, srcs, tbase, tl, mid, blockIdx.x - nbig,
+                     gridDim.x - nbig);
 }
 
 // ------------------------------------------------------------------ query
-__global__ __launch_bounds__(kThreads) void k_answer(GraphView g, const uint32_t* vals,
-                                                     const uint8_t* mark, uint64_t n,
-                                                     uint8_t* out) {
+__global__ __launch_bounds__(kThreads) void k_answer(GraphView g, const BatchCtr* bc,
+                                                     const uint32_t* vals, const uint8_t* mark,
+                                                     uint64_t n, uint8_t* out) {
     const uint64_t i = thread_index();
     if (batch_failed(g.ctr)) return;  // the answers are not written; the call reports the error
-    const unsigned long long nv = g.ctr->tot[kTotValid];
-    if (i == 0) {
-        DevCounters* c = g.ctr;
-        c->c_batches[kQuery] += 1;
-        c->c_pairs[kQuery] += n;
-        c->c_touched[kQuery] += c->tot[kTotSeg] & 0xffffffffull;
-        c->c_scanned[kQuery] += (c->tot[kTotItems] >> 32) << g.log2B;
+    const unsigned long long nv = min((uint64_t)bc->n_valid, n);
+    if (i < 64) {
+        const unsigned long long blocks = wave_sum(bc->stripe[i][kStripeBlocks]);
+        if (i == 0) {
+            DevCounters* c = g.ctr;
+            c->c_batches[kQuery] += 1;
+            c->c_pairs[kQuery] += n;
+            c->c_touched[kQuery] += bc->alloc_t;
+            c->c_scanned[kQuery] += blocks << g.log2B;
+        }
     }
     if (i < nv && vals[i] < n) out[vals[i]] = mark[i];
 }
@@ -1625,13 +1625,14 @@ __global__ __launch_bounds__(kThreads) void k_answer(GraphView g, const uint32_t
 // ------------------------------------------------------------------ attributes
 // get: a found pair's attributes (read at the slot the probe recorded) at
 // its input position; a pair not found reads zeros
-__global__ __launch_bounds__(kThreads) void k_attr_get(GraphView g, const uint64_t* keys,
+__global__ __launch_bounds__(kThreads) void k_attr_get(GraphView g, const BatchCtr* bc,
+                                                       const uint64_t* keys,
                                                        const uint32_t* vals, const uint8_t* mark,
                                                        const uint32_t* hitpos, uint64_t n,
                                                        uint32_t* out) {
     const uint64_t i = thread_index();
     if (batch_failed(g.ctr)) return;
-    const uint64_t nv = min((uint64_t)g.ctr->tot[kTotValid], n);
+    const uint64_t nv = min((uint64_t)bc->n_valid, n);
     if (i >= nv || vals[i] >= n) return;
     const uint64_t o = (uint64_t)vals[i] * g.A;
     if (!mark[i]) {
@@ -1645,14 +1646,16 @@ __global__ __launch_bounds__(kThreads) void k_attr_get(GraphView g, const uint64
 // set: the last occurrence of each found pair in input order (the sort is
 // stable, so the last of its run) writes its attributes; counts for the
 // statistics
-__global__ __launch_bounds__(kThreads) void k_attr_set(GraphView g, const uint64_t* keys,
+__global__ __launch_bounds__(kThreads) void k_attr_set(GraphView g, const BatchCtr* bc,
+                                                       const uint64_t* keys,
                                                        const uint32_t* vals, const uint8_t* mark,
                                                        const uint32_t* hitpos, uint64_t n,
                                                        const uint32_t* in) {
     __shared__ unsigned long long lds[kWaves];
     const uint64_t i = thread_index();
     if (batch_failed(g.ctr)) return;
-    const uint64_t nv = min((uint64_t)g.ctr->tot[kTotValid], n);
+    const uint64_t nv = min((uint64_t)bc->n_valid, n);
+    if (i == 0) g.ctr->st_valid = nv;
     unsigned long long distinct = 0, applied = 0;
     if (i < nv) {
         const bool last = i + 1 >= nv || keys[i + 1] != keys[i];
@@ -1724,7 +1727,6 @@ void edge_batch_warm(const gv_graph* g) {
             with_probe<kLocate>(pg, pu, warm);
         }
     }
-    resident_grid(k_grow, kThreads);
     resident_grid(k_compact, kThreads);
     resident_grid(k_os_pass<uint64_t, false>, kOsThreads);
     resident_grid(k_os_pass<uint64_t, true>, kOsThreads);
@@ -1743,22 +1745,26 @@ size_t edge_batch_bytes(const gv_graph* g, EdgeMode mode, uint64_t n) {
 
 // Insert and delete batches whose keys arrive sorted (keys[0, *count), the
 // count on the device; they come from the library's own sort of a mixed
-// list): one kernel clears the marks, and its first workgroup clears the
-// batch counters, sets the valid count and turns the probe's multiset check
-// off (there is no packing to compare with; the segment scan still checks
-// the order).
-__global__ __launch_bounds__(kThreads) void k_sorted_prep(GraphView g,
-                                                          const unsigned long long* count,
-                                                          uint64_t n, uint8_t* mark) {
-    const uint64_t i = thread_index();
-    if (i < n) mark[i] = 0;
-    if (blockIdx.x == 0) {
-        clear_batch_counters(g.ctr, threadIdx.x);
-        if (threadIdx.x == 0) {
-            g.ctr->tot[kTotValid] = *count;
-            g.ctr->tot[kTotNoHash] = 1;
-        }
+// list): clears the batch counters, sets the valid count and turns the
+// probe's multiset check off (there is no packing to compare with; the
+// segments kernel still checks the order).
+__global__ __launch_bounds__(kThreads) void k_sorted_prep(BatchCtr* bc,
+                                                          const unsigned long long* count) {
+    clear_batch(bc, threadIdx.x, kThreads);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        bc->n_valid = *count;
+        bc->nohash = 1;
     }
+}
+
+// Insert and delete batches of at most this many pairs are sorted by rank: up
+// to the tuning's small_sort_max, whose largest value stands for kRankMax
+// (where the two ways cross, see k_rank_sort) unless the sort overlap is on,
+// which hides the radix passes of larger batches.
+static uint64_t rank_limit(const gv_graph* g) {
+    const uint64_t m = g->tune.small_sort_max;
+    return m < kOsTile || g->tune.overlap ? m : kRankMax;
 }
 
 static void edge_run(gv_graph* g, EdgeMode mode, const uint32_t* src, const uint32_t* dst,
@@ -1793,17 +1799,6 @@ void edge_attrs(gv_graph* g, const uint32_t* src, const uint32_t* dst, uint64_t 
         c.launch("attr_set", k_attr_begin, 1, 1, g->v.ctr);
     }
     edge_run(g, kQuery, src, dst, nullptr, nullptr, n, found, true, nullptr, 0, nullptr, &op);
-}
-
-// First kernel of an overlapped batch on the graph's stream: clears the
-// batch counters and takes the valid-pair count and key sum that the batch's
-// packing left in its buffer.
-__global__ void k_ov_begin(GraphView g, const unsigned long long* stot) {
-    clear_batch_counters(g.ctr, threadIdx.x);
-    if (threadIdx.x == 0) {
-        g.ctr->tot[kTotValid] = stot[0];
-        g.ctr->tot[kTotHash] = stot[1];
-    }
 }
 
 void overlap_open(gv_graph* g) {
@@ -1857,8 +1852,9 @@ static void edge_run(gv_graph* g, EdgeMode mode, const uint32_t* src, const uint
     // sort overlap: this batch's pack and sort go to the side stream (also
     // while the graph's stream is captured: the side stream then joins the
     // capture through the first wait, and the recording keeps both branches)
+    const uint64_t rank_max = mode == kQuery ? kRankMax : rank_limit(g);
     const bool ovb = g->tune.overlap && !sorted && !fixed && mode != kQuery && bits > 0 &&
-                     n > std::min<uint64_t>(g->tune.small_sort_max, kOsTile);
+                     n > rank_max;
     if (ovb) overlap_capture(g);
     const int ob = (int)(g->ov.count & 1);  // its buffer
     BatchArrays A;
@@ -1883,89 +1879,77 @@ static void edge_run(gv_graph* g, EdgeMode mode, const uint32_t* src, const uint
     }
     DevCounters* ctr = v.ctr;
     uint32_t* err = &ctr->err_wait;
-    unsigned long long* tot = ctr->tot;
-    const unsigned long long* n_valid = &tot[kTotValid];
+    BatchCtr* bc = A.bc;
+    const unsigned long long* n_valid = &bc->n_valid;
     const uint64_t grid = div_up(n, kThreads);
 
     bool flip;
     const uint64_t* keys_in = nullptr;
     if (sorted) {
-        c.launch("pack", k_sorted_prep, grid, kThreads, v, sorted_n, n, A.mark);
+        c.launch("pack", k_sorted_prep, 1, kThreads, bc, sorted_n);
         keys_in = sorted;
         flip = false;
-    } else if (mode == kQuery && n <= kOsTile && bits + kTilePosBits < 64) {
-        c.launch("pack", k_query_sort_tile, 1, kOsThreads, v, src, dst, n,
-                 os_passes(bits + kTilePosBits), A.keys0, A.vals0, out, A.mark);
+    } else if (n <= rank_max) {
+        rank_sort(c, "pack", EdgeKeys{v, src, dst, out, bc}, n, A.keys0, A.vals0);
         flip = false;
     } else if (mode == kQuery) {
         c.launch("begin", k_begin, std::min<uint64_t>(div_up(A.state_words, kThreads), 1024),
-                 kThreads, v, A.state, A.state_words);
-        scan2(c, "pack", PackIn{v, src, dst}, PackOut{v.L, A.keys0, A.vals0, out, A.mark}, n,
-              A.part, &tot[kTotValid]);
+                 kThreads, bc, A.state, A.state_words);
+        scan2(c, "pack", PackIn{v, src, dst}, PackOut{v.L, A.keys0, A.vals0, out}, n, A.part,
+              &bc->n_valid);
         flip = onesweep<uint64_t, true>(c, A.keys0, A.keys1, A.vals0, A.vals1,
                                         (const uint32_t*)n_valid, n, bits, A.state, err,
                                         g->spin_limit);
-    } else if (n <= std::min<uint64_t>(g->tune.small_sort_max, kOsTile) && bits > 0) {
-        const uint64_t sentinel = bits >= 64 ? ~0ull : (1ull << bits) - 1;
-        c.launch("pack", k_pack_sort_tile, 1, kOsThreads, v, src, dst, n, os_passes(bits),
-                 sentinel, A.keys0, A.mark);
-        flip = false;
-    } else if (ovb) {
-        // The side stream reads the pairs and the activity bitmap (which no
+    } else {
+        // With the sort overlap the packing and the passes run on the side
+        // stream, which reads the pairs and the activity bitmap (which no
         // edge batch changes) and writes only this batch's buffer: it waits
         // for the graph's stream when anything else was queued there since
         // the last overlapped batch, and for the batch that used the buffer
-        // before.  The batch counters are cleared on the graph's stream, once
-        // the batch before has finished with them.
+        // before.
         gv_graph::Overlap& o = g->ov;
-        overlap_open(g);
-        Ctx& sc = o.ctx;
-        sc.prof = c.prof;
-        sc.only = c.only;
-        if (c.seq != o.seq) {
-            overlap_fence(g);
-        } else if (o.used[ob]) {
-            // (with a fence, the wait for the graph's stream covers this one)
-            hip_check(hipStreamWaitEvent(o.stream, o.done[ob], 0), "hipStreamWaitEvent");
+        if (ovb) {
+            overlap_open(g);
+            o.ctx.prof = c.prof;
+            o.ctx.only = c.only;
+            if (c.seq != o.seq) {
+                overlap_fence(g);
+            } else if (o.used[ob]) {
+                // (with a fence, the wait for the graph's stream covers this one)
+                hip_check(hipStreamWaitEvent(o.stream, o.done[ob], 0), "hipStreamWaitEvent");
+            }
         }
+        Ctx& sc = ovb ? o.ctx : c;
         const uint64_t sentinel = bits >= 64 ? ~0ull : (1ull << bits) - 1;
         sc.launch("pack", k_pack_hist, os_hist_groups(n), kOsThreads, v, src, dst, n,
-                  os_passes(bits), sentinel, A.keys0, A.mark, A.state, A.state_words,
-                  os_hpart(A.state, n, bits), A.vpart, A.hpart, 0);
-        os_hist_sum(sc, A.state, n, bits, (const uint32_t*)A.vpart, &A.stot[0],
-                    (const unsigned long long*)A.hpart, &A.stot[1]);
+                  bits > 0 ? os_passes(bits) : 0, sentinel, A.keys0, bc, A.state, A.state_words,
+                  os_hpart(A.state, n, bits), A.vpart, A.hpart);
+        os_hist_sum(sc, A.state, n, bits, (const uint32_t*)A.vpart, &bc->n_valid,
+                    (const unsigned long long*)A.hpart, &bc->key_sum);
         flip = onesweep_passes<uint64_t, false>(sc, A.keys0, A.keys1, nullptr, nullptr, nullptr, n,
-                                                bits, A.state, err, g->spin_limit, true);
-        sc.close_run();
-        hip_check(hipEventRecord(o.sorted[ob], o.stream), "hipEventRecord");
-        hip_check(hipStreamWaitEvent(c.stream, o.sorted[ob], 0), "hipStreamWaitEvent");
-        // the segment scan's first kernel clears the batch counters (a batch
-        // of one scan tile has no such kernel: a kernel of its own does it)
-        if (scan2_tiles<SegIn>(n) <= 1)
-            c.launch("pack", k_ov_begin, 1, 64, v, (const unsigned long long*)A.stot);
-    } else {
-        const uint64_t sentinel = bits >= 64 ? ~0ull : (1ull << bits) - 1;
-        c.launch("pack", k_pack_hist, os_hist_groups(n), kOsThreads, v, src, dst, n,
-                 bits > 0 ? os_passes(bits) : 0, sentinel, A.keys0, A.mark, A.state,
-                 A.state_words, os_hpart(A.state, n, bits), A.vpart, A.hpart, 1);
-        os_hist_sum(c, A.state, n, bits, (const uint32_t*)A.vpart, &tot[kTotValid],
-                    (const unsigned long long*)A.hpart, &tot[kTotHash]);
-        flip = onesweep_passes<uint64_t, false>(c, A.keys0, A.keys1, nullptr, nullptr, nullptr, n,
-                                                bits, A.state, err, g->spin_limit);
+                                                bits, A.state, err, g->spin_limit, ovb);
+        if (ovb) {
+            sc.close_run();
+            hip_check(hipEventRecord(o.sorted[ob], o.stream), "hipEventRecord");
+            hip_check(hipStreamWaitEvent(c.stream, o.sorted[ob], 0), "hipStreamWaitEvent");
+        }
     }
     const uint64_t* keys = keys_in ? keys_in : flip ? A.keys1 : A.keys0;
     const uint32_t* vals = flip ? A.vals1 : A.vals0;
 
-    const bool seg_clears = ovb && scan2_tiles<SegIn>(n) > 1;
-    scan2(c, "segments",
-          SegIn{keys, ctr, v.L, ovb ? (const unsigned long long*)A.stot : n_valid,
-                seg_clears ? ctr : nullptr},
-          SegOut{v.L, A.flags, A.a, A.t_vtx, A.t_start, ctr}, n, A.part,
-          &tot[kTotSeg]);
+    const uint32_t tl = tile_log(n);
+    const uint64_t ntiles = div_up(n, 1ull << tl);
+    // workgroups of 256 threads while a tile is at most four positions each
+    auto with_threads = [&](auto&& f) {
+        if ((1u << tl) <= kThreads * kTileRows) f(std::integral_constant<int, kThreads>{});
+        else f(std::integral_constant<int, 1024>{});
+    };
     const uint32_t chunk = g->tune.item_chunk;
-    scan2(c, "items", ItemIn{v, A.t_vtx, A.t_start, chunk},
-          ItemOut{A.items, A.small, v.B, icap, chunk, mode == kDelete ? A.b : nullptr}, n,
-          A.part, &tot[kTotItems]);
+    with_threads([&](auto tag) {
+        constexpr int T = decltype(tag)::value;
+        c.launch("segments", k_segments<T>, ntiles, T, v, keys, n, bc, tl, A.mark,
+                 mode == kInsert ? 1 : 0, A.srcs, A.tiles, A.items, icap, chunk);
+    });
     const uint32_t pg = g->tune.probe_group, pu = g->tune.probe_unroll;
     const uint64_t pwant = div_up(icap, (uint64_t)kWaves * (64 / pg));
     // launches the probe variant of the graph's tuning
@@ -1973,54 +1957,55 @@ static void edge_run(gv_graph* g, EdgeMode mode, const uint32_t* src, const uint
         constexpr int M = decltype(mode_tag)::value;
         with_probe<M>(pg, pu, [&](auto kernel) {
             c.launch(name, kernel, std::min<uint64_t>(pwant, resident_grid(kernel, kThreads)),
-                     kThreads, v, keys, (const Item*)A.items, (const Item*)A.small, A.mark,
-                     hitpos, A.b);
+                     kThreads, v, keys, (const BatchCtr*)bc, (const Item*)A.items,
+                     (const Src*)A.srcs, A.mark, hitpos);
         });
     };
-    const uint64_t tgrid = std::min<uint64_t>(div_up(n, kThreads), resident_grid(k_grow, kThreads));
 
     if (mode == kInsert) {
         probe(std::integral_constant<int, kInsert>{}, "probe_insert", nullptr);
-        scan2(c, "keep", KeepIn{A.flags, A.mark, ctr}, U32Out{A.b}, n + 1, A.part,
-              &tot[kTotA]);
-        c.launch("plan_insert", k_plan_ins, grid, kThreads, v, (const uint32_t*)A.t_vtx,
-                 (const uint32_t*)A.t_start, (const uint32_t*)A.b, A.t_need, A.t_dreq, A.t_drank,
-                 A.heavy);
-        scan2(c, "need", NeedIn{A.t_need, ctr}, NeedOut{A.t_need, A.rel, v, n, (int)sticky},
-              n + 1, A.part, &tot[kTotB]);
-        c.launch("append", k_append, grid, kThreads, v, keys, (const uint8_t*)A.flags,
-                 (const uint8_t*)A.mark, (const uint32_t*)A.a, (const uint32_t*)A.b,
-                 (const uint32_t*)A.t_vtx, (const uint32_t*)A.t_start,
-                 (const uint32_t*)A.t_need);
-        c.launch("grow", k_grow, tgrid, kThreads, v, (const uint32_t*)A.t_vtx,
-                 (const uint32_t*)A.t_start, (const uint32_t*)A.b, (const uint32_t*)A.t_need,
-                 (const uint32_t*)A.t_dreq, (const uint32_t*)A.t_drank, A.t_dold, A.t_doldc,
-                 (const uint32_t*)A.heavy);
+        with_threads([&](auto tag) {
+            constexpr int T = decltype(tag)::value;
+            c.launch("plan_insert", k_plan<true, T>, ntiles, T, v, n, bc, tl,
+                     (const uint8_t*)A.mark, A.srcs, (const uint2*)A.tiles, A.carry, A.tbase,
+                     A.t_dreq, A.t_drank, A.rel, A.heavy, (int)sticky);
+            c.launch("commit", k_commit<T>, ntiles, T, v, keys, n, (const BatchCtr*)bc, tl,
+                     (const uint8_t*)A.mark, (const Src*)A.srcs, (const uint2*)A.tiles,
+                     (const uint2*)A.carry, (const uint32_t*)A.tbase, (const uint32_t*)A.t_dreq,
+                     (const uint32_t*)A.t_drank, A.t_dold, A.t_doldc, (const uint32_t*)A.heavy);
+        });
         c.launch("final_insert", k_final_ins, std::min<uint64_t>(grid, 64), kThreads, v,
-                 (const uint32_t*)A.rel, (const uint32_t*)A.t_dold, (const uint32_t*)A.t_doldc);
+                 (const BatchCtr*)bc, (const uint32_t*)A.rel, (const uint32_t*)A.t_dold,
+                 (const uint32_t*)A.t_doldc);
     } else if (mode == kDelete) {
         probe(std::integral_constant<int, kDelete>{}, "probe_delete", A.hitpos);
-        scan2(c, "freed", FreedIn{v, A.t_vtx, A.t_start, A.b},
-              FreedOut{ctr, A.cdesc, A.big, A.heavy, v.vlost}, n, A.part, &tot[kTotB]);
+        with_threads([&](auto tag) {
+            constexpr int T = decltype(tag)::value;
+            c.launch("plan_delete", k_plan<false, T>, ntiles, T, v, n, bc, tl,
+                     (const uint8_t*)A.mark, A.srcs, (const uint2*)A.tiles, (uint2*)nullptr,
+                     A.tbase, (uint32_t*)nullptr, (uint32_t*)nullptr, A.heavy, A.big, 0);
+        });
         const uint32_t nbig = kBigGroups;
         c.launch("compact", k_compact,
                  nbig + std::min<uint64_t>(div_up(n, kThreads), resident_grid(k_compact, kThreads)),
                  kThreads, v, (const uint8_t*)A.mark, (const uint32_t*)A.hitpos, A.holes,
-                 (const CDesc*)A.cdesc, (const uint32_t*)A.heavy, (const uint32_t*)A.big, nbig);
-        c.launch("final_delete", k_final_del, 1, 1, v, n);
+                 (const BatchCtr*)bc, (const Src*)A.srcs, (const uint32_t*)A.tbase, tl,
+                 (const uint32_t*)A.heavy, (const uint32_t*)A.big, nbig);
     } else if (aop) {
         probe(std::integral_constant<int, kLocate>{}, "probe_locate", A.hitpos);
         if (aop->out) {
-            c.launch("answer", k_answer, grid, kThreads, v, vals, (const uint8_t*)A.mark, n, out);
-            c.launch("attr_get", k_attr_get, grid, kThreads, v, keys, vals,
+            c.launch("answer", k_answer, grid, kThreads, v, (const BatchCtr*)bc, vals,
+                     (const uint8_t*)A.mark, n, out);
+            c.launch("attr_get", k_attr_get, grid, kThreads, v, (const BatchCtr*)bc, keys, vals,
                      (const uint8_t*)A.mark, (const uint32_t*)A.hitpos, n, aop->out);
         } else {
-            c.launch("attr_set", k_attr_set, grid, kThreads, v, keys, vals,
+            c.launch("attr_set", k_attr_set, grid, kThreads, v, (const BatchCtr*)bc, keys, vals,
                      (const uint8_t*)A.mark, (const uint32_t*)A.hitpos, n, aop->in);
         }
     } else {
         probe(std::integral_constant<int, kQuery>{}, "probe_query", nullptr);
-        c.launch("answer", k_answer, grid, kThreads, v, vals, (const uint8_t*)A.mark, n, out);
+        c.launch("answer", k_answer, grid, kThreads, v, (const BatchCtr*)bc, vals,
+                 (const uint8_t*)A.mark, n, out);
     }
     if (ovb) {
         gv_graph::Overlap& o = g->ov;

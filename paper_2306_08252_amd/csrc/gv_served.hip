@@ -11,8 +11,8 @@
 // endpoint out of range or an op above 1 gets bit 2L, after every pair key),
 // sort them stably, and keep the last entry of every key whose endpoints are
 // both active: a scan writes the kept deletes and the kept inserts, compacted
-// and still sorted, to two key lists (a list of at most one tile is packed and
-// sorted by one workgroup).  The two lists are then applied as a delete batch
+// and still sorted, to two key lists (a short list is packed and sorted by
+// rank, in one kernel).  The two lists are then applied as a delete batch
 // and an insert batch that start from their sorted keys (no second sort); no
 // key is in both, so their order does not matter.
 //
@@ -44,36 +44,18 @@ __global__ __launch_bounds__(kThreads) void k_mixed_pack(uint32_t L, const uint8
     pos[i] = (uint32_t)i;
 }
 
-// Lists of at most one tile: one workgroup packs each entry as its key with
-// its list position in the low 12 bits ((pair << 12) | position, an invalid
-// entry with bit 2L set above the pair) and sorts the tile in LDS, which is
-// the stable order by pair; the pair keys and positions go out separately,
-// as the general path leaves them.
-constexpr int kTilePosBits = 12;  // kOsTile = 4096 positions
-__global__ __launch_bounds__(kOsThreads) void k_mixed_sort_tile(uint32_t L, const uint8_t* op,
-                                                                const uint32_t* src,
-                                                                const uint32_t* dst, uint64_t n,
-                                                                int passes, uint64_t* keys,
-                                                                uint32_t* pos) {
-    __shared__ TileSortLds lds;
-    uint64_t key[kOsRounds];
-#pragma unroll
-    for (int j = 0; j < kOsRounds; ++j) {
-        const uint64_t i = (uint64_t)j * kOsThreads + threadIdx.x;
-        uint64_t k = 0;
-        if (i < n) k = mixed_key(src[i], dst[i], op[i], L);
-        key[j] = (k << kTilePosBits) | (i & ((1u << kTilePosBits) - 1));
-    }
-    tile_sort(key, n, passes, ~0ull, lds);
-#pragma unroll
-    for (int j = 0; j < kOsRounds; ++j) {
-        const uint64_t i = (uint64_t)j * kOsThreads + threadIdx.x;
-        if (i < n) {
-            keys[i] = key[j] >> kTilePosBits;
-            pos[i] = (uint32_t)(key[j] & ((1u << kTilePosBits) - 1));
-        }
-    }
-}
+// Lists of at most kRankMax entries are packed and sorted by rank.
+struct MixedKeys {
+    uint32_t L;
+    const uint8_t* op;
+    const uint32_t* src;
+    const uint32_t* dst;
+    __device__ uint64_t load(uint64_t i) const { return mixed_key(src[i], dst[i], op[i], L); }
+    __device__ void own(uint64_t, uint64_t) const {}
+    __device__ void begin(uint32_t, uint32_t) const {}
+    __device__ bool counted(uint64_t) const { return false; }
+    __device__ void totals(unsigned long long, unsigned long long) const {}
+};
 
 // both endpoints of a pair key active (the key is below bit 2L)
 __device__ __forceinline__ bool pair_active(const uint32_t* active, uint64_t k, uint32_t L) {
@@ -315,9 +297,8 @@ bool mixed_sort(const gv_graph* g, Ctx& c, const uint8_t* op, const uint32_t* sr
                 const uint32_t* dst, uint64_t n, const MixSort& b, bool concurrent) {
     const uint32_t L = g->v.L;
     const int bits = 2 * (int)L + 1;
-    if (n <= kOsTile && bits + kTilePosBits <= 64) {
-        c.launch("mixed_pack", k_mixed_sort_tile, 1, kOsThreads, L, op, src, dst, n,
-                 os_passes(bits + kTilePosBits), b.k0, b.p0);
+    if (n <= kRankMax) {
+        rank_sort(c, "mixed_pack", MixedKeys{L, op, src, dst}, n, b.k0, b.p0);
         return false;
     }
     zero_words(c, b.state, os_zero_words(n, bits));
