@@ -270,7 +270,7 @@ def summarize_counters(pmc_dir, out_md, command, title):
 
 # library launch names -> kernel symbol prefix in rocprofv3 output
 KERNEL_SYMBOLS = {
-    "sort_pass": "gv::k_os_pass<unsigned long, false>",
+    "sort_pass": "gv::k_os_pass<unsigned long, false,",
     "sort_hist": "gv::k_os_hist_sum",
     "pack": "gv::k_pack_hist(",
     "probe_insert": "gv::k_probe<0,",

@@ -196,6 +196,13 @@ __device__ __forceinline__ uint64_t mix64(uint64_t z) {
     return z ^ (z >> 31);
 }
 
+// order of LDS accesses inside a wave
+__device__ __forceinline__ void wave_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // inclusive scan across the 64 lanes of a wave
 template <typename T>
 __device__ __forceinline__ T wave_incl_scan(T x) {

@@ -199,8 +199,8 @@ static void carve_batch(Carver& cv, BatchArrays& A, uint64_t n, uint64_t icap, E
         A.rel = cv.take<uint32_t>(n);
     }
     A.items = cv.take<Item>(icap);
-    A.state_words = os_zero_words(n, bits);  // the part the batch zeroes
-    A.state = cv.take<uint32_t>(os_words(n, bits));
+    A.state_words = os_zero_words(n, bits, mode == kQuery);  // the part the batch zeroes
+    A.state = cv.take<uint32_t>(os_words(n, bits, mode == kQuery));
     A.vpart = cv.take<uint32_t>(kHistGroups);
     A.hpart = cv.take<unsigned long long>(kHistGroups);
 }
@@ -587,12 +587,6 @@ __global__ __launch_bounds__(T) void k_segments(GraphView g, const uint64_t* key
 }
 
 // ------------------------------------------------------------------ probe
-__device__ __forceinline__ void wave_lds_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 template <int MODE, int G, int U>
 __device__ __forceinline__ void probe_load(const GraphView& g, const Item& I, const uint32_t* dp,
                                            uint32_t s, uint32_t (&x)[U],
@@ -849,7 +843,7 @@ __global__ __launch_bounds__(kThreads) void k_probe(GraphView g, const uint64_t*
             const uint32_t j = gl + r * G;
             if (r * G < (1u << steps)) st[j] = j < ns ? sv[r] : 0xFFFFFFFFu;
         }
-        wave_lds_sync();
+        wave_fence();
         // the loads of step k+1 are issued before step k is searched and
         // copied over after it, so they overlap the search
         while (true) {
@@ -866,7 +860,7 @@ __global__ __launch_bounds__(kThreads) void k_probe(GraphView g, const uint64_t*
                 addr[u] = a2[u];
             }
         }
-        wave_lds_sync();
+        wave_fence();
         if (itn >= nitems) break;
         it = itn;
         I = In;
@@ -1728,8 +1722,9 @@ void edge_batch_warm(const gv_graph* g) {
         }
     }
     resident_grid(k_compact, kThreads);
-    resident_grid(k_os_pass<uint64_t, false>, kOsThreads);
-    resident_grid(k_os_pass<uint64_t, true>, kOsThreads);
+    resident_grid(k_os_pass<uint64_t, false, kPsRounds>, kPsThreads);
+    resident_grid(k_os_pass<uint64_t, true, kPsRounds>, kPsThreads);
+    resident_grid(k_os_pass<uint64_t, false, kPsRoundsLong>, kPsThreads);
 }
 
 // bytes of g->scratch edge_batch carves for n pairs (edge_batch_sorted carves

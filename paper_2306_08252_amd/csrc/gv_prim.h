@@ -4,13 +4,10 @@
 // Scan: reduce-then-scan over tiles of kScanTile elements; inputs and outputs
 // are functors so that producers and consumers fuse into the scan kernels.
 //
-// Sort: 8-bit digits.  Per pass, a histogram kernel counts the digits of each
-// tile, the digit-major count matrix is scanned, and a scatter kernel ranks
-// every key inside its tile.  Ranking is contention-free: the 64 lanes of a
-// wave find the lanes holding the same digit with eight ballots (one per
-// digit bit); the lowest such lane publishes the count, and waves are ordered
-// through a small LDS table.  Keys keep their input order within a digit, so
-// the sort is stable.
+// Sort: 8-bit digits, one kernel per pass (below).  Ranking is
+// contention-free: the 64 lanes of a wave find the lanes holding the same
+// digit with eight ballots (one per digit bit).  Keys keep their input order
+// within a digit, so the sort is stable.
 #pragma once
 
 #include <algorithm>
@@ -24,8 +21,6 @@ namespace gv {
 
 constexpr int kScanItems = 8;
 constexpr uint64_t kScanTile = (uint64_t)kThreads * kScanItems;
-constexpr int kSortItems = 16;
-constexpr uint64_t kSortTile = (uint64_t)kThreads * kSortItems;
 constexpr int kRadixBits = 8;
 constexpr int kRadix = 1 << kRadixBits;
 
@@ -111,114 +106,21 @@ void scan_excl(Ctx& c, In in, Out out, uint64_t n, T* partial, T* total) {
 }
 
 // ------------------------------------------------------------------ sort
-// lanes of this wave that are active and hold the same digit as this lane
+// Lanes of this wave that are active and hold the same digit as this lane.
+// Four vector instructions per bit: the lane's bit spread over a word, the
+// ballot, and one three-input operation m & ~(ballot ^ bit) per half (nine as
+// the plain expression compiles).
 __device__ __forceinline__ uint64_t digit_peers(uint32_t d, bool act) {
-    uint64_t m = ballot(act);
+    const uint64_t m = ballot(act);
+    uint32_t lo = (uint32_t)m, hi = (uint32_t)(m >> 32);
 #pragma unroll
     for (int b = 0; b < kRadixBits; ++b) {
-        bool bit = (d >> b) & 1u;
-        uint64_t bal = ballot(bit);
-        m &= bit ? bal : ~bal;
+        const uint32_t bit = (uint32_t)((int32_t)(d << (31 - b)) >> 31);
+        const uint64_t bal = ballot(bit != 0u);
+        lo = __builtin_amdgcn_bitop3_b32(lo, (uint32_t)bal, bit, 0x90);
+        hi = __builtin_amdgcn_bitop3_b32(hi, (uint32_t)(bal >> 32), bit, 0x90);
     }
-    return m;
-}
-
-template <typename K>
-__global__ __launch_bounds__(kThreads) void k_rs_hist(const K* keys, uint64_t n, int shift,
-                                                       uint32_t* counts, uint64_t ntiles) {
-    __shared__ uint32_t hist[kRadix];
-    hist[threadIdx.x] = 0;
-    __syncthreads();
-    const uint64_t base = (uint64_t)blockIdx.x * kSortTile;
-#pragma unroll 4
-    for (int j = 0; j < kSortItems; ++j) {
-        uint64_t i = base + (uint64_t)j * kThreads + threadIdx.x;
-        bool act = i < n;
-        uint32_t d = act ? (uint32_t)(keys[i] >> shift) & (kRadix - 1) : 0u;
-        uint64_t peers = digit_peers(d, act);
-        if (act && rank_below(peers) == 0) atomicAdd(&hist[d], popc64(peers));
-    }
-    __syncthreads();
-    counts[(uint64_t)threadIdx.x * ntiles + blockIdx.x] = hist[threadIdx.x];
-}
-
-template <typename K, bool HasVal>
-__global__ __launch_bounds__(kThreads) void k_rs_scatter(const K* kin, K* kout, const uint32_t* vin,
-                                                          uint32_t* vout, uint64_t n, int shift,
-                                                          const uint32_t* offsets, uint64_t ntiles) {
-    __shared__ uint32_t run[kRadix];
-    __shared__ uint32_t wcnt[kWaves][kRadix];
-    const int w = threadIdx.x >> 6;
-    run[threadIdx.x] = offsets[(uint64_t)threadIdx.x * ntiles + blockIdx.x];
-#pragma unroll
-    for (int i = 0; i < kWaves; ++i) wcnt[i][threadIdx.x] = 0;
-    __syncthreads();
-    const uint64_t base = (uint64_t)blockIdx.x * kSortTile;
-#pragma unroll 1
-    for (int j = 0; j < kSortItems; ++j) {
-        uint64_t i = base + (uint64_t)j * kThreads + threadIdx.x;
-        bool act = i < n;
-        K key = act ? kin[i] : K(0);
-        uint32_t d = (uint32_t)(key >> shift) & (kRadix - 1);
-        uint64_t peers = digit_peers(d, act);
-        uint32_t r = rank_below(peers);
-        if (act && r == 0) wcnt[w][d] = popc64(peers);
-        __syncthreads();
-        if (act) {
-            uint32_t pos = run[d] + r;
-            for (int q = 0; q < w; ++q) pos += wcnt[q][d];
-            kout[pos] = key;
-            if (HasVal) vout[pos] = vin[i];
-        }
-        __syncthreads();
-        uint32_t add = 0;
-#pragma unroll
-        for (int q = 0; q < kWaves; ++q) {
-            add += wcnt[q][threadIdx.x];
-            wcnt[q][threadIdx.x] = 0;
-        }
-        run[threadIdx.x] += add;
-        __syncthreads();
-    }
-}
-
-struct SortScratch {
-    uint32_t* counts;   // kRadix * ntiles
-    uint32_t* partial;  // scan partials of counts
-};
-
-inline uint64_t sort_tiles(uint64_t n) { return div_up(n, kSortTile); }
-
-template <typename K>
-inline void carve_sort(Carver& cv, SortScratch& s, uint64_t n) {
-    uint64_t nc = (uint64_t)kRadix * sort_tiles(n);
-    s.counts = cv.take<uint32_t>(nc);
-    s.partial = cv.take<uint32_t>(scan_partials_needed(nc));
-}
-
-// Sorts keys ascending by bits [0, bits), stably, ping-ponging between k0 and
-// k1 (and v0/v1 when HasVal).  Returns true if the result ends in k1/v1.
-template <typename K, bool HasVal>
-bool radix_sort(Ctx& c, K* k0, K* k1, uint32_t* v0, uint32_t* v1, uint64_t n, int bits,
-                const SortScratch& s) {
-    if (n <= 1 || bits <= 0) return false;
-    if (n > 0xffffffffull) fail(GV_EINVAL, "sort too large");
-    const uint64_t nt = sort_tiles(n);
-    const uint64_t nc = (uint64_t)kRadix * nt;
-    bool flip = false;
-    for (int shift = 0; shift < bits; shift += kRadixBits) {
-        K* kin = flip ? k1 : k0;
-        K* kout = flip ? k0 : k1;
-        uint32_t* vin = flip ? v1 : v0;
-        uint32_t* vout = flip ? v0 : v1;
-        c.launch("sort_hist", k_rs_hist<K>, nt, kThreads, (const K*)kin, n, shift, s.counts, nt);
-        scan_excl<uint32_t>(c, ArrIn<uint32_t>{s.counts}, ArrOut<uint32_t>{s.counts}, nc, s.partial,
-                            (uint32_t*)nullptr);
-        c.launch("sort_scatter", k_rs_scatter<K, HasVal>, nt, kThreads, (const K*)kin, kout,
-                 (const uint32_t*)vin, vout, n, shift, (const uint32_t*)s.counts, nt);
-        flip = !flip;
-    }
-    return flip;
+    return ((uint64_t)hi << 32) | lo;
 }
 
 }  // namespace gv
@@ -551,10 +453,8 @@ void scan2(Ctx& c, const char* name, In in, Out out, uint64_t n, unsigned long l
 
 // ---------------------------------------------------------------- onesweep
 // Stable LSD radix sort: one histogram kernel for every pass, then one kernel
-// per 8-bit digit pass.  A pass ranks its 4096-key tile locally (ballot peer
-// masks per wave and round, LDS column scans), publishes its per-digit counts,
-// looks back per digit for the counts of earlier tiles, and scatters.  The
-// number of keys may live on the device (n_dev); grids are sized for n_max.
+// per 8-bit digit pass (k_os_pass).  The number of keys may live on the device
+// (n_dev); grids are sized for n_max.
 #ifndef GV_OS_ITEMS
 #define GV_OS_ITEMS 16
 #endif
@@ -570,29 +470,41 @@ constexpr uint64_t kHistGroups = 256;
 inline uint64_t os_hist_groups(uint64_t n) { return std::min<uint64_t>(os_tiles(n), kHistGroups); }
 // uint32 words of state a sort needs: tile counters and look-back status
 // (the first os_zero_words, which must be zeroed), then the histograms and
-// the per-group histograms
-// Tiles per group of the two-level prefix that workgroup-index tiles use.
+// the per-group histograms.
+// The pass kernel's own tiles, and its three-level prefix: a group is kOsGroup
+// tiles, a super group kOsGroup groups.
+// Keys per thread of a pass: 8 up to kPsLong keys, then 16, whose longer runs
+// (32 keys a digit on average) and half as many tiles cost less per key once
+// the device is full many times over: 10^6 keys 14.7 us a pass against 18.4,
+// 10^7 keys 66.1 against 58.5, 1.7 * 10^7 keys 104 against 89.
+constexpr int kPsThreads = 512, kPsWaves = kPsThreads / 64;
+constexpr int kPsRounds = 8, kPsRoundsLong = 16;
+constexpr uint64_t kPsLong = 1ull << 22;
 constexpr uint64_t kOsGroup = 16;
-inline uint64_t os_groups(uint64_t n) { return div_up(os_tiles(n), kOsGroup); }
-inline uint64_t os_zero_words(uint64_t n_max, int bits) {
-    const uint64_t p = (uint64_t)os_passes(bits);
-    return 64 + p * os_tiles(n_max) * kRadix + p * os_groups(n_max) * kRadix;
+// (with values the longer tile's LDS would leave one workgroup per unit)
+inline bool ps_long(uint64_t n, bool vals) { return n > kPsLong && !vals; }
+inline uint64_t ps_tiles(uint64_t n, bool vals) {
+    return div_up(std::max<uint64_t>(n, 1),
+                  (uint64_t)kPsThreads * (ps_long(n, vals) ? kPsRoundsLong : kPsRounds));
 }
-inline uint64_t os_words(uint64_t n_max, int bits) {
+// status words per digit and pass: tiles, groups, super groups
+inline uint64_t ps_status(uint64_t n, bool vals) {
+    const uint64_t t = ps_tiles(n, vals), g = div_up(t, kOsGroup);
+    return t + g + div_up(g, kOsGroup);
+}
+// (vals: the sort carries values)
+inline uint64_t os_zero_words(uint64_t n_max, int bits, bool vals = false) {
+    return 64 + (uint64_t)os_passes(bits) * ps_status(n_max, vals) * kRadix;
+}
+inline uint64_t os_words(uint64_t n_max, int bits, bool vals = false) {
     const uint64_t p = (uint64_t)os_passes(bits);
-    return os_zero_words(n_max, bits) + p * kRadix + os_hist_groups(n_max) * p * kRadix;
+    return os_zero_words(n_max, bits, vals) + p * kRadix + os_hist_groups(n_max) * p * kRadix;
 }
 
 constexpr int kOsThreads = 1024;
 constexpr int kOsWaves = kOsThreads / 64;
 static_assert(kOsThreads == 4 * kRadix, "the pass kernel works in four quarters of 256 threads");
 constexpr int kOsRounds = (int)(kOsTile / kOsThreads);  // keys per thread
-// earlier tiles whose status one look-back lane reads per round
-#ifndef GV_OS_LOOK_K
-#define GV_OS_LOOK_K 4
-#endif
-constexpr int kOsLookK = GV_OS_LOOK_K;
-
 // exclusive scan across a kOsThreads workgroup (all threads call it)
 __device__ __forceinline__ uint32_t os_block_scan(uint32_t x, uint32_t* lds, uint32_t& total) {
     uint32_t inc = wave_incl_scan(x);
@@ -604,26 +516,6 @@ __device__ __forceinline__ uint32_t os_block_scan(uint32_t x, uint32_t* lds, uin
     for (int i = 0; i < kOsWaves; ++i) {
         const uint32_t v = lds[i];
         off += (i < w) ? v : 0u;
-        tot += v;
-    }
-    __syncthreads();
-    total = tot;
-    return off + inc - x;
-}
-
-// the same for 64-bit values
-__device__ __forceinline__ unsigned long long os_block_scan64(unsigned long long x,
-                                                              unsigned long long* lds,
-                                                              unsigned long long& total) {
-    unsigned long long inc = wave_incl_scan(x);
-    const int w = threadIdx.x >> 6;
-    if (lane_id() == 63) lds[w] = inc;
-    __syncthreads();
-    unsigned long long off = 0, tot = 0;
-#pragma unroll
-    for (int i = 0; i < kOsWaves; ++i) {
-        const unsigned long long v = lds[i];
-        off += (i < w) ? v : 0ull;
         tot += v;
     }
     __syncthreads();
@@ -875,28 +767,44 @@ static __global__ __launch_bounds__(kThreads) void k_os_hist_sum(
     }
 }
 
-// One pass over 8 bits at `shift`: rank the tile locally (ballot peer masks
-// per wave and round, LDS column scans), publish per-digit tile counts, look
-// back per digit for the counts of earlier tiles, scatter.
-template <typename K, bool HasVal>
-__global__ __launch_bounds__(kOsThreads) void k_os_pass(const K* kin, K* kout, const uint32_t* vin,
+// One pass over 8 bits at `shift`.  A wave ranks its keys by itself: for each
+// row of 64, eight ballots find the lanes with the same digit, the wave's own
+// counter of the digit (LDS) gives the keys before the row, and the row's
+// first lane advances it, so ranking takes no barrier.  The tile's counts are
+// published, its keys placed in digit order in LDS, and only then are the
+// counts of earlier tiles gathered: the earlier tiles of the tile's group, the
+// earlier groups of its super group, and the super groups before it back to
+// the first whose inclusive prefix stands, all loads issued together (two
+// lanes per digit, eight words each per level).  The group's last tile
+// publishes the group's counts, the super group's last tile its counts and
+// its inclusive prefix.  Each digit's run is then written with consecutive
+// lanes.
+//
+// Bound: at 245 tiles (10^6 keys) the chain of dependent phases, from a few
+// thousand tiles on issue and the scattered writes (runs of 16 or 32 keys).  A
+// first form ranked with nine vector instructions per digit bit and a row of
+// LDS counters per 64 keys, and looked back before it placed its keys: 10^6
+// keys 16.9 us a pass, now 14.7; 10^7 keys 88 (1.8 TB/s), now 58 (2.7 TB/s).
+template <typename K, bool HasVal, int kRounds>
+__global__ __launch_bounds__(kPsThreads) void k_os_pass(const K* kin, K* kout, const uint32_t* vin,
                                                         uint32_t* vout, const uint32_t* n_dev,
                                                         uint64_t n_max, int shift,
                                                         const uint32_t* hist, uint32_t* status,
-                                                        uint32_t* gstatus, uint32_t* counter,
-                                                        int block_tiles, uint32_t* err,
-                                                        uint32_t spin_limit) {
-    // cnt[round * waves + wave][digit]: counts, then exclusive prefixes
-    __shared__ uint16_t cnt[kOsRounds * kOsWaves][kRadix];
-    __shared__ uint32_t part[4][kRadix];
-    __shared__ uint32_t s_base[kRadix];   // global start of digit run of this tile
-    __shared__ uint32_t s_lstart[kRadix]; // start of digit run inside the tile
-    __shared__ unsigned long long s_w64[kOsWaves];
+                                                        uint32_t* counter, int block_tiles,
+                                                        uint32_t* err, uint32_t spin_limit) {
+    static_assert(kPsThreads == 2 * kRadix, "two lanes per digit look back");
+    constexpr uint32_t kL = (uint32_t)kOsGroup / 2;  // words per lane and level
+    constexpr uint64_t kPsTile = (uint64_t)kPsThreads * kRounds;
+    constexpr uint32_t kWaveKeys = 64 * kRounds;
+    __shared__ uint16_t cnt[kPsWaves][kRadix];  // counts, then exclusive prefixes over the waves
+    __shared__ K skey[kPsTile];
+    __shared__ uint32_t sval[HasVal ? kPsTile : 1];
+    __shared__ uint32_t s_lstart[kRadix];  // start of the digit's run inside the tile
+    __shared__ uint32_t s_count[kRadix];   // its length
+    __shared__ uint32_t s_off[kRadix];     // its global start minus s_lstart
+    __shared__ unsigned long long s_w[kPsWaves];
     __shared__ uint32_t s_tile;
-    __shared__ K skey[kOsTile];
-    __shared__ uint32_t sval[HasVal ? kOsTile : 1];
-    const uint32_t t = threadIdx.x;
-    const int w = t >> 6;
+    const uint32_t t = threadIdx.x, w = t >> 6, lane = lane_id();
     // the pass histogram and the key count do not depend on the tile
     const uint32_t hv = t < kRadix ? hist[t] : 0u;
     const uint64_t n = n_dev ? min<uint64_t>(*n_dev, n_max) : n_max;
@@ -910,200 +818,165 @@ __global__ __launch_bounds__(kOsThreads) void k_os_pass(const K* kin, K* kout, c
         __syncthreads();
         tile = s_tile;
     }
-    const uint64_t base = tile * kOsTile;
-    K key[kOsRounds];
-    uint32_t val[kOsRounds];
-    uint16_t rk[kOsRounds];
+    const uint64_t base = tile * kPsTile;
+    const uint64_t mine = base + (uint64_t)w * kWaveKeys + lane;
+    // (a digit is a byte of the key: it lies in one half of it)
+    const int half = shift & 31;
+    auto digit = [&](K k) {
+        const uint32_t x = shift < 32 ? (uint32_t)k : (uint32_t)((uint64_t)k >> 32);
+        return (x >> half) & (kRadix - 1);
+    };
+    K key[kRounds];
+    uint32_t val[kRounds];
     // loads bounded by n_max (the buffer size), so they need not wait for n
 #pragma unroll
-    for (int j = 0; j < kOsRounds; ++j) {
-        const uint64_t i = base + (uint64_t)j * kOsThreads + t;
+    for (int j = 0; j < kRounds; ++j) {
+        const uint64_t i = mine + 64 * j;
         const bool in = i < n_max;
         key[j] = in ? kin[i] : K(0);
         if (HasVal) val[j] = in ? vin[i] : 0u;
     }
-    {
-        uint32_t* c32 = (uint32_t*)&cnt[0][0];
-        for (int i = t; i < kOsRounds * kOsWaves * kRadix / 2; i += kOsThreads) c32[i] = 0;
-    }
-    __syncthreads();
 #pragma unroll
-    for (int j = 0; j < kOsRounds; ++j) {
-        const uint64_t i = base + (uint64_t)j * kOsThreads + t;
-        if (i >= n) {
-            key[j] = K(0);
-            if (HasVal) val[j] = 0u;
-        }
-    }
+    for (int i = 0; i < kRadix / 64; ++i) cnt[w][i * 64 + lane] = 0;
+    uint32_t rk[kRounds];
+    wave_fence();
 #pragma unroll
-    for (int j = 0; j < kOsRounds; ++j) {
-        const uint64_t i = base + (uint64_t)j * kOsThreads + t;
-        const bool act = i < n;
-        const uint32_t d = (uint32_t)(key[j] >> shift) & (kRadix - 1);
+    for (int j = 0; j < kRounds; ++j) {
+        const bool act = mine + 64 * j < n;
+        const uint32_t d = digit(key[j]);
         const uint64_t peers = digit_peers(d, act);
-        rk[j] = (uint16_t)rank_below(peers);
-        if (act && rk[j] == 0) cnt[j * kOsWaves + w][d] = (uint16_t)popc64(peers);
+        const uint32_t r = rank_below(peers);
+        const uint32_t before = cnt[w][d];
+        wave_fence();
+        if (act && r == 0) cnt[w][d] = (uint16_t)(before + popc64(peers));
+        wave_fence();
+        rk[j] = before + r;
     }
     __syncthreads();
-    // column scans: digit d = t % 256, quarter q = t / 256 covers 16 rows
-    const uint32_t d = t & (kRadix - 1), q = t >> 8;
-    constexpr int kRows = kOsRounds * kOsWaves;
-    constexpr int kQRows = kRows / 4;
-    uint32_t run = 0;
+    uint32_t dcount = 0;
+    if (t < kRadix) {
+        uint32_t c[kPsWaves];
 #pragma unroll
-    for (int r = 0; r < kQRows; ++r) {
-        const uint32_t c = cnt[q * kQRows + r][d];
-        cnt[q * kQRows + r][d] = (uint16_t)run;
-        run += c;
-    }
-    part[q][d] = run;
-    __syncthreads();
-    uint32_t qoff = 0;
-    for (uint32_t qq = 0; qq < q; ++qq) qoff += part[qq][d];
-    const uint32_t dcount = part[0][d] + part[1][d] + part[2][d] + part[3][d];
-    if (qoff) {
+        for (int q = 0; q < kPsWaves; ++q) c[q] = cnt[q][t];
 #pragma unroll
-        for (int r = 0; r < kQRows; ++r) cnt[q * kQRows + r][d] += (uint16_t)qoff;
-    }
-    __shared__ uint32_t lb_prefix[kRadix];
-    if (block_tiles) {
-        // Every tile runs at once: a two-level prefix, two rounds of loads
-        // whatever the tile's position.  Four lanes per digit add the counts
-        // of the earlier tiles of the tile's group of kOsGroup; the group's
-        // last tile publishes the group total; then the four lanes add the
-        // totals of the earlier groups.
-        if (t < kRadix) st_status32(status + tile * kRadix + t, kOsAgg | dcount);
-        const uint32_t ld = t >> 2, lq = t & 3, gbase = lane_id() & ~3u;
-        const uint64_t G = tile / kOsGroup;
-        auto wait_sum = [&](uint32_t* base, uint64_t first, uint64_t end) {
-            uint32_t wv[kOsLookK];
-#pragma unroll
-            for (int kk = 0; kk < kOsLookK; ++kk) {
-                const uint64_t j = first + lq * kOsLookK + kk;
-                wv[kk] = j < end ? ld_status32(base + j * kRadix + ld) : kOsAgg;
-            }
-            uint32_t sum = 0;
-#pragma unroll
-            for (int kk = 0; kk < kOsLookK; ++kk) {
-                const uint64_t j = first + lq * kOsLookK + kk;
-                if ((wv[kk] >> 30) == 0 || spin_limit == 0) {
-                    uint32_t spins = 0;
-                    while ((wv[kk] >> 30) == 0 && spins++ < spin_limit)
-                        wv[kk] = ld_status32(base + j * kRadix + ld);
-                    if ((wv[kk] >> 30) == 0 || spin_limit == 0) {
-                        *err = 1;
-                        wv[kk] = kOsAgg;
-                    }
-                }
-                sum += wv[kk] & kOsMask;
-            }
-            uint32_t all = 0;
-#pragma unroll
-            for (int qq = 0; qq < 4; ++qq) all += __shfl(sum, (int)(gbase + qq), 64);
-            return all;
-        };
-        static_assert(kOsGroup == 4 * kOsLookK, "a group is one round of four lanes");
-        const uint32_t local = wait_sum(status, G * kOsGroup, tile);
-        if (tile % kOsGroup == kOsGroup - 1 && lq == 0) {
-            const uint32_t own = part[0][ld] + part[1][ld] + part[2][ld] + part[3][ld];
-            st_status32(gstatus + G * kRadix + ld, kOsAgg | (local + own));
+        for (int q = 0; q < kPsWaves; ++q) {
+            cnt[q][t] = (uint16_t)dcount;
+            dcount += c[q];
         }
-        uint32_t global = 0;
-        for (uint64_t g0 = 0; g0 < G; g0 += kOsGroup) global += wait_sum(gstatus, g0, G);
-        if (lq == 0) lb_prefix[ld] = local + global;
-    } else {
-    // publish this tile's counts, then look back with four consecutive lanes
-    // per digit: each round a lane reads the status of kOsLookK earlier
-    // tiles with independent loads, and the four lanes add them, newest
-    // first, up to the first inclusive one
-    if (t < kRadix) st_status32(status + tile * kRadix + t, (tile == 0 ? kOsIncl : kOsAgg) | dcount);
-    {
-        const uint32_t ld = t >> 2, lq = t & 3, gbase = lane_id() & ~3u;
-        uint32_t lp = 0;
-        bool open = tile > 0;
-        int64_t j0 = (int64_t)tile - 1;
-        while (open) {
-            uint32_t wv[kOsLookK];
-#pragma unroll
-            for (int kk = 0; kk < kOsLookK; ++kk) {
-                const int64_t j = j0 - (int64_t)(lq * kOsLookK + kk);
-                // before tile 0: an inclusive zero
-                wv[kk] = j >= 0 ? ld_status32(status + (uint64_t)j * kRadix + ld) : kOsIncl;
-            }
-#pragma unroll
-            for (int kk = 0; kk < kOsLookK; ++kk) {
-                const int64_t j = j0 - (int64_t)(lq * kOsLookK + kk);
-                if ((wv[kk] >> 30) == 0 || (spin_limit == 0 && j >= 0)) {
-                    uint32_t spins = 0;
-                    while ((wv[kk] >> 30) == 0 && spins++ < spin_limit)
-                        wv[kk] = ld_status32(status + (uint64_t)j * kRadix + ld);
-                    if ((wv[kk] >> 30) == 0 || spin_limit == 0) {
-                        *err = 1;
-                        wv[kk] = kOsIncl;
-                    }
-                }
-            }
-            uint32_t ls = 0;
-            bool lh = false;
-#pragma unroll
-            for (int kk = 0; kk < kOsLookK; ++kk) {
-                if (!lh) {
-                    ls += wv[kk] & kOsMask;
-                    lh = (wv[kk] >> 30) == 2;
-                }
-            }
-            bool hit = false;
-#pragma unroll
-            for (int qq = 0; qq < 4; ++qq) {
-                const uint32_t vs = __shfl(ls, (int)(gbase + qq), 64);
-                const int vh = __shfl((int)lh, (int)(gbase + qq), 64);
-                if (!hit) {
-                    lp += vs;
-                    hit = vh != 0;
-                }
-            }
-            open = !hit;
-            j0 -= 4 * kOsLookK;
-        }
-        if (lq == 0) lb_prefix[ld] = lp;
+        st_status32(status + tile * kRadix + t, kOsAgg | dcount);
     }
-    }
-    __syncthreads();
-    const uint32_t prefix = t < kRadix ? lb_prefix[t] : 0u;
-    if (!block_tiles && t < kRadix && tile > 0)
-        st_status32(status + tile * kRadix + t, kOsIncl | (prefix + dcount));
     // global start of each digit (pass histogram) and start inside the tile:
     // one scan of both, the histogram in the high half (neither half carries)
-    unsigned long long tot;
-    const unsigned long long both =
-        os_block_scan64(((unsigned long long)hv << 32) | (t < kRadix ? dcount : 0u), s_w64, tot);
-    const uint32_t gex = (uint32_t)(both >> 32), lex = (uint32_t)both;
-    if (t < kRadix) {
-        s_base[t] = gex + prefix;
-        s_lstart[t] = lex;
+    {
+        const unsigned long long x = ((unsigned long long)hv << 32) | dcount;
+        const unsigned long long inc = wave_incl_scan(x);
+        if (lane == 63) s_w[w] = inc;
+        __syncthreads();
+        if (t < kRadix) {
+            unsigned long long ex = inc - x;
+            for (uint32_t i = 0; i < w; ++i) ex += s_w[i];
+            s_lstart[t] = (uint32_t)ex;
+            s_count[t] = dcount;
+            s_off[t] = (uint32_t)(ex >> 32) - (uint32_t)ex;
+        }
     }
     __syncthreads();
-    // place keys in tile order of their digit, then write each digit run
-    // with consecutive lanes (coalesced)
+    // place keys in tile order of their digit
 #pragma unroll
-    for (int j = 0; j < kOsRounds; ++j) {
-        const uint64_t i = base + (uint64_t)j * kOsThreads + t;
-        if (i < n) {
-            const uint32_t dd = (uint32_t)(key[j] >> shift) & (kRadix - 1);
-            const uint32_t lp = s_lstart[dd] + cnt[j * kOsWaves + w][dd] + rk[j];
+    for (int j = 0; j < kRounds; ++j) {
+        if (mine + 64 * j < n) {
+            const uint32_t d = digit(key[j]);
+            const uint32_t lp = s_lstart[d] + cnt[w][d] + rk[j];
             skey[lp] = key[j];
             if (HasVal) sval[lp] = val[j];
         }
     }
-    __syncthreads();
-    const uint64_t tn = n > base ? min<uint64_t>(n - base, kOsTile) : 0;
+    {
+        // (32-bit places: a pass has fewer than 2^30 / kPsTile tiles)
+        const uint32_t tl = (uint32_t)tile, nt = gridDim.x;
+        const uint32_t ld = t >> 1, lq = t & 1, q8 = lq * kL;
+        const uint32_t G = tl / (uint32_t)kOsGroup, S = G / (uint32_t)kOsGroup;
+        const uint32_t g0 = G * (uint32_t)kOsGroup, s0 = S * (uint32_t)kOsGroup;
+        uint32_t* tst = status + ld;
+        uint32_t* gst = tst + (uint64_t)nt * kRadix;
+        // waits for one word, which is polled again until it is set
+        auto settle = [&](uint32_t x, uint32_t* p, bool real) {
+            if (real && ((x >> 30) == 0 || spin_limit == 0)) {
+                uint32_t spins = 0;
+                while ((x >> 30) == 0 && spins++ < spin_limit) x = ld_status32(p);
+                if ((x >> 30) == 0 || spin_limit == 0) {
+                    *err = 1;
+                    x = kOsIncl;
+                }
+            }
+            return x;
+        };
+        uint32_t a[kL], b[kL];
 #pragma unroll
-    for (int j = 0; j < kOsRounds; ++j) {
-        const uint32_t lp = j * kOsThreads + t;
+        for (uint32_t k = 0; k < kL; ++k)
+            a[k] = g0 + q8 + k < tl ? ld_status32(tst + (uint64_t)(g0 + q8 + k) * kRadix) : kOsAgg;
+#pragma unroll
+        for (uint32_t k = 0; k < kL; ++k)
+            b[k] = s0 + q8 + k < G ? ld_status32(gst + (uint64_t)(s0 + q8 + k) * kRadix) : kOsAgg;
+        uint32_t local = 0, groups = 0;
+#pragma unroll
+        for (uint32_t k = 0; k < kL; ++k)
+            local += settle(a[k], tst + (uint64_t)(g0 + q8 + k) * kRadix, g0 + q8 + k < tl) &
+                     kOsMask;
+        local += __shfl_xor(local, 1, 64);
+        const uint32_t own = s_count[ld];
+        if (tl - g0 == kOsGroup - 1 && lq == 0)
+            st_status32(gst + (uint64_t)G * kRadix, kOsAgg | (local + own));
+#pragma unroll
+        for (uint32_t k = 0; k < kL; ++k)
+            groups += settle(b[k], gst + (uint64_t)(s0 + q8 + k) * kRadix, s0 + q8 + k < G) &
+                      kOsMask;
+        groups += __shfl_xor(groups, 1, 64);
+        uint32_t prefix = local + groups;
+        uint32_t* sst = gst + (uint64_t)((nt + kOsGroup - 1) / kOsGroup) * kRadix;
+        const bool last = tl % (kOsGroup * kOsGroup) == kOsGroup * kOsGroup - 1;
+        if (S > 0) {  // uniform over the workgroup
+            if (last && lq == 0) st_status32(sst + (uint64_t)S * kRadix, kOsAgg | (prefix + own));
+            for (uint32_t s1 = S;; s1 -= (uint32_t)kOsGroup) {
+                // super groups s1 - 1, s1 - 2, ...: this lane's eight, newest
+                // first; before the first stands an inclusive zero
+                uint32_t sum = 0;
+                bool incl = false;
+#pragma unroll
+                for (uint32_t k = 0; k < kL; ++k)
+                    a[k] = q8 + k < s1 ? ld_status32(sst + (uint64_t)(s1 - 1 - q8 - k) * kRadix)
+                                       : kOsIncl;
+#pragma unroll
+                for (uint32_t k = 0; k < kL; ++k) {
+                    if (!incl) {
+                        const uint32_t x =
+                            settle(a[k], sst + (uint64_t)(s1 - 1 - q8 - k) * kRadix, q8 + k < s1);
+                        sum += x & kOsMask;
+                        incl = (x >> 30) == 2;
+                    }
+                }
+                const uint32_t osum = __shfl_xor(sum, 1, 64);
+                const bool oincl = __shfl_xor((int)incl, 1, 64) != 0;
+                // the first lane's words are the newer ones
+                const bool incl0 = lq ? oincl : incl, incl1 = lq ? incl : oincl;
+                prefix += lq ? osum : sum;
+                if (!incl0) prefix += lq ? sum : osum;
+                if (incl0 || incl1) break;
+            }
+        }
+        if (last && lq == 0) st_status32(sst + (uint64_t)S * kRadix, kOsIncl | (prefix + own));
+        if (lq == 0) s_off[ld] += prefix;
+    }
+    __syncthreads();
+    // write each digit run with consecutive lanes (coalesced)
+    const uint64_t tn = n > base ? min<uint64_t>(n - base, kPsTile) : 0;
+#pragma unroll
+    for (int j = 0; j < kRounds; ++j) {
+        const uint32_t lp = j * kPsThreads + t;
         if (lp < tn) {
             const K k = skey[lp];
-            const uint32_t dd = (uint32_t)(k >> shift) & (kRadix - 1);
-            const uint32_t pos = s_base[dd] + (lp - s_lstart[dd]);
+            const uint32_t dd = digit(k);
+            const uint32_t pos = s_off[dd] + lp;
             // stays below n unless a look-back wait ran out (err is set);
             // then the write is dropped rather than sent out of bounds
             if (pos < n) {
@@ -1140,7 +1013,7 @@ bool onesweep(Ctx& c, K* k0, K* k1, uint32_t* v0, uint32_t* v1, const uint32_t* 
     if (passes > 8) fail(GV_EINVAL, "too many radix passes");
     const uint64_t hg = os_hist_groups(n_max);
     const uint32_t hwords = (uint32_t)passes * kRadix;
-    uint32_t* hist = state + os_zero_words(n_max, bits);  // passes * 256 counters
+    uint32_t* hist = state + os_zero_words(n_max, bits, HasVal);  // passes * 256 counters
     uint32_t* hpart = hist + hwords;      // per histogram workgroup
     c.launch("sort_hist", k_os_hist<K>, hg, kOsThreads, (const K*)k0, n_dev, n_max, passes, hpart);
     c.launch("sort_hist", k_os_hist_sum, div_up(hwords, 16), kThreads, (const uint32_t*)hpart,
@@ -1179,25 +1052,24 @@ bool onesweep_passes(Ctx& c, K* k0, K* k1, uint32_t* v0, uint32_t* v1, const uin
     if (n_max >= kOsMaxKeys) fail(GV_EINVAL, "sort of 2^30 or more keys");
     const int passes = os_passes(bits);
     if (passes > 8) fail(GV_EINVAL, "too many radix passes");
-    const uint64_t nt = os_tiles(n_max);
+    const uint64_t nt = ps_tiles(n_max, HasVal), per = ps_status(n_max, HasVal) * kRadix;
     uint32_t* counters = state;           // 64 words
-    uint32_t* status = state + 64;        // passes * tiles * 256
-    uint32_t* gstatus = status + (uint64_t)passes * nt * kRadix;  // passes * groups * 256
-    const uint64_t ng = os_groups(n_max);
-    uint32_t* hist = state + os_zero_words(n_max, bits);  // passes * 256 counters
-    const int block_tiles =
-        !concurrent && nt <= resident_grid(k_os_pass<K, HasVal>, kOsThreads) ? 1 : 0;
+    uint32_t* hist = state + os_zero_words(n_max, bits, HasVal);  // passes * 256 counters
+    auto kernel = k_os_pass<K, HasVal, kPsRounds>;
+    if constexpr (!HasVal) {
+        if (ps_long(n_max, false)) kernel = k_os_pass<K, false, kPsRoundsLong>;
+    }
+    const int block_tiles = !concurrent && nt <= resident_grid(kernel, kPsThreads) ? 1 : 0;
     bool flip = false;
     for (int p = 0; p < passes; ++p) {
         K* kin = flip ? k1 : k0;
         K* kout = flip ? k0 : k1;
         uint32_t* vin = flip ? v1 : v0;
         uint32_t* vout = flip ? v0 : v1;
-        c.launch("sort_pass", k_os_pass<K, HasVal>, nt, kOsThreads, (const K*)kin, kout,
+        c.launch("sort_pass", kernel, nt, kPsThreads, (const K*)kin, kout,
                  (const uint32_t*)vin, vout, n_dev, n_max, p * kRadixBits,
                  (const uint32_t*)(hist + (uint64_t)p * kRadix),
-                 status + (uint64_t)p * nt * kRadix, gstatus + (uint64_t)p * ng * kRadix,
-                 counters + p, block_tiles, err, spin_limit);
+                 state + 64 + (uint64_t)p * per, counters + p, block_tiles, err, spin_limit);
         flip = !flip;
     }
     return flip;

@@ -264,7 +264,7 @@ struct MixSort {
         k1 = cv.take<uint64_t>(n);
         p0 = cv.take<uint32_t>(n);
         p1 = cv.take<uint32_t>(n);
-        state = cv.take<uint32_t>(os_words(n, bits));
+        state = cv.take<uint32_t>(os_words(n, bits, true));
     }
 };
 
@@ -301,7 +301,7 @@ bool mixed_sort(const gv_graph* g, Ctx& c, const uint8_t* op, const uint32_t* sr
         rank_sort(c, "mixed_pack", MixedKeys{L, op, src, dst}, n, b.k0, b.p0);
         return false;
     }
-    zero_words(c, b.state, os_zero_words(n, bits));
+    zero_words(c, b.state, os_zero_words(n, bits, true));
     c.launch("mixed_pack", k_mixed_pack, div_up(n, kThreads), kThreads, L, op, src, dst, n, b.k0,
              b.p0);
     return onesweep<uint64_t, true>(c, b.k0, b.k1, b.p0, b.p1, nullptr, n, bits, b.state,
