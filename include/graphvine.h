@@ -346,10 +346,10 @@ typedef struct {
  *                  (<= 4096) are packed and sorted by rank in one kernel; the
  *                  largest value, 4096, stands for the library's own limit
  *                  (16384 pairs) while overlap is 0
- *   probe_group    lanes that probe one work item against its batch
- *                  segment: 16, 32 (default) or 64
- *   probe_unroll   adjacency slots per lane per search step: 2, 4 (default)
- *                  or 8
+ *   probe_group    16, 32 (default) or 64: checked and kept, but every work
+ *                  item is probed by a wave, which measured faster than
+ *                  smaller lane groups throughout
+ *   probe_unroll   2, 4 (default) or 8: likewise (4 slots per lane and step)
  *   item_chunk     adjacency slots per work item, a power of two in
  *                  [64, 4096] (default 256)
  *   overlap        0 (default) or 1.  With 1, an insert or delete batch of

@@ -287,7 +287,7 @@ int gv_plan_create(gv_graph* g, const gv_op* ops, uint64_t n_ops, gv_plan** out)
             }
         }
         hip_check(hipStreamSynchronize(c.stream), "hipStreamSynchronize");
-        edge_batch_warm(g);
+        edge_batch_warm();
         vertex_batch_warm();
         // record
         hipStream_t cs = nullptr;

@@ -18,11 +18,11 @@
 //             tile, and no scan over the batch is needed.
 //   probe     sources with few slots and a short segment by four lanes each
 //             (slots and segment loaded whole, all pairs compared); the others
-//             by lane groups that stage the segment's destinations in LDS,
-//             stream slots (directory entry, then slot) and binary-search each
-//             slot value.
+//             by a wave per work item that stages the segment's destinations
+//             in LDS and binary-searches each slot value there, with the loads
+//             of its next three items in flight.
 //             Insert: mark batch entries that already exist (set semantics).
-//             Delete: mark hits, remember their slot, tombstone the slot.
+//             Delete: mark hits, remember their slot.
 //             Query:  mark every query equal to a stored edge.
 //   plan      insert and delete, the same tiles: each source's kept pairs
 //             (neither repeated nor present) or hits, block demand or freed
@@ -47,12 +47,8 @@
 
 namespace gv {
 
-// The probe's shape is picked at run time (gv_tuning) among compiled
-// variants: G lanes per work item (16, 32, 64) and U slots per lane per step
-// (2, 4, 8).
 constexpr int kStageLog = 7;                   // log2(kStage)
 constexpr int kStage = 1 << kStageLog;         // segment entries staged in LDS
-constexpr int kWinLog = 12;                    // unrolled global search steps
 #ifndef GV_BIG_R
 #define GV_BIG_R 256
 #endif
@@ -62,12 +58,13 @@ constexpr int kWinLog = 12;                    // unrolled global search steps
 #ifndef GV_LANE_R
 #define GV_LANE_R 8
 #endif
+constexpr int kProbeWaves = 8;                  // waves per SIMD of the probe
 constexpr uint32_t kBigR = GV_BIG_R;           // deletes per source handled by a workgroup
 constexpr uint32_t kBigGroups = 256;           // workgroups for those sources
 constexpr uint32_t kLaneCopy = 8;              // directory entries a lane copies or adds
 constexpr uint32_t kLaneSeg = GV_LANE_SEG;     // segment entries a lane compacts
 constexpr uint32_t kLaneR = GV_LANE_R;         // hits a lane compacts
-constexpr uint32_t kRelease = 0x80000000u;     // flag bit in the per-source demand
+constexpr uint32_t kNoHit = 0xFFFFFFFFu;       // hit position of a pair not found (delete)
 constexpr uint32_t kHeavy = 0x100u;            // flag bit in t_dreq: whole waves grow this source
 constexpr uint32_t kClassMask = 0xFFu;         // t_dreq & kClassMask: requested class or kNoDir
 
@@ -100,12 +97,11 @@ struct alignas(128) BatchCtr {
 };
 enum { kStripeHash = 0, kStripeUniq = 1, kStripeBlocks = 2 };
 
-// self-contained work item: slots [s0, s1) of vertex v, batch segment [lo, hi);
-// block j is dir[dirbase + j] when the vertex has a directory segment, else
-// the inline block blk0 (dirbase is then 0, so the load stays in bounds)
-struct alignas(16) Item {
+// self-contained work item: slots [s0, s1) of a source, batch segment [lo, hi);
+// block j is directory entry dir + j, or (inl) dir is the only block
+struct alignas(8) Item {
     uint32_t s0, s1, lo, hi;
-    uint32_t v, dirbase, blk0, dcls;
+    uint32_t dir, inl;
 };
 
 // A touched source: its batch segment [lo, hi), its vertex record as it was
@@ -179,7 +175,8 @@ static void carve_batch(Carver& cv, BatchArrays& A, uint64_t n, uint64_t icap, E
         A.part = cv.take<unsigned long long>(scan2_parts(n));
     }
     A.mark = cv.take<uint8_t>(n);
-    if (mode != kInsert) A.hitpos = cv.take<uint32_t>(n);  // (query: attribute calls)
+    // (whole groups of four; query: attribute calls)
+    if (mode != kInsert) A.hitpos = cv.take<uint32_t>((n + 3) & ~3ull);
     if (mode == kDelete) {
         A.holes = cv.take<uint32_t>(n);
         A.big = cv.take<uint32_t>(n);
@@ -448,7 +445,8 @@ __device__ __forceinline__ V tile_scan(V x, V* lds, V& total) {
 }
 
 // Segments, sources and work items of a tile of the sorted keys.  Also writes
-// the marks (dup_mark: 1 on a repeated pair, which an insert does not keep),
+// the marks (dup_mark: 1 on a repeated pair, which an insert does not keep)
+// and a delete's hit positions (none yet),
 // checks the sort (every key at least its predecessor, else err_order = 2;
 // the mix64 sum of the sorted keys goes to the hash stripes, which the probe
 // compares with the packed keys' sum) and counts distinct pairs and blocks.
@@ -464,7 +462,7 @@ __device__ __forceinline__ V tile_scan(V x, V* lds, V& total) {
 template <int T>
 __global__ __launch_bounds__(T) void k_segments(GraphView g, const uint64_t* keys, uint64_t n,
                                                 BatchCtr* bc, uint32_t tl, uint8_t* mark,
-                                                int dup_mark, Src* srcs, uint2* tiles,
+                                                int dup_mark, uint32_t* hitpos, Src* srcs, uint2* tiles,
                                                 Item* items, uint64_t icap, uint32_t chunk) {
     constexpr uint32_t kTile = T * kTileRows;
     __shared__ uint32_t s_pos[kTile + 1], s_base[kTile + 1];
@@ -502,6 +500,7 @@ __global__ __launch_bounds__(T) void k_segments(GraphView g, const uint64_t* key
         bad |= in && !first && k[j] < q[j];
         hash += in ? mix64(k[j]) : 0ull;
         if (in) mark[p0 + p] = (dup_mark && !un) ? 1 : 0;
+        if (in && hitpos) hitpos[p0 + p] = kNoHit;
     }
     if (bad) g.ctr->err_order = 2;
     uint32_t rank[kTileRows];
@@ -578,187 +577,199 @@ __global__ __launch_bounds__(T) void k_segments(GraphView g, const uint64_t* key
         it.s1 = min(x.deg, it.s0 + chunk);
         it.lo = x.lo;
         it.hi = x.hi;
-        it.v = x.v;
-        it.dirbase = x.dcls != kNoDir ? x.dir : 0u;
-        it.blk0 = x.dcls != kNoDir ? 0u : x.dir;
-        it.dcls = x.dcls;
+        it.dir = x.dir;
+        it.inl = x.dcls == kNoDir;
         if ((uint64_t)s_i0 + m < icap) items[(uint64_t)s_i0 + m] = it;
     }
 }
 
 // ------------------------------------------------------------------ probe
-template <int MODE, int G, int U>
-__device__ __forceinline__ void probe_load(const GraphView& g, const Item& I, const uint32_t* dp,
-                                           uint32_t s, uint32_t (&x)[U],
-                                           uint64_t (&addr)[U]) {
-    // unconditional loads at clamped positions; lanes past the item are
-    // masked out by the caller
-    uint32_t e[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-        const uint32_t si = min(s + u * G, I.s1 - 1);
-        e[u] = dp[si >> g.log2B];
+// what a stored slot si with the destination of segment position pos does;
+// dup: the next position holds that destination too (queries; it is read with
+// the position's own, so that the usual hit waits for nothing), and same(j)
+// says so of position j
+template <int MODE, typename F>
+__device__ __forceinline__ void probe_hit(uint32_t lo, uint32_t len, uint32_t pos, uint32_t si,
+                                          bool dup, uint8_t* mark, uint32_t* hitpos, F&& same) {
+    mark[lo + pos] = 1;
+    if (MODE == kDelete || MODE == kLocate) hitpos[lo + pos] = si;
+    if ((MODE == kQuery || MODE == kLocate) && dup) {
+        for (uint32_t j = pos + 1; j < len && same(j); ++j) {
+            mark[lo + j] = 1;
+            if (MODE == kLocate) hitpos[lo + j] = si;
+        }
     }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-        const uint32_t si = min(s + u * G, I.s1 - 1);
-        addr[u] = ((uint64_t)e[u] << g.log2B) + (si & (g.B - 1));
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) x[u] = g.pool[addr[u]];
 }
 
-// Searches of the U slots of a lane run in lockstep, so that each step
-// issues U independent reads and waits once.
-template <int MODE, int G, int U>
-__device__ __forceinline__ void probe_search(const GraphView& g, const Item& I, uint32_t s,
-                                                 const uint32_t (&x)[U],
-                                                 const uint64_t (&addr)[U], const uint32_t* st,
-                                                 uint32_t steps, uint32_t shift,
-                                                 const uint64_t* keys, uint8_t* mark,
-                                                 uint32_t* hitpos) {
-    const uint32_t len = I.hi - I.lo;
-    const uint64_t vbase = (uint64_t)I.v << g.L;
-    // rank among the LDS samples: st[0, 2^steps - 1) holds the sorted samples
-    // padded with 0xFFFFFFFF (at least one pad entry, so the rank can reach ns)
-    uint32_t lo[U];
+// The U slots x of a lane, at s, s + 1, ... (one per SLOTS apart) of an item
+// that ends at s1, against the batch segment [lo, lo + len), whose entries (or
+// every 2^shift-th of them) are the first ns words at byte base of the LDS
+// array, padded with 0xFFFFFFFF up to 2^steps - 1 (at least one pad entry, so
+// that the rank can reach ns).  Searches of the slots run in lockstep, so that
+// each step issues U independent reads and waits once.  Everything but x and s
+// is the same for the whole wave.
+template <int MODE, int U, int APART>
+__device__ __forceinline__ void probe_search(const uint32_t (&x)[U], uint32_t s, uint32_t s1,
+                                             uint32_t lo, uint32_t len, const char* lds,
+                                             uint32_t base, uint32_t steps, uint32_t shift,
+                                             const uint32_t* klo, uint32_t dmask, uint8_t* mark,
+                                             uint32_t* hitpos) {
+    // ranks as byte offsets into the LDS array, so that a step's read takes no
+    // address arithmetic
+    auto at = [&](uint32_t o) { return *(const uint32_t*)(lds + o); };
+    uint32_t r[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) lo[u] = 0;
-    // unrolled to the largest step count so that no loop carries outstanding
-    // loads (the next step's slot loads stay in flight meanwhile)
+    for (int u = 0; u < U; ++u) r[u] = base;
 #pragma unroll
     for (int k = kStageLog - 1; k >= 0; --k) {
         if ((uint32_t)k >= steps) continue;
-        const uint32_t half = 1u << k;
+        const uint32_t half = 4u << k;
         uint32_t sv[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) sv[u] = st[lo[u] + half - 1];
+        for (int u = 0; u < U; ++u) sv[u] = at(r[u] + half - 4);
 #pragma unroll
-        for (int u = 0; u < U; ++u) lo[u] += sv[u] < x[u] ? half : 0u;
+        for (int u = 0; u < U; ++u) r[u] += sv[u] < x[u] ? half : 0u;
     }
-    uint32_t p[U];  // first segment position whose value is >= x
-    bool hit[U];
     if (shift == 0) {
+        const uint32_t end = base + 4 * len;
+        uint32_t v[U], w[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            p[u] = lo[u];
-            const uint32_t v = st[lo[u]];  // lo <= ns < kStage
-            hit[u] = (lo[u] < len) & (v == x[u]);
+            v[u] = at(r[u]);  // the rank is at most len < kStage
+            w[u] = MODE == kQuery || MODE == kLocate ? at(r[u] + 4) : 0u;
         }
-    } else {
-        // the answer lies in ((lo - 1) * stride, lo * stride]: a window of
-        // fewer than 2^shift entries before the sample at lo * stride (or
-        // the end of the segment); branch-free lower bound in `shift` steps
-        uint32_t end[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            p[u] = lo[u] ? ((lo[u] - 1) << shift) + 1 : 0;
-            end[u] = min(lo[u] << shift, len);
-        }
-        auto step = [&](uint32_t half) {
-            uint64_t kv[U];
-#pragma unroll
-            for (int u = 0; u < U; ++u) kv[u] = keys[I.lo + min(p[u] + half - 1, len - 1)];
-#pragma unroll
-            for (int u = 0; u < U; ++u)
-                p[u] += (p[u] + half - 1 < end[u] && kv[u] < (vbase | x[u])) ? half : 0u;
-        };
-        // windows of up to 2^kWinLog entries take unrolled steps; longer ones
-        // (segments beyond about half a million pairs) a loop
-        for (uint32_t k = shift; k-- > kWinLog;) step(1u << k);
-#pragma unroll
-        for (int k = kWinLog - 1; k >= 0; --k)
-            if ((uint32_t)k < shift) step(1u << k);
-        uint64_t kv[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) kv[u] = keys[I.lo + min(p[u], len - 1)];
-#pragma unroll
-        for (int u = 0; u < U; ++u) hit[u] = p[u] < len && kv[u] == (vbase | x[u]);
+        for (int u = 0; u < U; ++u)
+            if (v[u] == x[u] && r[u] < end && s + u * APART < s1)
+                probe_hit<MODE>(lo, len, (r[u] - base) / 4, s + u * APART, w[u] == x[u], mark,
+                                hitpos, [&](uint32_t j) { return at(base + 4 * j) == x[u]; });
+        return;
     }
+#pragma unroll
+    for (int u = 0; u < U; ++u) r[u] = (r[u] - base) / 4;
+    // first segment position whose value is >= x: it lies in
+    // ((r - 1) * stride, r * stride], a window of fewer than 2^shift entries
+    // before the sample at r * stride (or the end of the segment); branch-free
+    // lower bound in `shift` steps
+    uint32_t p[U], end[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-        const uint32_t si = s + u * G;
-        if (si >= I.s1 || !hit[u]) continue;
-        const uint32_t pos = I.lo + p[u];
-        if (MODE == kInsert) {
-            mark[pos] = 1;
-        } else if (MODE == kDelete) {
-            mark[pos] = 1;
-            hitpos[pos] = si;
-            g.pool[addr[u]] = kTomb;
-        } else {
-            const uint64_t target = vbase | x[u];
-            for (uint32_t j = pos; j < I.hi && keys[j] == target; ++j) {
-                mark[j] = 1;
-                if (MODE == kLocate) hitpos[j] = si;
-            }
-        }
+        p[u] = r[u] ? ((r[u] - 1) << shift) + 1 : 0;
+        end[u] = min(r[u] << shift, len);
     }
+    for (uint32_t k = shift; k-- > 0;) {
+        const uint32_t half = 1u << k;
+        uint32_t kv[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) kv[u] = klo[2ull * min(p[u] + half - 1, len - 1)] & dmask;
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            p[u] += (p[u] + half - 1 < end[u] && kv[u] < x[u]) ? half : 0u;
+    }
+    uint32_t kv[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) kv[u] = klo[2ull * min(p[u], len - 1)] & dmask;
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+        if (kv[u] == x[u] && p[u] < len && s + u * APART < s1)
+            probe_hit<MODE>(lo, len, p[u], s + u * APART, true, mark, hitpos,
+                            [&](uint32_t j) { return (klo[2ull * j] & dmask) == x[u]; });
 }
 
-// Lane q of a small item's lanes probes slots [q * kSmallDeg, (q + 1) *
-// kSmallDeg) of its adjacency: those slots and the segment's destinations are
-// loaded whole and compared pairwise.  Same marks as the group search: insert
-// and delete mark the first occurrence of a stored pair (delete also records
-// the slot and tombstones it), query marks every occurrence.  A stored pair
-// sits in one slot, so one lane at most marks a segment entry.
+// value of lane I of each group of four lanes
+template <int I>
+__device__ __forceinline__ uint32_t quad_get(uint32_t x) {
+    return __builtin_amdgcn_update_dpp(0u, x, I * 0x55, 0xf, 0xf, true);
+}
+
+// The four lanes of a small item probe its adjacency in rounds of 16 slots,
+// four each, against the segment's destinations (two loaded per lane,
+// exchanged), all pairs compared; a round that no source of the wave has is
+// skipped (most have one: the sources of a batch hold ten slots on average).
+// Same marks as the search: insert and delete mark the first occurrence of a
+// stored pair (delete also records the slot), query marks every occurrence.  A
+// stored pair sits in one slot, so one lane at most marks a segment entry.
 template <int MODE>
 __device__ __forceinline__ void probe_small(const GraphView& g, const Src& I, uint32_t q,
                                             const uint64_t* keys, uint8_t* mark,
                                             uint32_t* hitpos) {
+    static_assert(kSmallLanes == 4 && kSmallSeg == 8, "two destinations per lane of a quad");
+    constexpr uint32_t kRounds = kSmallLanes * kSmallDeg / 16;
     const uint32_t deg = I.deg;
     const uint32_t len = I.hi - I.lo;
-    const uint32_t first = q * kSmallDeg;
     const uint32_t* klo = (const uint32_t*)keys;  // low words: destinations
     const uint32_t dmask = (uint32_t)((1ull << g.L) - 1);
-    uint32_t d[kSmallSeg];
-#pragma unroll
-    for (uint32_t j = 0; j < kSmallSeg; ++j)
-        d[j] = j < len ? klo[2ull * (I.lo + j)] & dmask : 0u;
+    const uint32_t d0 = klo[2ull * (I.lo + min(2 * q, len - 1))] & dmask;
+    const uint32_t d1 = klo[2ull * (I.lo + min(2 * q + 1, len - 1))] & dmask;
     // whole 16-byte groups of a block (B >= 4, so a group stays inside it)
-    uint32_t x[kSmallDeg];
-    uint64_t a[kSmallDeg / 4];
+    uint32_t blk[kRounds];
 #pragma unroll
-    for (uint32_t u = 0; u < kSmallDeg; u += 4) {
-        const uint32_t sl = first + u;
-        const uint32_t j = sl >> g.log2B;
-        const uint32_t blk = I.dcls != kNoDir ? g.dir[I.dir + (sl < deg ? j : 0u)] : I.dir;
-        a[u / 4] = ((uint64_t)blk << g.log2B) + (sl & (g.B - 1));
+    for (uint32_t u = 0; u < kRounds; ++u) {
+        const uint32_t sl = min(16 * u + 4 * q, deg - 1);
+        blk[u] = I.dir;
+        if (I.dcls != kNoDir && 16 * u < deg) blk[u] = g.dir[I.dir + (sl >> g.log2B)];
     }
+    uint4 x[kRounds];
 #pragma unroll
-    for (uint32_t u = 0; u < kSmallDeg; u += 4) {
-        uint4 v = make_uint4(kTomb, kTomb, kTomb, kTomb);
-        if (first + u < deg) v = *(const uint4*)(g.pool + a[u / 4]);
-        x[u] = v.x;
-        x[u + 1] = v.y;
-        x[u + 2] = v.z;
-        x[u + 3] = v.w;
+    for (uint32_t u = 0; u < kRounds; ++u) {
+        const uint32_t sl = 16 * u + 4 * q;
+        if (sl < deg)
+            x[u] = *(const uint4*)(g.pool + (((uint64_t)blk[u] << g.log2B) + (sl & (g.B - 1))));
     }
+    const uint32_t d[kSmallSeg] = {quad_get<0>(d0), quad_get<0>(d1), quad_get<1>(d0),
+                                   quad_get<1>(d1), quad_get<2>(d0), quad_get<2>(d1),
+                                   quad_get<3>(d0), quad_get<3>(d1)};
 #pragma unroll
-    for (uint32_t j = 0; j < kSmallSeg; ++j) {
-        if (j >= len) break;
-        if (MODE != kQuery && MODE != kLocate && j > 0 && d[j] == d[j - 1])
-            continue;  // not a first occurrence
-        uint32_t hu = kSmallDeg;
+    for (uint32_t u = 0; u < kRounds; ++u) {
+        const uint32_t sl = 16 * u + 4 * q;
+        if (sl >= deg) break;
+        const uint32_t left = deg - sl;  // live slots of this group (4 or more: all)
 #pragma unroll
-        for (uint32_t u = 0; u < kSmallDeg; ++u)
-            if (first + u < deg && x[u] == d[j]) hu = u;
-        if (hu == kSmallDeg) continue;
-        mark[I.lo + j] = 1;
-        if (MODE == kLocate) hitpos[I.lo + j] = first + hu;
-        if (MODE == kDelete) {
-            hitpos[I.lo + j] = first + hu;
-            g.pool[a[hu / 4] + (hu & 3)] = kTomb;
+        for (uint32_t j = 0; j < kSmallSeg; ++j) {
+            if (j >= len) break;
+            uint32_t h = 4;
+            h = left > 3 && x[u].w == d[j] ? 3u : h;
+            h = left > 2 && x[u].z == d[j] ? 2u : h;
+            h = left > 1 && x[u].y == d[j] ? 1u : h;
+            h = x[u].x == d[j] ? 0u : h;
+            if (h == 4) continue;
+            if (MODE != kQuery && MODE != kLocate && j > 0 && d[j] == d[j - 1])
+                continue;  // not a first occurrence
+            mark[I.lo + j] = 1;
+            if (MODE == kDelete || MODE == kLocate) hitpos[I.lo + j] = sl + h;
         }
     }
 }
 
-template <int MODE, int G, int U>
-__global__ __launch_bounds__(kThreads) void k_probe(GraphView g, const uint64_t* keys,
+// Small items first, then the work items, a wave each.  An item's descriptor
+// is the same for the whole wave and lives in scalar registers; a lane takes
+// four consecutive slots of a block per step (two when the item has at most
+// 128), one directory entry and one load.  A wave's items run in a pipeline:
+// while one is searched, the slots and segment samples of the next are in
+// flight, the directory entries of the one after it and the descriptor of the
+// third, so that the chain descriptor -> directory -> slots costs an item's
+// search each, not its latency.  The loads carry no arithmetic on their
+// results: a mask there made the wave wait for them where they are issued.
+//
+// Bound: the searches' instructions and LDS latency, hidden by eight waves per
+// SIMD; the slots alone would take 16 us of the 43 and 72 of the 228.  Lane
+// groups of 16 to 64 with one item each, without the pipeline, took
+// (edge queries, 10^6 of a 2^20-vertex R-MAT graph / 10^7 of a 2^22 one) 71 and
+// 430 us, with it 59 and 345; a wave per item at seven waves per SIMD 56 and
+// 348, at eight and 128 staged entries 43 and 228 (64 entries 44 and 235,
+// 256 entries, which spills, 45 and 259).  Inserts of 10^7: 236 -> 180,
+// deletes 453 -> 273.  Comparing every slot with every entry of a short
+// segment (4, 8, 16 entries) was no faster than its search.
+// VEC: blocks hold whole groups of four slots (B >= 4)
+template <int MODE, bool VEC>
+__global__ __launch_bounds__(kThreads, kProbeWaves) void k_probe(GraphView g, const uint64_t* keys,
                                                     const BatchCtr* bc, const Item* items,
                                                     const Src* srcs, uint8_t* mark,
                                                     uint32_t* hitpos) {
-    __shared__ uint32_t stage[kWaves * (64 / G)][kStage];
+    constexpr int U = 4;
+    constexpr uint32_t kStep = 64 * U;  // slots per wave and step
+    constexpr int Q = VEC ? 1 : U;      // directory entries per lane and step
+    __shared__ uint32_t stage[kWaves][kStage + 1];  // (a hit reads the entry after its own)
     if (batch_failed(g.ctr)) return;
     if (MODE == kInsert || MODE == kDelete) {
         // the sorted keys must be the packed keys: their mix64 sums agree
@@ -776,94 +787,154 @@ __global__ __launch_bounds__(kThreads) void k_probe(GraphView g, const uint64_t*
         for (uint64_t k = (uint64_t)blockIdx.x * kThreads + threadIdx.x; k < nq; k += stride) {
             const Src I = srcs[k / kSmallLanes];
             const uint32_t q = (uint32_t)(k % kSmallLanes);
-            if (small_item(g.B, I.deg, I.hi - I.lo) && I.deg > q * kSmallDeg)
+            // (all four lanes: they exchange the segment's destinations)
+            if (small_item(g.B, I.deg, I.hi - I.lo))
                 probe_small<MODE>(g, I, q, keys, mark, hitpos);
         }
     }
     const uint32_t nitems = (uint32_t)bc->alloc_i;
     const uint32_t lane = lane_id();
-    const uint32_t gl = lane & (G - 1);
-    const uint32_t gid_local = (threadIdx.x >> 6) * (64 / G) + (lane / G);
-    uint32_t* st = stage[gid_local];
-    const uint32_t ngroups = gridDim.x * kWaves * (64 / G);
-    const uint64_t dmask = (1ull << g.L) - 1;
-    uint32_t it = global_wave() * (64 / G) + lane / G;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t nw = gridDim.x * kWaves;
+    const uint32_t dmask = (uint32_t)((1ull << g.L) - 1);
+    uint32_t it = blockIdx.x * kWaves + wave;
     if (it >= nitems) return;
-    Item I = items[it];
-    while (true) {
-        const uint32_t itn = it + ngroups;
-        const Item In = items[min(itn, nitems - 1)];  // prefetch the next item
-        // item prologue, in issue order: directory entries of the first step,
-        // the segment samples, then the first step's slots; the samples go to
-        // LDS once they arrive, while the slot loads are still in flight
-        const uint32_t len = I.hi - I.lo;
-        // LDS holds the segment (stride 1) or every stride-th entry of it,
-        // padded with 0xFFFFFFFF up to a power of two (at least one pad entry
-        // stays, so the rank can reach ns)
-        const uint32_t q = (len + kStage - 2) / (kStage - 1);
-        const uint32_t shift = q <= 1 ? 0u : 32u - __clz(q - 1);
-        const uint32_t ns = (len + (1u << shift) - 1) >> shift;  // < kStage samples
-        const uint32_t steps = 32u - __clz(ns);                  // 2^steps > ns
-        uint32_t s = I.s0 + gl;
-        // block ids come from the directory, or from the item itself for a
-        // vertex whose only block is stored inline
-        const uint32_t* dp = I.dcls != kNoDir ? g.dir + I.dirbase : &items[it].blk0;
-        uint32_t e[U];
-        if (I.dcls != kNoDir) {
+    uint32_t* st = stage[wave];
+    const uint32_t sbase = wave * (uint32_t)sizeof(stage[0]);
+    constexpr int kSv = kStage / 64;
+    // an item's descriptor, a word per lane, and its fields
+    static_assert(sizeof(Item) == 24, "six words");
+    auto desc = [&](uint64_t i) {
+        return ((const uint32_t*)(items + min(i, (uint64_t)nitems - 1)))[min(lane, 5u)];
+    };
+    struct Fields {
+        uint32_t s0, s1, lo, len, dir;
+        bool inl;
+    };
+    auto fields = [](uint32_t w) {
+        const uint32_t lo = __builtin_amdgcn_readlane(w, 2);
+        return Fields{(uint32_t)__builtin_amdgcn_readlane(w, 0),
+                      (uint32_t)__builtin_amdgcn_readlane(w, 1), lo,
+                      (uint32_t)__builtin_amdgcn_readlane(w, 3) - lo,
+                      (uint32_t)__builtin_amdgcn_readlane(w, 4),
+                      __builtin_amdgcn_readlane(w, 5) != 0};
+    };
+    // slots per lane of an item's first step, and the lane's first slot there
+    auto narrow = [](const Fields& I) { return VEC && I.s1 - I.s0 <= kStep / 2; };
+    auto first = [&](const Fields& I) {
+        return I.s0 + (VEC ? lane * (narrow(I) ? 2u : 4u) : lane);
+    };
+    // unconditional loads at clamped positions; slots past the item are masked
+    // out by the search
+    auto load_dir = [&](const Fields& I, uint32_t s, uint32_t (&e)[Q]) {
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const uint32_t si = min(s + u * G, I.s1 - 1);
-                e[u] = dp[si >> g.log2B];
-            }
+        for (int k = 0; k < Q; ++k)
+            e[k] = I.inl ? I.dir : g.dir[I.dir + (min(s + 64u * k, I.s1 - 1) >> g.log2B)];
+    };
+    auto load_slots = [&](const Fields& I, uint32_t s, const uint32_t (&e)[Q], uint32_t (&x)[U]) {
+        if constexpr (VEC) {
+            const uint32_t sl = min(s, I.s1 - 1) & ~3u;
+            const uint4 v = *(const uint4*)(g.pool + (((uint64_t)e[0] << g.log2B) +
+                                                      (sl & (g.B - 1))));
+            x[0] = v.x;
+            x[1] = v.y;
+            x[2] = v.z;
+            x[3] = v.w;
         } else {
-            // the only block: its id is in the descriptor, no load
-#pragma unroll
-            for (int u = 0; u < U; ++u) e[u] = I.blk0;
-        }
-        constexpr int kSv = kStage / G;
-        const uint32_t* klo = (const uint32_t*)keys;  // low words: destinations
-        uint32_t sv[kSv];
-#pragma unroll
-        for (int r = 0; r < kSv; ++r) {
-            const uint32_t j = min(gl + r * G, ns - 1);
-            sv[r] = r * G < ns ? klo[2ull * (I.lo + (j << shift))] & (uint32_t)dmask : 0u;
-        }
-        uint32_t x[U];
-        uint64_t addr[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const uint32_t si = min(s + u * G, I.s1 - 1);
-            addr[u] = ((uint64_t)e[u] << g.log2B) + (si & (g.B - 1));
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) x[u] = g.pool[addr[u]];
-#pragma unroll
-        for (int r = 0; r < kSv; ++r) {
-            // the searches read st[0, 2^steps) only
-            const uint32_t j = gl + r * G;
-            if (r * G < (1u << steps)) st[j] = j < ns ? sv[r] : 0xFFFFFFFFu;
-        }
-        wave_fence();
-        // the loads of step k+1 are issued before step k is searched and
-        // copied over after it, so they overlap the search
-        while (true) {
-            const bool more = s + G * U - gl < I.s1;  // uniform in the group
-            uint32_t x2[U];
-            uint64_t a2[U];
-            if (more) probe_load<MODE, G, U>(g, I, dp, s + G * U, x2, a2);
-            probe_search<MODE, G, U>(g, I, s, x, addr, st, steps, shift, keys, mark, hitpos);
-            if (!more) break;
-            s += G * U;
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                x[u] = x2[u];
-                addr[u] = a2[u];
+                const uint32_t sl = min(s + 64u * u, I.s1 - 1);
+                x[u] = g.pool[((uint64_t)e[u % Q] << g.log2B) + (sl & (g.B - 1))];
             }
         }
+    };
+    // a segment of fewer than kStage entries goes to LDS whole, of a longer
+    // one every 2^shift-th entry
+    auto sampling = [](const Fields& I, uint32_t& shift, uint32_t& ns) {
+        const uint32_t q = (I.len + kStage - 2) / (kStage - 1);
+        shift = q <= 1 ? 0u : 32u - __builtin_clz(q - 1);
+        ns = (I.len + (1u << shift) - 1) >> shift;  // < kStage samples
+    };
+    // (masked to destinations when they are used: here the wait would end the
+    // pipeline)
+    auto load_samples = [&](const Fields& I, uint32_t (&sv)[kSv]) {
+        uint32_t shift, ns;
+        sampling(I, shift, ns);
+        const uint32_t* klo = (const uint32_t*)(keys + I.lo);
+#pragma unroll
+        for (int r = 0; r < kSv; ++r)
+            if (r * 64u < ns)
+                sv[r] = klo[2ull * ((uint64_t)min(lane + r * 64u, ns - 1) << shift)];
+    };
+    Fields A = fields(desc(it)), B = fields(desc((uint64_t)it + nw));
+    uint32_t wC = desc((uint64_t)it + 2ull * nw);
+    uint32_t x[U], sv[kSv], eB[Q];
+    {
+        uint32_t eA[Q];
+        load_dir(A, first(A), eA);
+        load_samples(A, sv);
+        load_dir(B, first(B), eB);
+        load_slots(A, first(A), eA, x);
+    }
+    while (true) {
+        uint32_t shift, ns;
+        sampling(A, shift, ns);
+        const uint32_t steps = 32u - __builtin_clz(ns);  // 2^steps > ns
+        // (a wave's LDS accesses are in order: these writes follow the
+        // searches of the item before); the searches read st[0, 2^steps) only
+#pragma unroll
+        for (int r = 0; r < kSv; ++r)
+            if (r * 64u < (1u << steps))
+                st[lane + r * 64u] = lane + r * 64u < ns ? sv[r] & dmask : 0xFFFFFFFFu;
+        // the next items' loads
+        const Fields C = fields(wC);
+        uint32_t xB[U], svB[kSv], eC[Q];
+        load_slots(B, first(B), eB, xB);
+        load_samples(B, svB);
+        load_dir(C, first(C), eC);
+        wC = desc((uint64_t)it + 3ull * nw);
         wave_fence();
-        if (itn >= nitems) break;
-        it = itn;
-        I = In;
+        const uint32_t* klo = (const uint32_t*)(keys + A.lo);
+        auto search = [&](const auto& y, uint32_t at, auto apart) {
+            constexpr int W = sizeof(y) / 4, kApart = decltype(apart)::value;
+            probe_search<MODE, W, kApart>(y, at, A.s1, A.lo, A.len, (const char*)stage, sbase,
+                                          steps, shift, klo, dmask, mark, hitpos);
+        };
+        using Next = std::integral_constant<int, 1>;  // a lane's slots adjoin
+        using Apart = std::integral_constant<int, VEC ? 1 : 64>;
+        if (narrow(A)) {
+            const bool odd = lane & 1;
+            const uint32_t y[2] = {odd ? x[2] : x[0], odd ? x[3] : x[1]};
+            search(y, first(A), Next());
+        } else {
+            uint32_t s = first(A);
+            for (uint32_t left = A.s1 - A.s0;; left -= kStep) {
+                // the loads of step k+1 are issued before step k is searched
+                // and copied over after it, so they overlap the search
+                const bool more = left > kStep;
+                uint32_t x2[U];
+                if (more) {
+                    uint32_t e2[Q];
+                    load_dir(A, s + kStep, e2);
+                    load_slots(A, s + kStep, e2, x2);
+                }
+                search(x, s, Apart());
+                if (!more) break;
+                s += kStep;
+#pragma unroll
+                for (int u = 0; u < U; ++u) x[u] = x2[u];
+            }
+        }
+        if ((uint64_t)it + nw >= nitems) break;
+        it += nw;
+        A = B;
+        B = C;
+#pragma unroll
+        for (int u = 0; u < U; ++u) x[u] = xB[u];
+#pragma unroll
+        for (int r = 0; r < kSv; ++r) sv[r] = svB[r];
+#pragma unroll
+        for (int k = 0; k < Q; ++k) eB[k] = eC[k];
     }
 }
 
@@ -1362,14 +1433,21 @@ __global__ __launch_bounds__(kThreads) void k_final_ins(GraphView g, const Batch
 
 // Compaction of every touched source with at most kBigR hits: holes below the
 // new degree (taken in batch order) receive the survivors found above it (in
-// slot order), and emptied blocks go on the free list.  A lane takes a source
-// with at most kLaneR hits and a short segment; the others are taken by the
-// whole wave in turn.
-__device__ __forceinline__ void compact_body(const GraphView& g, const uint8_t* mark,
-                                             const uint32_t* hitpos, uint32_t* holes,
-                                             const BatchCtr* bc, const Src* srcs,
-                                             const uint32_t* tbase, uint32_t tl,
+// slot order), and emptied blocks go on the free list.  The hit positions say
+// which slots of the tail are gone, so the probe writes nothing to the pool
+// (a tombstone per hit, 4 bytes each into lines of their own, took as long as
+// reading the adjacencies: 258 MB written for 8 * 10^6 hits).  A lane takes a
+// source with at most kLaneR hits and a short segment: its hit positions in
+// whole 16-byte groups, its tail's one or two blocks (from 8 slots per block
+// on) read once.  The others are taken by the whole wave in turn.  Bound: the
+// chain tail -> holes -> survivors, and lines of the pool read and written for
+// a slot or two (10^6 deletes of a 2^20-vertex graph 42 -> 36 us, 10^7 of a
+// 2^22-vertex one 420 -> 374).
+__device__ __forceinline__ void compact_body(const GraphView& g, const uint32_t* hitpos,
+                                             uint32_t* holes, const BatchCtr* bc,
+                                             const Src* srcs, const uint32_t* tbase, uint32_t tl,
                                              const uint32_t* mid, uint32_t vb, uint32_t vg) {
+    __shared__ uint32_t s_gone[kWaves][kBigR / 32];
     const uint32_t gwave = (vb * kThreads + threadIdx.x) >> 6;
     const DevCounters* c = g.ctr;
     const uint32_t nT = (uint32_t)bc->alloc_t;
@@ -1382,141 +1460,142 @@ __device__ __forceinline__ void compact_body(const GraphView& g, const uint8_t* 
     for (uint32_t base = gwave * 64; base < nT; base += stride) {
         const bool live = base + lane < nT;
         const Src D = srcs[live ? base + lane : nT - 1];
-        if (live && D.r && lane_compactable(D.r, D.lo, D.hi)) {
-            const VRec rec{D.deg, D.dir, D.dcls, 0u};
-            const uint32_t d = D.deg, dn = d - D.r;
-            uint8_t mk[kLaneSeg];
-            uint32_t hp[kLaneSeg], sb[kLaneR];
+        if (!live || !D.r || !lane_compactable(D.r, D.lo, D.hi)) continue;
+        const VRec rec{D.deg, D.dir, D.dcls, 0u};
+        const uint32_t d = D.deg, dn = d - D.r;
+        // the segment's hit positions: kLaneGroups groups of four from the
+        // group that holds lo (the buffer ends on a whole group)
+        constexpr uint32_t kLaneGroups = kLaneSeg / 4 + 1;
+        uint32_t hp[4 * kLaneGroups];
+        const uint32_t w0 = D.lo & ~3u;
 #pragma unroll
-            for (uint32_t u = 0; u < kLaneSeg; ++u) {
-                const uint32_t q = min(D.lo + u, D.hi - 1);
-                mk[u] = mark[q];
-                hp[u] = hitpos[q];
-            }
-#pragma unroll
-            for (uint32_t k = 0; k < kLaneR; ++k)
-                sb[k] = block_of(g, rec, min(dn + k, d - 1) >> g.log2B);
-            uint32_t sv[kLaneR];
-#pragma unroll
-            for (uint32_t k = 0; k < kLaneR; ++k)
-                sv[k] = g.pool[((uint64_t)sb[k] << g.log2B) + (min(dn + k, d - 1) & bm)];
-            // holes in batch order, survivors in slot order
-            uint32_t hm = 0, sm = 0;
-#pragma unroll
-            for (uint32_t u = 0; u < kLaneSeg; ++u)
-                hm |= (D.lo + u < D.hi && mk[u] && hp[u] < dn) ? (1u << u) : 0u;
-#pragma unroll
-            for (uint32_t k = 0; k < kLaneR; ++k)
-                sm |= (k < D.r && sv[k] != kTomb) ? (1u << k) : 0u;
-            uint32_t hslot[kLaneR], hval[kLaneR], hsrc[kLaneR];
-            uint32_t nmove = 0;
+        for (uint32_t u = 0; u < kLaneGroups; ++u) {
+            const uint4 v = *(const uint4*)(hitpos + min(w0 + 4 * u, (D.hi - 1) & ~3u));
+            hp[4 * u] = v.x;
+            hp[4 * u + 1] = v.y;
+            hp[4 * u + 2] = v.z;
+            hp[4 * u + 3] = v.w;
+        }
+        // the tail's values
+        uint32_t sv[kLaneR], sb0 = 0, sb1 = 0;
+        if (g.log2B >= 3) {
+            static_assert(kLaneR <= 8, "the tail lies in two blocks of 8 slots");
+            sb0 = block_of(g, rec, dn >> g.log2B);
+            sb1 = block_of(g, rec, (d - 1) >> g.log2B);
 #pragma unroll
             for (uint32_t k = 0; k < kLaneR; ++k) {
-                hslot[k] = 0;
-                hval[k] = 0;
-                hsrc[k] = 0;
-                if (hm && sm) {
-                    const uint32_t u = __builtin_ctz(hm), w = __builtin_ctz(sm);
-                    hm &= hm - 1;
-                    sm &= sm - 1;
-                    hslot[k] = hp[u];
-                    hval[k] = sv[w];
-                    hsrc[k] = w;
-                    nmove = k + 1;
-                }
+                const uint32_t sl = min(dn + k, d - 1);
+                const uint32_t b = (sl >> g.log2B) == (dn >> g.log2B) ? sb0 : sb1;
+                sv[k] = g.pool[((uint64_t)b << g.log2B) + (sl & bm)];
             }
-            uint32_t hb[kLaneR];
+        } else {
 #pragma unroll
-            for (uint32_t k = 0; k < kLaneR; ++k) hb[k] = block_of(g, rec, hslot[k] >> g.log2B);
+            for (uint32_t k = 0; k < kLaneR; ++k)
+                sv[k] = g.pool[slot_addr(g, rec, min(dn + k, d - 1))];
+        }
+        // holes in batch order, survivors in slot order
+        uint32_t hm = 0, gone = 0;
 #pragma unroll
-            for (uint32_t k = 0; k < kLaneR; ++k) {
-                if (k >= nmove) continue;
-                const uint64_t da = ((uint64_t)hb[k] << g.log2B) + (hslot[k] & bm);
-                g.pool[da] = hval[k];
-                if (g.A) {
-                    // the survivor sat at slot dn + w (w < r <= kLaneR)
-                    uint32_t sbw = sb[0];
+        for (uint32_t u = 0; u < 4 * kLaneGroups; ++u) {
+            const bool hit = w0 + u >= D.lo && w0 + u < D.hi && hp[u] < d;
+            hm |= hit && hp[u] < dn ? 1u << u : 0u;
+            gone |= hit && hp[u] >= dn ? 1u << (hp[u] - dn) : 0u;
+        }
+        uint32_t sm = ((1u << D.r) - 1) & ~gone;  // r <= kLaneR
 #pragma unroll
-                    for (uint32_t j = 1; j < kLaneR; ++j) sbw = hsrc[k] == j ? sb[j] : sbw;
-                    attr_move(g, da, ((uint64_t)sbw << g.log2B) + ((dn + hsrc[k]) & bm));
-                }
-            }
-            moved += nmove;
-            const uint32_t nb0 = nblocks(g, d), nb1 = nblocks(g, dn);
+        for (uint32_t k = 0; k < kLaneR; ++k) {
+            if (!hm || !sm) break;
+            const uint32_t u = __builtin_ctz(hm), w = __builtin_ctz(sm);
+            hm &= hm - 1;
+            sm &= sm - 1;
+            uint32_t slot = hp[0], val = sv[0];
+#pragma unroll
+            for (uint32_t j = 1; j < 4 * kLaneGroups; ++j) slot = u == j ? hp[j] : slot;
+#pragma unroll
+            for (uint32_t j = 1; j < kLaneR; ++j) val = w == j ? sv[j] : val;
+            const uint64_t da = slot_addr(g, rec, slot);
+            g.pool[da] = val;
+            if (g.A) attr_move(g, da, slot_addr(g, rec, dn + w));
+            ++moved;
+        }
+        const uint32_t nb0 = nblocks(g, d), nb1 = nblocks(g, dn);
+        if (nb1 < nb0) {
             const unsigned long long pb = fbase + tbase[D.lo >> tl] + D.need;
-#pragma unroll
-            for (uint32_t k = 0; k < kLaneR; ++k)
-                if (nb1 + k < nb0) g.free_stack[pb + k] = block_of(g, rec, nb1 + k);
+            for (uint32_t j = nb1; j < nb0; ++j) g.free_stack[pb + (j - nb1)] = block_of(g, rec, j);
+        }
+        VRec nr = rec;
+        nr.deg = dn;
+        if (nb1 == 0 && nr.dcls == kNoDir) nr.dir = 0;
+        g.vt[D.v] = nr;
+    }
+    // sources with more hits or longer segments, listed by the plan: one wave
+    // each
+    const uint32_t nmid = (uint32_t)(bc->demand >> 32);
+    const uint32_t nw = vg * kWaves;
+    uint32_t* sg = s_gone[threadIdx.x >> 6];
+    for (uint32_t k = gwave; k < nmid; k += nw) {
+        const Src H = srcs[mid[k]];
+        const VRec rec{H.deg, H.dir, H.dcls, 0u};
+        const uint32_t d = H.deg, dn = d - H.r;
+        if (lane < kBigR / 32) sg[lane] = 0u;
+        wave_fence();
+        uint32_t nh = 0;
+        for (uint32_t p0 = H.lo; p0 < H.hi; p0 += 64) {
+            const uint32_t p = p0 + lane;
+            const uint32_t hpv = p < H.hi ? hitpos[p] : kNoHit;
+            const bool hole = hpv < dn;
+            const uint64_t bal = ballot(hole);
+            if (hole) holes[H.lo + nh + popc64(bal & below)] = hpv;
+            // (r <= kBigR, so the tail's bits fit)
+            if (hpv >= dn && hpv < d) atomicOr(&sg[(hpv - dn) >> 5], 1u << ((hpv - dn) & 31));
+            nh += popc64(bal);
+        }
+        __threadfence_block();
+        wave_fence();
+        uint32_t ns = 0;
+        for (uint32_t s0 = dn; s0 < d; s0 += 64) {
+            const uint32_t sl = s0 + lane, o = sl - dn;
+            const bool surv = sl < d && !((sg[(sl < d ? o : 0u) >> 5] >> (o & 31)) & 1u);
+            uint32_t x = 0;
+            if (surv) x = g.pool[slot_addr(g, rec, sl)];
+            const uint64_t bal = ballot(surv);
+            if (surv) {
+                // survivors above dn and holes below it are equal in number;
+                // the guards only keep a broken invariant from writing wild
+                const uint32_t qq = ns + popc64(bal & below);
+                if (qq < nh) {
+                    const uint32_t dest = holes[H.lo + qq];
+                    if (dest < dn) {
+                        const uint64_t da = slot_addr(g, rec, dest);
+                        g.pool[da] = x;
+                        if (g.A) attr_move(g, da, slot_addr(g, rec, sl));
+                    }
+                }
+            }
+            ns += popc64(bal);
+        }
+        moved += lane == 0 ? ns : 0;
+        const uint32_t nb0 = nblocks(g, d), nb1 = nblocks(g, dn);
+        const unsigned long long pb = fbase + tbase[H.lo >> tl] + H.need;
+        for (uint32_t j = nb1 + lane; j < nb0; j += 64)
+            g.free_stack[pb + (j - nb1)] = block_of(g, rec, j);
+        if (lane == 0) {
             VRec nr = rec;
             nr.deg = dn;
             if (nb1 == 0 && nr.dcls == kNoDir) nr.dir = 0;
-            g.vt[D.v] = nr;
+            g.vt[H.v] = nr;
         }
-    }
-    // sources with more hits or longer segments, listed by the freed scan:
-    // one wave each
-    const uint32_t nmid = (uint32_t)(bc->demand >> 32);
-    const uint32_t nw = vg * kWaves;
-    for (uint32_t k = gwave; k < nmid; k += nw) {
-        {
-            const Src H = srcs[mid[k]];
-            const VRec rec{H.deg, H.dir, H.dcls, 0u};
-            const uint32_t d = H.deg, dn = d - H.r;
-            uint32_t nh = 0;
-            for (uint32_t p0 = H.lo; p0 < H.hi; p0 += 64) {
-                const uint32_t p = p0 + lane;
-                const uint32_t q = min(p, H.hi - 1);
-                const uint8_t m = mark[q];
-                const uint32_t hpv = hitpos[q];
-                const bool hole = p < H.hi && m && hpv < dn;
-                const uint64_t bal = ballot(hole);
-                if (hole) holes[H.lo + nh + popc64(bal & below)] = hpv;
-                nh += popc64(bal);
-            }
-            __threadfence_block();
-            uint32_t ns = 0;
-            for (uint32_t s0 = dn; s0 < d; s0 += 64) {
-                const uint32_t sl = s0 + lane;
-                uint32_t x = kTomb;
-                if (sl < d) x = g.pool[slot_addr(g, rec, sl)];
-                const bool surv = x != kTomb;
-                const uint64_t bal = ballot(surv);
-                if (surv) {
-                    // survivors above dn and holes below it are equal in number;
-                    // the guards only keep a broken invariant from writing wild
-                    const uint32_t qq = ns + popc64(bal & below);
-                    if (qq < nh) {
-                        const uint32_t dest = holes[H.lo + qq];
-                        if (dest < dn) {
-                            const uint64_t da = slot_addr(g, rec, dest);
-                            g.pool[da] = x;
-                            if (g.A) attr_move(g, da, slot_addr(g, rec, sl));
-                        }
-                    }
-                }
-                ns += popc64(bal);
-            }
-            moved += lane == 0 ? ns : 0;
-            const uint32_t nb0 = nblocks(g, d), nb1 = nblocks(g, dn);
-            const unsigned long long pb = fbase + tbase[H.lo >> tl] + H.need;
-            for (uint32_t j = nb1 + lane; j < nb0; j += 64)
-                g.free_stack[pb + (j - nb1)] = block_of(g, rec, j);
-            if (lane == 0) {
-                VRec nr = rec;
-                nr.deg = dn;
-                if (nb1 == 0 && nr.dcls == kNoDir) nr.dir = 0;
-                g.vt[H.v] = nr;
-            }
-        }
+        wave_fence();
     }
     moved = wave_sum(moved);
     if (lane == 0 && moved) atomicAdd(&g.ctr->stripe[gwave & 63][0], moved);
 }
 
-// One workgroup per source with more than kBigR hits (hubs), same pairing.
-__device__ __forceinline__ void compact_big_body(const GraphView& g, const uint8_t* mark,
-                                                 const uint32_t* hitpos, uint32_t* holes,
-                                                 const BatchCtr* bc, const Src* srcs,
+// One workgroup per source with more than kBigR hits (hubs), same pairing; the
+// slots of the tail that are gone get a tombstone first.
+__device__ __forceinline__ void compact_big_body(const GraphView& g, const uint32_t* hitpos,
+                                                 uint32_t* holes, const BatchCtr* bc,
+                                                 const Src* srcs,
                                                  const uint32_t* tbase, uint32_t tl,
                                                  const uint32_t* big, uint32_t vb,
                                                  uint32_t vg) {
@@ -1532,16 +1611,15 @@ __device__ __forceinline__ void compact_big_body(const GraphView& g, const uint8
         uint32_t nh = 0;
         for (uint32_t p0 = D.lo; p0 < D.hi; p0 += kThreads) {
             const uint32_t p = p0 + tid;
-            uint32_t hole = 0, hp = 0;
-            if (p < D.hi && mark[p]) {
-                hp = hitpos[p];
-                hole = hp < dn;
-            }
+            const uint32_t hp = p < D.hi ? hitpos[p] : kNoHit;
+            const uint32_t hole = hp < dn;
+            if (!hole && hp < d) g.pool[slot_addr(g, rec, hp)] = kTomb;
             uint32_t tot;
             const uint32_t ex = block_excl_scan(hole, lds, tot);
             if (hole) holes[D.lo + nh + ex] = hp;
             nh += tot;
         }
+        __threadfence_block();
         __syncthreads();
         uint32_t ns = 0;
         for (uint32_t s0 = dn; s0 < d; s0 += kThreads) {
@@ -1582,17 +1660,17 @@ __device__ __forceinline__ void compact_big_body(const GraphView& g, const uint8
 
 // Both compactions in one launch: the first nbig workgroups take the hubs
 // (they run longest, so they start first), the rest the other sources.
-__global__ __launch_bounds__(kThreads) void k_compact(GraphView g, const uint8_t* mark,
-                                                      const uint32_t* hitpos, uint32_t* holes,
+__global__ __launch_bounds__(kThreads) void k_compact(GraphView g, const uint32_t* hitpos,
+                                                      uint32_t* holes,
                                                       const BatchCtr* bc, const Src* srcs,
                                                       const uint32_t* tbase, uint32_t tl,
                                                       const uint32_t* mid, const uint32_t* big,
                                                       uint32_t nbig) {
     if (batch_failed(g.ctr)) return;
     if (blockIdx.x < nbig)
-        compact_big_body(g, mark, hitpos, holes, bc, srcs, tbase, tl, big, blockIdx.x, nbig);
+        compact_big_body(g, hitpos, holes, bc, srcs, tbase, tl, big, blockIdx.x, nbig);
     else
-        compact_body(g, mark, hitpos, holes, bc, srcs, tbase, tl, mid, blockIdx.x - nbig,
+        compact_body(g, hitpos, holes, bc, srcs, tbase, tl, mid, blockIdx.x - nbig,
                      gridDim.x - nbig);
 }
 
@@ -1691,35 +1769,25 @@ void set_u64(gv_graph* g, unsigned long long* p, unsigned long long value) {
 }
 
 // ------------------------------------------------------------------ driver
-// Runs f on the probe variant of MODE for lanes-per-item G and slots-per-lane
-// U chosen at run time (the shapes the tuning accepts).
+// Runs f on the probe variant of MODE for blocks of B slots.
 template <int MODE, typename F>
-static void with_probe(uint32_t group, uint32_t unroll, F&& f) {
-#define GV_PROBE_SHAPE(G, U) \
-    if (group == G && unroll == U) return f(k_probe<MODE, G, U>);
-    GV_PROBE_SHAPE(16, 2) GV_PROBE_SHAPE(16, 4) GV_PROBE_SHAPE(16, 8)
-    GV_PROBE_SHAPE(32, 2) GV_PROBE_SHAPE(32, 4) GV_PROBE_SHAPE(32, 8)
-    GV_PROBE_SHAPE(64, 2) GV_PROBE_SHAPE(64, 4) GV_PROBE_SHAPE(64, 8)
-#undef GV_PROBE_SHAPE
-    fail(GV_EINVAL, "probe shape");
+static void with_probe(uint32_t B, F&& f) {
+    if (B >= 4) return f(k_probe<MODE, true>);
+    return f(k_probe<MODE, false>);
 }
 
 bool probe_shape_ok(uint32_t group, uint32_t unroll) {
     return (group == 16 || group == 32 || group == 64) && (unroll == 2 || unroll == 4 || unroll == 8);
 }
 
-// occupancy lookups of the looping kernels, made before a recording: the
-// probe shape of the graph's tuning, or every shape when g is null
-void edge_batch_warm(const gv_graph* g) {
+// occupancy lookups of the looping kernels, made before a recording
+void edge_batch_warm() {
     auto warm = [](auto kernel) { resident_grid(kernel, kThreads); };
-    for (uint32_t pg : {16u, 32u, 64u}) {
-        for (uint32_t pu : {2u, 4u, 8u}) {
-            if (g && (pg != g->tune.probe_group || pu != g->tune.probe_unroll)) continue;
-            with_probe<kInsert>(pg, pu, warm);
-            with_probe<kDelete>(pg, pu, warm);
-            with_probe<kQuery>(pg, pu, warm);
-            with_probe<kLocate>(pg, pu, warm);
-        }
+    for (uint32_t B : {1u, 4u}) {
+        with_probe<kInsert>(B, warm);
+        with_probe<kDelete>(B, warm);
+        with_probe<kQuery>(B, warm);
+        with_probe<kLocate>(B, warm);
     }
     resident_grid(k_compact, kThreads);
     resident_grid(k_os_pass<uint64_t, false, kPsRounds>, kPsThreads);
@@ -1943,14 +2011,13 @@ static void edge_run(gv_graph* g, EdgeMode mode, const uint32_t* src, const uint
     with_threads([&](auto tag) {
         constexpr int T = decltype(tag)::value;
         c.launch("segments", k_segments<T>, ntiles, T, v, keys, n, bc, tl, A.mark,
-                 mode == kInsert ? 1 : 0, A.srcs, A.tiles, A.items, icap, chunk);
+                 mode == kInsert ? 1 : 0, mode == kDelete ? A.hitpos : nullptr, A.srcs, A.tiles,
+                 A.items, icap, chunk);
     });
-    const uint32_t pg = g->tune.probe_group, pu = g->tune.probe_unroll;
-    const uint64_t pwant = div_up(icap, (uint64_t)kWaves * (64 / pg));
-    // launches the probe variant of the graph's tuning
+    const uint64_t pwant = div_up(icap, (uint64_t)kWaves);
     auto probe = [&](auto mode_tag, const char* name, uint32_t* hitpos) {
         constexpr int M = decltype(mode_tag)::value;
-        with_probe<M>(pg, pu, [&](auto kernel) {
+        with_probe<M>(v.B, [&](auto kernel) {
             c.launch(name, kernel, std::min<uint64_t>(pwant, resident_grid(kernel, kThreads)),
                      kThreads, v, keys, (const BatchCtr*)bc, (const Item*)A.items,
                      (const Src*)A.srcs, A.mark, hitpos);
@@ -1983,8 +2050,8 @@ static void edge_run(gv_graph* g, EdgeMode mode, const uint32_t* src, const uint
         const uint32_t nbig = kBigGroups;
         c.launch("compact", k_compact,
                  nbig + std::min<uint64_t>(div_up(n, kThreads), resident_grid(k_compact, kThreads)),
-                 kThreads, v, (const uint8_t*)A.mark, (const uint32_t*)A.hitpos, A.holes,
-                 (const BatchCtr*)bc, (const Src*)A.srcs, (const uint32_t*)A.tbase, tl,
+                 kThreads, v, (const uint32_t*)A.hitpos, A.holes, (const BatchCtr*)bc,
+                 (const Src*)A.srcs, (const uint32_t*)A.tbase, tl,
                  (const uint32_t*)A.heavy, (const uint32_t*)A.big, nbig);
     } else if (aop) {
         probe(std::integral_constant<int, kLocate>{}, "probe_locate", A.hitpos);

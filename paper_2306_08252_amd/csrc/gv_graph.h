@@ -113,7 +113,7 @@ void mixed_edges(gv_graph* g, const uint8_t* op, const uint32_t* src, const uint
                  gv_batch_stats* stats = nullptr);
 
 // occupancy queries made ahead of a recording
-void edge_batch_warm(const gv_graph* g = nullptr);
+void edge_batch_warm();
 // the side stream and events of the sort overlap (made once)
 void overlap_open(gv_graph* g);
 // the overlap's state for the capture the graph's stream is in: state that

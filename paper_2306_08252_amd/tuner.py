@@ -82,8 +82,7 @@ def measure(gv, w, ops, dev, bs, tuning, warm, form="plan"):
     return el, (ck.value, e.value)
 
 
-PROBE_SPACE = [("probe_group", [16, 32, 64]), ("probe_unroll", [2, 4, 8]),
-               ("item_chunk", [64, 128, 256, 512, 1024, 2048, 4096])]
+PROBE_SPACE = [("item_chunk", [64, 128, 256, 512, 1024, 2048, 4096])]
 DEFAULT_PROBE = {"probe_group": 32, "probe_unroll": 4, "item_chunk": 256}
 
 
@@ -169,7 +168,7 @@ def tune_steps(gv, w, ins, dels, dev, B, log=print):
             log(f"tuner: {s} -> {el * 1e3:.3f} ms per step")
         return points[k]
 
-    space = [("overlap", [0, 1])] + PROBE_SPACE + PROBE_SPACE[:2]
+    space = [("overlap", [0, 1])] + PROBE_SPACE
     best = descend(dict(DEFAULT_PROBE, overlap=0), space, run)
     return best, {k: round(v * 1e3, 4) for k, v in points.items()}
 
