@@ -339,15 +339,19 @@ __global__ __launch_bounds__(kOsThreads) void k_pack_hist(GraphView g, const uin
 
 // Batches of at most kRankMax pairs: packed and sorted by rank (gv_prim.h).
 struct EdgeKeys {
+    static constexpr bool kGathers = true;
     GraphView g;
     const uint32_t* src;
     const uint32_t* dst;
     uint8_t* answer;  // queries: invalid pairs are answered here
     BatchCtr* bc;
-    __device__ uint64_t load(uint64_t i) const {
-        const uint32_t s = src[i], d = dst[i];
-        const bool ok = active_bit(g, s) & active_bit(g, d);
-        return ok ? ((uint64_t)s << g.L) | d : 1ull << (2 * g.L);
+    struct Raw {
+        uint32_t s, d;
+    };
+    __device__ Raw raw(uint64_t i) const { return Raw{src[i], dst[i]}; }
+    __device__ uint64_t key(const Raw& r) const {
+        const bool ok = active_bit(g, r.s) & active_bit(g, r.d);
+        return ok ? ((uint64_t)r.s << g.L) | r.d : 1ull << (2 * g.L);
     }
     __device__ void own(uint64_t i, uint64_t key) const {
         if (answer && (key >> (2 * g.L))) answer[i] = 0;
@@ -1953,7 +1957,7 @@ static void edge_run(gv_graph* g, EdgeMode mode, const uint32_t* src, const uint
         keys_in = sorted;
         flip = false;
     } else if (n <= rank_max) {
-        rank_sort(c, "pack", EdgeKeys{v, src, dst, out, bc}, n, A.keys0, A.vals0);
+        rank_sort(c, "pack", EdgeKeys{v, src, dst, out, bc}, n, A.keys1, A.keys0, A.vals0);
         flip = false;
     } else if (mode == kQuery) {
         c.launch("begin", k_begin, std::min<uint64_t>(div_up(A.state_words, kThreads), 1024),

@@ -1087,126 +1087,128 @@ inline void zero_words(Ctx& c, uint32_t* p, uint64_t n) {
 
 // ---------------------------------------------------------------- rank sort
 // Sort by rank of at most kRankMax keys in one kernel.  A workgroup owns
-// kRankTile keys, which it orders by counting (each key against the tile's
-// others, in four quarters), and reads all the other keys: each is placed
-// among the tile's by an eight-step search in LDS and counted there, and the
+// kRankTile keys, a wave's worth, which it orders by counting (every wave
+// holds them all and compares its share), and reads all the other keys: each
+// is placed among the tile's by a search in LDS and counted there, and the
 // running sum of the counts is how many foreign keys stand before each of the
 // tile's.  Equal keys rank in input order, so the sort is stable.  Every
 // workgroup makes the keys anew from the input, so packing is not a kernel of
-// its own.
+// its own; a thread has the inputs of all its kRows keys in flight at once,
+// ahead of the tile's ordering.
 //
 // Work grows with n^2 / kRankTile searches, but over the whole chip and
-// without a chain of passes: 10^4 pairs take 18 us where packing, the digit
-// sums and five radix passes took 56, 2000 queries 9.8 us where a bitonic
-// network in one workgroup took 18.6.
+// without a chain of passes.  Bound: the searches past some thousand keys, the
+// latency input -> activity word below: 1000 pairs 9.8 -> 4.9 us, 10^4 pairs
+// 18.5 -> 13.6 (3.2 of them the keys) against tiles of 256 keys that read the
+// others in turn; packing, digit sums and five radix passes took 56.  Comparing
+// the upper 32 bits first (10.6 us) and eight copies of the counts (10.1) were
+// no better.
 //
-// P: uint64_t load(i) the key of input i (below 2^63); void own(i, key) once
-// per input; void begin(t, nt) by the first workgroup; bool counted(key) and
-// void totals(n, sum): the number and the mix64 sum of the counted keys, by
-// one thread.
-constexpr uint32_t kRankTile = 256;
+// P: Raw raw(i) input i; uint64_t key(raw) its key (below 2^63); void own(i,
+// key) once per input; void begin(t, nt) by the first workgroup; bool
+// counted(key) and void totals(n, sum): the number and the mix64 sum of the
+// counted keys, by one thread.
+constexpr uint32_t kRankTile = 64;
 constexpr uint64_t kRankMax = 16384;
 constexpr uint32_t kRankThreads = 1024;
+constexpr uint32_t kRankRows = kRankMax / kRankThreads;
 
-template <typename P>
+template <typename P, uint32_t kRows>
 __global__ __launch_bounds__(kRankThreads) void k_rank_sort(P pk, uint32_t n, uint64_t* keys,
                                                             uint32_t* vals) {
-    static_assert(kRankThreads == 4 * kRankTile, "a tile is ordered in four quarters");
-    constexpr uint32_t kU = 4;  // foreign keys per thread in flight
-    __shared__ uint64_t s_key[kRankTile], s_srt[kRankTile];
-    __shared__ uint32_t s_q[4][kRankTile], s_idx[kRankTile], s_add[kRankTile];
-    __shared__ uint32_t s_w[kRankTile / 64];
+    constexpr uint32_t W = kRankThreads / 64;
+    static_assert(kRankTile == 64 && kRankTile % W == 0, "a tile key per lane");
+    __shared__ uint64_t s_srt[kRankTile];
+    __shared__ uint32_t s_q[W][kRankTile], s_idx[kRankTile], s_add[kRankTile];
     __shared__ unsigned long long s_tot[2];
-    const uint32_t t = threadIdx.x;
+    const uint32_t t = threadIdx.x, lane = lane_id();
+    const uint32_t w = __builtin_amdgcn_readfirstlane(t >> 6);
     const uint32_t tb = blockIdx.x * kRankTile;
     const bool first = blockIdx.x == 0;
+    // unconditional loads at clamped positions
+    const typename P::Raw mine = pk.raw(min(tb + lane, n - 1));
+    typename P::Raw raw[kRows];
+#pragma unroll
+    for (uint32_t u = 0; u < kRows; ++u) raw[u] = pk.raw(min(u * kRankThreads + t, n - 1));
     if (first) {
         pk.begin(t, kRankThreads);
         if (t < 2) s_tot[t] = 0ull;
     }
-    unsigned long long cnt = 0, sum = 0;
-    if (t < kRankTile) {
-        uint64_t k = ~0ull;  // past every key
-        if (tb + t < n) {
-            k = pk.load(tb + t);
-            pk.own(tb + t, k);
-            if (first && pk.counted(k)) {
-                ++cnt;
-                sum += mix64(k);
-            }
-        }
-        s_key[t] = k;
-        s_add[t] = 0;
-    }
-    __syncthreads();
+    uint64_t my = pk.key(mine);
+    uint64_t x[kRows];
+#pragma unroll
+    for (uint32_t u = 0; u < kRows; ++u) x[u] = pk.key(raw[u]);
+    if (tb + lane >= n) my = ~0ull;  // past every key
     {
-        const uint32_t i = t % kRankTile, q = t / kRankTile;
-        const uint64_t my = s_key[i];
         uint32_t c = 0;
-#pragma unroll 8
-        for (uint32_t m = q * (kRankTile / 4); m < (q + 1) * (kRankTile / 4); ++m) {
-            const uint64_t o = s_key[m];
-            c += (o < my) | ((o == my) & (m < i));
+#pragma unroll
+        for (uint32_t i = 0; i < kRankTile / W; ++i) {
+            const uint32_t m = w * (kRankTile / W) + i;
+            const uint64_t o = (uint64_t)__builtin_amdgcn_readlane((uint32_t)(my >> 32), m) << 32 |
+                               (uint32_t)__builtin_amdgcn_readlane((uint32_t)my, m);
+            c += (o < my) | ((o == my) & (m < lane));
         }
-        s_q[q][i] = c;
+        s_q[w][lane] = c;
+    }
+    if (t < kRankTile) s_add[t] = 0;
+    __syncthreads();
+    if (w == 0) {
+        uint32_t r = 0;
+#pragma unroll
+        for (uint32_t i = 0; i < W; ++i) r += s_q[i][lane];
+        s_srt[r] = my;
+        s_idx[r] = lane;
+        if (tb + lane < n) pk.own(tb + lane, my);
     }
     __syncthreads();
-    if (t < kRankTile) {
-        const uint32_t r = s_q[0][t] + s_q[1][t] + s_q[2][t] + s_q[3][t];
-        s_srt[r] = s_key[t];
-        s_idx[r] = t;
-    }
-    __syncthreads();
-    for (uint32_t b = 0; b < n; b += kU * kRankThreads) {
-        uint64_t x[kU];
-        bool live[kU];
+    unsigned long long cnt = 0, sum = 0;
+    if (first) {
 #pragma unroll
-        for (uint32_t u = 0; u < kU; ++u) {
-            const uint32_t j = b + u * kRankThreads + t;
-            live[u] = j < n && (j < tb || j >= tb + kRankTile);
-            x[u] = live[u] ? pk.load(j) : 0ull;
-        }
-        uint32_t p[kU];
-#pragma unroll
-        for (uint32_t u = 0; u < kU; ++u) {
-            if (first && live[u] && pk.counted(x[u])) {
+        for (uint32_t u = 0; u < kRows; ++u)
+            if (u * kRankThreads + t < n && pk.counted(x[u])) {
                 ++cnt;
                 sum += mix64(x[u]);
             }
+    }
+    constexpr uint32_t kU = kRows < 4 ? kRows : 4;  // searches in lockstep
+#pragma unroll
+    for (uint32_t u0 = 0; u0 < kRows; u0 += kU) {
+        if (u0 * kRankThreads >= n) break;
+        uint32_t p[kU];  // byte offset into s_srt
+#pragma unroll
+        for (uint32_t u = 0; u < kU; ++u) {
             // an equal key of the tile stands before a later foreign key
-            x[u] += b + u * kRankThreads + t < tb ? 0ull : 1ull;
+            x[u0 + u] += (u0 + u) * kRankThreads + t < tb ? 0ull : 1ull;
             p[u] = 0;
         }
+        auto at = [&](uint32_t o) { return *(const uint64_t*)((const char*)s_srt + o); };
 #pragma unroll
-        for (uint32_t half = kRankTile / 2; half > 0; half >>= 1) {
+        for (uint32_t half = 8 * kRankTile / 2; half >= 8; half >>= 1) {
 #pragma unroll
-            for (uint32_t u = 0; u < kU; ++u) p[u] += s_srt[p[u] + half - 1] < x[u] ? half : 0u;
+            for (uint32_t u = 0; u < kU; ++u)
+                p[u] += at(p[u] + half - 8) < x[u0 + u] ? half : 0u;
         }
 #pragma unroll
         for (uint32_t u = 0; u < kU; ++u) {
-            p[u] += s_srt[p[u]] < x[u] ? 1u : 0u;
-            if (live[u] && p[u] < kRankTile) atomicAdd(&s_add[p[u]], 1u);
+            const uint32_t j = (u0 + u) * kRankThreads + t;
+            p[u] += at(p[u]) < x[u0 + u] ? 8u : 0u;
+            if (j < n && j / kRankTile != blockIdx.x && p[u] < 8 * kRankTile)
+                atomicAdd(&s_add[p[u] / 8], 1u);
         }
     }
     __syncthreads();
-    uint32_t inc = 0;
-    if (t < kRankTile) {
-        inc = wave_incl_scan(s_add[t]);
-        if (lane_id() == 63) s_w[t >> 6] = inc;
-    }
-    __syncthreads();
-    if (t < kRankTile) {
-        for (uint32_t w = 0; w < (t >> 6); ++w) inc += s_w[w];
-        const uint32_t i = tb + s_idx[t];
+    if (w == 0) {
+        const uint32_t at = lane + wave_incl_scan(s_add[lane]);
+        const uint32_t i = tb + s_idx[lane];
         if (i < n) {
-            keys[t + inc] = s_srt[t];
-            if (vals) vals[t + inc] = i;
+            keys[at] = s_srt[lane];
+            if (vals) vals[at] = i;
         }
     }
     if (first) {
         cnt = wave_sum(cnt);
         sum = wave_sum(sum);
-        if (lane_id() == 0) {
+        if (lane == 0) {
             atomicAdd(&s_tot[0], cnt);
             atomicAdd(&s_tot[1], sum);
         }
@@ -1215,12 +1217,61 @@ __global__ __launch_bounds__(kRankThreads) void k_rank_sort(P pk, uint32_t n, ui
     }
 }
 
-// the n keys of pk in order, and (vals not null) their input positions
+// the keys of pk, made once (k) for a kernel whose workgroups all read them
 template <typename P>
-void rank_sort(Ctx& c, const char* name, P pk, uint64_t n, uint64_t* keys, uint32_t* vals) {
+struct RankPacked {
+    using Raw = uint64_t;
+    P pk;
+    const uint64_t* k;
+    __device__ Raw raw(uint64_t i) const { return k[i]; }
+    __device__ uint64_t key(Raw r) const { return r; }
+    __device__ void own(uint64_t i, uint64_t key) const { pk.own(i, key); }
+    __device__ void begin(uint32_t t, uint32_t nt) const { pk.begin(t, nt); }
+    __device__ bool counted(uint64_t key) const { return pk.counted(key); }
+    __device__ void totals(unsigned long long n, unsigned long long sum) const {
+        pk.totals(n, sum);
+    }
+};
+
+template <typename P>
+__global__ __launch_bounds__(kThreads) void k_rank_pack(P pk, uint32_t n, uint64_t* packed) {
+    const uint32_t i = blockIdx.x * kThreads + threadIdx.x;
+    if (i < n) packed[i] = pk.key(pk.raw(i));
+}
+
+// calls f with the kernel for n keys, at most kMost rows of them
+template <typename P, uint32_t kMost, uint32_t kRows = 1, typename F>
+void with_rank_sort(uint64_t n, F&& f) {
+    if constexpr (kRows < kMost) {
+        if (n > kRows * kRankThreads) return with_rank_sort<P, kMost, 2 * kRows>(n, f);
+    }
+    f(k_rank_sort<P, kRows>);
+}
+
+// the n > 0 keys of pk in order, and (vals not null) their input positions;
+// packed: n words of scratch.  Keys that take gathered reads (P::kGathers: the activity
+// words, a line per lane) are made by a kernel of their own past
+// kRankFused keys: made anew by every workgroup they cost 12 of 18 us at 10^4
+// pairs, below that limit less than the launch.
+constexpr uint64_t kRankFused = 4 * kRankThreads;
+template <typename P>
+void rank_sort(Ctx& c, const char* name, P pk, uint64_t n, uint64_t* packed, uint64_t* keys,
+               uint32_t* vals) {
     if (n > kRankMax) fail(GV_EINVAL, "too many keys to sort by rank");
-    c.launch(name, k_rank_sort<P>, div_up(n, kRankTile), kRankThreads, pk, (uint32_t)n, keys,
-             vals);
+    const uint64_t nt = div_up(n, kRankTile);
+    if constexpr (P::kGathers) {
+        if (n > kRankFused) {
+            c.launch(name, k_rank_pack<P>, div_up(n, kThreads), kThreads, pk, (uint32_t)n, packed);
+            auto run = [&](auto kernel) {
+                c.launch(name, kernel, nt, kRankThreads, RankPacked<P>{pk, packed}, (uint32_t)n,
+                         keys, vals);
+            };
+            return with_rank_sort<RankPacked<P>, kRankRows, 8>(n, run);
+        }
+    }
+    with_rank_sort<P, P::kGathers ? kRankFused / kRankThreads : kRankRows>(n, [&](auto kernel) {
+        c.launch(name, kernel, nt, kRankThreads, pk, (uint32_t)n, keys, vals);
+    });
 }
 
 }  // namespace gv

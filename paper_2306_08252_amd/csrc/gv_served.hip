@@ -46,11 +46,17 @@ __global__ __launch_bounds__(kThreads) void k_mixed_pack(uint32_t L, const uint8
 
 // Lists of at most kRankMax entries are packed and sorted by rank.
 struct MixedKeys {
+    static constexpr bool kGathers = false;
     uint32_t L;
     const uint8_t* op;
     const uint32_t* src;
     const uint32_t* dst;
-    __device__ uint64_t load(uint64_t i) const { return mixed_key(src[i], dst[i], op[i], L); }
+    struct Raw {
+        uint32_t s, d;
+        uint8_t o;
+    };
+    __device__ Raw raw(uint64_t i) const { return Raw{src[i], dst[i], op[i]}; }
+    __device__ uint64_t key(const Raw& r) const { return mixed_key(r.s, r.d, r.o, L); }
     __device__ void own(uint64_t, uint64_t) const {}
     __device__ void begin(uint32_t, uint32_t) const {}
     __device__ bool counted(uint64_t) const { return false; }
@@ -298,7 +304,7 @@ bool mixed_sort(const gv_graph* g, Ctx& c, const uint8_t* op, const uint32_t* sr
     const uint32_t L = g->v.L;
     const int bits = 2 * (int)L + 1;
     if (n <= kRankMax) {
-        rank_sort(c, "mixed_pack", MixedKeys{L, op, src, dst}, n, b.k0, b.p0);
+        rank_sort(c, "mixed_pack", MixedKeys{L, op, src, dst}, n, b.k1, b.k0, b.p0);
         return false;
     }
     zero_words(c, b.state, os_zero_words(n, bits, true));
