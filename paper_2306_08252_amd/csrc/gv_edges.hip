@@ -79,20 +79,19 @@ constexpr int kLocate = 3;
 // workgroup touches once.
 struct alignas(128) BatchCtr {
     unsigned long long n_valid, key_sum;  // valid pairs, and the mix64 sum of their keys
-    unsigned long long alloc_t;           // touched sources placed
     uint32_t n_big, n_heavy;              // sources left to workgroups / to whole waves
     uint32_t nohash, pad0;                // keys arrived sorted: no multiset check
-    unsigned long long pad1[11];
-    unsigned long long alloc_i;           // work items placed
+    unsigned long long pad1[12];
+    // touched sources (high) and work items (low: at most one per pair and one
+    // per 64 slots of the pool) placed
+    unsigned long long alloc;
     unsigned long long pad2[15];
     // insert: blocks needed (low), directory segments given back (high);
     // delete: blocks freed (low), sources for whole waves (high)
     unsigned long long demand;
     unsigned long long pad3[15];
-    unsigned long long changed;           // pairs kept (insert), hits (delete)
+    unsigned long long done;  // tiles planned (high); their pairs kept or hits (low)
     unsigned long long pad4[15];
-    unsigned long long done;              // tiles planned
-    unsigned long long pad5[15];
     unsigned long long stripe[64][16];    // kStripe* sums, a line each
 };
 enum { kStripeHash = 0, kStripeUniq = 1, kStripeBlocks = 2 };
@@ -429,6 +428,27 @@ __device__ __forceinline__ uint32_t tile_ranks(const bool (&f)[R], uint32_t (&ra
     return total;
 }
 
+// The same for counts: exclusive sums in position order, and their total.
+template <int T, uint32_t R>
+__device__ __forceinline__ uint32_t tile_sums(const uint32_t (&x)[R], uint32_t (&ex)[R],
+                                              uint32_t* cnt) {
+    constexpr uint32_t W = T / 64, N = R * W;
+    static_assert(N <= 64, "one wave scans the sums");
+    const uint32_t w = threadIdx.x >> 6;
+#pragma unroll
+    for (uint32_t j = 0; j < R; ++j) {
+        const uint32_t inc = wave_incl_scan(x[j]);
+        if (lane_id() == 63) cnt[j * W + w] = inc;
+        ex[j] = inc - x[j];
+    }
+    __syncthreads();
+    const uint32_t c = lane_id() < N ? cnt[lane_id()] : 0u;
+    const uint32_t inc = wave_incl_scan(c);
+#pragma unroll
+    for (uint32_t j = 0; j < R; ++j) ex[j] += __shfl(inc - c, (int)(j * W + w), 64);
+    return __shfl(inc, 63, 64);
+}
+
 // exclusive scan across T threads and their sum; lds holds T / 64 words
 template <int T, typename V>
 __device__ __forceinline__ V tile_scan(V x, V* lds, V& total) {
@@ -456,46 +476,63 @@ __device__ __forceinline__ V tile_scan(V x, V* lds, V& total) {
 // compares with the packed keys' sum) and counts distinct pairs and blocks.
 //
 // A segment that runs past the tile belongs to the tile of its head, which
-// finds its end by a wave-wide search.  Work items are written by all the
-// threads of the workgroup, each finding its item's source among the tile's
-// (a hub's items spread over the workgroup).  Bound: the latency of key ->
-// vertex record -> item; it replaces two scans over the batch (their reduce
-// and apply kernels, a middle one past 2^21 pairs, and 32 bytes written per
-// source for its small item): 10^4 pairs 21.8 -> 10.0 us, 10^6 pairs 33.3 ->
-// 25.5 us, 10^7 pairs 218 -> 114 us (R-MAT 2^20 / 2^24, the last 2^22 / 2^26).
-template <int T>
-__global__ __launch_bounds__(T) void k_segments(GraphView g, const uint64_t* keys, uint64_t n,
+// finds its end by a wave-wide search.  Every position reads its source's
+// vertex record with its key, before it is known to be a head, and both before
+// the batch's counters have arrived (at positions clamped to the buffers).
+// Work items are written by all the threads of the workgroup, each finding its
+// item's source among the tile's (a hub's items spread over the workgroup;
+// written by its own lane or wave they took up to 1.7 times as long).  Bound: latency, keys -> records -> the tile's places -> the
+// sources: 10^3 pairs 10.2 -> 7.7 us, 10^4 pairs 10.0 -> 7.4, 10^6 pairs 25.5
+// -> 19.5, 10^7 pairs 99 -> 73 (R-MAT 2^20 / 2^24, the last 2^22 / 2^26)
+// against records read by the heads alone, after the counters and the keys.
+// The two scans over the batch that it replaced (their reduce and apply
+// kernels, a middle one past 2^21 pairs, and 32 bytes written per source for
+// its small item) took 21.8, 33.3 and 218 us.
+template <int T, uint32_t R>
+__global__ __launch_bounds__(T, 8) void k_segments(GraphView g, const uint64_t* keys, uint64_t n,
                                                 BatchCtr* bc, uint32_t tl, uint8_t* mark,
-                                                int dup_mark, uint32_t* hitpos, Src* srcs, uint2* tiles,
-                                                Item* items, uint64_t icap, uint32_t chunk) {
-    constexpr uint32_t kTile = T * kTileRows;
-    __shared__ uint32_t s_pos[kTile + 1], s_base[kTile + 1];
-    __shared__ uint32_t s_cnt[kTileRows * T / 64];
-    __shared__ uint32_t s_scan[T / 64];
-    __shared__ unsigned long long s_sum[3];
-    __shared__ uint32_t s_end, s_t0, s_i0;
-    const uint32_t t = threadIdx.x;
-    const uint64_t lim = batch_pairs(g.ctr, bc, n);
+                                                int dup_mark, uint32_t* hitpos, Src* srcs,
+                                                uint2* tiles, Item* items, uint64_t icap,
+                                                uint32_t chunk) {
+    constexpr uint32_t kTile = T * R;
+    // the tile's sources: position (and whether `dir` is the only block),
+    // degree, directory, first work item
+    __shared__ uint32_t s_pos[kTile], s_deg[kTile], s_dir[kTile], s_base[kTile];
+    constexpr uint32_t kInl = 1u << 31;
+    __shared__ uint32_t s_cnt[R * T / 64], s_cnt2[R * T / 64];
+    __shared__ unsigned long long s_sum[3], s_at;
+    __shared__ uint32_t s_end;
+    const uint32_t t = threadIdx.x, lane = lane_id();
     const uint64_t p0 = (uint64_t)blockIdx.x << tl;
+    const uint32_t L = g.L;
+    const uint32_t tile = 1u << tl;
+    uint64_t k[R], q[R];
+#pragma unroll
+    for (uint32_t j = 0; j < R; ++j) {
+        const uint64_t i = min(p0 + min(j * T + t, tile - 1), n - 1);
+        k[j] = keys[i];
+        q[j] = keys[i ? i - 1 : 0];
+    }
+    const uint64_t ka = keys[min(p0 + tile, n) - 1], kb = keys[min(p0 + tile, n - 1)];
+    const uint64_t lim = batch_pairs(g.ctr, bc, n);
+    // a valid key's source is below n_cap already; the bound keeps even a
+    // corrupted key's record read inside the table
+    VRec rec[R];
+#pragma unroll
+    for (uint32_t j = 0; j < R; ++j)
+        rec[j] = g.vt[min((uint32_t)(k[j] >> L) & (uint32_t)((1ull << L) - 1),
+                           (uint32_t)(g.n_cap - 1))];
     if (p0 >= lim) {
         if (t == 0) tiles[blockIdx.x] = make_uint2(0u, 0u);
         return;
     }
-    const uint32_t np = (uint32_t)min((uint64_t)1 << tl, lim - p0);
-    const uint32_t L = g.L;
+    const uint32_t np = (uint32_t)min((uint64_t)tile, lim - p0);
     if (t < 3) s_sum[t] = 0ull;
-    uint64_t k[kTileRows], q[kTileRows];
-#pragma unroll
-    for (uint32_t j = 0; j < kTileRows; ++j) {
-        const uint64_t i = p0 + min(j * T + t, np - 1);
-        k[j] = keys[i];
-        q[j] = keys[i ? i - 1 : 0];
-    }
-    bool head[kTileRows];
+    bool head[R];
     unsigned long long hash = 0, uniq = 0;
     bool bad = false;
 #pragma unroll
-    for (uint32_t j = 0; j < kTileRows; ++j) {
+    for (uint32_t j = 0; j < R; ++j) {
         const uint32_t p = j * T + t;
         const bool in = p < np, first = p0 + p == 0;
         head[j] = in && (first || (k[j] >> L) != (q[j] >> L));
@@ -507,66 +544,68 @@ __global__ __launch_bounds__(T) void k_segments(GraphView g, const uint64_t* key
         if (in && hitpos) hitpos[p0 + p] = kNoHit;
     }
     if (bad) g.ctr->err_order = 2;
-    uint32_t rank[kTileRows];
+    uint32_t rank[R];
     const uint32_t nh = tile_ranks<T>(head, rank, s_cnt);
-    // the sources' places, while the records are read
-    if (t == 0) s_t0 = nh ? (uint32_t)atomicAdd(&bc->alloc_t, (unsigned long long)nh) : 0u;
 #pragma unroll
-    for (uint32_t j = 0; j < kTileRows; ++j)
-        if (head[j]) s_pos[rank[j]] = j * T + t;
-    if (t < 64) {
+    for (uint32_t j = 0; j < R; ++j)
+        if (head[j]) {
+            s_pos[rank[j]] = j * T + t | (rec[j].dcls == kNoDir ? kInl : 0u);
+            s_deg[rank[j]] = rec[j].deg;
+            s_dir[rank[j]] = rec[j].dir;
+        }
+    if (t >= T - 64) {
         // the end of the segment that holds the tile's last key
         const uint64_t pe = p0 + np;
         uint64_t end = pe;
-        if (pe < lim) {
-            const uint64_t v = keys[pe - 1] >> L;
-            if ((keys[pe] >> L) == v) end = wave_lower_bound(keys, pe, lim, (v + 1) << L);
-        }
-        if (t == 0) s_end = (uint32_t)end;
+        if (pe < lim && (ka >> L) == (kb >> L))  // (then the tile is full)
+            end = wave_lower_bound(keys, pe, lim, ((ka >> L) + 1) << L);
+        if (lane == 0) s_end = (uint32_t)end;
+    }
+    __syncthreads();
+    uint32_t cnt[R], ex[R], end[R];
+    unsigned long long blocks = 0;
+#pragma unroll
+    for (uint32_t j = 0; j < R; ++j) {
+        cnt[j] = end[j] = 0;
+        if (!head[j]) continue;
+        end[j] = rank[j] + 1 < nh ? (uint32_t)p0 + (s_pos[rank[j] + 1] & ~kInl) : s_end;
+        blocks += nblocks(g, rec[j].deg);
+        if (!small_item(g.B, rec[j].deg, end[j] - ((uint32_t)p0 + j * T + t)))
+            cnt[j] = (rec[j].deg + chunk - 1) / chunk;
+    }
+    const uint32_t ni = tile_sums<T>(cnt, ex, s_cnt2);
+#pragma unroll
+    for (uint32_t j = 0; j < R; ++j)
+        if (head[j]) s_base[rank[j]] = ex[j];
+    if (t == 0) {
+        s_at = nh ? atomicAdd(&bc->alloc, (unsigned long long)nh << 32 | ni) : 0ull;
+        tiles[blockIdx.x] = make_uint2((uint32_t)(s_at >> 32), nh);
     }
     hash = wave_sum(hash);
     uniq = wave_sum(uniq);
-    if (lane_id() == 0) {
+    blocks = wave_sum(blocks);
+    if (lane == 0) {
         atomicAdd(&s_sum[0], hash);
         atomicAdd(&s_sum[1], uniq);
+        atomicAdd(&s_sum[2], blocks);
     }
     __syncthreads();
-    const uint32_t t0 = s_t0;
-    uint32_t ni = 0;  // the tile's work items
-    unsigned long long blocks = 0;
-    for (uint32_t h0 = 0; h0 < nh; h0 += T) {
-        const uint32_t h = h0 + t;
-        uint32_t cnt = 0;
-        if (h < nh) {
-            Src x;
-            x.lo = (uint32_t)p0 + s_pos[h];
-            x.hi = h + 1 < nh ? (uint32_t)p0 + s_pos[h + 1] : s_end;
-            // masked to the table: a valid key's source is below 2^L already;
-            // the mask keeps even a corrupted key's record read in bounds
-            x.v = (uint32_t)(keys[x.lo] >> L) & (uint32_t)((1ull << L) - 1);
-            const VRec r = g.vt[x.v];
-            x.r = 0;
-            x.deg = r.deg;
-            x.dir = r.dir;
-            x.dcls = r.dcls;
-            x.need = 0;
-            srcs[t0 + h] = x;
-            blocks += nblocks(g, r.deg);
-            if (!small_item(g.B, r.deg, x.hi - x.lo)) cnt = (r.deg + chunk - 1) / chunk;
-        }
-        uint32_t tot;
-        const uint32_t ex = tile_scan<T>(cnt, s_scan, tot);
-        if (h < nh) s_base[h] = ni + ex;
-        ni += tot;
-    }
-    blocks = wave_sum(blocks);
-    if (lane_id() == 0 && blocks) atomicAdd(&s_sum[2], blocks);
-    if (t == 0) {
-        tiles[blockIdx.x] = make_uint2(t0, nh);
-        s_i0 = ni ? (uint32_t)atomicAdd(&bc->alloc_i, (unsigned long long)ni) : 0u;
-    }
-    __syncthreads();  // (the source records are in place for the workgroup)
     if (t < 3) atomicAdd(&bc->stripe[blockIdx.x & 63][t], s_sum[t]);
+    const uint32_t t0 = (uint32_t)(s_at >> 32), i0 = (uint32_t)s_at;
+#pragma unroll
+    for (uint32_t j = 0; j < R; ++j) {
+        if (!head[j]) continue;
+        Src x;
+        x.lo = (uint32_t)p0 + j * T + t;
+        x.hi = end[j];
+        x.r = 0;
+        x.v = (uint32_t)(k[j] >> L) & (uint32_t)((1ull << L) - 1);
+        x.deg = rec[j].deg;
+        x.dir = rec[j].dir;
+        x.dcls = rec[j].dcls;
+        x.need = 0;
+        srcs[t0 + rank[j]] = x;
+    }
     for (uint32_t m = t; m < ni; m += T) {
         // the last source whose items start at or before m
         uint32_t lo = 0, hi = nh;
@@ -575,15 +614,15 @@ __global__ __launch_bounds__(T) void k_segments(GraphView g, const uint64_t* key
             if (s_base[mid] <= m) lo = mid;
             else hi = mid;
         }
-        const Src x = srcs[t0 + lo];
+        const uint32_t a = s_pos[lo];
         Item it;
         it.s0 = (m - s_base[lo]) * chunk;
-        it.s1 = min(x.deg, it.s0 + chunk);
-        it.lo = x.lo;
-        it.hi = x.hi;
-        it.dir = x.dir;
-        it.inl = x.dcls == kNoDir;
-        if ((uint64_t)s_i0 + m < icap) items[(uint64_t)s_i0 + m] = it;
+        it.s1 = min(s_deg[lo], it.s0 + chunk);
+        it.lo = (uint32_t)p0 + (a & ~kInl);
+        it.hi = lo + 1 < nh ? (uint32_t)p0 + (s_pos[lo + 1] & ~kInl) : s_end;
+        it.dir = s_dir[lo];
+        it.inl = (a & kInl) != 0;
+        if ((uint64_t)i0 + m < icap) items[(uint64_t)i0 + m] = it;
     }
 }
 
@@ -786,7 +825,7 @@ __global__ __launch_bounds__(kThreads, kProbeWaves) void k_probe(GraphView g, co
     }
     {
         // small items first, kSmallLanes consecutive lanes per touched source
-        const uint64_t nq = bc->alloc_t * kSmallLanes;
+        const uint64_t nq = (uint64_t)(uint32_t)(bc->alloc >> 32) * kSmallLanes;
         const uint64_t stride = (uint64_t)gridDim.x * kThreads;
         for (uint64_t k = (uint64_t)blockIdx.x * kThreads + threadIdx.x; k < nq; k += stride) {
             const Src I = srcs[k / kSmallLanes];
@@ -796,7 +835,7 @@ __global__ __launch_bounds__(kThreads, kProbeWaves) void k_probe(GraphView g, co
                 probe_small<MODE>(g, I, q, keys, mark, hitpos);
         }
     }
-    const uint32_t nitems = (uint32_t)bc->alloc_i;
+    const uint32_t nitems = __builtin_amdgcn_readfirstlane((uint32_t)bc->alloc);
     const uint32_t lane = lane_id();
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t nw = gridDim.x * kWaves;
@@ -944,8 +983,9 @@ __global__ __launch_bounds__(kThreads, kProbeWaves) void k_probe(GraphView g, co
 
 // ------------------------------------------------------------------ plan
 __device__ __forceinline__ void plan_insert(const GraphView& g, const BatchCtr* bc, uint64_t n,
-                                            int sticky);
-__device__ __forceinline__ void plan_delete(const GraphView& g, const BatchCtr* bc, uint64_t n);
+                                            uint32_t applied, int sticky);
+__device__ __forceinline__ void plan_delete(const GraphView& g, const BatchCtr* bc, uint64_t n,
+                                            uint32_t applied);
 
 // a source that one lane compacts by itself
 __device__ __forceinline__ bool lane_compactable(uint32_t r, uint32_t lo, uint32_t hi) {
@@ -973,44 +1013,50 @@ __device__ __forceinline__ uint32_t wave_count(const uint8_t* mark, uint64_t a, 
 //
 // Bound: latency (marks, then source records: both streams).  It replaces a
 // scan over the pairs, a kernel over the sources and a scan over them
-// (insert: 19 -> 9.3 us at 10^4 pairs, 46 -> 22 at 10^6), or a scan over the
+// (insert: 19 -> 7.8 us at 10^4 pairs, 46 -> 22 at 10^6), or a scan over the
 // sources that read their records anew and two hit counters kept by the probe
-// (delete: 8.3 -> 8.0 us, with the counters and a last kernel of 3.4 us gone).
-template <bool INS, int T>
+// (delete: 8.3 -> 7.1 us, with the counters and a last kernel of 3.4 us gone).
+template <bool INS, int T, uint32_t R>
 __global__ __launch_bounds__(T) void k_plan(GraphView g, uint64_t n, BatchCtr* bc, uint32_t tl,
                                             const uint8_t* mark, Src* srcs, const uint2* tiles,
                                             uint2* carry, uint32_t* tbase, uint32_t* t_dreq,
                                             uint32_t* t_drank, uint32_t* list, uint32_t* list2,
                                             int sticky) {
-    constexpr uint32_t kTile = T * kTileRows;
+    constexpr uint32_t kTile = T * R;
     __shared__ uint32_t s_pre[kTile + 1];
-    __shared__ uint32_t s_cnt[kTileRows * T / 64];
+    __shared__ uint32_t s_cnt[R * T / 64];
     __shared__ unsigned long long s_scan[T / 64];
     __shared__ uint32_t lcnt[kMaxClass], lbase[kMaxClass];
     __shared__ uint32_t s_tail[T / 64];
-    __shared__ unsigned long long s_demand;
-    __shared__ uint32_t s_last;
+    __shared__ unsigned long long s_demand, s_done;
     const uint32_t t = threadIdx.x, w = t >> 6;
+    const uint64_t p0 = (uint64_t)blockIdx.x << tl;
+    const uint32_t tile = 1u << tl;
+    // read before the batch's counters have arrived, at positions inside the
+    // buffers
+    const uint2 td = tiles[blockIdx.x];
+    uint8_t m[R];
+#pragma unroll
+    for (uint32_t j = 0; j < R; ++j)
+        m[j] = mark[min(p0 + min(j * T + t, tile - 1), n - 1)];
     // (an order check that failed leaves nothing to plan)
     const uint64_t lim = batch_failed(g.ctr) ? 0ull : min((uint64_t)bc->n_valid, n);
-    const uint64_t p0 = (uint64_t)blockIdx.x << tl;
-    const uint32_t np = p0 < lim ? (uint32_t)min((uint64_t)1 << tl, lim - p0) : 0u;
+    const uint32_t np = p0 < lim ? (uint32_t)min((uint64_t)tile, lim - p0) : 0u;
     if (t < kMaxClass) lcnt[t] = 0;
-    unsigned long long changed = 0;
+    uint32_t changed = 0;
     if (np) {  // uniform over the workgroup
-        const uint2 td = tiles[blockIdx.x];
         const uint32_t t0 = td.x, nh = td.y;
-        bool f[kTileRows];
-        uint32_t rank[kTileRows];
+        // the first row's sources and the last one, while the marks are ranked
+        const Src row0 = srcs[t0 + (nh ? min(t, nh - 1) : 0u)];
+        const uint2 last = *(const uint2*)&srcs[t0 + (nh ? nh - 1 : 0u)];  // lo, hi
+        bool f[R];
+        uint32_t rank[R];
 #pragma unroll
-        for (uint32_t j = 0; j < kTileRows; ++j) {
-            const uint32_t p = j * T + t;
-            const uint8_t m = mark[p0 + min(p, np - 1)];
-            f[j] = p < np && (INS ? m == 0 : m != 0);
-        }
+        for (uint32_t j = 0; j < R; ++j)
+            f[j] = j * T + t < np && (INS ? m[j] == 0 : m[j] != 0);
         const uint32_t tot = tile_ranks<T>(f, rank, s_cnt);
 #pragma unroll
-        for (uint32_t j = 0; j < kTileRows; ++j) {
+        for (uint32_t j = 0; j < R; ++j) {
             const uint32_t p = j * T + t;
             if (p < np) s_pre[p] = rank[j];
         }
@@ -1021,16 +1067,16 @@ __global__ __launch_bounds__(T) void k_plan(GraphView g, uint64_t n, BatchCtr* b
         uint32_t tail = 0;
         const uint64_t pe = p0 + np;
         if (nh) {
-            const Src last = srcs[t0 + nh - 1];
-            if (last.hi > pe) {
-                const uint32_t in_tile = tot - s_pre[last.lo - (uint32_t)p0];
-                const uint64_t b0 = blockIdx.x + 1, b1 = ((uint64_t)last.hi - 1) >> tl;
+            const uint32_t last_lo = last.x, last_hi = last.y;
+            if (last_hi > pe) {
+                const uint32_t in_tile = tot - s_pre[last_lo - (uint32_t)p0];
+                const uint64_t b0 = blockIdx.x + 1, b1 = ((uint64_t)last_hi - 1) >> tl;
                 for (uint64_t b = b0; b <= b1; b += T / 64) {
                     const uint64_t mb = b + w;
                     uint32_t c = 0;
                     if (mb <= b1)
                         c = wave_count<INS>(mark, mb << tl,
-                                            min((uint64_t)last.hi, (mb + 1) << tl));
+                                            min((uint64_t)last_hi, (mb + 1) << tl));
                     if (lane_id() == 0) s_tail[w] = c;
                     __syncthreads();
                     uint32_t before = 0, all = 0;
@@ -1048,10 +1094,10 @@ __global__ __launch_bounds__(T) void k_plan(GraphView g, uint64_t n, BatchCtr* b
         }
         // the sources: blocks (low) and listed sources (high) of the tile
         unsigned long long run = 0;
-        uint32_t cls[kTileRows], lrank[kTileRows], lpos[kTileRows];
-        bool listed[kTileRows];
+        uint32_t cls[R], lrank[R], lpos[R];
+        bool listed[R];
 #pragma unroll
-        for (uint32_t j = 0; j < kTileRows; ++j) {
+        for (uint32_t j = 0; j < R; ++j) {
             cls[j] = kNoDir;
             listed[j] = false;
             if (j * T >= nh) continue;  // uniform
@@ -1059,7 +1105,7 @@ __global__ __launch_bounds__(T) void k_plan(GraphView g, uint64_t n, BatchCtr* b
             uint32_t need = 0;
             bool heavy = false;
             if (h < nh) {
-                Src x = srcs[t0 + h];
+                Src x = j == 0 ? row0 : srcs[t0 + h];
                 x.r = s_pre[(uint32_t)(min((uint64_t)x.hi, pe) - p0)] -
                       s_pre[x.lo - (uint32_t)p0] + (h + 1 == nh ? tail : 0u);
                 if (INS) {
@@ -1108,20 +1154,16 @@ __global__ __launch_bounds__(T) void k_plan(GraphView g, uint64_t n, BatchCtr* b
         __syncthreads();
         const uint32_t lb = (uint32_t)(s_demand >> 32);
 #pragma unroll
-        for (uint32_t j = 0; j < kTileRows; ++j) {
+        for (uint32_t j = 0; j < R; ++j) {
             if (listed[j]) list[lb + rank[j]] = lpos[j];
             if (INS && cls[j] != kNoDir) t_drank[lpos[j]] = lbase[cls[j]] + lrank[j];
         }
     }
-    if (t == 0) {
-        // (the value returned by each atomic is used before the next is issued)
-        const unsigned long long had = changed ? atomicAdd(&bc->changed, changed) : 0ull;
-        s_last = had != ~0ull && atomicAdd(&bc->done, 1ull) == gridDim.x - 1 ? 1u : 0u;
-    }
+    if (t == 0) s_done = atomicAdd(&bc->done, (1ull << 32) + changed) + (1ull << 32) + changed;
     __syncthreads();
-    if (s_last && t < 64) {
-        if (INS) plan_insert(g, bc, n, sticky);
-        else plan_delete(g, bc, n);
+    if (s_done >> 32 == gridDim.x && t < 64) {
+        if (INS) plan_insert(g, bc, n, (uint32_t)s_done, sticky);
+        else plan_delete(g, bc, n, (uint32_t)s_done);
     }
 }
 
@@ -1135,7 +1177,7 @@ __device__ __forceinline__ V ld_agent(const V* p) {
 // capacity is checked before any state is written, so a failing batch leaves
 // the graph unchanged.  Run by the first wave of the last tile planned.
 __device__ __forceinline__ void plan_insert(const GraphView& g, const BatchCtr* bc, uint64_t n,
-                                            int sticky) {
+                                            uint32_t applied, int sticky) {
     DevCounters* c = g.ctr;
     const uint32_t k = lane_id();
     if (batch_failed(c)) {
@@ -1170,10 +1212,9 @@ __device__ __forceinline__ void plan_insert(const GraphView& g, const BatchCtr* 
     const unsigned long long blocks = wave_sum(bc->stripe[k][kStripeBlocks]);
     if (k != 0) return;
     const unsigned long long nv = min((uint64_t)bc->n_valid, n);
-    const unsigned long long applied = ld_agent(&bc->changed);
     c->c_batches[kInsert] += 1;
     c->c_pairs[kInsert] += n;
-    c->c_touched[kInsert] += bc->alloc_t;
+    c->c_touched[kInsert] += bc->alloc >> 32;
     c->c_scanned[kInsert] += blocks << g.log2B;
     c->err_batch = 0;
     if (!ok) {
@@ -1198,7 +1239,8 @@ __device__ __forceinline__ void plan_insert(const GraphView& g, const BatchCtr* 
 }
 
 // The free-list places and the statistics of a delete batch, one wave.
-__device__ __forceinline__ void plan_delete(const GraphView& g, const BatchCtr* bc, uint64_t n) {
+__device__ __forceinline__ void plan_delete(const GraphView& g, const BatchCtr* bc, uint64_t n,
+                                            uint32_t applied) {
     DevCounters* c = g.ctr;
     const uint32_t k = lane_id();
     if (batch_failed(c)) {
@@ -1209,7 +1251,6 @@ __device__ __forceinline__ void plan_delete(const GraphView& g, const BatchCtr* 
     const unsigned long long blocks = wave_sum(bc->stripe[k][kStripeBlocks]);
     if (k != 0) return;
     const unsigned long long nv = min((uint64_t)bc->n_valid, n);
-    const unsigned long long applied = ld_agent(&bc->changed);
     const unsigned long long freed = ld_agent(&bc->demand) & 0xffffffffull;
     c->err_batch = 0;
     c->plan_free_top = c->free_cnt;  // the compaction pushes above it
@@ -1219,7 +1260,7 @@ __device__ __forceinline__ void plan_delete(const GraphView& g, const BatchCtr* 
     c->st_dups = nv - nuniq;
     c->c_batches[kDelete] += 1;
     c->c_pairs[kDelete] += n;
-    c->c_touched[kDelete] += bc->alloc_t;
+    c->c_touched[kDelete] += bc->alloc >> 32;
     c->c_scanned[kDelete] += blocks << g.log2B;
     c->c_freed_blocks += freed;
     c->live_edges -= applied;
@@ -1290,8 +1331,11 @@ __device__ __forceinline__ void grow_lane(const GraphView& g, const DevCounters*
 // read the records as they were before the batch from the sources' own
 // copies, and only directory entries that the batch does not write, so they
 // need no order between them.  One kernel in place of two, each with its own
-// pass over flags, ranks and segment starts (10^4 pairs: 9.6 -> 7.0 us).
-template <int T>
+// pass over flags, ranks and segment starts, took 9.6 us for 10^4 pairs.  Bound:
+// latency, keys -> source -> directory entry or free block -> slot; every step
+// is issued for all of a thread's pairs at once (10^4 pairs 6.9 -> 5.7 us, 10^7
+// 148 -> 118 against pair after pair).
+template <int T, uint32_t R>
 __global__ __launch_bounds__(T) void k_commit(GraphView g, const uint64_t* keys, uint64_t n,
                                               const BatchCtr* bc, uint32_t tl,
                                               const uint8_t* mark, const Src* srcs,
@@ -1299,32 +1343,39 @@ __global__ __launch_bounds__(T) void k_commit(GraphView g, const uint64_t* keys,
                                               const uint32_t* tbase, const uint32_t* t_dreq,
                                               const uint32_t* t_drank, uint32_t* t_dold,
                                               uint32_t* t_doldc, const uint32_t* heavy) {
-    constexpr uint32_t kTile = T * kTileRows;
+    constexpr uint32_t kTile = T * R;
     __shared__ uint32_t s_pre[kTile];
-    __shared__ uint32_t s_cnt[kTileRows * T / 64], s_cnt2[kTileRows * T / 64];
+    __shared__ uint32_t s_cnt[R * T / 64], s_cnt2[R * T / 64];
     const DevCounters* c = g.ctr;
-    if (c->err_batch) return;
     const uint32_t t = threadIdx.x;
-    const uint64_t lim = min((uint64_t)bc->n_valid, n);
     const uint64_t p0 = (uint64_t)blockIdx.x << tl;
     const uint32_t L = g.L;
+    const uint32_t tile = 1u << tl;
+    // read before the batch's counters have arrived, at positions inside the
+    // buffers
+    const uint2 td = tiles[blockIdx.x], cr = carry[blockIdx.x];
+    uint64_t k[R], q[R];
+    uint8_t m[R];
+#pragma unroll
+    for (uint32_t j = 0; j < R; ++j) {
+        const uint64_t i = min(p0 + min(j * T + t, tile - 1), n - 1);
+        k[j] = keys[i];
+        q[j] = keys[i ? i - 1 : 0];
+        m[j] = mark[i];
+    }
+    if (c->err_batch) return;
+    const uint64_t lim = min((uint64_t)bc->n_valid, n);
     if (p0 < lim) {  // uniform over the workgroup
-        const uint32_t np = (uint32_t)min((uint64_t)1 << tl, lim - p0);
-        const uint2 td = tiles[blockIdx.x];
+        const uint32_t np = (uint32_t)min((uint64_t)tile, lim - p0);
         const uint32_t t0 = td.x, nh = td.y, base0 = tbase[blockIdx.x];
-        uint64_t k[kTileRows], q[kTileRows];
-        uint8_t m[kTileRows];
+        // the first of the sources that a thread grows, while the pairs are ranked
+        const uint32_t h0 = t0 + (nh ? min(t, nh - 1) : 0u);
+        const Src row0 = srcs[h0];
+        const uint32_t req0 = t_dreq[h0];
+        bool head[R], kept[R];
+        uint32_t hr[R], kr[R];
 #pragma unroll
-        for (uint32_t j = 0; j < kTileRows; ++j) {
-            const uint64_t i = p0 + min(j * T + t, np - 1);
-            k[j] = keys[i];
-            q[j] = keys[i ? i - 1 : 0];
-            m[j] = mark[i];
-        }
-        bool head[kTileRows], kept[kTileRows];
-        uint32_t hr[kTileRows], kr[kTileRows];
-#pragma unroll
-        for (uint32_t j = 0; j < kTileRows; ++j) {
+        for (uint32_t j = 0; j < R; ++j) {
             const uint32_t p = j * T + t;
             head[j] = p < np && (p0 + p == 0 || (k[j] >> L) != (q[j] >> L));
             kept[j] = p < np && m[j] == 0;
@@ -1332,35 +1383,54 @@ __global__ __launch_bounds__(T) void k_commit(GraphView g, const uint64_t* keys,
         tile_ranks<T>(head, hr, s_cnt);
         tile_ranks<T>(kept, kr, s_cnt2);
 #pragma unroll
-        for (uint32_t j = 0; j < kTileRows; ++j) s_pre[j * T + t] = kr[j];
+        for (uint32_t j = 0; j < R; ++j) s_pre[j * T + t] = kr[j];
         __syncthreads();
+        // The rows' sources, then their blocks, then the slots: every step
+        // reads for all rows at once, a pair that is not kept something in
+        // its place.
+        uint32_t lo[R], deg[R], dir[R], dcls[R], need[R], pb[R], h[R];
 #pragma unroll
-        for (uint32_t j = 0; j < kTileRows; ++j) {
+        for (uint32_t j = 0; j < R; ++j) {
+            h[j] = hr[j] + (head[j] ? 1u : 0u);  // heads up to this position
+            // (none: a segment that began in an earlier tile)
+            const Src x = srcs[!kept[j] ? h0 : h[j] ? t0 + h[j] - 1 : cr.x];
+            lo[j] = kept[j] ? x.lo : (uint32_t)p0;
+            deg[j] = x.deg;
+            dir[j] = x.dir;
+            dcls[j] = x.dcls;
+            need[j] = x.need;
+        }
+        uint32_t blk[R];
+#pragma unroll
+        for (uint32_t j = 0; j < R; ++j) pb[j] = tbase[lo[j] >> tl];
+#pragma unroll
+        for (uint32_t j = 0; j < R; ++j) {
+            const uint32_t rank = h[j] ? kr[j] - s_pre[kept[j] ? lo[j] - (uint32_t)p0 : 0u]
+                                       : cr.y + kr[j];
+            const uint32_t nb0 = nblocks(g, deg[j]);
+            deg[j] += rank;  // the slot
+            const uint32_t b = deg[j] >> g.log2B;
+            // an entry of the directory, the only block, a block of the free
+            // list or one past the pool's bump pointer
+            const uint64_t p = (uint64_t)pb[j] + need[j] + (b - nb0);
+            const bool old = b < nb0, inl = dcls[j] == kNoDir, fl = p < c->plan_from_free;
+            const uint32_t* at = (const uint32_t*)keys;
+            if (kept[j] && old && !inl) at = g.dir + (uint64_t)dir[j] + b;
+            if (kept[j] && !old && fl) at = g.free_stack + (c->plan_free_top - 1 - p);
+            const uint32_t v = *at;
+            blk[j] = old ? (inl ? dir[j] : v)
+                         : (fl ? v : (uint32_t)(c->plan_bump0 + (p - c->plan_from_free)));
+        }
+#pragma unroll
+        for (uint32_t j = 0; j < R; ++j) {
             if (!kept[j]) continue;
-            const uint32_t h = hr[j] + (head[j] ? 1u : 0u);  // heads up to this position
-            uint32_t ts = t0 + h - 1, rank, pb = base0;
-            Src x;
-            if (h) {
-                x = srcs[ts];
-                rank = kr[j] - s_pre[x.lo - (uint32_t)p0];
-            } else {  // a segment that began in an earlier tile
-                const uint2 cr = carry[blockIdx.x];
-                x = srcs[cr.x];
-                rank = cr.y + kr[j];
-                pb = tbase[x.lo >> tl];
-            }
-            const VRec r{x.deg, x.dir, x.dcls, 0u};
-            const uint32_t sl = r.deg + rank;
-            const uint32_t b = sl >> g.log2B, nb0 = nblocks(g, r.deg);
-            const uint32_t blk = b < nb0 ? block_of(g, r, b)
-                                         : planned_block(g, c, (uint64_t)pb + x.need + (b - nb0));
-            const uint64_t sa = ((uint64_t)blk << g.log2B) + (sl & (g.B - 1));
+            const uint64_t sa = ((uint64_t)blk[j] << g.log2B) + (deg[j] & (g.B - 1));
             g.pool[sa] = (uint32_t)(k[j] & ((1ull << L) - 1));
             attr_zero(g, sa);
         }
         for (uint32_t h = t; h < nh; h += T) {
-            const Src x = srcs[t0 + h];
-            const uint32_t req = t_dreq[t0 + h];
+            const Src x = h == t ? row0 : srcs[t0 + h];
+            const uint32_t req = h == t ? req0 : t_dreq[t0 + h];
             if (!x.r || (req & kHeavy)) continue;
             const uint32_t cls = req & kClassMask;
             const uint32_t rk = cls != kNoDir ? t_drank[t0 + h] : 0u;
@@ -1454,7 +1524,7 @@ __device__ __forceinline__ void compact_body(const GraphView& g, const uint32_t*
     __shared__ uint32_t s_gone[kWaves][kBigR / 32];
     const uint32_t gwave = (vb * kThreads + threadIdx.x) >> 6;
     const DevCounters* c = g.ctr;
-    const uint32_t nT = (uint32_t)bc->alloc_t;
+    const uint32_t nT = (uint32_t)(bc->alloc >> 32);
     const uint32_t lane = lane_id();
     const uint64_t below = (1ull << lane) - 1;
     const uint32_t stride = vg * kThreads;
@@ -1691,7 +1761,7 @@ __global__ __launch_bounds__(kThreads) void k_answer(GraphView g, const BatchCtr
             DevCounters* c = g.ctr;
             c->c_batches[kQuery] += 1;
             c->c_pairs[kQuery] += n;
-            c->c_touched[kQuery] += bc->alloc_t;
+            c->c_touched[kQuery] += bc->alloc >> 32;
             c->c_scanned[kQuery] += blocks << g.log2B;
         }
     }
@@ -2006,15 +2076,23 @@ static void edge_run(gv_graph* g, EdgeMode mode, const uint32_t* src, const uint
 
     const uint32_t tl = tile_log(n);
     const uint64_t ntiles = div_up(n, 1ull << tl);
-    // workgroups of 256 threads while a tile is at most four positions each
+    // workgroups of 256 threads while a tile is at most four positions each,
+    // and no code for rows that a small tile does not have (a small
+    // batch's workgroups each fetch the kernel's instructions anew: segments
+    // and plan of 10^3 pairs 1 us less each)
     auto with_threads = [&](auto&& f) {
-        if ((1u << tl) <= kThreads * kTileRows) f(std::integral_constant<int, kThreads>{});
-        else f(std::integral_constant<int, 1024>{});
+        using std::integral_constant;
+        using One = integral_constant<uint32_t, 1>;
+        using Rows = integral_constant<uint32_t, kTileRows>;
+        if ((1u << tl) <= kThreads) f(integral_constant<int, kThreads>{}, One{});
+        else if ((1u << tl) <= kThreads * kTileRows) f(integral_constant<int, kThreads>{}, Rows{});
+        else f(integral_constant<int, 1024>{}, Rows{});
     };
     const uint32_t chunk = g->tune.item_chunk;
-    with_threads([&](auto tag) {
-        constexpr int T = decltype(tag)::value;
-        c.launch("segments", k_segments<T>, ntiles, T, v, keys, n, bc, tl, A.mark,
+    with_threads([&](auto threads, auto rows) {
+        constexpr int T = decltype(threads)::value;
+        constexpr uint32_t R = decltype(rows)::value;
+        c.launch("segments", k_segments<T, R>, ntiles, T, v, keys, n, bc, tl, A.mark,
                  mode == kInsert ? 1 : 0, mode == kDelete ? A.hitpos : nullptr, A.srcs, A.tiles,
                  A.items, icap, chunk);
     });
@@ -2030,12 +2108,13 @@ static void edge_run(gv_graph* g, EdgeMode mode, const uint32_t* src, const uint
 
     if (mode == kInsert) {
         probe(std::integral_constant<int, kInsert>{}, "probe_insert", nullptr);
-        with_threads([&](auto tag) {
-            constexpr int T = decltype(tag)::value;
-            c.launch("plan_insert", k_plan<true, T>, ntiles, T, v, n, bc, tl,
+        with_threads([&](auto threads, auto rows) {
+            constexpr int T = decltype(threads)::value;
+            constexpr uint32_t R = decltype(rows)::value;
+            c.launch("plan_insert", k_plan<true, T, R>, ntiles, T, v, n, bc, tl,
                      (const uint8_t*)A.mark, A.srcs, (const uint2*)A.tiles, A.carry, A.tbase,
                      A.t_dreq, A.t_drank, A.rel, A.heavy, (int)sticky);
-            c.launch("commit", k_commit<T>, ntiles, T, v, keys, n, (const BatchCtr*)bc, tl,
+            c.launch("commit", k_commit<T, R>, ntiles, T, v, keys, n, (const BatchCtr*)bc, tl,
                      (const uint8_t*)A.mark, (const Src*)A.srcs, (const uint2*)A.tiles,
                      (const uint2*)A.carry, (const uint32_t*)A.tbase, (const uint32_t*)A.t_dreq,
                      (const uint32_t*)A.t_drank, A.t_dold, A.t_doldc, (const uint32_t*)A.heavy);
@@ -2045,9 +2124,10 @@ static void edge_run(gv_graph* g, EdgeMode mode, const uint32_t* src, const uint
                  (const uint32_t*)A.t_doldc);
     } else if (mode == kDelete) {
         probe(std::integral_constant<int, kDelete>{}, "probe_delete", A.hitpos);
-        with_threads([&](auto tag) {
-            constexpr int T = decltype(tag)::value;
-            c.launch("plan_delete", k_plan<false, T>, ntiles, T, v, n, bc, tl,
+        with_threads([&](auto threads, auto rows) {
+            constexpr int T = decltype(threads)::value;
+            constexpr uint32_t R = decltype(rows)::value;
+            c.launch("plan_delete", k_plan<false, T, R>, ntiles, T, v, n, bc, tl,
                      (const uint8_t*)A.mark, A.srcs, (const uint2*)A.tiles, (uint2*)nullptr,
                      A.tbase, (uint32_t*)nullptr, (uint32_t*)nullptr, A.heavy, A.big, 0);
         });
