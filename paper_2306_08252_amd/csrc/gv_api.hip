@@ -69,7 +69,7 @@ void free_graph(gv_graph* g) {
     void* mem[] = {g->mem_vt, g->mem_active, g->mem_ctr, g->mem_vlost, g->mem_chain};
     for (void* p : mem)
         if (p) hipFree(p);
-    if (g->hctr) hipHostFree(g->hctr);
+    if (g->hmem) hipHostFree(g->hmem);
     delete g;
 }
 
@@ -150,8 +150,10 @@ int gv_graph_init(gv_graph** out, uint64_t num_vertices, const uint32_t* d_src,
         hip_check(hipMalloc(&g->mem_vlost, cap * sizeof(uint32_t)), "hipMalloc vertex scratch");
         hip_check(hipMemsetAsync(g->mem_vlost, 0, cap * sizeof(uint32_t), g->ctx.stream),
                   "hipMemsetAsync");
-        hip_check(hipHostMalloc((void**)&g->hctr, sizeof(DevCounters), hipHostMallocDefault),
+        hip_check(hipHostMalloc((void**)&g->hmem, sizeof(HostCounters), hipHostMallocDefault),
                   "hipHostMalloc");
+        std::memset(g->hmem, 0, sizeof(HostCounters));
+        g->hctr = &g->hmem->c;
         hip_check(hipMemsetAsync(g->mem_ctr, 0, sizeof(DevCounters), g->ctx.stream),
                   "hipMemsetAsync");
         v.vt = (VRec*)g->mem_vt;
@@ -195,7 +197,7 @@ static int edge_update(gv_graph* g, EdgeMode mode, const uint32_t* s, const uint
     int rc = guarded(g, [&] {
         edge_batch(g, mode, s, d, n, nullptr, st == nullptr);
         if (st) {
-            read_counters(g);
+            read_stats(g);
             check_sort(g);
             if (g->hctr->err_batch) fail((int)g->hctr->err_batch, "batch failed");
             fill_stats(g, st);
@@ -277,7 +279,7 @@ int gv_set_edge_attrs(gv_graph* g, const uint32_t* d_src, const uint32_t* d_dst,
     int rc = guarded(g, [&] {
         edge_attrs(g, d_src, d_dst, n, nullptr, nullptr, d_attr);
         if (st) {
-            read_counters(g);
+            read_stats(g);
             check_sort(g);
             const uint64_t valid = g->hctr->st_valid;
             st->applied = g->hctr->st_applied;

@@ -5,11 +5,22 @@
 #include "gv_device.h"
 #include "gv_host.h"
 
+namespace gv {
+// the counters' pinned host copy and the number of the last statistics read
+// that has arrived there
+struct HostCounters {
+    DevCounters c;
+    alignas(128) unsigned long long number;
+};
+}  // namespace gv
+
 struct gv_graph {
     int device = 0;
     gv::Ctx ctx;
     gv::GraphView v{};            // device pointers and sizes
-    gv::DevCounters* hctr = nullptr;  // pinned host copy for read-back
+    gv::HostCounters* hmem = nullptr;  // pinned
+    gv::DevCounters* hctr = nullptr;   // its counters
+    unsigned long long stat_reads = 0;
     gv::Scratch scratch;          // per-call temporaries
     gv::Scratch vscr[3];          // vertex-batch buffers that outlive an inner edge batch
     gv::Scratch cscr;             // a coalesced run of edge batches (batched form)
@@ -163,6 +174,9 @@ uint64_t audit(gv_graph* g);
 
 // copy the device counters into g->hctr (synchronous)
 void read_counters(gv_graph* g);
+// the same without the stripes, and without a stream synchronisation: what
+// was queued before has run, but only the counters are known to have arrived
+void read_stats(gv_graph* g);
 // set one 32-bit or 64-bit device word from a kernel (stream ordered)
 void set_u32(gv_graph* g, uint32_t* p, uint32_t value);
 void set_u64(gv_graph* g, unsigned long long* p, unsigned long long value);

@@ -666,7 +666,7 @@ void vertex_insert(gv_graph* g, const uint32_t* ids, uint64_t n, gv_batch_stats*
         c.launch("vfit", k_vfit, div_up(n, kThreads), kThreads, g->v, ids, n);
     } else {
         c.launch("vmax", k_vmax, div_up(n, kThreads), kThreads, ids, n, g->v.ctr);
-        read_counters(g);
+        read_stats(g);
         if (g->hctr->vany && (uint64_t)g->hctr->vmax >= g->v.n_cap) {
             uint64_t cap = g->v.n_cap;
             while (cap <= (uint64_t)g->hctr->vmax) cap <<= 1;
@@ -678,7 +678,7 @@ void vertex_insert(gv_graph* g, const uint32_t* ids, uint64_t n, gv_batch_stats*
     c.launch("vzero", k_vzero, div_up(words, kThreads), kThreads, seen, words);
     c.launch("vinsert", k_vins, div_up(n, kThreads), kThreads, g->v, ids, n, seen);
     if (st) {
-        read_counters(g);
+        read_stats(g);
         st->applied = g->hctr->st_applied;
         st->rejected = g->hctr->st_rejected;
         st->batch_duplicates = n - g->hctr->st_rejected - g->hctr->n_uniq;
@@ -785,7 +785,7 @@ void vertex_delete(gv_graph* g, const uint32_t* ids, uint64_t n, gv_batch_stats*
     c.launch("vdel_finish", k_vdel_finish, div_up(n, kThreads), kThreads, g->v, ids, n,
              (const uint8_t*)first, (const uint32_t*)gone);
     if (st) {
-        read_counters(g);
+        read_stats(g);
         st->applied = g->hctr->st_applied;
         st->rejected = g->hctr->st_rejected;
         st->batch_duplicates = n - g->hctr->st_rejected - g->hctr->n_uniq;
