@@ -85,13 +85,14 @@ struct DevCounters {
     uint32_t err_order;                // a batch's sorted keys failed their check
     uint32_t sort_n, sort_err;  // count and look-back error word of whole-graph sorts
     // vertex delete: slots hit, vertices touched, hole entries reserved
-    unsigned long long vd_hits, vd_touched, vd_pairs;
+    unsigned long long vd_hits, vd_pairs;
     unsigned long long st_valid;       // valid pairs of the last attribute write
     // statistics of the last batch
     unsigned long long st_applied, st_rejected, st_dups;
     // cumulative work counters
     unsigned long long c_batches[3], c_pairs[3], c_touched[3], c_scanned[3];
     unsigned long long c_new_blocks, c_freed_blocks, c_written, c_moved;
+    unsigned long long vd_touched;     // (a line apart from vd_hits: both are counted up at once)
     // striped accumulators (one 128-byte line each) for per-wave counts
     unsigned long long stripe[64][16];
     // verification
@@ -235,9 +236,9 @@ __device__ __forceinline__ void wave_append(bool take, uint32_t x, uint32_t* cou
     if (take) list[base + rank_below(m)] = x;
 }
 
-// exclusive scan across a kThreads workgroup; `total` receives the sum.
-// lds must hold kWaves entries; contains barriers (call uniformly).
-template <typename T>
+// exclusive scan across a workgroup of W waves; `total` receives the sum.
+// lds must hold W entries; contains barriers (call uniformly).
+template <int W = kWaves, typename T>
 __device__ __forceinline__ T block_excl_scan(T x, T* lds, T& total) {
     T inc = wave_incl_scan(x);
     const int w = threadIdx.x >> 6;
@@ -245,7 +246,7 @@ __device__ __forceinline__ T block_excl_scan(T x, T* lds, T& total) {
     __syncthreads();
     T off = 0, tot = 0;
 #pragma unroll
-    for (int i = 0; i < kWaves; ++i) {
+    for (int i = 0; i < W; ++i) {
         T v = lds[i];
         off += (i < w) ? v : T(0);
         tot += v;

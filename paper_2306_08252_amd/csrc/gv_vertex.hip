@@ -30,22 +30,26 @@ __device__ __forceinline__ bool bit_of(const uint32_t* bm, uint32_t x) {
     return (bm[x >> 5] >> (x & 31)) & 1u;
 }
 
+// one atomic per workgroup (same-address atomics pass one after the other)
 __global__ __launch_bounds__(kThreads) void k_vmax(const uint32_t* ids, uint64_t n,
                                                    DevCounters* ctr) {
-    const uint64_t i = vt_tidx();
-    uint32_t m = 0, any = 0;
-    if (i < n && ids[i] <= kMaxId) {
-        m = ids[i];
-        any = 1;
+    __shared__ uint32_t s_m[kWaves];
+    uint32_t m = 0;  // the largest id + 1, or 0
+    for (uint64_t i = vt_tidx(); i < n; i += (uint64_t)gridDim.x * kThreads) {
+        const uint32_t id = ids[i];
+        if (id <= kMaxId) m = max(m, id + 1);
     }
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        m = max(m, (uint32_t)__shfl_xor((int)m, o, 64));
-        any |= (uint32_t)__shfl_xor((int)any, o, 64);
-    }
-    if (lane_id() == 0 && any) {
-        atomicMax(&ctr->vmax, m);
-        ctr->vany = 1;
+    for (int o = 32; o > 0; o >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, o, 64));
+    if (lane_id() == 0) s_m[threadIdx.x >> 6] = m;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+#pragma unroll
+        for (int w = 1; w < kWaves; ++w) m = max(m, s_m[w]);
+        if (m) {
+            atomicMax(&ctr->vmax, m - 1);
+            ctr->vany = 1;
+        }
     }
 }
 
@@ -83,7 +87,11 @@ __global__ __launch_bounds__(kThreads) void k_grow_table(const VRec* vt, const u
     }
 }
 
-__global__ void k_vreset(DevCounters* c) {
+// The counters of a vertex batch reset, its bitmaps zeroed.
+__global__ __launch_bounds__(kThreads) void k_vbegin(DevCounters* c, uint32_t* a, uint64_t n) {
+    const uint64_t i = vt_tidx();
+    if (i < n) a[i] = 0;
+    if (i != 0) return;
     c->st_applied = c->st_rejected = c->st_dups = 0;
     c->n_uniq = 0;
     c->vmax = 0;
@@ -128,11 +136,12 @@ __global__ __launch_bounds__(kThreads) void k_vins(GraphView g, const uint32_t* 
 
 // Ids in input order: the first occurrence of each valid id (its atomicOr
 // sets the bit in `seen`) gets first[i] = 1, and marks the id in the `gone`
-// bitmap when it is active; the later kernels of the delete take an id at
-// its first occurrence only.
+// bitmap and its summary when it is active; the later kernels of the delete
+// take an id at its first occurrence only.
 __global__ __launch_bounds__(kThreads) void k_vdel_mark(GraphView g, const uint32_t* ids,
                                                         uint64_t n, uint32_t* seen,
-                                                        uint32_t* gone, uint8_t* first) {
+                                                        uint32_t* gone, uint32_t* summary,
+                                                        uint32_t sum_shift, uint8_t* first) {
     __shared__ unsigned long long lds[kWaves];
     const uint64_t i = vt_tidx();
     unsigned long long rej = 0, uniq = 0, app = 0;
@@ -147,6 +156,8 @@ __global__ __launch_bounds__(kThreads) void k_vdel_mark(GraphView g, const uint3
             uniq = 1;
             if (is_active(g, id)) {
                 atomicOr(&gone[id >> 5], bit);
+                const uint32_t b = id >> sum_shift;
+                atomicOr(&summary[b >> 5], 1u << (b & 31));
                 app = 1;
             }
         }
@@ -180,8 +191,10 @@ __global__ __launch_bounds__(kThreads) void k_vdel_mark(GraphView g, const uint3
 constexpr uint32_t kVSumBits = 1u << 17;
 constexpr uint32_t kVSumWords = kVSumBits / 32;
 constexpr uint32_t kVQuads = 4;        // 4-slot groups per thread per round of the pass
-constexpr uint32_t kVHitBuf = 1024;    // hits staged in LDS per workgroup
-constexpr uint32_t kVLane = 32;        // tails and frees a lane takes; larger ones take the wave
+constexpr uint32_t kVScan = 512;       // threads per workgroup of the pass
+constexpr uint32_t kVHitBuf = 4096;    // slots to check staged in LDS per workgroup
+constexpr uint32_t kVLane = 32;        // frees a lane takes; larger ones take the wave
+constexpr uint32_t kVTail = 32;        // tail slots a lane takes
 constexpr uint32_t kVErrBound = 4;     // err_order value: a device-side bound was exceeded
 
 struct VDel {
@@ -207,30 +220,6 @@ __device__ __forceinline__ VRec vd_record(const GraphView& g, VRec r, uint32_t n
     r.deg = nd;
     if (nblocks(g, nd) == 0 && r.dcls == kNoDir) r.dir = 0;
     return r;
-}
-
-// the summary into LDS (every thread calls it; one barrier)
-__device__ __forceinline__ void vd_load_summary(const VDel& d, uint32_t* s_sum) {
-    for (uint32_t i = threadIdx.x; i < d.sum_words; i += kThreads) s_sum[i] = d.summary[i];
-    __syncthreads();
-}
-
-// is destination x deleted: the LDS summary first, the bitmap only when the
-// summary's range holds a deleted id
-__device__ __forceinline__ bool vd_gone(const VDel& d, const uint32_t* s_sum, uint32_t x) {
-    const uint32_t b = x >> d.sum_shift;
-    if (!((s_sum[b >> 5] >> (b & 31)) & 1u)) return false;
-    return bit_of(d.gone, x);
-}
-
-// summary bits of the deleted set (one thread per bitmap word)
-__global__ __launch_bounds__(kThreads) void k_vd_summary(VDel d, uint64_t words) {
-    const uint64_t w = vt_tidx();
-    if (w >= words) return;
-    for (uint32_t m = d.gone[w]; m; m &= m - 1) {
-        const uint64_t b = ((w << 5) + (uint32_t)__ffs(m) - 1) >> d.sum_shift;
-        atomicOr(&d.summary[b >> 5], 1u << (b & 31));
-    }
 }
 
 // exclusive prefix of x over the workgroup and one atomic add of the total
@@ -279,88 +268,74 @@ __device__ __forceinline__ bool vd_hit(const GraphView& g, const VDel& d, uint64
 
 // The pass over the pool's handed-out blocks [0, bump), grid-stride in rounds
 // of kThreads * kVQuads groups of 4 slots, with no barrier between rounds.
-// Hits, and the vertices whose first hit this is, are staged in LDS and
-// appended with one atomic per workgroup at the end (a full stage spills to
-// direct appends).
-__global__ __launch_bounds__(kThreads) void k_vd_scan(GraphView g, VDel d) {
+// Slots whose value is deleted are staged in LDS and checked together at the
+// end, a lane each: the check is a chain of four reads (owner record, vertex
+// record, directory, the owner's counter), which each round waited for as
+// many times as its busiest lane had such slots.  A full stage
+// checks the rest on the spot.  Hits, and the vertices whose first hit this
+// is, take one atomic per workgroup and turn, 512 threads each: atomics on one
+// address pass one after the other, 6 ns each, and two of them (on one line)
+// and the edge count for every 256 threads were 20 us at the end.  Bound: the
+// instructions of the pass; 10^4 ids of a 2^20-vertex graph of 2^24 edges 77 ->
+// 43 us (staged 66, larger workgroups 46, whole rounds unchecked 43).
+__global__ __launch_bounds__(kVScan, 6) void k_vd_scan(GraphView g, VDel d) {
     __shared__ uint32_t s_sum[kVSumWords];
-    __shared__ uint2 s_hit[kVHitBuf];
-    __shared__ uint32_t s_tv[kVHitBuf];
-    __shared__ uint32_t s_nh, s_nt;
+    __shared__ uint32_t s_slot[kVHitBuf];  // round * kRoundSlots + slot of the round
+    __shared__ uint32_t s_n;
     __shared__ unsigned long long s_bh, s_bt;
-    __shared__ unsigned long long lds[kWaves];
-    vd_load_summary(d, s_sum);
-    if (threadIdx.x == 0) s_nh = s_nt = 0u;
+    __shared__ unsigned long long lds[kVScan / 64];
+    if (threadIdx.x == 0) s_n = 0u;
+    for (uint32_t i = threadIdx.x; i < d.sum_words; i += kVScan) s_sum[i] = d.summary[i];
     __syncthreads();
     const uint64_t slots = (uint64_t)g.ctr->bump << g.log2B;
     const uint64_t nq = (slots + 3) / 4;
-    constexpr uint64_t kRound = (uint64_t)kThreads * kVQuads;
-    unsigned long long lost = 0;
-    auto add_hit = [&](uint32_t v, uint32_t p) {
-        ++lost;
-        const uint32_t k = atomicAdd(&s_nh, 1u);
-        if (k < kVHitBuf) {
-            s_hit[k] = make_uint2(v, p);
-        } else {
-            const unsigned long long i = atomicAdd(&g.ctr->vd_hits, 1ull);
-            if (i < d.hcap) d.hits[i] = make_uint2(v, p);
-            else vd_error(g);
-        }
-        if (atomicAdd(&g.vlost[v], 1u) == 0u) {
-            const uint32_t kt = atomicAdd(&s_nt, 1u);
-            if (kt < kVHitBuf) {
-                s_tv[kt] = v;
-            } else {
-                const unsigned long long i = atomicAdd(&g.ctr->vd_touched, 1ull);
-                if (i < d.tcapn) d.touched[i] = v;
-                else vd_error(g);
-            }
-        }
-    };
-    // the slots of one round: kVQuads groups of 4 per thread (zeros past the
-    // handed-out slots)
+    constexpr uint64_t kRound = (uint64_t)kVScan * kVQuads;
+    constexpr uint32_t kRoundSlots = 4 * kRound;
+    // the slots of one round: kVQuads groups of 4 per thread (no id past
+    // the handed-out slots)
     auto load_round = [&](uint64_t q0, uint32_t (&xs)[kVQuads][4]) {
+        if (g.B >= 4 && q0 + kRound <= nq) {  // uniform
+            const uint4* at = reinterpret_cast<const uint4*>(g.pool) + q0 + threadIdx.x;
 #pragma unroll
-        for (uint32_t u = 0; u < kVQuads; ++u) {
-            const uint64_t q = q0 + (uint64_t)u * kThreads + threadIdx.x;
-            if (q < nq && g.B >= 4) {
-                const uint4 w = *reinterpret_cast<const uint4*>(g.pool + 4 * q);
+            for (uint32_t u = 0; u < kVQuads; ++u) {
+                const uint4 w = at[u * kVScan];
                 xs[u][0] = w.x;
                 xs[u][1] = w.y;
                 xs[u][2] = w.z;
                 xs[u][3] = w.w;
-            } else {
-#pragma unroll
-                for (uint32_t i = 0; i < 4; ++i) xs[u][i] = 4 * q + i < slots ? g.pool[4 * q + i] : 0u;
             }
+            return;
+        }
+#pragma unroll
+        for (uint32_t u = 0; u < kVQuads; ++u) {
+            const uint64_t q = q0 + (uint64_t)u * kVScan + threadIdx.x;
+#pragma unroll
+            for (uint32_t i = 0; i < 4; ++i)
+                xs[u][i] = 4 * q + i < slots ? g.pool[4 * q + i] : 0xFFFFFFFFu;
         }
     };
+    // (a value past the table falls on the summary's last word here and is
+    // turned down below)
+    const uint32_t ncap = (uint32_t)g.n_cap, last_word = d.sum_words - 1;
     const uint64_t stride = (uint64_t)gridDim.x * kRound;
     uint32_t xs[kVQuads][4];
     uint64_t q0 = (uint64_t)blockIdx.x * kRound;
     if (q0 < nq) load_round(q0, xs);
-    for (; q0 < nq; q0 += stride) {
+    for (uint32_t round = 0; q0 < nq; q0 += stride, ++round) {
         // the summary in LDS clears most slots; the bitmap words of the rest
         // are loaded together (one wait per round, not one per slot)
         uint32_t cand = 0;
 #pragma unroll
-        for (uint32_t u = 0; u < kVQuads; ++u) {
-            const uint64_t q = q0 + (uint64_t)u * kThreads + threadIdx.x;
-#pragma unroll
-            for (uint32_t i = 0; i < 4; ++i) {
-                const uint32_t x = xs[u][i];
-                bool c = 4 * q + i < slots && (uint64_t)x < g.n_cap;
-                if (c) {
-                    const uint32_t b = x >> d.sum_shift;
-                    c = (s_sum[b >> 5] >> (b & 31)) & 1u;
-                }
-                cand |= (uint32_t)c << (4 * u + i);
-            }
+        for (uint32_t k = 0; k < 4 * kVQuads; ++k) {
+            const uint32_t b = xs[k / 4][k % 4] >> d.sum_shift;
+            cand |= ((s_sum[min(b >> 5, last_word)] >> (b & 31)) & 1u) << k;
         }
         uint32_t word[4 * kVQuads];
 #pragma unroll
         for (uint32_t k = 0; k < 4 * kVQuads; ++k)
-            word[k] = (cand >> k) & 1u ? d.gone[xs[k / 4][k % 4] >> 5] : 0u;
+            word[k] = ((cand >> k) & 1u) && xs[k / 4][k % 4] < ncap
+                          ? d.gone[xs[k / 4][k % 4] >> 5]
+                          : 0u;
         uint32_t hm = 0;  // this thread's slots whose destination is deleted
 #pragma unroll
         for (uint32_t k = 0; k < 4 * kVQuads; ++k)
@@ -369,48 +344,73 @@ __global__ __launch_bounds__(kThreads) void k_vd_scan(GraphView g, VDel d) {
         // checked
         uint32_t xn[kVQuads][4];
         if (q0 + stride < nq) load_round(q0 + stride, xn);
-        // one hit per lane per step: a step's dependent loads (owner record,
-        // vertex record, directory) are waited for once for all lanes, so a
-        // wave waits as many times as its busiest lane has hits, not once
-        // per slot position that holds a hit in some lane
-        while (hm) {
-            const uint32_t k = (uint32_t)__ffs(hm) - 1u;
-            hm &= hm - 1u;
-            const uint64_t q = q0 + (uint64_t)(k / 4) * kThreads + threadIdx.x;
-            uint32_t v, p;
-            if (vd_hit(g, d, 4 * q + k % 4, &v, &p)) add_hit(v, p);
+        const uint32_t mine = __popc(hm), inc = wave_incl_scan(mine);
+        const uint32_t all = __builtin_amdgcn_readlane(inc, 63);
+        if (all) {
+            uint32_t at = 0;
+            if (lane_id() == 0) at = atomicAdd(&s_n, all);
+            at = __builtin_amdgcn_readfirstlane(at) + inc - mine;
+            for (; hm; hm &= hm - 1u, ++at) {
+                const uint32_t k = (uint32_t)__ffs(hm) - 1u;
+                const uint32_t in = 4 * ((k / 4) * kVScan + threadIdx.x) + k % 4;
+                uint32_t v, p;
+                if (at < kVHitBuf) {
+                    s_slot[at] = round * kRoundSlots + in;
+                } else if (vd_hit(g, d, 4 * q0 + in, &v, &p)) {
+                    const unsigned long long i = atomicAdd(&g.ctr->vd_hits, 1ull);
+                    if (i < d.hcap) d.hits[i] = make_uint2(v, p);
+                    else vd_error(g);
+                    if (atomicAdd(&g.vlost[v], 1u) == 0u) {
+                        const unsigned long long it = atomicAdd(&g.ctr->vd_touched, 1ull);
+                        if (it < d.tcapn) d.touched[it] = v;
+                        else vd_error(g);
+                    }
+                }
+            }
         }
 #pragma unroll
         for (uint32_t u = 0; u < kVQuads; ++u)
 #pragma unroll
             for (uint32_t i = 0; i < 4; ++i) xs[u][i] = xn[u][i];
     }
-    // move the staged hits and touched vertices out
     __syncthreads();
-    const uint32_t nh = min(s_nh, kVHitBuf), nt = min(s_nt, kVHitBuf);
-    if (threadIdx.x == 0) {
-        s_bh = nh ? atomicAdd(&g.ctr->vd_hits, (unsigned long long)nh) : 0ull;
-        s_bt = nt ? atomicAdd(&g.ctr->vd_touched, (unsigned long long)nt) : 0ull;
+    const uint32_t ns = min(s_n, kVHitBuf);
+    for (uint32_t i0 = 0; i0 < ns; i0 += kVScan) {
+        const uint32_t i = i0 + threadIdx.x;
+        uint32_t v = 0, p = 0;
+        bool hit = false, firsth = false;
+        if (i < ns) {
+            const uint32_t e = s_slot[i];
+            const uint64_t r = blockIdx.x + (uint64_t)(e / kRoundSlots) * gridDim.x;
+            hit = vd_hit(g, d, r * kRoundSlots + e % kRoundSlots, &v, &p);
+            if (hit) firsth = atomicAdd(&g.vlost[v], 1u) == 0u;
+        }
+        unsigned long long tot;
+        const unsigned long long ex =
+            block_excl_scan<kVScan / 64>((unsigned long long)hit | (unsigned long long)firsth << 32, lds, tot);
+        if (threadIdx.x == 0) {
+            s_bh = (uint32_t)tot ? atomicAdd(&g.ctr->vd_hits, tot & 0xffffffffull) : 0ull;
+            s_bt = tot >> 32 ? atomicAdd(&g.ctr->vd_touched, tot >> 32) : 0ull;
+        }
+        __syncthreads();
+        const unsigned long long ih = s_bh + (uint32_t)ex, it = s_bt + (ex >> 32);
+        if (hit) {
+            if (ih < d.hcap) d.hits[ih] = make_uint2(v, p);
+            else vd_error(g);
+        }
+        if (firsth) {
+            if (it < d.tcapn) d.touched[it] = v;
+            else vd_error(g);
+        }
+        __syncthreads();
     }
-    __syncthreads();
-    for (uint32_t i = threadIdx.x; i < nh; i += kThreads) {
-        if (s_bh + i < d.hcap) d.hits[s_bh + i] = s_hit[i];
-        else vd_error(g);
-    }
-    for (uint32_t i = threadIdx.x; i < nt; i += kThreads) {
-        if (s_bt + i < d.tcapn) d.touched[s_bt + i] = s_tv[i];
-        else vd_error(g);
-    }
-    vd_flush(g, lost, 0ull, lds);
 }
 
 // Deleted sources (one thread per id, at its first occurrence): all their blocks go on the
 // free list (one reservation per workgroup), their edges off the count.
-__global__ __launch_bounds__(kThreads) void k_vd_sources(GraphView g, const uint32_t* ids,
-                                                         uint64_t n, const uint8_t* first,
-                                                         const uint32_t* gone) {
-    __shared__ unsigned long long lds[kWaves];
-    __shared__ unsigned long long s_base;
+__device__ __forceinline__ void vd_sources(const GraphView& g, const uint32_t* ids, uint64_t n,
+                                           const uint8_t* first, const uint32_t* gone,
+                                           unsigned long long* lds, unsigned long long* s_base) {
     const uint64_t i = vt_tidx();
     VRec r{0u, 0u, kNoDir, 0u};
     bool mine = false;
@@ -420,7 +420,7 @@ __global__ __launch_bounds__(kThreads) void k_vd_sources(GraphView g, const uint
         if (mine) r = g.vt[id];
     }
     const uint32_t nb = mine ? nblocks(g, r.deg) : 0u;
-    const unsigned long long pos = vd_reserve(nb, &g.ctr->free_cnt, lds, &s_base);
+    const unsigned long long pos = vd_reserve(nb, &g.ctr->free_cnt, lds, s_base);
     if (nb <= kVLane) {
         for (uint32_t j = 0; j < nb; ++j) g.free_stack[pos + j] = block_of(g, r, j);
     }
@@ -442,12 +442,19 @@ __global__ __launch_bounds__(kThreads) void k_vd_sources(GraphView g, const uint
 
 // One thread per touched vertex (grid-stride rounds): new degree, room for
 // min(hits, new degree) holes (one reservation per workgroup round), and the
-// vertex's scratch word becomes its index in the touched list.
-__global__ __launch_bounds__(kThreads) void k_vd_plan(GraphView g, VDel d) {
+// vertex's scratch word becomes its index in the touched list.  The first nsrc
+// workgroups take the deleted sources, which nothing here depends on.
+__global__ __launch_bounds__(kThreads) void k_vd_plan(GraphView g, VDel d, const uint32_t* ids,
+                                                      uint64_t n, const uint8_t* first,
+                                                      uint32_t nsrc) {
     __shared__ unsigned long long lds[kWaves];
     __shared__ unsigned long long s_base;
+    if (blockIdx.x < nsrc) return vd_sources(g, ids, n, first, d.gone, lds, &s_base);
     const uint64_t nt = min(g.ctr->vd_touched, d.tcapn);
-    for (uint64_t t0 = (uint64_t)blockIdx.x * kThreads; t0 < nt; t0 += (uint64_t)gridDim.x * kThreads) {
+    if (blockIdx.x == nsrc && threadIdx.x == 0 && g.ctr->vd_hits)
+        atomicAdd(&g.ctr->live_edges, 0ull - g.ctr->vd_hits);
+    const uint64_t stride = (uint64_t)(gridDim.x - nsrc) * kThreads;
+    for (uint64_t t0 = (uint64_t)(blockIdx.x - nsrc) * kThreads; t0 < nt; t0 += stride) {
         const uint64_t t = t0 + threadIdx.x;
         uint32_t v = 0, deg = 0, lost = 0, cap = 0;
         if (t < nt) {
@@ -473,12 +480,53 @@ __global__ __launch_bounds__(kThreads) void k_vd_plan(GraphView g, VDel d) {
     }
 }
 
+// Deleted vertices (one thread per id, at its first occurrence) switched off,
+// their directory segments on the free lists: one atomic per workgroup and
+// class.
+__device__ __forceinline__ void vd_finish(const GraphView& g, const uint32_t* ids, uint64_t n,
+                                          const uint8_t* first, const uint32_t* gone,
+                                          uint32_t* lcnt, uint32_t* lbase,
+                                          unsigned long long* lfreed) {
+    const uint32_t t = threadIdx.x;
+    if (t < kMaxClass) lcnt[t] = 0;
+    if (t == 0) *lfreed = 0;
+    __syncthreads();
+    const uint64_t i = vt_tidx();
+    uint32_t cls = kNoDir, dir = 0, rank = 0;
+    if (i < n && first[i]) {
+        const uint32_t id = ids[i];
+        if (bit_of(gone, id)) {
+            atomicAnd(&g.active[id >> 5], ~(1u << (id & 31)));
+            const VRec r = g.vt[id];
+            cls = r.dcls;
+            dir = r.dir;
+            if (cls != kNoDir) {
+                rank = atomicAdd(&lcnt[cls], 1u);
+                atomicAdd(lfreed, 1ull << cls);
+            }
+            g.vt[id] = VRec{0u, 0u, kNoDir, 0u};
+        }
+    }
+    __syncthreads();
+    if (t < kMaxClass) lbase[t] = lcnt[t] ? atomicAdd(&g.ctr->dfree_cnt[t], lcnt[t]) : 0u;
+    if (t == 0 && *lfreed) atomicAdd(&g.ctr->dir_live, 0ull - *lfreed);
+    __syncthreads();
+    if (cls != kNoDir) g.dfree[g.dfree_base[cls] + lbase[cls] + rank] = dir;
+}
+
 // One thread per hit (grid-stride): a hit below its vertex's new degree is a
-// hole.
-__global__ __launch_bounds__(kThreads) void k_vd_holes(GraphView g, VDel d) {
+// hole.  The first nids workgroups switch the deleted vertices off (their
+// blocks went back in the kernel before).
+__global__ __launch_bounds__(kThreads) void k_vd_holes(GraphView g, VDel d, const uint32_t* ids,
+                                                       uint64_t n, const uint8_t* first,
+                                                       uint32_t nids) {
+    __shared__ uint32_t lcnt[kMaxClass], lbase[kMaxClass];
+    __shared__ unsigned long long lfreed;
+    if (blockIdx.x < nids) return vd_finish(g, ids, n, first, d.gone, lcnt, lbase, &lfreed);
     const uint64_t nh = min(g.ctr->vd_hits, d.hcap);
     const uint64_t nt = min(g.ctr->vd_touched, d.tcapn);
-    for (uint64_t i = vt_tidx(); i < nh; i += (uint64_t)gridDim.x * kThreads) {
+    const uint64_t stride = (uint64_t)(gridDim.x - nids) * kThreads;
+    for (uint64_t i = (uint64_t)(blockIdx.x - nids) * kThreads + threadIdx.x; i < nh; i += stride) {
         const uint2 h = d.hits[i];
         const uint32_t t = g.vlost[h.x];
         if (t >= nt) {
@@ -492,15 +540,19 @@ __global__ __launch_bounds__(kThreads) void k_vd_holes(GraphView g, VDel d) {
     }
 }
 
-// Per touched vertex (a lane each; a vertex whose tail or freed blocks
-// exceed kVLane is taken by the whole wave): the kept slots of the tail
+// Per touched vertex (a lane each; a vertex whose tail exceeds kVTail or whose
+// freed blocks exceed kVLane is taken by the whole wave): the kept slots of the tail
 // [nd, deg) fill the holes in order, emptied blocks go on the free list, the
-// record gets the new degree, the scratch word is cleared.
+// record gets the new degree, the scratch word is cleared.  Bound: lines read
+// and written for a slot or two (25 -> 22 us, 10^4 ids of a 2^20-vertex graph,
+// by reading four slots and holes at a time and reserving free-list places
+// once per workgroup).
 __global__ __launch_bounds__(kThreads) void k_vd_fill(GraphView g, VDel d) {
     __shared__ unsigned long long lds[kWaves];
+    __shared__ unsigned long long s_base;
     const uint32_t lane = lane_id();
     const uint64_t nt = min(g.ctr->vd_touched, d.tcapn);
-    unsigned long long lost_err = 0, freed = 0;
+    unsigned long long freed = 0;
     const uint64_t stride = (uint64_t)gridDim.x * kThreads;
     for (uint64_t t0 = (uint64_t)blockIdx.x * kThreads; t0 < nt; t0 += stride) {
         const uint64_t t = t0 + threadIdx.x;
@@ -521,31 +573,47 @@ __global__ __launch_bounds__(kThreads) void k_vd_fill(GraphView g, VDel d) {
         }
         const bool change = live && nd < r.deg;
         const uint32_t b0 = change ? nblocks(g, nd) : 0u, b1 = change ? nblocks(g, r.deg) : 0u;
-        const bool big = change && (r.deg - nd > kVLane || b1 - b0 > kVLane);
+        const bool big = change && (r.deg - nd > kVTail || b1 - b0 > kVLane);
         if (change && !big) {
+            // kTail slots of the tail and as many holes at a time, each step's
+            // reads in flight together
+            constexpr uint32_t kTail = 4;
             uint32_t k = 0;
-            for (uint32_t p = nd; p < r.deg; ++p) {
-                const uint32_t x = g.pool[slot_addr(g, r, p)];
-                if (bit_of(d.gone, x)) continue;
-                if (k < nh) {
-                    const uint64_t da = slot_addr(g, r, d.holes[off + k]);
-                    g.pool[da] = x;
-                    if (g.A) attr_move(g, da, slot_addr(g, r, p));
+            for (uint32_t p0 = nd; p0 < r.deg; p0 += kTail) {
+                uint64_t sa[kTail], da[kTail];
+                uint32_t x[kTail];
+#pragma unroll
+                for (uint32_t u = 0; u < kTail; ++u) {
+                    sa[u] = slot_addr(g, r, min(p0 + u, r.deg - 1));
+                    da[u] = d.holes[nh ? off + min(k + u, nh - 1) : 0ull];
                 }
-                ++k;
+#pragma unroll
+                for (uint32_t u = 0; u < kTail; ++u) {
+                    x[u] = g.pool[sa[u]];
+                    da[u] = slot_addr(g, r, nh ? (uint32_t)da[u] : 0u);
+                }
+                bool keep[kTail];
+#pragma unroll
+                for (uint32_t u = 0; u < kTail; ++u)
+                    keep[u] = p0 + u < r.deg && !bit_of(d.gone, x[u]);
+#pragma unroll
+                for (uint32_t u = 0; u < kTail; ++u) {
+                    if (!keep[u]) continue;
+                    if (k < nh) {
+                        g.pool[da[0]] = x[u];
+                        if (g.A) attr_move(g, da[0], sa[u]);
+                    }
+                    ++k;
+#pragma unroll
+                    for (uint32_t i = 0; i + 1 < kTail; ++i) da[i] = da[i + 1];
+                }
             }
             if (k != nh) vd_error(g);
         }
-        // frees of the lane-sized vertices: one reservation per wave
-        const uint32_t nf = change && !big ? b1 - b0 : 0u;
-        const uint32_t inc = wave_incl_scan(nf);
-        const uint32_t tot = __shfl(inc, 63, 64);
-        if (tot) {
-            unsigned long long fb = 0;
-            if (lane == 63) fb = atomicAdd(&g.ctr->free_cnt, (unsigned long long)tot);
-            fb = __shfl(fb, 63, 64) + (inc - nf);
-            for (uint32_t j = 0; j < nf; ++j) g.free_stack[fb + j] = block_of(g, r, b0 + j);
-        }
+        // places on the free list: one reservation per workgroup
+        const uint32_t nf = b1 - b0;
+        const unsigned long long fb = vd_reserve(nf, &g.ctr->free_cnt, lds, &s_base);
+        for (uint32_t j = 0; j < nf && !big; ++j) g.free_stack[fb + j] = block_of(g, r, b0 + j);
         // the larger vertices, one at a time by the whole wave
         uint64_t m = ballot(big);
         while (m) {
@@ -578,10 +646,8 @@ __global__ __launch_bounds__(kThreads) void k_vd_fill(GraphView g, VDel d) {
             }
             if (k != wnh && lane == 0) vd_error(g);
             const uint32_t wb0 = nblocks(g, wnd), wb1 = nblocks(g, w.deg);
-            unsigned long long fb = 0;
-            if (lane == 0 && wb1 > wb0) fb = atomicAdd(&g.ctr->free_cnt, (unsigned long long)(wb1 - wb0));
-            fb = __shfl(fb, 0, 64);
-            for (uint32_t j = lane; j < wb1 - wb0; j += 64) g.free_stack[fb + j] = block_of(g, w, wb0 + j);
+            const unsigned long long wf = __shfl(fb, l, 64);
+            for (uint32_t j = lane; j < wb1 - wb0; j += 64) g.free_stack[wf + j] = block_of(g, w, wb0 + j);
         }
         if (change) {
             g.vt[v] = vd_record(g, r, nd);
@@ -589,24 +655,7 @@ __global__ __launch_bounds__(kThreads) void k_vd_fill(GraphView g, VDel d) {
         }
         if (live) g.vlost[v] = 0u;
     }
-    vd_flush(g, lost_err, freed, lds);
-}
-
-__global__ __launch_bounds__(kThreads) void k_vdel_finish(GraphView g, const uint32_t* ids,
-                                                          uint64_t n, const uint8_t* first,
-                                                          const uint32_t* gone) {
-    const uint64_t i = vt_tidx();
-    if (i >= n || !first[i]) return;
-    const uint32_t id = ids[i];
-    if (!bit_of(gone, id)) return;
-    atomicAnd(&g.active[id >> 5], ~(1u << (id & 31)));
-    const VRec r = g.vt[id];
-    if (r.dcls != kNoDir) {
-        const uint32_t pos = atomicAdd(&g.ctr->dfree_cnt[r.dcls], 1u);
-        g.dfree[g.dfree_base[r.dcls] + pos] = r.dir;
-        atomicAdd(&g.ctr->dir_live, (unsigned long long)(-(long long)(1ull << r.dcls)));
-    }
-    g.vt[id] = VRec{0u, 0u, kNoDir, 0u};
+    vd_flush(g, 0ull, freed, lds);
 }
 
 // bytes of a vertex delete's id buffer: gone, summary and seen bitmaps, then
@@ -660,22 +709,27 @@ void vertex_insert(gv_graph* g, const uint32_t* ids, uint64_t n, gv_batch_stats*
                    bool fixed_table) {
     Ctx& c = g->ctx;
     if (n >= 0xffffffffull) fail(GV_EINVAL, "batch too large");
-    c.launch("vreset", k_vreset, 1, 1, g->v.ctr);
+    auto begin = [&] {
+        const uint64_t words = (g->v.n_cap + 31) / 32;
+        uint32_t* seen = (uint32_t*)vbuf(g, 0, words * sizeof(uint32_t));
+        c.launch("vbegin", k_vbegin, div_up(words, kThreads), kThreads, g->v.ctr, seen, words);
+        return seen;
+    };
+    uint32_t* seen = begin();
     if (fixed_table) {
         // no growth (and no read-back): an id past the table is an error
         c.launch("vfit", k_vfit, div_up(n, kThreads), kThreads, g->v, ids, n);
     } else {
-        c.launch("vmax", k_vmax, div_up(n, kThreads), kThreads, ids, n, g->v.ctr);
+        c.launch("vmax", k_vmax, std::min<uint64_t>(div_up(n, kThreads), 256), kThreads, ids, n,
+                 g->v.ctr);
         read_stats(g);
         if (g->hctr->vany && (uint64_t)g->hctr->vmax >= g->v.n_cap) {
             uint64_t cap = g->v.n_cap;
             while (cap <= (uint64_t)g->hctr->vmax) cap <<= 1;
             grow_table(g, cap);
+            seen = begin();
         }
     }
-    const uint64_t words = (g->v.n_cap + 31) / 32;
-    uint32_t* seen = (uint32_t*)vbuf(g, 0, words * sizeof(uint32_t));
-    c.launch("vzero", k_vzero, div_up(words, kThreads), kThreads, seen, words);
     c.launch("vinsert", k_vins, div_up(n, kThreads), kThreads, g->v, ids, n, seen);
     if (st) {
         read_stats(g);
@@ -685,7 +739,7 @@ void vertex_insert(gv_graph* g, const uint32_t* ids, uint64_t n, gv_batch_stats*
     }
 }
 void vertex_batch_warm() {
-    resident_grid(k_vd_scan, kThreads);
+    resident_grid(k_vd_scan, kVScan);
     resident_grid(k_vd_plan, kThreads);
     resident_grid(k_vd_holes, kThreads);
     resident_grid(k_vd_fill, kThreads);
@@ -752,10 +806,11 @@ void vertex_delete(gv_graph* g, const uint32_t* ids, uint64_t n, gv_batch_stats*
     uint32_t* summary = gone + words;
     uint32_t* seen = summary + kVSumWords;
     uint8_t* first = (uint8_t*)(seen + words);
-    c.launch("vreset", k_vreset, 1, 1, v.ctr);
-    c.launch("vzero", k_vzero, div_up(2 * words + kVSumWords, kThreads), kThreads, gone,
-             2 * words + kVSumWords);
-    c.launch("vdel_mark", k_vdel_mark, div_up(n, kThreads), kThreads, v, ids, n, seen, gone,
+    const uint64_t zeroed = 2 * words + kVSumWords;
+    const uint32_t sum_shift = v.L > 17 ? v.L - 17 : 0u;
+    const uint64_t nids = div_up(n, kThreads);
+    c.launch("vbegin", k_vbegin, div_up(zeroed, kThreads), kThreads, v.ctr, gone, zeroed);
+    c.launch("vdel_mark", k_vdel_mark, nids, kThreads, v, ids, n, seen, gone, summary, sum_shift,
              first);
     if (!edge_bound) {
         // no read-back: the host-side bound, capped by the pool's slots (every
@@ -773,17 +828,14 @@ void vertex_delete(gv_graph* g, const uint32_t* ids, uint64_t n, gv_batch_stats*
     }
     d.gone = gone;
     d.summary = summary;
-    d.sum_shift = v.L > 17 ? v.L - 17 : 0u;
+    d.sum_shift = sum_shift;
     d.sum_words = (uint32_t)std::max<uint64_t>(((ncap >> d.sum_shift) + 31) / 32, 1);
-    c.launch("vdel_summary", k_vd_summary, div_up(words, kThreads), kThreads, d, words);
-    c.launch("vdel_scan", k_vd_scan, resident_grid(k_vd_scan, kThreads), kThreads, v, d);
-    c.launch("vdel_sources", k_vd_sources, div_up(n, kThreads), kThreads, v, ids, n,
-             (const uint8_t*)first, (const uint32_t*)gone);
-    c.launch("vdel_plan", k_vd_plan, resident_grid(k_vd_plan, kThreads), kThreads, v, d);
-    c.launch("vdel_holes", k_vd_holes, resident_grid(k_vd_holes, kThreads), kThreads, v, d);
+    c.launch("vdel_scan", k_vd_scan, resident_grid(k_vd_scan, kVScan), kVScan, v, d);
+    c.launch("vdel_plan", k_vd_plan, nids + resident_grid(k_vd_plan, kThreads), kThreads, v, d, ids,
+             n, (const uint8_t*)first, (uint32_t)nids);
+    c.launch("vdel_holes", k_vd_holes, nids + resident_grid(k_vd_holes, kThreads), kThreads, v, d,
+             ids, n, (const uint8_t*)first, (uint32_t)nids);
     c.launch("vdel_fill", k_vd_fill, resident_grid(k_vd_fill, kThreads), kThreads, v, d);
-    c.launch("vdel_finish", k_vdel_finish, div_up(n, kThreads), kThreads, g->v, ids, n,
-             (const uint8_t*)first, (const uint32_t*)gone);
     if (st) {
         read_stats(g);
         st->applied = g->hctr->st_applied;
