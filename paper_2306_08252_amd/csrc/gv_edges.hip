@@ -1867,6 +1867,8 @@ void edge_batch_warm() {
     resident_grid(k_os_pass<uint64_t, false, kPsRounds>, kPsThreads);
     resident_grid(k_os_pass<uint64_t, true, kPsRounds>, kPsThreads);
     resident_grid(k_os_pass<uint64_t, false, kPsRoundsLong>, kPsThreads);
+    resident_grid(k_os_pass<uint64_t, false, kPsRoundsShort>, kPsThreads);
+    resident_grid(k_os_pass<uint64_t, true, kPsRoundsShort>, kPsThreads);
 }
 
 // bytes of g->scratch edge_batch carves for n pairs (edge_batch_sorted carves

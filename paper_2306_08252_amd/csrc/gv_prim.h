@@ -478,14 +478,18 @@ inline uint64_t os_hist_groups(uint64_t n) { return std::min<uint64_t>(os_tiles(
 // the device is full many times over: 10^6 keys 14.7 us a pass against 18.4,
 // 10^7 keys 66.1 against 58.5, 1.7 * 10^7 keys 104 against 89.
 constexpr int kPsThreads = 512, kPsWaves = kPsThreads / 64;
-constexpr int kPsRounds = 8, kPsRoundsLong = 16;
-constexpr uint64_t kPsLong = 1ull << 22;
+constexpr int kPsRounds = 8, kPsRoundsLong = 16, kPsRoundsShort = 4;
 constexpr uint64_t kOsGroup = 16;
-// (with values the longer tile's LDS would leave one workgroup per unit)
-inline bool ps_long(uint64_t n, bool vals) { return n > kPsLong && !vals; }
+constexpr uint64_t kPsLong = 1ull << 22, kPsShort = 1ull << 18;
+// (Below a tile per compute unit, shorter tiles give more of them and a
+// shorter chain each: 10^5 keys 8.4 us a pass against 7.9, with values 9.3
+// against 7.8, 10^6 keys 17.0 against 21.0; two keys per thread 8.5 and 8.2.
+// With values the longest tile's LDS would leave one workgroup per unit.)
+inline int ps_rounds(uint64_t n, bool vals) {
+    return n <= kPsShort ? kPsRoundsShort : n > kPsLong && !vals ? kPsRoundsLong : kPsRounds;
+}
 inline uint64_t ps_tiles(uint64_t n, bool vals) {
-    return div_up(std::max<uint64_t>(n, 1),
-                  (uint64_t)kPsThreads * (ps_long(n, vals) ? kPsRoundsLong : kPsRounds));
+    return div_up(std::max<uint64_t>(n, 1), (uint64_t)kPsThreads * ps_rounds(n, vals));
 }
 // status words per digit and pass: tiles, groups, super groups
 inline uint64_t ps_status(uint64_t n, bool vals) {
@@ -1056,8 +1060,10 @@ bool onesweep_passes(Ctx& c, K* k0, K* k1, uint32_t* v0, uint32_t* v1, const uin
     uint32_t* counters = state;           // 64 words
     uint32_t* hist = state + os_zero_words(n_max, bits, HasVal);  // passes * 256 counters
     auto kernel = k_os_pass<K, HasVal, kPsRounds>;
+    const int rounds = ps_rounds(n_max, HasVal);
+    if (rounds == kPsRoundsShort) kernel = k_os_pass<K, HasVal, kPsRoundsShort>;
     if constexpr (!HasVal) {
-        if (ps_long(n_max, false)) kernel = k_os_pass<K, false, kPsRoundsLong>;
+        if (rounds == kPsRoundsLong) kernel = k_os_pass<K, false, kPsRoundsLong>;
     }
     const int block_tiles = !concurrent && nt <= resident_grid(kernel, kPsThreads) ? 1 : 0;
     bool flip = false;
