@@ -429,43 +429,34 @@ __device__ __forceinline__ uint32_t tile_ranks(const bool (&f)[R], uint32_t (&ra
 }
 
 // The same for counts: exclusive sums in position order, and their total.
-template <int T, uint32_t R>
-__device__ __forceinline__ uint32_t tile_sums(const uint32_t (&x)[R], uint32_t (&ex)[R],
-                                              uint32_t* cnt) {
+template <int T, typename V, uint32_t R>
+__device__ __forceinline__ V tile_sums(const V (&x)[R], V (&ex)[R], V* cnt) {
     constexpr uint32_t W = T / 64, N = R * W;
     static_assert(N <= 64, "one wave scans the sums");
     const uint32_t w = threadIdx.x >> 6;
 #pragma unroll
     for (uint32_t j = 0; j < R; ++j) {
-        const uint32_t inc = wave_incl_scan(x[j]);
+        const V inc = wave_incl_scan(x[j]);
         if (lane_id() == 63) cnt[j * W + w] = inc;
         ex[j] = inc - x[j];
     }
     __syncthreads();
-    const uint32_t c = lane_id() < N ? cnt[lane_id()] : 0u;
-    const uint32_t inc = wave_incl_scan(c);
+    if constexpr (R == 1) {  // few: every thread adds them up
+        V before = 0, all = 0;
+#pragma unroll
+        for (uint32_t i = 0; i < W; ++i) {
+            const V v = cnt[i];
+            before += i < w ? v : V(0);
+            all += v;
+        }
+        ex[0] += before;
+        return all;
+    }
+    const V c = lane_id() < N ? cnt[lane_id()] : V(0);
+    const V inc = wave_incl_scan(c);
 #pragma unroll
     for (uint32_t j = 0; j < R; ++j) ex[j] += __shfl(inc - c, (int)(j * W + w), 64);
     return __shfl(inc, 63, 64);
-}
-
-// exclusive scan across T threads and their sum; lds holds T / 64 words
-template <int T, typename V>
-__device__ __forceinline__ V tile_scan(V x, V* lds, V& total) {
-    const V inc = wave_incl_scan(x);
-    const int w = threadIdx.x >> 6;
-    if (lane_id() == 63) lds[w] = inc;
-    __syncthreads();
-    V off = 0, tot = 0;
-#pragma unroll
-    for (int i = 0; i < T / 64; ++i) {
-        const V v = lds[i];
-        off += i < w ? v : V(0);
-        tot += v;
-    }
-    __syncthreads();
-    total = tot;
-    return off + inc - x;
 }
 
 // Segments, sources and work items of a tile of the sorted keys.  Also writes
@@ -1013,11 +1004,14 @@ __device__ __forceinline__ uint32_t wave_count(const uint8_t* mark, uint64_t a, 
 //
 // Bound: latency (marks, then source records: both streams).  It replaces a
 // scan over the pairs, a kernel over the sources and a scan over them
-// (insert: 19 -> 7.8 us at 10^4 pairs, 46 -> 22 at 10^6), or a scan over the
+// (insert: 19 -> 8.0 us at 10^4 pairs, 46 -> 25 at 10^6), or a scan over the
 // sources that read their records anew and two hit counters kept by the probe
 // (delete: 8.3 -> 7.1 us, with the counters and a last kernel of 3.4 us gone).
+// All of a thread's sources are read together and placed by one scan (deletes
+// of 10^6 pairs 25 -> 18 us, of 10^7 93 -> 75, inserts 26 -> 25 and 76 -> 80;
+// a line of its own for each class's requests 30 and 88).
 template <bool INS, int T, uint32_t R>
-__global__ __launch_bounds__(T) void k_plan(GraphView g, uint64_t n, BatchCtr* bc, uint32_t tl,
+__global__ __launch_bounds__(T, 8) void k_plan(GraphView g, uint64_t n, BatchCtr* bc, uint32_t tl,
                                             const uint8_t* mark, Src* srcs, const uint2* tiles,
                                             uint2* carry, uint32_t* tbase, uint32_t* t_dreq,
                                             uint32_t* t_drank, uint32_t* list, uint32_t* list2,
@@ -1025,9 +1019,9 @@ __global__ __launch_bounds__(T) void k_plan(GraphView g, uint64_t n, BatchCtr* b
     constexpr uint32_t kTile = T * R;
     __shared__ uint32_t s_pre[kTile + 1];
     __shared__ uint32_t s_cnt[R * T / 64];
-    __shared__ unsigned long long s_scan[T / 64];
+    __shared__ unsigned long long s_scan[R * T / 64];
     __shared__ uint32_t lcnt[kMaxClass], lbase[kMaxClass];
-    __shared__ uint32_t s_tail[T / 64];
+    __shared__ uint32_t s_tail[T / 64], s_at2;
     __shared__ unsigned long long s_demand, s_done;
     const uint32_t t = threadIdx.x, w = t >> 6;
     const uint64_t p0 = (uint64_t)blockIdx.x << tl;
@@ -1092,71 +1086,77 @@ __global__ __launch_bounds__(T) void k_plan(GraphView g, uint64_t n, BatchCtr* b
                 }
             }
         }
-        // the sources: blocks (low) and listed sources (high) of the tile
-        unsigned long long run = 0;
-        uint32_t cls[R], lrank[R], lpos[R];
-        bool listed[R];
+        // The sources: blocks (bits 0-31), listed sources (from bit 32) and
+        // sources of list2 (from bit 48) of the tile.  All of a thread's
+        // sources at once: read, then one scan.
+        Src x[R];
+        uint32_t cls[R], lrank[R];
+        unsigned long long add[R], ex[R];
+#pragma unroll
+        for (uint32_t j = 0; j < R; ++j)
+            x[j] = j == 0 ? row0 : srcs[t0 + (nh ? min(j * T + t, nh - 1) : 0u)];
 #pragma unroll
         for (uint32_t j = 0; j < R; ++j) {
-            cls[j] = kNoDir;
-            listed[j] = false;
-            if (j * T >= nh) continue;  // uniform
             const uint32_t h = j * T + t;
+            cls[j] = kNoDir;
+            lrank[j] = 0;
+            add[j] = 0;
+            if (h >= nh) continue;
+            const uint32_t r = s_pre[(uint32_t)(min((uint64_t)x[j].hi, pe) - p0)] -
+                               s_pre[x[j].lo - (uint32_t)p0] + (h + 1 == nh ? tail : 0u);
+            x[j].r = r;
             uint32_t need = 0;
-            bool heavy = false;
-            if (h < nh) {
-                Src x = j == 0 ? row0 : srcs[t0 + h];
-                x.r = s_pre[(uint32_t)(min((uint64_t)x.hi, pe) - p0)] -
-                      s_pre[x.lo - (uint32_t)p0] + (h + 1 == nh ? tail : 0u);
-                if (INS) {
-                    const uint32_t nb0 = nblocks(g, x.deg), nb1 = nblocks(g, x.deg + x.r);
-                    const uint64_t cap0 = x.dcls == kNoDir ? 1ull : (1ull << x.dcls);
-                    if (nb1 > cap0) {
-                        cls[j] = ceil_log2(nb1);
-                        lrank[j] = atomicAdd(&lcnt[cls[j]], 1u);
-                    }
-                    need = nb1 - nb0;
-                    // the source gives back a directory segment
-                    listed[j] = cls[j] != kNoDir && x.dcls != kNoDir;
-                    // the commit kernel takes this decision from here: its
-                    // heavy sources' records change while other waves still
-                    // run the lane loop, so it must not be made again there
-                    heavy = (cls[j] != kNoDir && nb0 > kLaneCopy) || need > kLaneCopy;
-                    t_dreq[t0 + h] = cls[j] | (heavy ? kHeavy : 0u);
-                } else if (x.r) {
-                    need = nblocks(g, x.deg) - nblocks(g, x.deg - x.r);
-                    listed[j] = x.r <= kBigR && !lane_compactable(x.r, x.lo, x.hi);
-                    if (x.r > kBigR) list2[atomicAdd(&bc->n_big, 1u)] = t0 + h;
+            bool listed = false, second = false;
+            if (INS) {
+                const uint32_t nb0 = nblocks(g, x[j].deg), nb1 = nblocks(g, x[j].deg + r);
+                const uint64_t cap0 = x[j].dcls == kNoDir ? 1ull : (1ull << x[j].dcls);
+                if (nb1 > cap0) {
+                    cls[j] = ceil_log2(nb1);
+                    lrank[j] = atomicAdd(&lcnt[cls[j]], 1u);
                 }
-                lpos[j] = t0 + h;
-                srcs[t0 + h].r = x.r;
+                need = nb1 - nb0;
+                // the source gives back a directory segment
+                listed = cls[j] != kNoDir && x[j].dcls != kNoDir;
+                // the commit kernel takes this decision from here: its heavy
+                // sources' records change while other waves still run the
+                // lane loop, so it must not be made again there
+                second = (cls[j] != kNoDir && nb0 > kLaneCopy) || need > kLaneCopy;
+                t_dreq[t0 + h] = cls[j] | (second ? kHeavy : 0u);
+            } else if (r) {
+                need = nblocks(g, x[j].deg) - nblocks(g, x[j].deg - r);
+                listed = r <= kBigR && !lane_compactable(r, x[j].lo, x[j].hi);
+                second = r > kBigR;
             }
-            if (INS) wave_append(heavy, t0 + h, &bc->n_heavy, list2);
-            unsigned long long all;
-            const unsigned long long ex = tile_scan<T>(
-                (unsigned long long)need | ((unsigned long long)listed[j] << 32), s_scan, all);
-            if (h < nh) srcs[t0 + h].need = (uint32_t)(run + ex);
-            if (!INS || cls[j] == kNoDir) lrank[j] = 0;
-            // (the list place, until the tile's base is known)
-            rank[j] = (uint32_t)((run + ex) >> 32);
-            run += all;
+            add[j] = (unsigned long long)need | (unsigned long long)listed << 32 |
+                     (unsigned long long)second << 48;
         }
-        if (INS) {
-            if (t < kMaxClass) {
-                const uint32_t c = lcnt[t];
-                lbase[t] = c ? atomicAdd(&g.ctr->dreq[t], c) : 0u;
-            }
-        }
+        const unsigned long long run = tile_sums<T>(add, ex, s_scan);
+        const uint32_t n2 = (uint32_t)(run >> 48);
+        constexpr unsigned long long kLow48 = (1ull << 48) - 1;
         if (t == 0) {
-            s_demand = run ? atomicAdd(&bc->demand, run) : 0ull;
+            s_demand = run & kLow48 ? atomicAdd(&bc->demand, run & kLow48) : 0ull;
             tbase[blockIdx.x] = (uint32_t)s_demand;
         }
+        if (t == 64) s_at2 = n2 ? atomicAdd(INS ? &bc->n_heavy : &bc->n_big, n2) : 0u;
+        if (INS && t >= 128 && t < 128 + kMaxClass) {
+            const uint32_t c = lcnt[t - 128];
+            lbase[t - 128] = c ? atomicAdd(&g.ctr->dreq[t - 128], c) : 0u;
+        }
+#pragma unroll
+        for (uint32_t j = 0; j < R; ++j)
+            if (j * T + t < nh) {
+                Src* to = srcs + t0 + j * T + t;
+                to->r = x[j].r;
+                to->need = (uint32_t)ex[j];
+            }
         __syncthreads();
-        const uint32_t lb = (uint32_t)(s_demand >> 32);
+        const uint32_t lb = (uint32_t)(s_demand >> 32), lb2 = s_at2;
 #pragma unroll
         for (uint32_t j = 0; j < R; ++j) {
-            if (listed[j]) list[lb + rank[j]] = lpos[j];
-            if (INS && cls[j] != kNoDir) t_drank[lpos[j]] = lbase[cls[j]] + lrank[j];
+            const uint32_t at = t0 + j * T + t;
+            if (add[j] >> 32 & 1) list[lb + ((uint32_t)(ex[j] >> 32) & 0xFFFFu)] = at;
+            if (add[j] >> 48) list2[lb2 + (uint32_t)(ex[j] >> 48)] = at;
+            if (INS && cls[j] != kNoDir) t_drank[at] = lbase[cls[j]] + lrank[j];
         }
     }
     if (t == 0) s_done = atomicAdd(&bc->done, (1ull << 32) + changed) + (1ull << 32) + changed;
