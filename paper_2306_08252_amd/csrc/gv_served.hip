@@ -369,7 +369,8 @@ void mixed_bytes(const gv_graph* g, uint64_t n, size_t out[2]) {
     Carver m(nullptr);
     MixSort s;
     s.carve(m, n, bits);
-    out[0] = std::max(m.used, edge_batch_bytes(g, kInsert, n));
+    // (its deletes, then its inserts, take the same buffer)
+    out[0] = std::max({m.used, edge_batch_bytes(g, kDelete, n), edge_batch_bytes(g, kInsert, n)});
     Carver k(nullptr);
     MixKeep keep;
     keep.carve(k, n, false);
