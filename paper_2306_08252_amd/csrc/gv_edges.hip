@@ -1887,12 +1887,13 @@ size_t edge_batch_bytes(const gv_graph* g, EdgeMode mode, uint64_t n) {
 // list): clears the batch counters, sets the valid count and turns the
 // probe's multiset check off (there is no packing to compare with; the
 // segments kernel still checks the order).
-__global__ __launch_bounds__(kThreads) void k_sorted_prep(BatchCtr* bc,
-                                                          const unsigned long long* count) {
-    clear_batch(bc, threadIdx.x, kThreads);
+__global__ __launch_bounds__(kOsThreads) void k_sorted_prep(BatchCtr* bc,
+                                                            const unsigned long long* count) {
+    const unsigned long long n = *count;
+    clear_batch(bc, threadIdx.x, kOsThreads);
     __syncthreads();
     if (threadIdx.x == 0) {
-        bc->n_valid = *count;
+        bc->n_valid = n;
         bc->nohash = 1;
     }
 }
@@ -2025,7 +2026,7 @@ static void edge_run(gv_graph* g, EdgeMode mode, const uint32_t* src, const uint
     bool flip;
     const uint64_t* keys_in = nullptr;
     if (sorted) {
-        c.launch("pack", k_sorted_prep, 1, kThreads, bc, sorted_n);
+        c.launch("pack", k_sorted_prep, 1, kOsThreads, bc, sorted_n);
         keys_in = sorted;
         flip = false;
     } else if (n <= rank_max) {
