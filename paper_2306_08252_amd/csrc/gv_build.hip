@@ -609,7 +609,7 @@ __global__ __launch_bounds__(kThreads) void k_dump_rows(GraphView g,
             w.dir = __builtin_amdgcn_readlane(r.dir, l);
             w.dcls = __builtin_amdgcn_readlane(r.dcls, l);
             const uint64_t wu = q * 4 + ((uint32_t)l >> 4);
-            uint32_t* wo = out + __shfl((unsigned long long)off, l, 64);
+            uint32_t* wo = out + wave_read((unsigned long long)off, l);
             if (w.deg <= 64) h += dump_row<1>(g, wu, w, lane, wo);
             else if (w.deg <= 128) h += dump_row<2>(g, wu, w, lane, wo);
             else if (w.deg <= 256) h += dump_row<4>(g, wu, w, lane, wo);

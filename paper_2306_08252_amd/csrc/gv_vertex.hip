@@ -429,12 +429,12 @@ __device__ __forceinline__ void vd_sources(const GraphView& g, const uint32_t* i
         const int l = __ffsll((unsigned long long)m) - 1;
         m &= m - 1;
         VRec w;
-        w.deg = __shfl(r.deg, l, 64);
-        w.dir = __shfl(r.dir, l, 64);
-        w.dcls = __shfl(r.dcls, l, 64);
+        w.deg = wave_read(r.deg, l);
+        w.dir = wave_read(r.dir, l);
+        w.dcls = wave_read(r.dcls, l);
         w.aux = 0;
-        const uint32_t wn = __shfl(nb, l, 64);
-        const unsigned long long wp = __shfl(pos, l, 64);
+        const uint32_t wn = wave_read(nb, l);
+        const unsigned long long wp = wave_read(pos, l);
         for (uint32_t j = lane_id(); j < wn; j += 64) g.free_stack[wp + j] = block_of(g, w, j);
     }
     vd_flush(g, mine ? r.deg : 0u, nb, lds);
@@ -620,12 +620,12 @@ __global__ __launch_bounds__(kThreads) void k_vd_fill(GraphView g, VDel d) {
             const int l = __ffsll((unsigned long long)m) - 1;
             m &= m - 1;
             VRec w;
-            w.deg = __shfl(r.deg, l, 64);
-            w.dir = __shfl(r.dir, l, 64);
-            w.dcls = __shfl(r.dcls, l, 64);
+            w.deg = wave_read(r.deg, l);
+            w.dir = wave_read(r.dir, l);
+            w.dcls = wave_read(r.dcls, l);
             w.aux = 0;
-            const uint32_t wnd = __shfl(nd, l, 64), wnh = __shfl(nh, l, 64);
-            const unsigned long long woff = __shfl(off, l, 64);
+            const uint32_t wnd = wave_read(nd, l), wnh = wave_read(nh, l);
+            const unsigned long long woff = wave_read(off, l);
             uint32_t k = 0;
             for (uint32_t p0 = wnd; p0 < w.deg; p0 += 64) {
                 const uint32_t p = p0 + lane;
@@ -646,7 +646,7 @@ __global__ __launch_bounds__(kThreads) void k_vd_fill(GraphView g, VDel d) {
             }
             if (k != wnh && lane == 0) vd_error(g);
             const uint32_t wb0 = nblocks(g, wnd), wb1 = nblocks(g, w.deg);
-            const unsigned long long wf = __shfl(fb, l, 64);
+            const unsigned long long wf = wave_read(fb, l);
             for (uint32_t j = lane; j < wb1 - wb0; j += 64) g.free_stack[wf + j] = block_of(g, w, wb0 + j);
         }
         if (change) {
