@@ -113,26 +113,16 @@ __global__ __launch_bounds__(kOsThreads) void k_init_pack(GraphView g, const uin
     __syncthreads();
     const uint32_t copy = kOsHistCopies == 1 ? 0u : (t >> 6) & (kOsHistCopies - 1);
     bool bad = false;
-    const uint64_t ntiles = (m + kOsTile - 1) / kOsTile;
+    const uint64_t ntiles = (m + kHistTile - 1) / kHistTile;
     for (uint64_t tl = blockIdx.x; tl < ntiles; tl += gridDim.x) {
-        const uint64_t base = tl * kOsTile;
-        uint32_t su[kOsRounds], du[kOsRounds];
-#pragma unroll
-        for (int j = 0; j < kOsRounds; ++j) {
-            const uint64_t i = base + (uint64_t)j * kOsThreads + t;
-            su[j] = i < m ? src[i] : 0u;
-            du[j] = i < m ? dst[i] : 0u;
-        }
-#pragma unroll
-        for (int j = 0; j < kOsRounds; ++j) {
-            const uint64_t i = base + (uint64_t)j * kOsThreads + t;
-            if (i >= m) continue;
-            bad |= ((uint64_t)su[j] >= n) | ((uint64_t)du[j] >= n);
-            const uint64_t key = ((uint64_t)su[j] << g.L) | du[j];
-            keys[i] = key;
-            for (int p = 0; p < passes; ++p)
-                atomicAdd(&h[copy][p][(uint32_t)(key >> (p * kRadixBits)) & (kRadix - 1)], 1u);
-        }
+        const uint64_t i = tl * kHistTile + t;
+        if (i >= m) continue;
+        const uint32_t su = src[i], du = dst[i];
+        bad |= ((uint64_t)su >= n) | ((uint64_t)du >= n);
+        const uint64_t key = ((uint64_t)su << g.L) | du;
+        keys[i] = key;
+        for (int p = 0; p < passes; ++p)
+            atomicAdd(&h[copy][p][(uint32_t)(key >> (p * kRadixBits)) & (kRadix - 1)], 1u);
     }
     if (bad) g.ctr->vany = 1;
     __syncthreads();

@@ -285,30 +285,18 @@ __global__ __launch_bounds__(kOsThreads) void k_pack_hist(GraphView g, const uin
     const uint32_t copy = kOsHistCopies == 1 ? 0u : (t >> 6) & (kOsHistCopies - 1);
     uint32_t valid = 0;
     unsigned long long khash = 0;  // multiset hash of the valid keys (checked after the sort)
-    const uint64_t ntiles = (n + kOsTile - 1) / kOsTile;
+    const uint64_t ntiles = (n + kHistTile - 1) / kHistTile;
     for (uint64_t tl = blockIdx.x; tl < ntiles; tl += gridDim.x) {
-        const uint64_t base = tl * kOsTile;
-        uint32_t su[kOsRounds], du[kOsRounds];
-        bool ok[kOsRounds];
-#pragma unroll
-        for (int j = 0; j < kOsRounds; ++j) {
-            const uint64_t i = base + (uint64_t)j * kOsThreads + t;
-            su[j] = i < n ? src[i] : 0u;
-            du[j] = i < n ? dst[i] : 0u;
-        }
-#pragma unroll
-        for (int j = 0; j < kOsRounds; ++j) ok[j] = active_bit(g, su[j]) & active_bit(g, du[j]);
-#pragma unroll
-        for (int j = 0; j < kOsRounds; ++j) {
-            const uint64_t i = base + (uint64_t)j * kOsThreads + t;
-            if (i >= n) continue;
-            const uint64_t key = ok[j] ? ((uint64_t)su[j] << g.L) | du[j] : sentinel;
-            keys[i] = key;
-            valid += ok[j] ? 1u : 0u;
-            khash += ok[j] ? mix64(key) : 0ull;
-            for (int p = 0; p < passes; ++p)
-                atomicAdd(&h[copy][p][(uint32_t)(key >> (p * kRadixBits)) & (kRadix - 1)], 1u);
-        }
+        const uint64_t i = tl * kHistTile + t;
+        if (i >= n) continue;
+        const uint32_t su = src[i], du = dst[i];
+        const bool ok = active_bit(g, su) & active_bit(g, du);
+        const uint64_t key = ok ? ((uint64_t)su << g.L) | du : sentinel;
+        keys[i] = key;
+        valid += ok ? 1u : 0u;
+        khash += ok ? mix64(key) : 0ull;
+        for (int p = 0; p < passes; ++p)
+            atomicAdd(&h[copy][p][(uint32_t)(key >> (p * kRadixBits)) & (kRadix - 1)], 1u);
     }
     const uint32_t vw = (uint32_t)wave_sum((unsigned long long)valid);
     const unsigned long long kw = wave_sum(khash);

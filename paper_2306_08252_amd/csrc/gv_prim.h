@@ -465,9 +465,15 @@ constexpr uint32_t kOsAgg = 1u << 30, kOsIncl = 2u << 30, kOsMask = (1u << 30) -
 inline int os_passes(int bits) { return (bits + kRadixBits - 1) / kRadixBits; }
 inline uint64_t os_tiles(uint64_t n) { return div_up(std::max<uint64_t>(n, 1), kOsTile); }
 // Digit histograms: every histogram workgroup writes its own counts (no
-// atomics), one small kernel adds them up.
-constexpr uint64_t kHistGroups = 256;
-inline uint64_t os_hist_groups(uint64_t n) { return std::min<uint64_t>(os_tiles(n), kHistGroups); }
+// atomics), one small kernel adds them up.  A workgroup takes a key per thread and turn, two workgroups a compute unit:
+// with four keys per thread 10^5 pairs filled 25 units (pack 13.8 us, now 6.8),
+// 10^6 pairs one workgroup a unit (21.7, now 16.7; building from 1.7 * 10^7
+// 88 -> 69); 10^7 pairs take 109 us either way.
+constexpr uint64_t kHistGroups = 512;
+constexpr uint64_t kHistTile = 1024;
+inline uint64_t os_hist_groups(uint64_t n) {
+    return std::min<uint64_t>(div_up(std::max<uint64_t>(n, 1), kHistTile), kHistGroups);
+}
 // uint32 words of state a sort needs: tile counters and look-back status
 // (the first os_zero_words, which must be zeroed), then the histograms and
 // the per-group histograms.
@@ -506,6 +512,7 @@ inline uint64_t os_words(uint64_t n_max, int bits, bool vals = false) {
 }
 
 constexpr int kOsThreads = 1024;
+static_assert(kHistTile == kOsThreads, "a key per thread");
 constexpr int kOsWaves = kOsThreads / 64;
 static_assert(kOsThreads == 4 * kRadix, "the pass kernel works in four quarters of 256 threads");
 constexpr int kOsRounds = (int)(kOsTile / kOsThreads);  // keys per thread
@@ -694,27 +701,18 @@ __global__ __launch_bounds__(kOsThreads) void k_os_hist(const K* keys, const uin
     __syncthreads();
     const uint32_t copy = kOsHistCopies == 1 ? 0u : (threadIdx.x >> 6) & (kOsHistCopies - 1);
     // tiles of n_max: loads need not wait for n, counting masks with it
-    const uint64_t ntiles = (n_max + kOsTile - 1) / kOsTile;
+    const uint64_t ntiles = (n_max + kHistTile - 1) / kHistTile;
     for (uint64_t tl = blockIdx.x; tl < ntiles; tl += gridDim.x) {
-        const uint64_t base = tl * kOsTile;
-        K kk[kOsRounds];
-#pragma unroll
-        for (int j = 0; j < kOsRounds; ++j) {
-            const uint64_t i = base + (uint64_t)j * kOsThreads + threadIdx.x;
-            kk[j] = i < n_max ? keys[i] : K(0);
-        }
-#pragma unroll
-        for (int j = 0; j < kOsRounds; ++j) {
-            const uint64_t i = base + (uint64_t)j * kOsThreads + threadIdx.x;
-            const bool act = i < n;
-            for (int p = 0; p < passes; ++p) {
-                const uint32_t d = (uint32_t)(kk[j] >> (p * kRadixBits)) & (kRadix - 1);
-                if (kOsHistMode == 1) {
-                    if (act) atomicAdd(&h[copy][p][d], 1u);
-                } else {
-                    const uint64_t peers = digit_peers(d, act);
-                    if (act && rank_below(peers) == 0) atomicAdd(&h[0][p][d], popc64(peers));
-                }
+        const uint64_t i = tl * kHistTile + threadIdx.x;
+        const K k = i < n_max ? keys[i] : K(0);
+        const bool act = i < n;
+        for (int p = 0; p < passes; ++p) {
+            const uint32_t d = (uint32_t)(k >> (p * kRadixBits)) & (kRadix - 1);
+            if (kOsHistMode == 1) {
+                if (act) atomicAdd(&h[copy][p][d], 1u);
+            } else {
+                const uint64_t peers = digit_peers(d, act);
+                if (act && rank_below(peers) == 0) atomicAdd(&h[0][p][d], popc64(peers));
             }
         }
     }
@@ -739,10 +737,12 @@ static __global__ __launch_bounds__(kThreads) void k_os_hist_sum(
     __shared__ uint32_t red[16][17];
     __shared__ unsigned long long s_v[kWaves];
     if (vpart && blockIdx.x == 0) {
-        static_assert(kHistGroups <= kThreads, "one thread per histogram group");
-        const unsigned long long x = threadIdx.x < groups ? vpart[threadIdx.x] : 0u;
+        unsigned long long x = 0, y = 0;
+        for (uint32_t i = threadIdx.x; i < groups; i += kThreads) {
+            x += vpart[i];
+            y += kpart[i];
+        }
         const unsigned long long t = block_sum(x, s_v);
-        const unsigned long long y = threadIdx.x < groups ? kpart[threadIdx.x] : 0ull;
         const unsigned long long u = block_sum(y, s_v);
         if (threadIdx.x == 0) {
             *vtotal = t;
@@ -1030,7 +1030,7 @@ bool onesweep(Ctx& c, K* k0, K* k1, uint32_t* v0, uint32_t* v1, const uint32_t* 
 // Per-group digit counts of a sort whose histogram kernel is fused into the
 // kernel that writes the keys: group g writes os_passes(bits) * kRadix counts
 // at os_hpart(...) + g * os_passes(bits) * kRadix, for os_hist_groups(n_max)
-// groups of kOsTile-key tiles (tile t to group t % groups).
+// groups of kHistTile-key tiles (tile t to group t % groups).
 inline uint32_t* os_hpart(uint32_t* state, uint64_t n_max, int bits) {
     return state + os_zero_words(n_max, bits) + (uint64_t)os_passes(bits) * kRadix;
 }
