@@ -440,7 +440,6 @@ static const uint64_t* cbt_group(gv_cbt* g, CbtArrays& A, const uint32_t* src,
     const uint64_t sentinel = 1ull << (2 * v.L);
     c.launch("cbt_pack", k_cbt_pack, div_up(n, kThreads), kThreads, v, src, dst, n, sentinel,
              A.keys0, A.mark);
-    zero_words(c, A.state, os_zero_words(std::max<uint64_t>(n, 2), bits));
     const bool flip = onesweep<uint64_t, false>(c, A.keys0, A.keys1, nullptr, nullptr, nullptr, n,
                                                 bits, A.state, (uint32_t*)&v.ctr[kCbtSortErr]);
     const uint64_t* keys = flip ? A.keys1 : A.keys0;
@@ -616,7 +615,6 @@ static void cbt_dump(gv_cbt* g, uint64_t* offsets, uint32_t* dst, uint64_t cap, 
     }
     c.launch("cbt_gather", k_cbt_gather, div_up(v.n_cap, kThreads), kThreads, v,
              (const unsigned long long*)offs, k0);
-    zero_words(c, state, os_zero_words(std::max<uint64_t>(e, 2), bits));
     const bool flip = onesweep<uint64_t, false>(c, k0, k1, nullptr, nullptr, nullptr, e, bits, state,
                                                 (uint32_t*)&v.ctr[kCbtSortErr]);
     c.launch("cbt_extract", k_cbt_extract, div_up(e, kThreads), kThreads,

@@ -40,6 +40,7 @@
 //             (reclamation, Sec. 4.2).
 //   query:    answers are scattered back to input order.
 #include <algorithm>
+#include <cstddef>
 #include <type_traits>
 
 #include "gv_graph.h"
@@ -216,11 +217,8 @@ __device__ __forceinline__ void clear_batch(BatchCtr* bc, uint32_t t, uint32_t n
     for (uint32_t i = t; i < sizeof(BatchCtr) / 4; i += nt) w[i] = 0u;
 }
 
-__global__ __launch_bounds__(kThreads) void k_begin(BatchCtr* bc, uint32_t* state,
-                                                    uint64_t words) {
-    const uint64_t stride = (uint64_t)gridDim.x * kThreads;
-    for (uint64_t i = thread_index(); i < words; i += stride) state[i] = 0;
-    if (blockIdx.x == 0) clear_batch(bc, threadIdx.x, kThreads);
+__global__ __launch_bounds__(kThreads) void k_begin(BatchCtr* bc) {
+    clear_batch(bc, threadIdx.x, kThreads);
 }
 
 // ------------------------------------------------------------------ pack
@@ -2021,13 +2019,16 @@ static void edge_run(gv_graph* g, EdgeMode mode, const uint32_t* src, const uint
         rank_sort(c, "pack", EdgeKeys{v, src, dst, out, bc}, n, A.keys1, A.keys0, A.vals0);
         flip = false;
     } else if (mode == kQuery) {
-        c.launch("begin", k_begin, std::min<uint64_t>(div_up(A.state_words, kThreads), 1024),
-                 kThreads, bc, A.state, A.state_words);
+        // (keys of no bits take no sort, whose first kernel clears the counters
+        // that follow n_valid, the scan's total)
+        static_assert(offsetof(BatchCtr, n_valid) == 0, "the first word");
+        if (bits == 0) c.launch("begin", k_begin, 1, kThreads, bc);
         scan2(c, "pack", PackIn{v, src, dst}, PackOut{v.L, A.keys0, A.vals0, out}, n, A.part,
               &bc->n_valid);
         flip = onesweep<uint64_t, true>(c, A.keys0, A.keys1, A.vals0, A.vals1,
                                         (const uint32_t*)n_valid, n, bits, A.state, err,
-                                        g->spin_limit);
+                                        g->spin_limit, false, (uint32_t*)bc + 2,
+                                        sizeof(BatchCtr) / 4 - 2);
     } else {
         // With the sort overlap the packing and the passes run on the side
         // stream, which reads the pairs and the activity bitmap (which no

@@ -346,7 +346,6 @@ bool mixed_sort(const gv_graph* g, Ctx& c, const uint8_t* op, const uint32_t* sr
         rank_sort(c, "mixed_pack", MixedKeys{L, op, src, dst}, n, b.k1, b.k0, b.p0);
         return false;
     }
-    zero_words(c, b.state, os_zero_words(n, bits, true));
     c.launch("mixed_pack", k_mixed_pack, div_up(n, kThreads), kThreads, L, op, src, dst, n, b.k0,
              b.p0);
     return onesweep<uint64_t, true>(c, b.k0, b.k1, b.p0, b.p1, nullptr, n, bits, b.state,
