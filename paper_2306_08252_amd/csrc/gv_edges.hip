@@ -447,10 +447,10 @@ __device__ __forceinline__ V tile_sums(const V (&x)[R], V (&ex)[R], V* cnt) {
 
 // Segments, sources and work items of a tile of the sorted keys.  Also writes
 // the marks (dup_mark: 1 on a repeated pair, which an insert does not keep)
-// and a delete's hit positions (none yet),
-// checks the sort (every key at least its predecessor, else err_order = 2;
-// the mix64 sum of the sorted keys goes to the hash stripes, which the probe
-// compares with the packed keys' sum) and counts distinct pairs and blocks.
+// and a delete's hit positions (none yet), checks the sort (every key at least
+// its predecessor, else err_order = 2; the mix64 sum of the sorted keys goes to
+// the hash stripes, which the probe compares with the packed keys' sum) and
+// counts distinct pairs and blocks.
 //
 // A segment that runs past the tile belongs to the tile of its head, which
 // finds its end by a wave-wide search.  Every position reads its source's
@@ -458,13 +458,15 @@ __device__ __forceinline__ V tile_sums(const V (&x)[R], V (&ex)[R], V* cnt) {
 // the batch's counters have arrived (at positions clamped to the buffers).
 // Work items are written by all the threads of the workgroup, each finding its
 // item's source among the tile's (a hub's items spread over the workgroup;
-// written by its own lane or wave they took up to 1.7 times as long).  Bound: latency, keys -> records -> the tile's places -> the
-// sources: 10^3 pairs 10.2 -> 6.6 us, 10^4 pairs 10.0 -> 6.3, 10^6 pairs 25.5
-// -> 15.6, 10^7 pairs 99 -> 62 (R-MAT 2^20 / 2^24, the last 2^22 / 2^26)
-// against records read by the heads alone, after the counters and the keys.
-// The two scans over the batch that it replaced (their reduce and apply
-// kernels, a middle one past 2^21 pairs, and 32 bytes written per source for
-// its small item) took 21.8, 33.3 and 218 us.
+// written by its own lane or wave they took up to 1.7 times as long).
+//
+// Bound: latency, keys -> records -> the tile's places -> the sources: 10^3
+// pairs 10.2 -> 6.6 us, 10^4 pairs 10.0 -> 6.3, 10^6 pairs 25.5 -> 15.6, 10^7
+// pairs 99 -> 62 (R-MAT 2^20 / 2^24, the last 2^22 / 2^26) against records read
+// by the heads alone, after the counters and the keys.  The two scans over the
+// batch that it replaced (their reduce and apply kernels, a middle one past
+// 2^21 pairs, and 32 bytes written per source for its small item) took 21.8 us
+// for 10^4 pairs, 33.3 and 218.
 template <int T, uint32_t R>
 __global__ __launch_bounds__(T, 8) void k_segments(GraphView g, const uint64_t* keys, uint64_t n,
                                                 BatchCtr* bc, uint32_t tl, uint8_t* mark,
@@ -790,19 +792,23 @@ __global__ __launch_bounds__(kThreads, kProbeWaves) void k_probe(GraphView g, co
     constexpr uint32_t kStep = 64 * U;  // slots per wave and step
     constexpr int Q = VEC ? 1 : U;      // directory entries per lane and step
     __shared__ uint32_t stage[kWaves][kStage + 1];  // (a hit reads the entry after its own)
+    // the batch's counters, read together
+    const unsigned long long alloc = bc->alloc, key_sum = bc->key_sum;
+    const uint32_t nohash = bc->nohash;
+    const unsigned long long stripe =
+        MODE == kInsert || MODE == kDelete ? bc->stripe[lane_id()][kStripeHash] : 0ull;
     if (batch_failed(g.ctr)) return;
     if (MODE == kInsert || MODE == kDelete) {
         // the sorted keys must be the packed keys: their mix64 sums agree
         // (per-workgroup sums of the segments kernel in 64 stripes; one load a lane)
-        const unsigned long long sorted = wave_sum(bc->stripe[lane_id()][kStripeHash]);
-        if (!bc->nohash && sorted != bc->key_sum) {
+        if (wave_sum(stripe) != key_sum && !nohash) {
             if (lane_id() == 0) g.ctr->err_order = 3;
             return;
         }
     }
     {
         // small items first, kSmallLanes consecutive lanes per touched source
-        const uint64_t nq = (uint64_t)(uint32_t)(bc->alloc >> 32) * kSmallLanes;
+        const uint64_t nq = (uint64_t)(uint32_t)(alloc >> 32) * kSmallLanes;
         const uint64_t stride = (uint64_t)gridDim.x * kThreads;
         for (uint64_t k = (uint64_t)blockIdx.x * kThreads + threadIdx.x; k < nq; k += stride) {
             const Src I = srcs[k / kSmallLanes];
@@ -812,12 +818,17 @@ __global__ __launch_bounds__(kThreads, kProbeWaves) void k_probe(GraphView g, co
                 probe_small<MODE>(g, I, q, keys, mark, hitpos);
         }
     }
-    const uint32_t nitems = __builtin_amdgcn_readfirstlane((uint32_t)bc->alloc);
+    const uint32_t nitems = __builtin_amdgcn_readfirstlane((uint32_t)alloc);
     const uint32_t lane = lane_id();
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t nw = gridDim.x * kWaves;
     const uint32_t dmask = (uint32_t)((1ull << g.L) - 1);
-    uint32_t it = blockIdx.x * kWaves + wave;
+    // Where both kinds fit the grid's waves, items go to the last waves, so that
+    // no wave has both (10^3 pairs 7.0 -> 6.1 us); beyond that the last waves,
+    // which start last, would have two items (10^6 pairs 49 -> 57).
+    const uint32_t mine = blockIdx.x * kWaves + wave;
+    const uint64_t small = ((alloc >> 32) * kSmallLanes + 63) / 64;
+    uint32_t it = __builtin_amdgcn_readfirstlane(nitems + small <= nw ? nw - 1 - mine : mine);
     if (it >= nitems) return;
     uint32_t* st = stage[wave];
     const uint32_t sbase = wave * (uint32_t)sizeof(stage[0]);
@@ -1501,8 +1512,8 @@ __global__ __launch_bounds__(kThreads) void k_final_ins(GraphView g, const Batch
 // whole 16-byte groups, its tail's one or two blocks (from 8 slots per block
 // on) read once.  The others are taken by the whole wave in turn.  Bound: the
 // chain tail -> holes -> survivors, and lines of the pool read and written for
-// a slot or two (10^6 deletes of a 2^20-vertex graph 42 -> 36 us, 10^7 of a
-// 2^22-vertex one 420 -> 374).
+// a slot or two (10^6 deletes of a 2^20-vertex graph 42 -> 40 us, 10^7 of a
+// 2^22-vertex one 420 -> 353).
 __device__ __forceinline__ void compact_body(const GraphView& g, const uint32_t* hitpos,
                                              uint32_t* holes, const BatchCtr* bc,
                                              const Src* srcs, const uint32_t* tbase, uint32_t tl,

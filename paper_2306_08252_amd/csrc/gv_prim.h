@@ -463,7 +463,6 @@ constexpr uint64_t kOsTile = (uint64_t)kThreads * kOsItems;  // 4096
 constexpr uint32_t kOsAgg = 1u << 30, kOsIncl = 2u << 30, kOsMask = (1u << 30) - 1;
 
 inline int os_passes(int bits) { return (bits + kRadixBits - 1) / kRadixBits; }
-inline uint64_t os_tiles(uint64_t n) { return div_up(std::max<uint64_t>(n, 1), kOsTile); }
 // Digit histograms: every histogram workgroup writes its own counts (no
 // atomics), one small kernel adds them up.  A workgroup takes a key per thread and turn, two workgroups a compute unit:
 // with four keys per thread 10^5 pairs filled 25 units (pack 13.8 us, now 6.8),

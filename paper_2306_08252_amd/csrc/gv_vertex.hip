@@ -387,7 +387,8 @@ __global__ __launch_bounds__(kVScan, 6) void k_vd_scan(GraphView g, VDel d) {
         }
         unsigned long long tot;
         const unsigned long long ex =
-            block_excl_scan<kVScan / 64>((unsigned long long)hit | (unsigned long long)firsth << 32, lds, tot);
+            block_excl_scan<kVScan / 64>((unsigned long long)hit | (unsigned long long)firsth << 32,
+                                         lds, tot);
         if (threadIdx.x == 0) {
             s_bh = (uint32_t)tot ? atomicAdd(&g.ctr->vd_hits, tot & 0xffffffffull) : 0ull;
             s_bt = tot >> 32 ? atomicAdd(&g.ctr->vd_touched, tot >> 32) : 0ull;
