@@ -92,7 +92,7 @@ def bytes_model(name, per_launch):
         # M1: the touched adjacency, scanned once (block-granular slots)
         return 4 * S
     tiles = (k + 4095) // 4096
-    groups = min(tiles, 256)
+    groups = min((k + 1023) // 1024, 512)  # workgroups that count digits
     if name == "sort_pass":
         # M1: grouping is one write and one read of the packed pairs per
         # batch (16 B per pair), shared by the batch's radix passes
@@ -277,7 +277,7 @@ KERNEL_SYMBOLS = {
     "probe_delete": "gv::k_probe<1,",
     "probe_query": "gv::k_probe<2,",
     "compact": "gv::k_compact(",
-    "commit": "gv::k_commit<",
+    "commit": "gv::k_commit<1024,",
 }
 
 
@@ -686,7 +686,7 @@ def main():
         k = args.batch
         grid = {"sort_pass": (k + 4095) // 4096, "probe_insert": None, "probe_delete": None,
                 "probe_query": None, "compact": None, "commit": None,
-                "sort_hist": None, "pack": min((k + 4095) // 4096, 256)}
+                "sort_hist": None, "pack": min((k + 1023) // 1024, 512)}
         summarize_traffic(*args.summarize_traffic[:4], grid, args.summarize_traffic[4],
                           args.command)
         return
