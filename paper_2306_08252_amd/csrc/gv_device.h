@@ -80,7 +80,8 @@ struct DevCounters {
     // distinct ids of a vertex batch, distinct pairs of an attribute write
     unsigned long long n_uniq;
     // errors: err_batch is reset per batch, err_sticky accumulates; err_wait
-    // is set if a bounded look-back wait ever ran out
+    // is set if a bounded look-back wait ever ran out (by kernels of the
+    // graph's stream only)
     uint32_t err_batch, err_sticky, err_wait;
     uint32_t err_order;                // a batch's sorted keys failed their check
     uint32_t sort_n, sort_err;  // count and look-back error word of whole-graph sorts

@@ -81,7 +81,8 @@ constexpr int kLocate = 3;
 struct alignas(128) BatchCtr {
     unsigned long long n_valid, key_sum;  // valid pairs, and the mix64 sum of their keys
     uint32_t n_big, n_heavy;              // sources left to workgroups / to whole waves
-    uint32_t nohash, pad0;                // keys arrived sorted: no multiset check
+    uint32_t nohash;                      // keys arrived sorted: no multiset check
+    uint32_t sort_err;                    // a wait of the batch's own sort ran out
     unsigned long long pad1[12];
     // touched sources (high) and work items (low: at most one per pair and one
     // per 64 slots of the pool) placed
@@ -365,10 +366,15 @@ __device__ __forceinline__ bool small_item(uint32_t B, uint32_t deg, uint32_t le
 }
 
 // Valid pairs of the batch: none after a look-back wait ran out (the keys are
-// not sorted).
+// not sorted).  Every kernel of a batch has to decide alike in all of its
+// workgroups, and alike with the kernels after it: a tile planned as failed has
+// no block places for the commit.  So nothing that runs beside the batch writes
+// what it reads: a sort, which may be that of a later batch on the side stream,
+// flags its own batch's counters only, and the batch's first kernel on the
+// graph's stream carries the flag over to the graph's.
 __device__ __forceinline__ uint64_t batch_pairs(const DevCounters* c, const BatchCtr* bc,
                                                 uint64_t n) {
-    return c->err_wait ? 0ull : min((uint64_t)bc->n_valid, n);
+    return (c->err_wait | bc->sort_err) ? 0ull : min((uint64_t)bc->n_valid, n);
 }
 
 // First position in keys[lo, hi) whose key is at least x, by one wave: 64
@@ -494,6 +500,7 @@ __global__ __launch_bounds__(T, 8) void k_segments(GraphView g, const uint64_t* 
     }
     const uint64_t ka = keys[min(p0 + tile, n) - 1], kb = keys[min(p0 + tile, n - 1)];
     const uint64_t lim = batch_pairs(g.ctr, bc, n);
+    if (blockIdx.x == 0 && t == 0 && bc->sort_err) g.ctr->err_wait = 1u;
     // a valid key's source is below n_cap already; the bound keeps even a
     // corrupted key's record read inside the table
     VRec rec[R];
@@ -2014,9 +2021,8 @@ static void edge_run(gv_graph* g, EdgeMode mode, const uint32_t* src, const uint
         // wants it (n_max bytes)
         if (mark_out && sorted) A.mark = mark_out;
     }
-    DevCounters* ctr = v.ctr;
-    uint32_t* err = &ctr->err_wait;
     BatchCtr* bc = A.bc;
+    uint32_t* err = &bc->sort_err;
     const unsigned long long* n_valid = &bc->n_valid;
     const uint64_t grid = div_up(n, kThreads);
 

@@ -51,6 +51,7 @@ struct MixedKeys {
     const uint8_t* op;
     const uint32_t* src;
     const uint32_t* dst;
+    uint32_t* err;  // the list's error word, which no sort by rank sets
     struct Raw {
         uint32_t s, d;
         uint8_t o;
@@ -58,7 +59,9 @@ struct MixedKeys {
     __device__ Raw raw(uint64_t i) const { return Raw{src[i], dst[i], op[i]}; }
     __device__ uint64_t key(const Raw& r) const { return mixed_key(r.s, r.d, r.o, L); }
     __device__ void own(uint64_t, uint64_t) const {}
-    __device__ void begin(uint32_t, uint32_t) const {}
+    __device__ void begin(uint32_t t, uint32_t) const {
+        if (t == 0) *err = 0u;
+    }
     __device__ bool counted(uint64_t) const { return false; }
     __device__ void totals(unsigned long long, unsigned long long) const {}
 };
@@ -97,7 +100,7 @@ struct SplitIn {
         return r;
     }
     __device__ void deref(Rec& r) const {
-        r.o = op[r.p];
+        r.o = op[min((uint64_t)r.p, n - 1)];  // (anything, after a sort that failed)
         r.act = (r.k >> (2 * L)) == 0 && pair_active(active, r.k, L);
     }
     // 0 = not kept, 1 = kept delete, 2 = kept insert
@@ -114,13 +117,17 @@ struct SplitIn {
 constexpr uint32_t kRefIns = 0x80000000u;  // a place in the insert keys
 
 // The scan total holds both counts; finish() splits it for the two sorted
-// batches, which read one each (cnt[1] deletes, cnt[2] inserts).
+// batches, which read one each (cnt[1] deletes, cnt[2] inserts), and carries a
+// failure of the list's sort, which may have run on the side stream, over to
+// the graph's counters: the kernels after it do nothing then.
 struct SplitOut {
     SplitIn in;
     uint64_t* del_keys;
     uint64_t* ins_keys;
     unsigned long long* cnt;  // [0] the scan total
     uint32_t* at;             // (may be null) where each kept entry's key went
+    const uint32_t* err;
+    DevCounters* ctr;
     __device__ void operator()(uint64_t i, const SplitIn::Rec& r, uint64_t,
                                unsigned long long pre) const {
         const int k = in.kind(r);
@@ -133,6 +140,7 @@ struct SplitOut {
         if (threadIdx.x == 0) {
             cnt[1] = cnt[0] & 0xffffffffull;
             cnt[2] = cnt[0] >> 32;
+            if (*err) ctr->err_wait = 1u;
         }
     }
 };
@@ -189,7 +197,7 @@ __global__ __launch_bounds__(kThreads) void k_mixed_flags(
     gv_batch_stats* stats) {
     const uint64_t i = (uint64_t)blockIdx.x * kThreads + threadIdx.x;
     if (i < n_req) stats[i] = gv_batch_stats{0ull, 0ull, 0ull};
-    if (i >= n) return;
+    if (i >= n || batch_failed(g.ctr)) return;
     const uint64_t k = sk[i];
     const uint32_t p = sp[i];
     const uint8_t o = op[p];
@@ -223,13 +231,15 @@ __global__ __launch_bounds__(kThreads) void k_mixed_flags(
 // latency (2 * 10^5 entries 12.6 -> 10.1 us against
 // flag after flag and an atomic per lane and request)
 constexpr uint32_t kStatItems = 8;
-__global__ __launch_bounds__(kThreads) void k_request_stats(const uint64_t* end, uint64_t n_req,
+__global__ __launch_bounds__(kThreads) void k_request_stats(const DevCounters* ctr,
+                                                            const uint64_t* end, uint64_t n_req,
                                                             uint64_t n,
                                                             const uint8_t* flag,
                                                             const uint32_t* fref,
                                                             const uint8_t* del_found,
                                                             const uint8_t* ins_had,
                                                             gv_batch_stats* stats) {
+    if (batch_failed(ctr)) return;  // the flags may not have been written
     const uint64_t p0 = ((uint64_t)blockIdx.x * kThreads + threadIdx.x) * kStatItems;
     const bool live = p0 < n;
     uint32_t r = live ? request_of(end, (uint32_t)n_req, p0) : (uint32_t)n_req;
@@ -303,12 +313,14 @@ __global__ __launch_bounds__(kThreads) void k_stats_zero(gv_batch_stats* stats, 
 struct MixSort {
     uint64_t *k0, *k1;
     uint32_t *p0, *p1, *state;
+    uint32_t* err;  // a wait of the sort ran out (cleared by the sort's first kernel)
     void carve(Carver& cv, uint64_t n, int bits) {
         k0 = cv.take<uint64_t>(n);
         k1 = cv.take<uint64_t>(n);
         p0 = cv.take<uint32_t>(n);
         p1 = cv.take<uint32_t>(n);
         state = cv.take<uint32_t>(os_words(n, bits, true));
+        err = cv.take<uint32_t>(1);
     }
 };
 
@@ -343,21 +355,21 @@ bool mixed_sort(const gv_graph* g, Ctx& c, const uint8_t* op, const uint32_t* sr
     const uint32_t L = g->v.L;
     const int bits = 2 * (int)L + 1;
     if (n <= kRankMax) {
-        rank_sort(c, "mixed_pack", MixedKeys{L, op, src, dst}, n, b.k1, b.k0, b.p0);
+        rank_sort(c, "mixed_pack", MixedKeys{L, op, src, dst, b.err}, n, b.k1, b.k0, b.p0);
         return false;
     }
     c.launch("mixed_pack", k_mixed_pack, div_up(n, kThreads), kThreads, L, op, src, dst, n, b.k0,
              b.p0);
     return onesweep<uint64_t, true>(c, b.k0, b.k1, b.p0, b.p1, nullptr, n, bits, b.state,
-                                    &g->v.ctr->err_wait, g->spin_limit, concurrent);
+                                    b.err, g->spin_limit, concurrent, b.err, 1);
 }
 
-// the list's entries sorted (sk, sp): the kept key lists, then (when
-// `released` is given) released() once nothing reads the sorted entries or
-// the ops any more, then the two batches and the statistics
+// the list's entries sorted (sk, sp; sort_err: set when the sort failed): the
+// kept key lists, then (when `released` is given) released() once nothing reads
+// the sorted entries or the ops any more, then the two batches and the statistics
 void mixed_apply(gv_graph* g, const uint8_t* op, const uint64_t* sk, const uint32_t* sp,
-                 uint64_t n, const uint64_t* end, uint64_t n_req, gv_batch_stats* stats,
-                 const std::function<void()>* released) {
+                 const uint32_t* sort_err, uint64_t n, const uint64_t* end, uint64_t n_req,
+                 gv_batch_stats* stats, const std::function<void()>* released) {
     Ctx& c = g->ctx;
     const GraphView& v = g->v;
     MixKeep k;
@@ -369,8 +381,8 @@ void mixed_apply(gv_graph* g, const uint8_t* op, const uint64_t* sk, const uint3
         k.carve(cv, n, stats != nullptr);
     }
     const SplitIn in{sk, sp, op, v.active, n, v.L};
-    scan2(c, "mixed_split", in, SplitOut{in, k.del_keys, k.ins_keys, k.cnt, k.at}, n, k.part,
-          &k.cnt[0]);
+    scan2(c, "mixed_split", in,
+          SplitOut{in, k.del_keys, k.ins_keys, k.cnt, k.at, sort_err, v.ctr}, n, k.part, &k.cnt[0]);
     if (stats)
         c.launch("mixed_stats", k_mixed_flags, div_up(std::max<uint64_t>(n, n_req), kThreads),
                  kThreads, v, sk, sp, op, n, end, (uint32_t)n_req, (const uint32_t*)k.at, k.flag,
@@ -380,8 +392,9 @@ void mixed_apply(gv_graph* g, const uint8_t* op, const uint64_t* sk, const uint3
     edge_batch_sorted(g, kInsert, k.ins_keys, &k.cnt[2], n, true, k.ins_had);
     if (stats) {
         c.launch("mixed_stats", k_request_stats, div_up(n, (uint64_t)kThreads * kStatItems),
-                 kThreads, end, n_req, n, (const uint8_t*)k.flag, (const uint32_t*)k.fref,
-                 (const uint8_t*)k.del_found, (const uint8_t*)k.ins_had, stats);
+                 kThreads, (const DevCounters*)v.ctr, end, n_req, n, (const uint8_t*)k.flag,
+                 (const uint32_t*)k.fref, (const uint8_t*)k.del_found, (const uint8_t*)k.ins_had,
+                 stats);
     }
 }
 
@@ -442,8 +455,8 @@ void mixed_edges(gv_graph* g, const uint8_t* op, const uint32_t* src, const uint
     }
     const bool flip = mixed_sort(g, c, op, src, dst, n, b, false);
     // (the statistics' flags are taken before the batches reuse g->scratch)
-    mixed_apply(g, op, flip ? b.k1 : b.k0, flip ? b.p1 : b.p0, n, req_end, n_req, stats,
-                nullptr);
+    mixed_apply(g, op, flip ? b.k1 : b.k0, flip ? b.p1 : b.p0, b.err, n, req_end, n_req,
+                stats, nullptr);
 }
 
 void mixed_edges_side(gv_graph* g, uint64_t n, bool fence,
@@ -485,8 +498,8 @@ void mixed_edges_side(gv_graph* g, uint64_t n, bool fence,
         hip_check(hipEventRecord(o.mdone[ob], c.stream), "hipEventRecord");
         o.mused[ob] = true;
     };
-    mixed_apply(g, b.op, flip ? b.s.k1 : b.s.k0, flip ? b.s.p1 : b.s.p0, n, nullptr, 0, nullptr,
-                &released);
+    mixed_apply(g, b.op, flip ? b.s.k1 : b.s.k0, flip ? b.s.p1 : b.s.p0, b.s.err, n, nullptr, 0,
+                nullptr, &released);
     ++o.mcount;
 }
 
