@@ -343,11 +343,14 @@ inline void dev_free(void* p, bool reuse) {
 struct Scratch {
     void* ptr = nullptr;
     size_t cap = 0;
-    uint64_t gen = 0;  // counts reallocations
+    uint64_t gen = 0;  // counts the buffers had and given up
     void ensure(size_t bytes, hipStream_t s) {
         if (bytes <= cap) return;
         if (ptr) {
             hip_check(hipStreamSynchronize(s), "hipStreamSynchronize");
+            // (also when the allocation below fails: a plan recorded on the
+            // old buffer, which may be another graph's by then, is refused)
+            ++gen;
             dev_free(ptr, true);
             ptr = nullptr;
             cap = 0;
