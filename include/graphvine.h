@@ -27,7 +27,8 @@
  * stream has passed the call.  The library never frees caller memory.  The
  * graph owns all of its internal memory; gv_graph_destroy releases it (the
  * library keeps at most 4 GiB of large freed buffers per process for the next
- * graphs, and frees them when an allocation does not fit).
+ * graphs; they are freed when one of its allocations does not fit, when they
+ * have been passed over for long, and by gv_release_cached).
  * A gv_graph must be used by one host thread at a time.
  *
  * Errors.  Every int-returning function returns a GV_* code; no C++ exception
@@ -462,6 +463,11 @@ const char* gv_strerror(int code);
  * by a HIP call on this host thread ("" if none); owned by the library. */
 const char* gv_last_error(void);
 void gv_graph_destroy(gv_graph* g);
+
+/* Gives the buffers of destroyed graphs that the library still keeps back to
+ * the device, for the program's other allocators; *bytes (may be NULL)
+ * receives their size.  No graph's own memory is among them. */
+int gv_release_cached(uint64_t* bytes);
 
 #ifdef __cplusplus
 }

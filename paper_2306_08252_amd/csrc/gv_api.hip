@@ -141,13 +141,13 @@ int gv_graph_init(gv_graph** out, uint64_t num_vertices, const uint32_t* d_src,
         v.n_cap = cap;
         v.L = log2_exact(cap);
         v.A = c.edge_attr_words;
-        hip_check(hipMalloc(&g->mem_vt, cap * sizeof(VRec)), "hipMalloc vertex table");
-        hip_check(hipMalloc(&g->mem_active, ((cap + 31) / 32) * 4), "hipMalloc active");
-        hip_check(hipMalloc(&g->mem_ctr, sizeof(DevCounters)), "hipMalloc counters");
-        hip_check(hipMalloc(&g->mem_chain, sizeof(ChainState)), "hipMalloc scan state");
+        hip_check(dev_alloc(&g->mem_vt, cap * sizeof(VRec)), "hipMalloc vertex table");
+        hip_check(dev_alloc(&g->mem_active, ((cap + 31) / 32) * 4), "hipMalloc active");
+        hip_check(dev_alloc(&g->mem_ctr, sizeof(DevCounters)), "hipMalloc counters");
+        hip_check(dev_alloc(&g->mem_chain, sizeof(ChainState)), "hipMalloc scan state");
         hip_check(hipMemsetAsync(g->mem_chain, 0, sizeof(ChainState), g->ctx.stream),
                   "hipMemsetAsync");
-        hip_check(hipMalloc(&g->mem_vlost, cap * sizeof(uint32_t)), "hipMalloc vertex scratch");
+        hip_check(dev_alloc(&g->mem_vlost, cap * sizeof(uint32_t)), "hipMalloc vertex scratch");
         hip_check(hipMemsetAsync(g->mem_vlost, 0, cap * sizeof(uint32_t), g->ctx.stream),
                   "hipMemsetAsync");
         hip_check(hipHostMalloc((void**)&g->hmem, sizeof(HostCounters), hipHostMallocDefault),
@@ -176,6 +176,17 @@ int gv_graph_init(gv_graph** out, uint64_t num_vertices, const uint32_t* d_src,
     }
     *out = g;
     return GV_OK;
+}
+
+int gv_release_cached(uint64_t* bytes) {
+    if (bytes) *bytes = 0;
+    try {
+        const size_t n = dev_release_cached();
+        if (bytes) *bytes = n;
+        return GV_OK;
+    } catch (...) {  // (no memory for the list of buffers)
+        return GV_ENOMEM;
+    }
 }
 
 void gv_graph_destroy(gv_graph* g) {

@@ -1116,7 +1116,7 @@ struct DevBuf {
     }
     template <typename T>
     T* get(size_t count) {
-        hip_check(hipMalloc(&p, std::max<size_t>(count * sizeof(T), 8)), "hipMalloc relayout");
+        hip_check(dev_alloc(&p, std::max<size_t>(count * sizeof(T), 8)), "hipMalloc relayout");
         return (T*)p;
     }
 };

@@ -693,11 +693,11 @@ int gv_cbt_init(gv_cbt** out, uint64_t num_vertices, const uint32_t* d_src, cons
         v.B = block_slots;
         v.log2B = log2_exact(block_slots);
         v.cap_blocks = pool_blocks;
-        hip_check(hipMalloc(&g->mem_pool, pool_blocks * block_slots * 4ull), "hipMalloc pool");
-        hip_check(hipMalloc(&g->mem_child, pool_blocks * 8ull), "hipMalloc child links");
-        hip_check(hipMalloc(&g->mem_queue, pool_blocks * 4ull), "hipMalloc edge queue");
-        hip_check(hipMalloc(&g->mem_vt, cap * sizeof(CbtVert)), "hipMalloc sentinels");
-        hip_check(hipMalloc(&g->mem_ctr, kCbtWords * sizeof(unsigned long long)), "hipMalloc ctr");
+        hip_check(dev_alloc(&g->mem_pool, pool_blocks * block_slots * 4ull), "hipMalloc pool");
+        hip_check(dev_alloc(&g->mem_child, pool_blocks * 8ull), "hipMalloc child links");
+        hip_check(dev_alloc(&g->mem_queue, pool_blocks * 4ull), "hipMalloc edge queue");
+        hip_check(dev_alloc(&g->mem_vt, cap * sizeof(CbtVert)), "hipMalloc sentinels");
+        hip_check(dev_alloc(&g->mem_ctr, kCbtWords * sizeof(unsigned long long)), "hipMalloc ctr");
         hip_check(hipHostMalloc((void**)&g->hctr, kCbtWords * sizeof(unsigned long long),
                                 hipHostMallocDefault), "hipHostMalloc");
         v.pool = (uint32_t*)g->mem_pool;

@@ -215,10 +215,11 @@ struct Carver {
 // hipMalloc 40 us, and the driver hands freed memory back slowly: a program
 // that builds and drops graphs of 1 GB each waited 18 ms per graph once the
 // card's 288 GB had been through its hands.  What is kept is bounded
-// (kCacheMax over all devices, the oldest goes first), is freed when a
-// request does not fit the card, and is dropped when it was passed over by
-// kCacheAge requests and frees.  Callers free a buffer only after waiting for
-// the streams that used it, so the next owner may use any stream.
+// (kCacheMax over all devices, the oldest goes first), is freed when any
+// allocation of the library does not fit the card or the program asks for it
+// (gv_release_cached), and is dropped when it was passed over by kCacheAge
+// requests and frees.  Callers free a buffer only after waiting for the streams
+// that used it, so the next owner may use any stream.
 constexpr size_t kCacheMin = (size_t)32 << 20;
 constexpr size_t kCacheMax = (size_t)4 << 30;
 constexpr uint64_t kCacheAge = 64;
@@ -257,9 +258,38 @@ inline void dev_free_all(const std::vector<DevCache::Buf>& bufs) {
     for (const DevCache::Buf& b : bufs) (void)hipFree(b.p);
 }
 
+// Frees everything kept; returns how many bytes that was.
+inline size_t dev_release_cached() {
+    DevCache& c = dev_cache();
+    std::vector<DevCache::Buf> old;
+    {
+        std::lock_guard<std::mutex> lock(c.mu);
+        old.reserve(c.idle.size());
+        c.trim(old, 0);
+    }
+    dev_free_all(old);
+    size_t total = 0;
+    for (const DevCache::Buf& b : old) total += b.bytes;
+    return total;
+}
+
+// Every device allocation of the library: what is kept goes back to the card
+// before a request fails.  (A failure leaves no error behind for the check of
+// the next launch to find.)
+inline hipError_t dev_alloc(void** out, size_t bytes) {
+    hipError_t e = hipMalloc(out, bytes);
+    if (e == hipSuccess) return e;
+    (void)hipGetLastError();
+    if (!dev_release_cached()) return e;
+    e = hipMalloc(out, bytes);
+    if (e != hipSuccess) (void)hipGetLastError();
+    return e;
+}
+
+// a buffer from the cache where it has one, for dev_free to take back
 inline void dev_malloc(void** out, size_t bytes, const char* what) {
     if (bytes < kCacheMin) {
-        hip_check(hipMalloc(out, bytes), what);
+        hip_check(dev_alloc(out, bytes), what);
         return;
     }
     int dev = 0;
@@ -289,19 +319,7 @@ inline void dev_malloc(void** out, size_t bytes, const char* what) {
     }
     dev_free_all(old);
     if (got) return;
-    hipError_t e = hipMalloc(out, bytes);
-    if (e != hipSuccess) {
-        (void)hipGetLastError();
-        old.clear();
-        {
-            std::lock_guard<std::mutex> lock(c.mu);
-            old.reserve(c.idle.size());
-            c.trim(old, 0);
-        }
-        dev_free_all(old);
-        e = hipMalloc(out, bytes);
-    }
-    hip_check(e, what);
+    hip_check(dev_alloc(out, bytes), what);
     std::lock_guard<std::mutex> lock(c.mu);
     try {
         c.live.push_back({*out, bytes, dev, 0});

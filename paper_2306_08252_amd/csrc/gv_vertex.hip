@@ -675,16 +675,16 @@ static void grow_table(gv_graph* g, uint64_t new_cap) {
     Ctx& c = g->ctx;
     GraphView& v = g->v;
     void *vt2 = nullptr, *act2 = nullptr;
-    hip_check(hipMalloc(&vt2, new_cap * sizeof(VRec)), "hipMalloc vertex table");
+    hip_check(dev_alloc(&vt2, new_cap * sizeof(VRec)), "hipMalloc vertex table");
     const uint64_t words = (new_cap + 31) / 32;
-    if (hipMalloc(&act2, words * 4) != hipSuccess) {
+    if (dev_alloc(&act2, words * 4) != hipSuccess) {
         hipFree(vt2);
         fail(GV_ENOMEM, "hipMalloc active bitmap");
     }
     c.launch("grow_table", k_grow_table, div_up(new_cap, kThreads), kThreads, (const VRec*)v.vt,
              (const uint32_t*)v.active, (uint64_t)v.n_cap, (VRec*)vt2, (uint32_t*)act2, new_cap);
     void* vl2 = nullptr;
-    if (hipMalloc(&vl2, new_cap * sizeof(uint32_t)) != hipSuccess) {
+    if (dev_alloc(&vl2, new_cap * sizeof(uint32_t)) != hipSuccess) {
         hip_check(hipStreamSynchronize(c.stream), "hipStreamSynchronize");
         hipFree(vt2);
         hipFree(act2);

@@ -141,6 +141,7 @@ def lib():
             "gv_apply_ops": [vp, C.POINTER(gv_op), C.c_uint64],
             "gv_plan_create": [vp, C.POINTER(gv_op), C.c_uint64, C.POINTER(C.c_void_p)],
             "gv_plan_launch": [vp],
+            "gv_release_cached": [u64p],
         }
         for name, args in sig.items():
             f = getattr(L, name)
@@ -457,6 +458,13 @@ def gv_debug_spin_limit(g, limit):
 
 def gv_graph_destroy(g):
     lib().gv_graph_destroy(C.c_void_p(g))
+
+
+def gv_release_cached():
+    """Bytes of destroyed graphs' buffers given back to the device."""
+    n = C.c_uint64()
+    _check(lib().gv_release_cached(C.byref(n)), "gv_release_cached")
+    return n.value
 
 
 # ------------------------------------------------------------------ wrapper

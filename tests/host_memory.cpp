@@ -69,11 +69,65 @@ static const char* scratch_growth_fails() {
     return nullptr;
 }
 
+// any request of the library is served while buffers are only kept
+static const char* requests_empty_the_cache() {
+    for (size_t want : {48 * MiB, 8 * MiB, 65 * MiB}) {
+        void *a = nullptr, *b = nullptr;
+        dev_malloc(&a, 64 * MiB, "kept");
+        dev_free(a, true);
+        if (g_used != 64 * MiB) return "not kept";
+        g_card = 66 * MiB;
+        if (code_of([&] { dev_malloc(&b, want, "request"); }) != GV_OK) return "a request failed";
+        dev_free(b, false);
+        dev_malloc(&a, 64 * MiB, "kept");
+        dev_free(a, true);
+        if (dev_alloc(&b, want) != hipSuccess) return "a plain request failed";
+        hipFree(b);
+        if (g_used) return "still held";
+        // one that does not fit at all leaves no error to be found later
+        if (code_of([&] { dev_malloc(&b, 4 * want + 70 * MiB, "too much"); }) != GV_ENOMEM)
+            return "no error";
+        if (hipGetLastError() != hipSuccess) return "an error left behind";
+        g_card = (size_t)1 << 40;
+    }
+    return nullptr;
+}
+
+// what is kept is bounded, is found again by size, and ends by age or request
+static const char* bounded_and_given_back() {
+    std::vector<void*> p(12);
+    for (void*& x : p) dev_malloc(&x, 512 * MiB, "pool");
+    for (void* x : p) dev_free(x, true);
+    if (g_used > kCacheMax) return "more than the bound";
+    if (!g_used) return "nothing kept";
+    void* x = nullptr;
+    dev_malloc(&x, 420 * MiB, "fits one of them");
+    if (std::find(p.begin(), p.end(), x) == p.end()) return "a new buffer";
+    size_t held = g_used;
+    dev_free(x, false);  // (its streams were not waited for)
+    if (g_used != held - 512 * MiB) return "kept though it may be in use";
+    held = g_used;
+    if (dev_release_cached() != held || g_used) return "not given back";
+    dev_malloc(&x, 64 * MiB, "old");
+    dev_free(x, true);
+    for (uint64_t i = 0; i <= kCacheAge; ++i) {
+        void* y = nullptr;
+        dev_malloc(&y, 200 * MiB, "passing by");
+        dev_free(y, false);
+    }
+    if (g_used) return "kept for ever";
+    dev_malloc(&x, kCacheMax + 64 * MiB, "past the bound");
+    dev_free(x, true);
+    return g_used ? "kept past the bound" : nullptr;
+}
+
 int main(int argc, char** argv) {
     struct {
         const char* name;
         const char* (*run)();
-    } checks[] = {{"scratch_growth_fails", scratch_growth_fails}};
+    } checks[] = {{"scratch_growth_fails", scratch_growth_fails},
+                  {"requests_empty_the_cache", requests_empty_the_cache},
+                  {"bounded_and_given_back", bounded_and_given_back}};
     for (auto& c : checks)
         if (argc > 1 && !std::strcmp(argv[1], c.name)) {
             const char* bad = c.run();
