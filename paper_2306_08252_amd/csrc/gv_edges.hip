@@ -139,6 +139,8 @@ struct BatchArrays {
     uint2* carry;       // insert, per tile: the source whose segment runs into
                         // the tile, and that source's kept pairs before it
     uint32_t* tbase;    // per tile: first of its blocks among the batch's
+    uint32_t* tkept;    // per tile inside a segment: its kept pairs or hits, plus
+                        // one, once the plan has counted them (0 before)
     uint32_t* t_dreq;   // insert: requested directory class or kNoDir
     uint32_t* t_drank;  // insert: rank among requests of that class
     uint32_t* t_dold;   // insert: replaced directory segment offset
@@ -185,6 +187,7 @@ static void carve_batch(Carver& cv, BatchArrays& A, uint64_t n, uint64_t icap, E
     if (mode != kQuery) {
         A.heavy = cv.take<uint32_t>(n);
         A.tbase = cv.take<uint32_t>(nt);
+        A.tkept = cv.take<uint32_t>(nt);
     }
     A.srcs = cv.take<Src>(n);
     A.tiles = cv.take<uint2>(nt);
@@ -477,8 +480,8 @@ template <int T, uint32_t R>
 __global__ __launch_bounds__(T, 8) void k_segments(GraphView g, const uint64_t* keys, uint64_t n,
                                                 BatchCtr* bc, uint32_t tl, uint8_t* mark,
                                                 int dup_mark, uint32_t* hitpos, Src* srcs,
-                                                uint2* tiles, Item* items, uint64_t icap,
-                                                uint32_t chunk) {
+                                                uint2* tiles, uint32_t* tkept, Item* items,
+                                                uint64_t icap, uint32_t chunk) {
     constexpr uint32_t kTile = T * R;
     // the tile's sources: position (and whether `dir` is the only block),
     // degree, directory, first work item
@@ -514,6 +517,7 @@ __global__ __launch_bounds__(T, 8) void k_segments(GraphView g, const uint64_t* 
     }
     const uint32_t np = (uint32_t)min((uint64_t)tile, lim - p0);
     if (t < 3) s_sum[t] = 0ull;
+    if (t == 0 && tkept) tkept[blockIdx.x] = 0u;
     bool head[R];
     unsigned long long hash = 0, uniq = 0;
     bool bad = false;
@@ -996,15 +1000,45 @@ __device__ __forceinline__ uint32_t wave_count(const uint8_t* mark, uint64_t a, 
     return wave_sum(c);
 }
 
+// words that other workgroups of the same kernel add to or write
+template <typename V>
+__device__ __forceinline__ V ld_agent(const V* p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// The same of a tile inside a segment, by one lane: the tile publishes its
+// own count (tkept).  A tile like that waits for nothing and workgroups start
+// in order, so it comes; a wait that runs out all the same counts the marks
+// here (words of four, each 0 or 1).
+constexpr uint32_t kPlanSpins = 1u << 14;
+template <bool INS>
+__device__ __forceinline__ uint32_t inner_count(const uint32_t* tkept, const uint8_t* mark,
+                                                uint64_t tile, uint32_t tl) {
+    for (uint32_t spins = 0; spins < kPlanSpins; ++spins) {
+        const uint32_t x = ld_agent(tkept + tile);
+        if (x) return x - 1u;
+        __builtin_amdgcn_s_sleep(4);
+    }
+    const uint32_t* m = (const uint32_t*)(mark + (tile << tl));
+    const uint32_t words = 1u << (tl - 2);
+    uint32_t hits = 0;
+    for (uint32_t i = 0; i < words; ++i) hits += (uint32_t)__popc(m[i]);
+    return INS ? (1u << tl) - hits : hits;
+}
+
 // What every touched source of a tile needs: its kept pairs or hits r, then
 // (insert) its blocks and directory request, or (delete) its freed blocks and
 // who compacts it.  The tile's blocks and listed sources are placed with one
 // atomic on the batch's demand; the last tile to finish runs the batch's
 // plan.  The words the plan adds up are written by returning atomics only, so
 // every tile's share is in them once its `done` is counted, and no fence is
-// needed.  A segment that runs past the tile is counted by its head's tile,
-// one wave per further tile (insert: which also leaves the running count to
-// those tiles).
+// needed.  A segment that runs past the tile is counted by its head's tile
+// (insert: which also leaves the running count to the further tiles): one wave
+// per further tile, or, where that would take several rounds, a thread per
+// tile that reads the count which the tile itself published; only the last,
+// which the segment may end inside of, is still counted here.  (10^6 stored
+// pairs of one vertex inserted again, 489 tiles: 449 us for the batch by waves
+// alone, now 166.)
 //
 // Bound: latency (marks, then source records: both streams).  It replaces a
 // scan over the pairs, a kernel over the sources and a scan over them
@@ -1017,7 +1051,8 @@ __device__ __forceinline__ uint32_t wave_count(const uint8_t* mark, uint64_t a, 
 template <bool INS, int T, uint32_t R>
 __global__ __launch_bounds__(T, 8) void k_plan(GraphView g, uint64_t n, BatchCtr* bc, uint32_t tl,
                                             const uint8_t* mark, Src* srcs, const uint2* tiles,
-                                            uint2* carry, uint32_t* tbase, uint32_t* t_dreq,
+                                            uint2* carry, uint32_t* tbase, uint32_t* tkept,
+                                            uint32_t* t_dreq,
                                             uint32_t* t_drank, uint32_t* list, uint32_t* list2,
                                             int sticky) {
     constexpr uint32_t kTile = T * R;
@@ -1058,7 +1093,12 @@ __global__ __launch_bounds__(T, 8) void k_plan(GraphView g, uint64_t n, BatchCtr
             const uint32_t p = j * T + t;
             if (p < np) s_pre[p] = rank[j];
         }
-        if (t == 0) s_pre[np] = tot;
+        if (t == 0) {
+            s_pre[np] = tot;
+            if (!nh)
+                __hip_atomic_store(tkept + blockIdx.x, tot + 1u, __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
+        }
         changed = tot;
         __syncthreads();
         // the rest of a segment that runs past the tile
@@ -1068,8 +1108,22 @@ __global__ __launch_bounds__(T, 8) void k_plan(GraphView g, uint64_t n, BatchCtr
             const uint32_t last_lo = last.x, last_hi = last.y;
             if (last_hi > pe) {
                 const uint32_t in_tile = tot - s_pre[last_lo - (uint32_t)p0];
-                const uint64_t b0 = blockIdx.x + 1, b1 = ((uint64_t)last_hi - 1) >> tl;
-                for (uint64_t b = b0; b <= b1; b += T / 64) {
+                const uint64_t b1 = ((uint64_t)last_hi - 1) >> tl;
+                uint64_t b = blockIdx.x + 1;
+                if (b1 - b >= T / 64) {
+                    for (; b < b1; b += T) {
+                        const uint64_t mb = b + t;
+                        uint32_t c[1] = {0}, before[1];
+                        if (mb < b1) c[0] = inner_count<INS>(tkept, mark, mb, tl);
+                        const uint32_t all = tile_sums<T>(c, before, s_tail);
+                        if (INS && mb < b1)
+                            carry[mb] = make_uint2(t0 + nh - 1, in_tile + tail + before[0]);
+                        tail += all;
+                        __syncthreads();
+                    }
+                    b = b1;
+                }
+                for (; b <= b1; b += T / 64) {
                     const uint64_t mb = b + w;
                     uint32_t c = 0;
                     if (mb <= b1)
@@ -1169,12 +1223,6 @@ __global__ __launch_bounds__(T, 8) void k_plan(GraphView g, uint64_t n, BatchCtr
         if (INS) plan_insert(g, bc, n, (uint32_t)s_done, sticky);
         else plan_delete(g, bc, n, (uint32_t)s_done);
     }
-}
-
-// sums the plan adds up from atomics of other workgroups
-template <typename V>
-__device__ __forceinline__ V ld_agent(const V* p) {
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Allocation plan for the whole batch, one wave (a lane per directory class):
@@ -2103,7 +2151,7 @@ static void edge_run(gv_graph* g, EdgeMode mode, const uint32_t* src, const uint
         constexpr uint32_t R = decltype(rows)::value;
         c.launch("segments", k_segments<T, R>, ntiles, T, v, keys, n, bc, tl, A.mark,
                  mode == kInsert ? 1 : 0, mode == kDelete ? A.hitpos : nullptr, A.srcs, A.tiles,
-                 A.items, icap, chunk);
+                 A.tkept, A.items, icap, chunk);
     });
     const uint64_t pwant = div_up(icap, (uint64_t)kWaves);
     auto probe = [&](auto mode_tag, const char* name, uint32_t* hitpos) {
@@ -2122,7 +2170,7 @@ static void edge_run(gv_graph* g, EdgeMode mode, const uint32_t* src, const uint
             constexpr uint32_t R = decltype(rows)::value;
             c.launch("plan_insert", k_plan<true, T, R>, ntiles, T, v, n, bc, tl,
                      (const uint8_t*)A.mark, A.srcs, (const uint2*)A.tiles, A.carry, A.tbase,
-                     A.t_dreq, A.t_drank, A.rel, A.heavy, (int)sticky);
+                     A.tkept, A.t_dreq, A.t_drank, A.rel, A.heavy, (int)sticky);
             c.launch("commit", k_commit<T, R>, ntiles, T, v, keys, n, (const BatchCtr*)bc, tl,
                      (const uint8_t*)A.mark, (const Src*)A.srcs, (const uint2*)A.tiles,
                      (const uint2*)A.carry, (const uint32_t*)A.tbase, (const uint32_t*)A.t_dreq,
@@ -2138,7 +2186,7 @@ static void edge_run(gv_graph* g, EdgeMode mode, const uint32_t* src, const uint
             constexpr uint32_t R = decltype(rows)::value;
             c.launch("plan_delete", k_plan<false, T, R>, ntiles, T, v, n, bc, tl,
                      (const uint8_t*)A.mark, A.srcs, (const uint2*)A.tiles, (uint2*)nullptr,
-                     A.tbase, (uint32_t*)nullptr, (uint32_t*)nullptr, A.heavy, A.big, 0);
+                     A.tbase, A.tkept, (uint32_t*)nullptr, (uint32_t*)nullptr, A.heavy, A.big, 0);
         });
         const uint32_t nbig = kBigGroups;
         c.launch("compact", k_compact,
