@@ -1666,15 +1666,24 @@ __device__ __forceinline__ void compact_body(const GraphView& g, const uint32_t*
         if (lane < kBigR / 32) sg[lane] = 0u;
         wave_fence();
         uint32_t nh = 0;
-        for (uint32_t p0 = H.lo; p0 < H.hi; p0 += 64) {
-            const uint32_t p = p0 + lane;
-            const uint32_t hpv = p < H.hi ? hitpos[p] : kNoHit;
-            const bool hole = hpv < dn;
-            const uint64_t bal = ballot(hole);
-            if (hole) holes[H.lo + nh + popc64(bal & below)] = hpv;
-            // (r <= kBigR, so the tail's bits fit)
-            if (hpv >= dn && hpv < d) atomicOr(&sg[(hpv - dn) >> 5], 1u << ((hpv - dn) & 31));
-            nh += popc64(bal);
+        // (kMidRows rows of the segment in flight: a segment may be long and
+        // hold few hits, one pair 10^6 times, inserted and deleted, 5.29 -> 2.30 ms)
+        constexpr uint32_t kMidRows = 4;
+        for (uint32_t p0 = H.lo; p0 < H.hi; p0 += 64 * kMidRows) {
+            uint32_t hp[kMidRows];
+#pragma unroll
+            for (uint32_t j = 0; j < kMidRows; ++j)
+                hp[j] = hitpos[min(p0 + 64 * j + lane, H.hi - 1)];
+#pragma unroll
+            for (uint32_t j = 0; j < kMidRows; ++j) {
+                const uint32_t hpv = p0 + 64 * j + lane < H.hi ? hp[j] : kNoHit;
+                const bool hole = hpv < dn;
+                const uint64_t bal = ballot(hole);
+                if (hole) holes[H.lo + nh + popc64(bal & below)] = hpv;
+                // (r <= kBigR, so the tail's bits fit)
+                if (hpv >= dn && hpv < d) atomicOr(&sg[(hpv - dn) >> 5], 1u << ((hpv - dn) & 31));
+                nh += popc64(bal);
+            }
         }
         __threadfence_block();
         wave_fence();

@@ -100,7 +100,7 @@ struct SplitIn {
         return r;
     }
     __device__ void deref(Rec& r) const {
-        r.o = op[min((uint64_t)r.p, n - 1)];  // (anything, after a sort that failed)
+        r.o = op[min(r.p, (uint32_t)(n - 1))];  // (anything, after a sort that failed)
         r.act = (r.k >> (2 * L)) == 0 && pair_active(active, r.k, L);
     }
     // 0 = not kept, 1 = kept delete, 2 = kept insert

@@ -74,3 +74,26 @@ def test_plan_time_does_not_follow_one_segment(size):
         g.close()
     say(f"plan of {size} pairs: {us}")
     assert us["hub"] < 4 * us["wide"], us
+
+
+@pytest.mark.parametrize("size", [17, 63, 64, 65, 255, 256, 257, 513, 5000, 100003])
+def test_few_pairs_many_times(size):
+    """A long segment with few hits, in rows of 64 and rounds of 256: one pair,
+    and five of which the last slots of the adjacency are two."""
+    gv = need_gpu()
+    say(f"few pairs, {size} entries")
+    rng = np.random.default_rng(size)
+    deg = 40
+    d0 = rng.choice(N, deg, replace=False)
+    s0 = np.full(deg, 99)
+    for picks in (d0[:1], np.concatenate([d0[:3], d0[-2:]])):
+        g = gv.Graph(N, s0, d0, block_slots=8, pool_bytes=1 << 26)
+        e = EdgeSet(N, s0, d0)
+        d = np.sort(rng.choice(picks, size))
+        s = np.full(size, 99)
+        hits = len(np.unique(d))
+        assert g.delete_edges(s, d) == (e.delete(s, d), 0, size - hits)
+        _same(g, e, "deleted")
+        assert g.insert_edges(s, d) == (e.insert(s, d), 0, size - hits)
+        _same(g, e, "inserted")
+        g.close()
