@@ -192,7 +192,8 @@ constexpr uint32_t kVSumBits = 1u << 17;
 constexpr uint32_t kVSumWords = kVSumBits / 32;
 constexpr uint32_t kVQuads = 4;        // 4-slot groups per thread per round of the pass
 constexpr uint32_t kVScan = 512;       // threads per workgroup of the pass
-constexpr uint32_t kVHitBuf = 4096;    // slots to check staged in LDS per workgroup
+constexpr uint32_t kVHitBuf = 512;     // slots to check staged in LDS per wave
+constexpr uint32_t kVCheck = 2;        // of them checked by a lane at a time
 constexpr uint32_t kVLane = 32;        // frees a lane takes; larger ones take the wave
 constexpr uint32_t kVTail = 32;        // tail slots a lane takes
 constexpr uint32_t kVErrBound = 4;     // err_order value: a device-side bound was exceeded
@@ -266,25 +267,110 @@ __device__ __forceinline__ bool vd_hit(const GraphView& g, const VDel& d, uint64
     return true;
 }
 
+// kVHitBuf staged slots of a wave checked and appended, each step's reads in
+// flight for kVCheck of them per lane; the places of 64 * kVCheck slots take
+// one atomic for the hits and one for the vertices.
+__device__ __forceinline__ void vd_check_stage(const GraphView& g, const VDel& d,
+                                               const uint32_t* stage, uint32_t round_slots) {
+    const uint32_t lane = lane_id(), ncap = (uint32_t)g.n_cap, bm = g.B - 1;
+    for (uint32_t i0 = 0; i0 < kVHitBuf; i0 += 64 * kVCheck) {
+        uint64_t s[kVCheck];
+        uint2 ow[kVCheck];
+        bool hit[kVCheck], first[kVCheck];
+#pragma unroll
+        for (uint32_t j = 0; j < kVCheck; ++j) {
+            const uint32_t e = stage[i0 + 64 * j + lane];
+            const uint64_t r = blockIdx.x + (uint64_t)(e / round_slots) * gridDim.x;
+            s[j] = r * round_slots + e % round_slots;
+            ow[j] = g.bown[s[j] >> g.log2B];
+        }
+        uint32_t gw[kVCheck], aw[kVCheck];
+#pragma unroll
+        for (uint32_t j = 0; j < kVCheck; ++j) {
+            hit[j] = ow[j].x < ncap;
+            ow[j].x = hit[j] ? ow[j].x : 0u;
+            gw[j] = d.gone[ow[j].x >> 5];
+            aw[j] = g.active[ow[j].x >> 5];
+        }
+        bool any = false;
+        VRec r[kVCheck];
+#pragma unroll
+        for (uint32_t j = 0; j < kVCheck; ++j) {
+            hit[j] &= ((aw[j] & ~gw[j]) >> (ow[j].x & 31)) & 1u;
+            r[j] = g.vt[hit[j] ? ow[j].x : 0u];
+            any |= hit[j];
+        }
+        if (!ballot(any)) continue;  // (every owner is deleted too)
+        uint32_t at[kVCheck];
+#pragma unroll
+        for (uint32_t j = 0; j < kVCheck; ++j) {
+            hit[j] &= ow[j].y < nblocks(g, r[j].deg);
+            const bool dir = hit[j] && r[j].dcls != kNoDir;
+            // (any readable word for a slot that is no hit or has no directory)
+            const uint32_t* from = dir ? g.dir + (uint64_t)r[j].dir + ow[j].y : g.active;
+            at[j] = *from;
+            at[j] = dir ? at[j] : r[j].dir;
+        }
+        uint32_t nh = 0, nt = 0;
+        uint64_t mh[kVCheck], mt[kVCheck];
+#pragma unroll
+        for (uint32_t j = 0; j < kVCheck; ++j) {
+            const uint32_t p = (ow[j].y << g.log2B) + ((uint32_t)s[j] & bm);
+            hit[j] &= at[j] == (uint32_t)(s[j] >> g.log2B) && p < r[j].deg;
+            ow[j].y = p;
+            first[j] = false;
+            if (hit[j]) first[j] = atomicAdd(&g.vlost[ow[j].x], 1u) == 0u;
+        }
+#pragma unroll
+        for (uint32_t j = 0; j < kVCheck; ++j) {
+            mh[j] = ballot(hit[j]);
+            mt[j] = ballot(first[j]);
+            nh += popc64(mh[j]);
+            nt += popc64(mt[j]);
+        }
+        unsigned long long base = 0;
+        if (lane == 0 && nh) base = atomicAdd(&g.ctr->vd_hits, (unsigned long long)nh);
+        if (lane == 1 && nt) base = atomicAdd(&g.ctr->vd_touched, (unsigned long long)nt);
+        unsigned long long ih = wave_read(base, 0), it = wave_read(base, 1);
+#pragma unroll
+        for (uint32_t j = 0; j < kVCheck; ++j) {
+            const unsigned long long a = ih + rank_below(mh[j]), b = it + rank_below(mt[j]);
+            if (hit[j]) {
+                if (a < d.hcap) d.hits[a] = ow[j];
+                else vd_error(g);
+            }
+            if (first[j]) {
+                if (b < d.tcapn) d.touched[b] = ow[j].x;
+                else vd_error(g);
+            }
+            ih += popc64(mh[j]);
+            it += popc64(mt[j]);
+        }
+    }
+}
+
 // The pass over the pool's handed-out blocks [0, bump), grid-stride in rounds
-// of kThreads * kVQuads groups of 4 slots, with no barrier between rounds.
-// Slots whose value is deleted are staged in LDS and checked together at the
-// end, a lane each: the check is a chain of four reads (owner record, vertex
-// record, directory, the owner's counter), which each round waited for as
-// many times as its busiest lane had such slots.  A full stage
-// checks the rest on the spot.  Hits, and the vertices whose first hit this
-// is, take one atomic per workgroup and turn, 512 threads each: atomics on one
-// address pass one after the other, 6 ns each, and two of them (on one line)
-// and the edge count for every 256 threads were 20 us at the end.  Bound: the
-// instructions of the pass; 10^4 ids of a 2^20-vertex graph of 2^24 edges 77 ->
-// 43 us (staged 66, larger workgroups 46, whole rounds unchecked 43).
+// of kVScan * kVQuads groups of 4 slots, with no barrier between rounds.
+// Slots whose value is deleted are staged in LDS and checked together, a lane
+// each: the check is a chain of four reads (owner record, vertex record,
+// directory, the owner's counter), which each round waited for as many times
+// as its busiest lane had such slots.  A wave whose stage is full checks it; the
+// rest is checked at the end by the workgroup.  There the hits, and the vertices
+// whose first hit this is, take one atomic per workgroup and turn, 512 threads
+// each: atomics on one address pass one after the other, 6 ns each, and two of
+// them (on one line) and the edge count for every 256 threads were 20 us at the
+// end.  Bound: the instructions of the pass; 10^4 ids of a 2^20-vertex graph of
+// 2^24 edges 77 -> 43 us (staged 66, larger workgroups 46, whole rounds unchecked
+// 43).  With a stage of the workgroup's, whose surplus was checked slot by slot
+// as it came, 6 * 10^5 ids took 2362 us, now 910; the vertices then stood in the
+// order of single atomics, and the kernel that fills their holes took 1890 us,
+// now 929.
 __global__ __launch_bounds__(kVScan, 6) void k_vd_scan(GraphView g, VDel d) {
     __shared__ uint32_t s_sum[kVSumWords];
-    __shared__ uint32_t s_slot[kVHitBuf];  // round * kRoundSlots + slot of the round
-    __shared__ uint32_t s_n;
+    __shared__ uint32_t s_slot[kVScan / 64][kVHitBuf];  // round * kRoundSlots + slot of the round
+    __shared__ uint32_t s_n[kVScan / 64];
     __shared__ unsigned long long s_bh, s_bt;
     __shared__ unsigned long long lds[kVScan / 64];
-    if (threadIdx.x == 0) s_n = 0u;
     for (uint32_t i = threadIdx.x; i < d.sum_words; i += kVScan) s_sum[i] = d.summary[i];
     __syncthreads();
     const uint64_t slots = (uint64_t)g.ctr->bump << g.log2B;
@@ -320,6 +406,9 @@ __global__ __launch_bounds__(kVScan, 6) void k_vd_scan(GraphView g, VDel d) {
     const uint64_t stride = (uint64_t)gridDim.x * kRound;
     uint32_t xs[kVQuads][4];
     uint64_t q0 = (uint64_t)blockIdx.x * kRound;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    uint32_t* stage = s_slot[wave];
+    uint32_t staged = 0;  // the same in the whole wave
     if (q0 < nq) load_round(q0, xs);
     for (uint32_t round = 0; q0 < nq; q0 += stride, ++round) {
         // the summary in LDS clears most slots; the bitmap words of the rest
@@ -346,26 +435,21 @@ __global__ __launch_bounds__(kVScan, 6) void k_vd_scan(GraphView g, VDel d) {
         if (q0 + stride < nq) load_round(q0 + stride, xn);
         const uint32_t mine = __popc(hm), inc = wave_incl_scan(mine);
         const uint32_t all = __builtin_amdgcn_readlane(inc, 63);
-        if (all) {
-            uint32_t at = 0;
-            if (lane_id() == 0) at = atomicAdd(&s_n, all);
-            at = __builtin_amdgcn_readfirstlane(at) + inc - mine;
-            for (; hm; hm &= hm - 1u, ++at) {
+        uint32_t rank = inc - mine;  // of the lane's next slot among the wave's
+        for (uint32_t done = 0; done < all;) {
+            const uint32_t end = done + min(all - done, kVHitBuf - staged);
+            for (; hm && rank < end; hm &= hm - 1u, ++rank) {
                 const uint32_t k = (uint32_t)__ffs(hm) - 1u;
                 const uint32_t in = 4 * ((k / 4) * kVScan + threadIdx.x) + k % 4;
-                uint32_t v, p;
-                if (at < kVHitBuf) {
-                    s_slot[at] = round * kRoundSlots + in;
-                } else if (vd_hit(g, d, 4 * q0 + in, &v, &p)) {
-                    const unsigned long long i = atomicAdd(&g.ctr->vd_hits, 1ull);
-                    if (i < d.hcap) d.hits[i] = make_uint2(v, p);
-                    else vd_error(g);
-                    if (atomicAdd(&g.vlost[v], 1u) == 0u) {
-                        const unsigned long long it = atomicAdd(&g.ctr->vd_touched, 1ull);
-                        if (it < d.tcapn) d.touched[it] = v;
-                        else vd_error(g);
-                    }
-                }
+                stage[staged + rank - done] = round * kRoundSlots + in;
+            }
+            staged += end - done;
+            done = end;
+            if (staged == kVHitBuf) {
+                wave_fence();
+                vd_check_stage(g, d, stage, kRoundSlots);
+                wave_fence();
+                staged = 0;
             }
         }
 #pragma unroll
@@ -373,14 +457,24 @@ __global__ __launch_bounds__(kVScan, 6) void k_vd_scan(GraphView g, VDel d) {
 #pragma unroll
             for (uint32_t i = 0; i < 4; ++i) xs[u][i] = xn[u][i];
     }
+    if (lane_id() == 0) s_n[wave] = staged;
     __syncthreads();
-    const uint32_t ns = min(s_n, kVHitBuf);
+    uint32_t ns = 0;
+#pragma unroll
+    for (uint32_t w = 0; w < kVScan / 64; ++w) ns += s_n[w];
     for (uint32_t i0 = 0; i0 < ns; i0 += kVScan) {
         const uint32_t i = i0 + threadIdx.x;
         uint32_t v = 0, p = 0;
         bool hit = false, firsth = false;
         if (i < ns) {
-            const uint32_t e = s_slot[i];
+            // the i-th of the waves' stages one after the other
+            uint32_t at = i, end = 0;
+#pragma unroll
+            for (uint32_t w = 0; w < kVScan / 64; ++w) {
+                end += s_n[w];
+                if (i >= end) at = (w + 1) * kVHitBuf + i - end;
+            }
+            const uint32_t e = (&s_slot[0][0])[at];
             const uint64_t r = blockIdx.x + (uint64_t)(e / kRoundSlots) * gridDim.x;
             hit = vd_hit(g, d, r * kRoundSlots + e % kRoundSlots, &v, &p);
             if (hit) firsth = atomicAdd(&g.vlost[v], 1u) == 0u;
