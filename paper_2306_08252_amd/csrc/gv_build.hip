@@ -23,6 +23,7 @@ __device__ __forceinline__ uint32_t gwave() {
 }
 
 void read_counters(gv_graph* g) {
+    static_assert(sizeof(DevCounters) % 16 == 0, "copied by the short way");
     hip_check(hipMemcpyAsync(g->hctr, g->v.ctr, sizeof(DevCounters), hipMemcpyDeviceToHost,
                              g->ctx.stream),
               "hipMemcpyAsync counters");

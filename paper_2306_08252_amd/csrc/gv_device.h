@@ -61,7 +61,9 @@ struct ChainState {
     unsigned long long sum[kChainTiles];
 };
 
-struct DevCounters {
+// (whole lines: a copy to the host whose size is no multiple of 16 bytes takes
+// 0.9 us longer)
+struct alignas(128) DevCounters {
     // edge-block pool (free-list stack + bump pointer)
     unsigned long long free_cnt;
     unsigned long long bump;
