@@ -734,7 +734,7 @@ def main():
     init_s = time.perf_counter() - t0
     log(f"init {init_s * 1e3:.2f} ms")
 
-    # the step's tuning (probe shape, work-item size) stored by the tuner for
+    # the step's tuning (overlap, work-item size) stored by the tuner for
     # this workload, if any
     from paper_2306_08252_amd import tuner as Tu
     step_tuning = Tu.load(Tu.steps_key(args.scale, args.edges, k, B))

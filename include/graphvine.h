@@ -244,7 +244,7 @@ int gv_edge_exists(gv_graph* g, const uint32_t* d_src, const uint32_t* d_dst,
  * with every temporary of the query batch in one fixed 64 MiB device array
  * per GPU (a static __device__ array, looked up at graph creation), so the
  * call allocates nothing.  n <= 2^18 pairs, and the batch's temporaries
- * (about 120 bytes per pair plus 32 bytes per 256 pool slots of the graph)
+ * (about 100 bytes per pair plus 24 bytes per item_chunk pool slots of the graph)
  * must fit the array: GV_ERANGE otherwise, before any device work.  Same
  * arguments, result and asynchrony as gv_edge_exists.  Every call on one GPU
  * shares the array: calls that overlap on a GPU (several graphs or streams)

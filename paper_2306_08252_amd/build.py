@@ -33,7 +33,8 @@ def _compile(src: str, verbose: bool, out_dir: str, defines) -> str:
 
 def build(verbose: bool = False, jobs: int = 8, defines=None, lib: str = LIB) -> str:
     """Compile every csrc/*.hip and link `lib`.  `defines` are -D macros for
-    tuning constants (GV_PROBE_GROUP, GV_PROBE_UNROLL, GV_PROBE_CHUNK)."""
+    tuning constants (GV_BIG_R, GV_LANE_SEG, GV_LANE_R, GV_SMALL_SEG,
+    GV_OS_ITEMS, GV_OS_HIST_MODE, GV_OS_HIST_COPIES, GV_CHAIN_TILES)."""
     defines = dict(defines or {})
     out_dir = OUT_DIR if not defines else os.path.join(OUT_DIR, "v_" + "_".join(
         f"{k}{v}" for k, v in sorted(defines.items())))

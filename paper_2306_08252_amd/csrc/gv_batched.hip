@@ -111,8 +111,8 @@ void gather_run(Ctx& c, const gv_op* ops, uint64_t i, uint64_t j, uint8_t* op, u
     flush();
 }
 
-// Lists longer than one sort tile have their gather and sort overlapped
-// (with the overlap on); a list of one tile is sorted by one kernel.
+// Lists of more than kOsTile entries have their gather and sort overlapped
+// (with the overlap on): by rank up to kRankMax entries, by the passes beyond.
 bool side_run(const gv_graph* g, uint64_t pairs) { return g->tune.overlap && pairs > kOsTile; }
 
 // apply a run of edge batches as one mixed list; `fenced`: a list of this

@@ -913,11 +913,6 @@ __global__ __launch_bounds__(kThreads) void k_adj_low(const uint64_t* keys, uint
     if (i < n) out[i] = (uint32_t)keys[i];
 }
 
-__global__ __launch_bounds__(kThreads) void k_copy_u32(const uint32_t* a, uint32_t* b, uint64_t n) {
-    const uint64_t i = tidx();
-    if (i < n) b[i] = a[i];
-}
-
 void adjacency(gv_graph* g, uint32_t u, uint32_t* out, uint64_t cap, uint64_t* degree) {
     Ctx& c = g->ctx;
     const GraphView& v = g->v;

@@ -32,10 +32,6 @@ constexpr int kMaxClass = 32;
 constexpr uint32_t kSpinLimitDefault = 1u << 24;  // loads before a look-back wait gives up
 constexpr int kThreads = 256;            // threads per workgroup (4 waves)
 constexpr int kWaves = kThreads / 64;
-#ifndef GV_PROBE_CHUNK
-#define GV_PROBE_CHUNK 256
-#endif
-constexpr uint32_t kChunk = GV_PROBE_CHUNK;  // adjacency slots per probe work item
 
 // One vertex dictionary entry.  The adjacency of a vertex of degree deg is the
 // slots [0, deg) of its blocks 0 .. ceil(deg/B)-1 (always compacted).
@@ -304,17 +300,6 @@ __device__ __forceinline__ T block_sum(T x, T* lds) {
     for (int i = 0; i < kWaves; ++i) tot += lds[i];
     __syncthreads();
     return tot;
-}
-
-// first index in keys[lo, hi) whose value is >= x
-template <typename K>
-__device__ __forceinline__ uint32_t lower_bound(const K* keys, uint32_t lo, uint32_t hi, K x) {
-    while (lo < hi) {
-        uint32_t mid = lo + ((hi - lo) >> 1);
-        if (keys[mid] < x) lo = mid + 1;
-        else hi = mid;
-    }
-    return lo;
 }
 
 }  // namespace gv

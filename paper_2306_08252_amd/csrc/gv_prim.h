@@ -25,12 +25,6 @@ constexpr int kRadixBits = 8;
 constexpr int kRadix = 1 << kRadixBits;
 
 template <typename T>
-struct ArrIn {
-    const T* a;
-    __device__ T operator()(uint64_t i) const { return a[i]; }
-};
-
-template <typename T>
 struct ArrOut {
     T* a;
     __device__ void operator()(uint64_t i, T v) const { a[i] = v; }
@@ -464,10 +458,11 @@ constexpr uint32_t kOsAgg = 1u << 30, kOsIncl = 2u << 30, kOsMask = (1u << 30) -
 
 inline int os_passes(int bits) { return (bits + kRadixBits - 1) / kRadixBits; }
 // Digit histograms: every histogram workgroup writes its own counts (no
-// atomics), one small kernel adds them up.  A workgroup takes a key per thread and turn, two workgroups a compute unit:
-// with four keys per thread 10^5 pairs filled 25 units (pack 13.8 us, now 6.8),
-// 10^6 pairs one workgroup a unit (21.7, now 16.7; building from 1.7 * 10^7
-// 88 -> 69); 10^7 pairs take 109 us either way.
+// atomics), one small kernel adds them up.  A workgroup takes a key per thread
+// and turn, two workgroups a compute unit: with four keys per thread 10^5 pairs
+// filled 25 units (pack 13.8 us, now 6.8), 10^6 pairs one workgroup a unit (21.7,
+// now 16.7; building from 1.7 * 10^7 88 -> 69); 10^7 pairs take 109 us either
+// way.
 constexpr uint64_t kHistGroups = 512;
 constexpr uint64_t kHistTile = 1024;
 inline uint64_t os_hist_groups(uint64_t n) {
@@ -1009,7 +1004,7 @@ constexpr uint64_t kOsMaxKeys = 1ull << 30;
 
 // Sorts n keys (n on the device when n_dev != null, n_max bounds it) by bits
 // [0, bits), stably, ping-ponging k0/k1 (v0/v1).  `state` must hold
-// os_words(n_max, bits) uint32 words, which the digit counting clears as far
+// os_words(n_max, bits, HasVal) uint32 words, which the digit counting clears as far
 // as the passes need it, with `clear_words` words at `clear` for the caller
 // (a kernel for that alone took 2.1 us at 10^5 keys, 4.5 at 10^6);
 // `concurrent` as for onesweep_passes.  Returns true if the result is in

@@ -63,12 +63,6 @@ __global__ __launch_bounds__(kThreads) void k_vfit(GraphView g, const uint32_t* 
     }
 }
 
-__global__ __launch_bounds__(kThreads) void k_vcopy_ids(const uint32_t* ids, uint64_t n,
-                                                        uint32_t* out) {
-    const uint64_t i = vt_tidx();
-    if (i < n) out[i] = ids[i];
-}
-
 __global__ __launch_bounds__(kThreads) void k_vzero(uint32_t* a, uint64_t n) {
     const uint64_t i = vt_tidx();
     if (i < n) a[i] = 0;

@@ -6,11 +6,12 @@ workload, with the times it measured.  Two workloads:
   batched  a graph and a sequence of uneven batches (the batched form); knobs:
            block size B (8, 16, 32, 64 slots), coalescing of runs of edge
            batches into mixed lists, the longest run coalesced (pairs), the
-           largest batch sorted by one workgroup, and the probe's shape;
+           largest batch sorted by rank, the sort overlap, and the adjacency
+           slots per work item;
   steps    insert + delete steps of equal batches on one graph (the
            benchmark's step, block size fixed by the workload); knobs: the
-           probe's shape (lanes per work item, slots per lane per step) and
-           the adjacency slots per work item.  Every setting is timed eagerly
+           sort overlap and the adjacency slots per work item.
+Every setting is timed eagerly
 (gv_apply_ops, coalescing as set) on a fresh copy of the same graph after
 the same warm-up, and every run must end in the same graph (checksum and
 edge count), so a setting cannot win by computing something else.
@@ -83,7 +84,7 @@ def measure(gv, w, ops, dev, bs, tuning, warm, form="plan"):
 
 
 PROBE_SPACE = [("item_chunk", [64, 128, 256, 512, 1024, 2048, 4096])]
-DEFAULT_PROBE = {"probe_group": 32, "probe_unroll": 4, "item_chunk": 256}
+DEFAULT_PROBE = {"item_chunk": 256}
 
 
 def descend(best, space, run):
@@ -150,9 +151,8 @@ def measure_steps(gv, w, ins, dels, dev, B, tuning, warmup=2, steps=10):
 
 
 def tune_steps(gv, w, ins, dels, dev, B, log=print):
-    """Coordinate descent over the sort overlap, the probe's shape and the
-    work-item size for the benchmark's step; returns (best setting, measured
-    points in ms)."""
+    """Coordinate descent over the sort overlap and the work-item size for
+    the benchmark's step; returns (best setting, measured points in ms)."""
     points, want = {}, None
 
     def run(s):
