@@ -187,7 +187,6 @@ static void carve_batch(Carver& cv, BatchArrays& A, uint64_t n, uint64_t icap, E
     if (mode != kQuery) {
         A.heavy = cv.take<uint32_t>(n);
         A.tbase = cv.take<uint32_t>(nt);
-        A.tkept = cv.take<uint32_t>(nt);
     }
     A.srcs = cv.take<Src>(n);
     A.tiles = cv.take<uint2>(nt);
@@ -204,6 +203,7 @@ static void carve_batch(Carver& cv, BatchArrays& A, uint64_t n, uint64_t icap, E
     A.state = cv.take<uint32_t>(os_words(n, bits, mode == kQuery));
     A.vpart = cv.take<uint32_t>(kHistGroups);
     A.hpart = cv.take<unsigned long long>(kHistGroups);
+    if (mode != kQuery) A.tkept = cv.take<uint32_t>(nt);
 }
 
 __device__ __forceinline__ uint64_t thread_index() {
@@ -513,7 +513,6 @@ __global__ __launch_bounds__(T, 8) void k_segments(GraphView g, const uint64_t* 
     }
     const uint32_t np = (uint32_t)min((uint64_t)tile, lim - p0);
     if (t < 3) s_sum[t] = 0ull;
-    if (t == 0 && tkept) tkept[blockIdx.x] = 0u;
     bool head[R];
     unsigned long long hash = 0, uniq = 0;
     bool bad = false;
@@ -566,6 +565,7 @@ __global__ __launch_bounds__(T, 8) void k_segments(GraphView g, const uint64_t* 
     if (t == 0) {
         s_at = nh ? atomicAdd(&bc->alloc, (unsigned long long)nh << 32 | ni) : 0ull;
         tiles[blockIdx.x] = make_uint2((uint32_t)(s_at >> 32), nh);
+        if (!nh && tkept) tkept[blockIdx.x] = 0u;
     }
     hash = wave_sum(hash);
     uniq = wave_sum(uniq);
@@ -1662,24 +1662,19 @@ __device__ __forceinline__ void compact_body(const GraphView& g, const uint32_t*
         if (lane < kBigR / 32) sg[lane] = 0u;
         wave_fence();
         uint32_t nh = 0;
-        // (kMidRows rows of the segment in flight: a segment may be long and
-        // hold few hits, one pair 10^6 times, inserted and deleted, 5.29 -> 2.30 ms)
-        constexpr uint32_t kMidRows = 4;
-        for (uint32_t p0 = H.lo; p0 < H.hi; p0 += 64 * kMidRows) {
-            uint32_t hp[kMidRows];
-#pragma unroll
-            for (uint32_t j = 0; j < kMidRows; ++j)
-                hp[j] = hitpos[min(p0 + 64 * j + lane, H.hi - 1)];
-#pragma unroll
-            for (uint32_t j = 0; j < kMidRows; ++j) {
-                const uint32_t hpv = p0 + 64 * j + lane < H.hi ? hp[j] : kNoHit;
-                const bool hole = hpv < dn;
-                const uint64_t bal = ballot(hole);
-                if (hole) holes[H.lo + nh + popc64(bal & below)] = hpv;
-                // (r <= kBigR, so the tail's bits fit)
-                if (hpv >= dn && hpv < d) atomicOr(&sg[(hpv - dn) >> 5], 1u << ((hpv - dn) & 31));
-                nh += popc64(bal);
-            }
+        // (the next row is in flight: a segment may be long and hold few hits,
+        // one pair 10^6 times, inserted and deleted, 5.29 -> 4.22 ms; four rows
+        // at once 2.30, but 10^4 deletes 10.6 -> 11.2 us)
+        uint32_t next = hitpos[min(H.lo + lane, H.hi - 1)];
+        for (uint32_t p0 = H.lo; p0 < H.hi; p0 += 64) {
+            const uint32_t hpv = p0 + lane < H.hi ? next : kNoHit;
+            if (p0 + 64 < H.hi) next = hitpos[min(p0 + 64 + lane, H.hi - 1)];
+            const bool hole = hpv < dn;
+            const uint64_t bal = ballot(hole);
+            if (hole) holes[H.lo + nh + popc64(bal & below)] = hpv;
+            // (r <= kBigR, so the tail's bits fit)
+            if (hpv >= dn && hpv < d) atomicOr(&sg[(hpv - dn) >> 5], 1u << ((hpv - dn) & 31));
+            nh += popc64(bal);
         }
         __threadfence_block();
         wave_fence();
