@@ -26,7 +26,7 @@
  * stream order on the graph's stream; the caller keeps it alive until that
  * stream has passed the call.  The library never frees caller memory.  The
  * graph owns all of its internal memory; gv_graph_destroy releases it (the
- * library keeps at most 4 GiB of large freed buffers per process for the next
+ * library keeps at most 4 GiB of freed buffers per process for the next
  * graphs; they are freed when one of its allocations does not fit, when they
  * have been passed over for long, and by gv_release_cached).
  * A gv_graph must be used by one host thread at a time.

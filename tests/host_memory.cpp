@@ -7,7 +7,7 @@
 
 #include "gv_host.h"
 
-static size_t g_card = (size_t)1 << 40, g_used = 0;
+static size_t g_card = (size_t)1 << 40, g_used = 0, g_allocs = 0;
 static std::map<void*, size_t> g_bufs;
 static hipError_t g_last = hipSuccess;
 
@@ -17,6 +17,7 @@ hipError_t hipMalloc(void** p, size_t n) {
     *p = std::malloc(1);
     g_bufs[*p] = n;
     g_used += n;
+    ++g_allocs;
     return hipSuccess;
 }
 hipError_t hipFree(void* p) {
@@ -121,13 +122,30 @@ static const char* bounded_and_given_back() {
     return g_used ? "kept past the bound" : nullptr;
 }
 
+// a scratch buffer of a few MiB that grows and goes, graph after graph, comes
+// from what is kept
+static const char* growing_scratch_is_kept() {
+    size_t first = 0;
+    for (int i = 0; i < 8; ++i) {
+        Scratch s;
+        s.ensure(2 * MiB, nullptr);
+        s.ensure(4 * MiB, nullptr);
+        s.release(true);
+        if (i == 0) first = g_allocs;
+    }
+    if (g_allocs != first) return "allocated again";
+    dev_release_cached();
+    return g_used ? "still held" : nullptr;
+}
+
 int main(int argc, char** argv) {
     struct {
         const char* name;
         const char* (*run)();
     } checks[] = {{"scratch_growth_fails", scratch_growth_fails},
                   {"requests_empty_the_cache", requests_empty_the_cache},
-                  {"bounded_and_given_back", bounded_and_given_back}};
+                  {"bounded_and_given_back", bounded_and_given_back},
+                  {"growing_scratch_is_kept", growing_scratch_is_kept}};
     for (auto& c : checks)
         if (argc > 1 && !std::strcmp(argv[1], c.name)) {
             const char* bad = c.run();
