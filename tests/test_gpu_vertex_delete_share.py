@@ -11,7 +11,7 @@ pytestmark = pytest.mark.gpu
 
 
 def test_time_follows_the_slots():
-    """2^20 vertices, 2^24 edges: deleting 6 * 10^5 ids finds some 1.1 times
+    """2^20 vertices, 2^24 edges: deleting 6 * 10^5 ids finds some 1.2 times
     the slots of 3 * 10^5 (whose owner stays) among twice the candidates, and
     takes less than 2.4 times as long (2.8 with a stage whose surplus was
     checked slot by slot, its vertices listed in the order of single atomics)."""
