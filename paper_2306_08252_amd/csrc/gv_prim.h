@@ -166,27 +166,17 @@ __device__ __forceinline__ void st_status32(uint32_t* p, uint32_t v) {
 // element is live when i < lim.  A sink may also define
 //   void finish()                       run by the first wave of the last
 //                                       workgroup once the total is written
-// Elements per thread: In::kItems when the source defines it (sources with
-// large records take fewer, to keep registers low), else kScan1Items.
-template <typename In, typename = void>
-struct scan2_items {
-    static constexpr int value = kScan1Items;
-};
-template <typename In>
-struct scan2_items<In, std::void_t<decltype(In::kItems)>> {
-    static constexpr int value = In::kItems;
-};
+// A thread takes kScan1Items elements.
 template <typename Out, typename = void>
 struct scan2_has_finish : std::false_type {};
 template <typename Out>
 struct scan2_has_finish<Out, std::void_t<decltype(std::declval<const Out&>().finish())>>
     : std::true_type {};
-constexpr int kScan2MinItems = 2;  // the fewest any source takes (scan2 checks it)
 
 template <typename In>
 __global__ __launch_bounds__(kThreads) void k_scan2_reduce(In in, uint64_t n,
                                                            unsigned long long* part) {
-    constexpr int kI = scan2_items<In>::value;
+    constexpr int kI = kScan1Items;
     __shared__ unsigned long long s_w[kWaves];
     const uint64_t lim = in.limit(n);
     const uint64_t base = (uint64_t)blockIdx.x * kThreads * kI + threadIdx.x;
@@ -253,7 +243,7 @@ __global__ __launch_bounds__(kThreads) void k_scan2_apply(In in, Out out, uint64
                                                           const unsigned long long* part,
                                                           int scanned,
                                                           unsigned long long* total) {
-    constexpr int kI = scan2_items<In>::value;
+    constexpr int kI = kScan1Items;
     __shared__ unsigned long long s_w[kI][kWaves];
     __shared__ unsigned long long s_p[kWaves];
     const uint64_t lim = in.limit(n);
@@ -324,7 +314,7 @@ __global__ __launch_bounds__(kThreads) void k_scan2_chain(In in, Out out, uint64
                                                           uint32_t nt, ChainState* st,
                                                           uint32_t* err,
                                                           unsigned long long* total) {
-    constexpr int kI = scan2_items<In>::value;
+    constexpr int kI = kScan1Items;
     __shared__ unsigned long long s_w[kI][kWaves];
     __shared__ unsigned long long s_p[kWaves];
     __shared__ uint32_t s_tile, s_last;
@@ -413,24 +403,19 @@ __global__ __launch_bounds__(kThreads) void k_scan2_chain(In in, Out out, uint64
 constexpr uint64_t kScan2MaxTiles = 2048;
 // partial words any scan2 over n elements needs
 inline uint64_t scan2_parts(uint64_t n) {
-    return div_up(std::max<uint64_t>(n, 1), (uint64_t)kThreads * kScan2MinItems);
+    return div_up(std::max<uint64_t>(n, 1), (uint64_t)kThreads * kScan1Items);
 }
 
 // tiles of a scan2 over n elements (one tile: no reduce kernel)
-template <typename In>
-inline uint64_t scan2_tiles(uint64_t n) {
-    return div_up(n, (uint64_t)kThreads * scan2_items<In>::value);
-}
+inline uint64_t scan2_tiles(uint64_t n) { return div_up(n, (uint64_t)kThreads * kScan1Items); }
 
 // Exclusive scan of in(i), i < n, as out(i, rec, lim, prefix); total ->
 // *total.  `part` holds scan2_parts(n) words.
 template <typename In, typename Out>
 void scan2(Ctx& c, const char* name, In in, Out out, uint64_t n, unsigned long long* part,
            unsigned long long* total) {
-    static_assert(scan2_items<In>::value >= kScan2MinItems,
-                  "the partials are sized for kScan2MinItems elements per thread");
     if (n == 0) return;
-    const uint64_t nt = scan2_tiles<In>(n);
+    const uint64_t nt = scan2_tiles(n);
     if (nt > 0xffffffffull) fail(GV_EINVAL, "scan too large");
     if (nt > 1 && nt <= kChainTiles && c.chain) {
         c.launch(name, k_scan2_chain<In, Out>, nt, kThreads, in, out, n, (uint32_t)nt,

@@ -197,9 +197,11 @@ __global__ __launch_bounds__(kThreads) void k_mixed_flags(
     gv_batch_stats* stats) {
     const uint64_t i = (uint64_t)blockIdx.x * kThreads + threadIdx.x;
     if (i < n_req) stats[i] = gv_batch_stats{0ull, 0ull, 0ull};
-    if (i >= n || batch_failed(g.ctr)) return;
+    if (i >= n) return;
     const uint64_t k = sk[i];
     const uint32_t p = sp[i];
+    // (read beside the entry, not ahead of it)
+    if (batch_failed(g.ctr)) return;
     const uint8_t o = op[p];
     uint8_t f = kFNone;
     uint32_t ref = 0;
@@ -239,7 +241,6 @@ __global__ __launch_bounds__(kThreads) void k_request_stats(const DevCounters* c
                                                             const uint8_t* del_found,
                                                             const uint8_t* ins_had,
                                                             gv_batch_stats* stats) {
-    if (batch_failed(ctr)) return;  // the flags may not have been written
     const uint64_t p0 = ((uint64_t)blockIdx.x * kThreads + threadIdx.x) * kStatItems;
     const bool live = p0 < n;
     uint32_t r = live ? request_of(end, (uint32_t)n_req, p0) : (uint32_t)n_req;
@@ -259,6 +260,7 @@ __global__ __launch_bounds__(kThreads) void k_request_stats(const DevCounters* c
         fl[k] = flag[p];
         ref[k] = fref[p];
     }
+    if (batch_failed(ctr)) return;  // the flags may not have been written
 #pragma unroll
     for (uint32_t k = 0; k < kStatItems; ++k) {
         const uint32_t i = fl[k] >= kFNeedIns ? ref[k] & ~kRefIns : 0u;

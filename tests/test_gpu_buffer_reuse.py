@@ -66,3 +66,23 @@ def test_second_graph_on_kept_buffers(B):
     assert g.delete_edges(a[::3], b[::3]) == o.delete_edges(a[::3], b[::3])[1]
     assert_same(g, o, "updated")
     g.close()
+
+
+def test_allocation_that_fails_leaves_the_library_usable():
+    """A pool that no card holds: the kept buffers are given back first, and
+    the error stays with its call."""
+    gv = need_gpu()
+    rng = np.random.default_rng(5)
+    s, d = _pairs(rng, 20000)
+    g = gv.Graph(N, s, d, block_slots=8)
+    o = O.OracleGraph(N, s, d, block_slots=8)
+    _used_graph(gv)
+    with pytest.raises(gv.GraphVineError) as e:
+        gv.Graph(N, s, d, block_slots=16, pool_bytes=1 << 41)
+    assert e.value.code == gv.GV_ENOMEM
+    assert gv.gv_release_cached() < POOL  # (what the failed graph had taken)
+    a, b = _pairs(rng, 30000)
+    assert g.insert_edges(a, b) == o.insert_edges(a, b)[1]
+    assert g.sync() == 0
+    assert_same(g, o, "after the failed allocation")
+    g.close()
