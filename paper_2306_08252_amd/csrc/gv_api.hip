@@ -70,6 +70,7 @@ void free_graph(gv_graph* g) {
     for (void* p : mem)
         if (p) hipFree(p);
     if (g->hmem) hipHostFree(g->hmem);
+    (void)hipGetLastError();  // (of a stream or buffer that had failed)
     delete g;
 }
 

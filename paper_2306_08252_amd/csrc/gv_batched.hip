@@ -314,6 +314,7 @@ int gv_plan_create(gv_graph* g, const gv_op* ops, uint64_t n_ops, gv_plan** out)
             c.stream = saved;
             c.prof = saved_prof;
             hipStreamDestroy(cs);
+            (void)hipGetLastError();  // (of ending a capture that had failed)
             throw;
         }
         c.stream = saved;

@@ -653,6 +653,7 @@ static void cbt_free(gv_cbt* g) {
     for (void* p : mem)
         if (p) hipFree(p);
     if (g->hctr) hipHostFree(g->hctr);
+    (void)hipGetLastError();  // (of a stream or buffer that had failed)
     delete g;
 }
 

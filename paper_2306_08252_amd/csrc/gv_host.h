@@ -33,6 +33,9 @@ inline char* last_error_text() {
 
 inline void hip_check(hipError_t e, const char* what) {
     if (e == hipSuccess) return;
+    // the runtime keeps the error until it is asked for: left there, the next
+    // launch's check would report it for another graph
+    (void)hipGetLastError();
     std::snprintf(last_error_text(), 256, "%s: %s", what, hipGetErrorString(e));
     if (e == hipErrorOutOfMemory || e == hipErrorMemoryAllocation) fail(GV_ENOMEM, what);
     fail(GV_EDEVICE, what);

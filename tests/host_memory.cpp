@@ -138,6 +138,17 @@ static const char* growing_scratch_is_kept() {
     return g_used ? "still held" : nullptr;
 }
 
+// an error is reported by the call that met it, and by no other
+static const char* error_stays_with_its_call() {
+    for (hipError_t e : {hipErrorInvalidValue, hipErrorOutOfMemory}) {
+        g_last = e;  // as the runtime keeps it
+        const int want = e == hipErrorOutOfMemory ? GV_ENOMEM : GV_EDEVICE;
+        if (code_of([&] { hip_check(e, "a call"); }) != want) return "another code";
+        if (hipGetLastError() != hipSuccess) return "left for the next call";
+    }
+    return nullptr;
+}
+
 int main(int argc, char** argv) {
     struct {
         const char* name;
@@ -145,7 +156,8 @@ int main(int argc, char** argv) {
     } checks[] = {{"scratch_growth_fails", scratch_growth_fails},
                   {"requests_empty_the_cache", requests_empty_the_cache},
                   {"bounded_and_given_back", bounded_and_given_back},
-                  {"growing_scratch_is_kept", growing_scratch_is_kept}};
+                  {"growing_scratch_is_kept", growing_scratch_is_kept},
+                  {"error_stays_with_its_call", error_stays_with_its_call}};
     for (auto& c : checks)
         if (argc > 1 && !std::strcmp(argv[1], c.name)) {
             const char* bad = c.run();

@@ -45,11 +45,12 @@ def _reported(gv, g):
     assert e.value.code == gv.GV_EDEVICE
 
 
+@pytest.mark.parametrize("form", ["eager", "plan"])
 @pytest.mark.parametrize("last", ["insert", "delete"])
 @pytest.mark.parametrize("good", [1, 2, 30])
-def test_batches_before_a_failed_sort_are_whole(good, last):
+def test_batches_before_a_failed_sort_are_whole(good, last, form):
     gv = need_gpu()
-    say(f"failed sort behind {good} batches, {last}")
+    say(f"failed sort behind {good} batches, {last}, {form}")
     rng = np.random.default_rng(good)
     g, o, have = _graphs(gv, rng)
     gv.gv_set_tuning(g.h, overlap=1, small_sort_max=0)
@@ -61,7 +62,11 @@ def test_batches_before_a_failed_sort_are_whole(good, last):
     kind = gv.OP_INSERT_EDGES if last == "insert" else gv.OP_DELETE_EDGES
     bad = [(kind, *_pairs(rng, 60000)), (gv.OP_INSERT_EDGES, *_pairs(rng, 2048))]
     gv.gv_debug_spin_limit(g.h, 0)
-    keep = gv.gv_apply_ops(g.h, ops + bad, g.device)
+    if form == "plan":
+        keep = gv.Plan(g.h, ops + bad, g.device)
+        keep.launch()
+    else:
+        keep = gv.gv_apply_ops(g.h, ops + bad, g.device)
     torch.cuda.synchronize()
     _apply(gv, o, ops)
     assert_same(g, o, "as the batches before the failed one left it")

@@ -24,7 +24,8 @@ def program(tmp_path_factory):
 
 
 @pytest.mark.parametrize("check", ["scratch_growth_fails", "requests_empty_the_cache",
-                                   "bounded_and_given_back", "growing_scratch_is_kept"])
+                                   "bounded_and_given_back", "growing_scratch_is_kept",
+                                   "error_stays_with_its_call"])
 def test_device_memory(program, check):
     r = subprocess.run([program, check], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0, r.stdout
